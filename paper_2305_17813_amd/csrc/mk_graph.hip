@@ -167,9 +167,10 @@ __global__ void k_spare_merge(DView F, DView R, DView U, uint32_t views) {
   }
 }
 
-// Pool counters of every view and the overflow bits, gathered for one asynchronous copy.
+// Pool counters of every view and the overflow bits, gathered for one copy to the host; words
+// 14 and 15 take the 64-bit value at `extra`, if there is one.
 __global__ void k_pool_snapshot(const uint32_t* f, const uint32_t* r, const uint32_t* u,
-                                const uint32_t* overflow, uint32_t* out) {
+                                const uint32_t* overflow, uint32_t* out, const uint32_t* extra) {
   const uint32_t t = threadIdx.x;
   if (t < 12) {
     const uint32_t* c = t < 4 ? f : (t < 8 ? r : u);
@@ -177,7 +178,7 @@ __global__ void k_pool_snapshot(const uint32_t* f, const uint32_t* r, const uint
   } else if (t == 12) {
     out[t] = *overflow;
   } else if (t < 16) {
-    out[t] = 0u;
+    out[t] = extra && t >= 14 ? extra[t - 14] : 0u;
   }
 }
 
@@ -539,90 +540,207 @@ __global__ void __launch_bounds__(kBlock) k_check(DView V, uint32_t nv, uint32_t
 // Byte model: slabs one probe walks (op 0: until found / first EMPTY / end; op 1: to the
 // end of the chain unless the key is found first).  A second head access counts as a slab.
 // ------------------------------------------------------------ slab reclamation
-// Take back free-list entries that inserts asked for but did not get (the take counter
-// may run past the append counter).
-__global__ void k_free_fix(uint32_t* ctr) {
-  if (threadIdx.x == 0 && (int32_t)(ctr[1] - ctr[2]) < 0) ctr[2] = ctr[1];
+// Before a compaction: take back free-list entries that inserts asked for but did not get (the
+// take counter may run past the append counter), zero the freed-slab count, and clear the
+// chain bits of every view (`nbits` words each; null when the compaction sweeps every chain).
+struct ChainBits {
+  uint32_t* bits[3];
+  uint64_t words[3];
+};
+__global__ void k_compact_begin(DView F, DView R, DView U, uint32_t views, ChainBits cb,
+                                unsigned long long* freed) {
+  const uint32_t v = blockIdx.y;
+  if (!(views & (1u << v))) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    uint32_t* ctr = (v == 0 ? F : (v == 1 ? R : U)).pool_ctr;
+    if ((int32_t)(ctr[1] - ctr[2]) < 0) ctr[2] = ctr[1];
+    if (v == 0) *freed = 0;
+  }
+  if (!cb.bits[v]) return;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cb.words[v];
+       i += (uint64_t)gridDim.x * blockDim.x)
+    cb.bits[v][i] = 0;
 }
 
-// Rewrite every chain holding at least min_tomb tombstones with its live words packed from
-// its head slab in chain order, EMPTY after them, and the chain cut after the last slab it
-// still needs; the slabs after the cut are refilled with EMPTY words and appended to the
-// free list.  One 16-lane group per chain (head slab h: primary slabs [0, N), extra head
-// slabs after them).  Packing only moves a word to an earlier position of its own chain,
-// so the write position never passes the slab being read.
-__global__ void __launch_bounds__(kBlock) k_compact(DView V, uint64_t n_head, uint32_t nv, uint32_t min_tomb,
-                                                    unsigned long long* freed, uint64_t* marks) {
-  const uint64_t g0 = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kGroup;
-  const uint64_t ng = (uint64_t)gridDim.x * kGroupsPerBlock;
+// Slabs cut from their chains, staged per block: a block's cut chains take one atomic on the
+// view's free-list counter together.  (With an atomic per cut chain, a compaction after 1M
+// deletions took as long as the sweep over the whole graph: they all hit one address.)
+constexpr uint32_t kCompactRound = 16;  // chains a group packs between two hand-outs
+struct CutStage {
+  uint32_t n[3], total[3], base[3];                       // per view
+  uint32_t rest[3][kGroupsPerBlock * kCompactRound];      // first slab of each cut-off tail
+  uint32_t off[3][kGroupsPerBlock * kCompactRound];       // its place among the block's slabs
+};
+
+// Each lane with `send` sends its word to lane `to` (0 .. 14, distinct) of its group; the value
+// means something only in the lanes sent to.  (A lane that sends nothing targets lane 15,
+// which is never sent a word.)
+__device__ inline uint64_t group_push(uint64_t w, bool send, int to) {
+  const int dst = (group_base_lane() + (send ? to : 15)) * 4;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)(uint32_t)w);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)(uint32_t)(w >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Pack one chain (head slab `head`, whose words are x, one per lane of the calling group) if it
+// holds at least min_tomb tombstones: its live words in chain order from the head slab on,
+// EMPTY after them, and the chain cut after the last slab it still needs; the tail goes to the
+// block's stage.  The words of an output slab are gathered across the lanes and stored with one
+// 128-byte write, so a chain of one slab (most of them) costs one read and one write.  The
+// slab being written never lies past the one being read.
+__device__ inline void compact_chain(const DView& V, uint32_t head, uint64_t x, uint32_t nv,
+                                     uint32_t min_tomb, uint64_t* marks, CutStage& C, int v) {
   const int gl = glane();
   const uint32_t below = (1u << gl) - 1u;
-  unsigned long long total = 0;
-  for (uint64_t h = g0; h < n_head; h += ng) {
-    const uint32_t head = (uint32_t)h;
-    const uint64_t x = ld_word(slab_ptr(V, head) + gl);
-    const int nd0 = (head < nv && (uint32_t)(gbcast64(x, 15) >> 32) > 1) ? kKeysPerSlab - 1 : kKeysPerSlab;
-    uint32_t tomb = 0;
-    {
-      uint64_t y = x;
-      int nd = nd0;
-      while (true) {
-        tomb += __popc(gballot(gl < nd && y == kTombWord));
-        const uint32_t nx = gbcast((uint32_t)y, 15);
-        if (nx == kInvalid) break;
-        y = ld_word(slab_ptr(V, nx) + gl);
-        nd = kKeysPerSlab;
-      }
-    }
-    if (tomb < min_tomb || tomb == 0) continue;
-    // words move: the chain's update mark (if the view keeps marks) restarts at the head
-    if (marks && gl == 0) marks[h] = 0;
-    uint32_t ws = head;  // slab being written, its capacity and fill
-    int wcap = nd0, wpos = 0;
+  const int nd0 = (head < nv && (uint32_t)(gbcast64(x, 15) >> 32) > 1) ? kKeysPerSlab - 1 : kKeysPerSlab;
+  uint32_t tomb = 0, slabs = 0;
+  {
     uint64_t y = x;
-    int rnd = nd0;
+    int nd = nd0;
     while (true) {
-      const uint32_t next = gbcast((uint32_t)y, 15);
-      const bool live = gl < rnd && valid_key((uint32_t)y);
-      const uint32_t m = gballot(live);
-      const int r = __popc(m & below), cnt = __popc(m);
-      const int n1 = min(cnt, wcap - wpos);
-      if (live && r < n1) slab_ptr(V, ws)[wpos + r] = y;
-      wpos += n1;
-      if (cnt > n1) {  // spill into the next slab of the chain (not past the one being read)
-        ws = (uint32_t)ld_word(slab_ptr(V, ws) + 15);
-        wcap = kKeysPerSlab;
-        if (live && r >= n1) slab_ptr(V, ws)[r - n1] = y;
-        wpos = cnt - n1;
-      }
-      if (next == kInvalid) break;
-      y = ld_word(slab_ptr(V, next) + gl);
-      rnd = kKeysPerSlab;
+      ++slabs;
+      tomb += __popc(gballot(gl < nd && y == kTombWord));
+      const uint32_t nx = gbcast((uint32_t)y, 15);
+      if (nx == kInvalid) break;
+      y = ld_word(slab_ptr(V, nx) + gl);
+      nd = kKeysPerSlab;
     }
-    // end the chain at ws and hand the rest to the free list (each lane rewrites only the
-    // word it read itself; the link comes from lane 15)
-    const uint64_t xw = ld_word(slab_ptr(V, ws) + gl);
-    const uint64_t wl = gbcast64(xw, 15);
-    const uint32_t rest = (uint32_t)wl;
-    if (gl >= wpos && gl < wcap) slab_ptr(V, ws)[gl] = kEmptyWord;
-    if (gl == 15) slab_ptr(V, ws)[15] = (wl & 0xFFFFFFFF00000000ull) | kInvalid;
-    uint32_t k = 0;
-    for (uint32_t t = rest; t != kInvalid; t = (uint32_t)ld_word(slab_ptr(V, t) + 15)) ++k;
-    if (k == 0) continue;
-    uint32_t pos = 0;
-    if (gl == 0) pos = atomicAdd(V.pool_ctr + 1, k);
-    pos = gbcast(pos, 0);
-    for (uint32_t t = rest; t != kInvalid;) {
-      const uint64_t xt = ld_word(slab_ptr(V, t) + gl);
-      const uint32_t nx = (uint32_t)gbcast64(xt, 15);
-      slab_ptr(V, t)[gl] = gl == 15 ? kNextNone : kEmptyWord;
-      if (gl == 0) V.free_ids[pos % V.pool_cap] = t;
-      ++pos;
-      t = nx;
-    }
-    total += k;
   }
-  if (gl == 0 && total) atomicAdd(freed, total);
+  if (tomb < min_tomb || tomb == 0) return;
+  // words move: the chain's update mark (if the view keeps marks) restarts at the head
+  if (marks && gl == 0) marks[head] = 0;
+  uint32_t ws = head, written = 1;  // slab being written and its position in the chain
+  int wcap = nd0, wpos = 0;         // its capacity and fill
+  // its words: the lanes at and past its data words keep the head slab's (an extra-head index in
+  // lane 14 of a multi-bucket primary slab, the link in lane 15) or its own link
+  uint64_t o = gl < nd0 ? kEmptyWord : x;
+  uint64_t y = x;
+  int rnd = nd0;
+  while (true) {
+    const uint32_t next = gbcast((uint32_t)y, 15);
+    const bool live = gl < rnd && valid_key((uint32_t)y);
+    const uint32_t m = gballot(live);
+    const int r = __popc(m & below), cnt = __popc(m);
+    const int n1 = min(cnt, wcap - wpos);
+    uint64_t in = group_push(y, live && r < n1, wpos + r);
+    if (gl >= wpos && gl < wpos + n1) o = in;
+    wpos += n1;
+    if (cnt > n1) {  // full: store it and go on in the chain's next slab
+      slab_ptr(V, ws)[gl] = o;
+      ws = gbcast((uint32_t)o, 15);
+      ++written;
+      o = gl == 15 ? ld_word(slab_ptr(V, ws) + 15) : kEmptyWord;
+      wcap = kKeysPerSlab;
+      in = group_push(y, live && r >= n1, r - n1);
+      wpos = cnt - n1;
+      if (gl < wpos) o = in;
+    }
+    if (next == kInvalid) break;
+    y = ld_word(slab_ptr(V, next) + gl);
+    rnd = kKeysPerSlab;
+  }
+  const uint32_t rest = gbcast((uint32_t)o, 15);
+  slab_ptr(V, ws)[gl] = gl == 15 ? (o & 0xFFFFFFFF00000000ull) | kInvalid : o;
+  const uint32_t k = slabs - written;
+  if (k && gl == 0) {
+    const uint32_t e = atomicAdd(&C.n[v], 1u);
+    C.rest[v][e] = rest;
+    C.off[v][e] = atomicAdd(&C.total[v], k);
+  }
+}
+
+__device__ inline void cut_open(CutStage& C) {
+  if (threadIdx.x < 3) C.n[threadIdx.x] = C.total[threadIdx.x] = 0;
+  __syncthreads();
+}
+
+// Hand the staged tails to the free lists: refilled with EMPTY words, their ids appended.
+// Every thread of the block calls it.
+__device__ inline void cut_close(CutStage& C, const DView* const (&V)[3], unsigned long long* freed) {
+  __syncthreads();
+  if (threadIdx.x < 3 && C.total[threadIdx.x]) {
+    C.base[threadIdx.x] = atomicAdd(V[threadIdx.x]->pool_ctr + 1, C.total[threadIdx.x]);
+    atomicAdd(freed, (unsigned long long)C.total[threadIdx.x]);
+  }
+  __syncthreads();
+  const int gl = glane();
+  for (int v = 0; v < 3; ++v) {
+    const DView& W = *V[v];
+    for (uint32_t e = threadIdx.x / kGroup; e < C.n[v]; e += kGroupsPerBlock) {
+      uint32_t pos = C.base[v] + C.off[v][e];
+      for (uint32_t t = C.rest[v][e]; t != kInvalid; ++pos) {
+        const uint32_t nx = (uint32_t)ld_word(slab_ptr(W, t) + 15);
+        slab_ptr(W, t)[gl] = gl == 15 ? kNextNone : kEmptyWord;
+        if (gl == 0) W.free_ids[pos % W.pool_cap] = t;
+        t = nx;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Compaction by a sweep over every chain: one 16-lane group per chain (primary slabs [0, N),
+// extra head slabs after them), kCompactRound chains between two hand-outs.
+__global__ void __launch_bounds__(kBlock) k_compact(DView V, int v, uint64_t n_head, uint32_t nv, uint32_t min_tomb,
+                                                    unsigned long long* freed, uint64_t* marks) {
+  __shared__ CutStage C;
+  const DView* const views[3] = {&V, &V, &V};
+  const uint64_t g0 = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kGroup;
+  const uint64_t ng = (uint64_t)gridDim.x * kGroupsPerBlock;
+  for (uint64_t base = 0; base < n_head; base += ng * kCompactRound) {  // the same rounds in every block
+    cut_open(C);
+    for (uint32_t k = 0; k < kCompactRound; ++k) {
+      const uint64_t h = base + k * ng + g0;
+      if (h < n_head)
+        compact_chain(V, (uint32_t)h, ld_word(slab_ptr(V, (uint32_t)h) + glane()), nv, min_tomb, marks, C, v);
+    }
+    cut_close(C, views, freed);
+  }
+}
+
+// Compaction of the chains that the logged deletes touched, one per logged op and table that
+// held the arc (forward, reverse, both undirected directions).  First a lane per <op, table>
+// finds the chain its key hashed to and claims it by the chain's bit (several deletes may
+// have hit one chain), so that a wave has 64 of these dependent reads in flight; then the
+// block's groups pack the claimed chains.  Every other chain is free of tombstones (the host
+// checks that the log holds every delete since the last compaction of all chains), so the
+// work follows the deletions, not the graph.  `rounds` (1 .. kCompactRound): chains per group,
+// few for a small batch, whose time is the latency of one block.
+__global__ void __launch_bounds__(kBlock) k_compact_log(DView F, DView R, DView U, uint32_t views, Log log,
+                                                        uint64_t n, uint32_t nv, uint32_t min_tomb, uint32_t rounds,
+                                                        ChainBits cb, unsigned long long* freed, uint64_t* marks) {
+  __shared__ CutStage C;
+  __shared__ uint32_t nclaimed[3], chain[3][kGroupsPerBlock * kCompactRound];
+  const DView* const all[3] = {&F, &R, &U};
+  if (threadIdx.x < 3) nclaimed[threadIdx.x] = 0;
+  cut_open(C);
+  const uint32_t per = kGroupsPerBlock * rounds;  // <op, table> pairs of this block
+  if (threadIdx.x < per) {
+    const uint64_t op = (uint64_t)blockIdx.x * (per / 4) + threadIdx.x / 4;
+    const int task = (int)(threadIdx.x & 3);
+    const int v = task < 2 ? task : VU;
+    if (op < n && log.st[op] == 1 && (views & (1u << v)) && (v != VU || log.uf[op])) {
+      const DView& V = v == VF ? F : (v == VR ? R : U);
+      const uint32_t s = log.s[op], d = log.d[op];
+      const bool from_s = task == 0 || task == 2;
+      const uint32_t u = from_s ? s : d, key = from_s ? d : s;
+      const uint4 q = reinterpret_cast<const uint4*>(slab_ptr(V, u))[7];  // words 14 and 15
+      const uint32_t nb = q.w, b = nb > 1 ? bucket_of(key, nb, V.hash_a, V.hash_b) : 0u;
+      const uint32_t head = b ? q.x + b - 1 : u;
+      if (!(atomicOr(cb.bits[v] + (head >> 5), 1u << (head & 31)) >> (head & 31) & 1))
+        chain[v][atomicAdd(&nclaimed[v], 1u)] = head;
+    }
+  }
+  __syncthreads();
+  for (int v = 0; v < 3; ++v) {
+    const DView& V = *all[v];
+    const uint32_t nc = nclaimed[v];
+    for (uint32_t i = threadIdx.x / kGroup; i < nc; i += kGroupsPerBlock) {
+      const uint32_t head = chain[v][i];
+      compact_chain(V, head, ld_word(slab_ptr(V, head) + glane()), nv, min_tomb, v == VF ? marks : nullptr, C, v);
+    }
+  }
+  cut_close(C, all, freed);
 }
 
 __device__ inline uint32_t walk_cost(const DView& V, uint32_t u, uint32_t key, int op) {
@@ -724,6 +842,7 @@ bool layout(const mk_config* c, uint64_t m, char* base, mk_graph* g, size_t* tot
     uint32_t* pctr = cv.take<uint32_t>(64);
     uint32_t* free_ids = cv.take<uint32_t>(pc);
     uint32_t* spare_ids = cv.take<uint32_t>(pc);
+    uint32_t* chain_bits = cv.take<uint32_t>((hb + 31) / 32);
     uint32_t *pair_v = nullptr, *pair_i = nullptr, *pair_off = nullptr;
     if (v != VU) {  // IterationScheme2 work lists: one entry per head slab
       pair_v = cv.take<uint32_t>(hb);
@@ -745,6 +864,7 @@ bool layout(const mk_config* c, uint64_t m, char* base, mk_graph* g, size_t* tot
       vh.d.free_ids = free_ids;
       vh.d.spare_ids = spare_ids;
       vh.d.pool_cap = (uint32_t)pc;
+      vh.chain_bits = chain_bits;
       vh.pair_v = pair_v;
       vh.pair_i = pair_i;
       vh.pair_off = pair_off;
@@ -904,19 +1024,28 @@ uint64_t used_from(const ViewHost& vh, const uint32_t* c) {
   return hw - std::min<uint64_t>((uint64_t)avail, hw);
 }
 
-// Exact pool figures and the overflow bits (synchronizes the stream).
-mk_status refresh_pool(mk_graph* g, hipStream_t stream) {
-  for (int v = 0; v < 3; ++v)
-    if (g->view[v].on)
-      MK_HIP(g, hipMemcpyAsync(g->h_pin + 2 * v, g->view[v].d.pool_ctr, 3 * sizeof(uint32_t),
-                               hipMemcpyDeviceToHost, stream));
-  MK_HIP(g, hipMemcpyAsync(g->h_pin + 7, &g->ctr->overflow, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+// Gather the pool counters, the overflow bits and the 64-bit value at `extra` into ctr->snap.
+void launch_snapshot(mk_graph* g, const void* extra, hipStream_t stream) {
+  const auto ctr_of = [&](int v) -> const uint32_t* { return g->view[v].on ? g->view[v].d.pool_ctr : nullptr; };
+  hipLaunchKernelGGL(k_pool_snapshot, dim3(1), dim3(64), 0, stream, ctr_of(VF), ctr_of(VR), ctr_of(VU),
+                     &g->ctr->overflow, g->ctr->snap, (const uint32_t*)extra);
+}
+
+// Exact pool figures and the overflow bits (synchronizes the stream): one kernel and one copy,
+// where a copy per view and one for the bits cost about 5 us each.  *h_extra (nullable)
+// receives the 64-bit device value at `extra`.
+mk_status refresh_pool(mk_graph* g, hipStream_t stream, const void* extra = nullptr, uint64_t* h_extra = nullptr) {
+  launch_snapshot(g, extra, stream);
+  MK_LAUNCH(g, "k_pool_snapshot");
+  MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->snap, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
   MK_HIP(g, hipStreamSynchronize(stream));
-  g->overflowed.fetch_or(*reinterpret_cast<const uint32_t*>(g->h_pin + 7));
+  const uint32_t* h = reinterpret_cast<const uint32_t*>(g->h_pin);
+  g->overflowed.fetch_or(h[12]);
+  if (h_extra) *h_extra = g->h_pin[7];
   for (int v = 0; v < 3; ++v) {
     ViewHost& vh = g->view[v];
     if (!vh.on) continue;
-    const uint32_t* c = reinterpret_cast<const uint32_t*>(g->h_pin + 2 * v);
+    const uint32_t* c = h + 4 * v;
     vh.pool_hw = std::min<uint64_t>(c[0], vh.pool_cap);
     vh.pool_used_est = used_from(vh, c);
   }
@@ -928,6 +1057,12 @@ mk_status refresh_pool(mk_graph* g, hipStream_t stream) {
 bool stream_capturing(hipStream_t stream) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
+// A captured update may be replayed, with other arcs and over log entries that later batches took
+// since: from then on the log cannot say which chains hold tombstones.
+void note_capture(mk_graph* g, hipStream_t stream) {
+  if (!g->captured_update && stream_capturing(stream)) g->captured_update = true;
 }
 
 // Use the newest completed snapshot, if any: slabs in use then, plus the bound of every
@@ -958,9 +1093,7 @@ void poll_snapshots(mk_graph* g) {
 void enqueue_snapshot(mk_graph* g, hipStream_t stream) {
   PoolSnap& sn = g->snap[g->snap_next];
   if (sn.pending && hipEventQuery(sn.ev) != hipSuccess) return;  // ring slot still in flight
-  const auto ctr_of = [&](int v) -> const uint32_t* { return g->view[v].on ? g->view[v].d.pool_ctr : nullptr; };
-  hipLaunchKernelGGL(k_pool_snapshot, dim3(1), dim3(64), 0, stream, ctr_of(VF), ctr_of(VR), ctr_of(VU),
-                     &g->ctr->overflow, g->ctr->snap);
+  launch_snapshot(g, nullptr, stream);
   if (hipMemcpyAsync(sn.pin, g->ctr->snap, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream) != hipSuccess ||
       hipEventRecord(sn.ev, stream) != hipSuccess) {
     (void)hipGetLastError();
@@ -1039,6 +1172,17 @@ void launch_insert(mk_graph* g, const uint32_t* s, const uint32_t* d, const uint
   hipLaunchKernelGGL(k_spare_merge, dim3(3), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR), dv(g, VU),
                      g->cfg.views | MK_VIEW_FWD);
 }
+
+// A compaction visits the chains of the logged deletes while kCompactLogRatio times their number
+// is at most the number of head slabs; with more deletes the sweep, which reads in memory order,
+// costs less.  Both ways (logged / sweep), after deleting and inserting back present arcs of
+// R-MAT graphs with all views: scale 18 (2.1M head slabs) 100K ops 109 / 194 us, 300K 224 / 241,
+// 1M 577 / 281; scale 20 (8.6M) 300K 265 / 495, 1M 715 / 630; scale 22 (35M) 100K 121 / 1167,
+// 1M 783 / 1583, 2M 1479 / 1772.  (An atomic per cut chain and words packed by scattered 8-byte
+// stores took 1179 and 2503 us by a sweep at scale 22 with 100K and 1M ops.)
+constexpr uint64_t kCompactLogRatio = 8;
+// Blocks of a sweep: each then packs many chains between two hand-outs of its cut tails.
+constexpr uint32_t kSweepBlocks = 4096;
 
 }  // namespace
 
@@ -1199,6 +1343,7 @@ mk_status mk_insert_edges(mk_graph* g, const uint32_t* d_src, const uint32_t* d_
   st = ensure_pool(g, n, stream);
   if (st != MK_OK) return st;
   const uint64_t off = reserve_log(g, n);
+  note_capture(g, stream);
   launch_insert(g, d_src, d_dst, d_w, n, d_status, log_at(g, off), stream);
   MK_LAUNCH(g, "k_insert");
   for (int v = 0; v < 3; ++v)
@@ -1224,6 +1369,7 @@ mk_status mk_delete_edges(mk_graph* g, const uint32_t* d_src, const uint32_t* d_
   mk_status st = graph_guard(g, true);
   if (st != MK_OK) return st;
   const uint64_t off = reserve_log(g, n);
+  note_capture(g, stream);
   const Log lg = log_at(g, off);
   hipLaunchKernelGGL(k_delete_fwd, dim3(grid_for_lanes(n)), dim3(kBlock), 0, stream, dv(g, VF),
                      d_src, d_dst, n, g->n, d_status, lg);
@@ -1319,20 +1465,48 @@ mk_status mk_compact(mk_graph* g, uint32_t min_tombstones, uint64_t* h_freed, hi
   if (!g || !h_freed) return MK_ERR_INVALID_ARG;
   if (mk_status gs = graph_guard(g); gs != MK_OK) return gs;
   unsigned long long* freed = &g->ctr->u64tmp[2];
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, (uint32_t*)freed, 2, 0u);
-  for (int v = 0; v < 3; ++v) {
-    const ViewHost& vh = g->view[v];
-    if (!vh.on) continue;
-    hipLaunchKernelGGL(k_free_fix, dim3(1), dim3(64), 0, stream, vh.d.pool_ctr);
-    hipLaunchKernelGGL(k_compact, dim3(grid_for_groups(std::min<uint64_t>(vh.n_head, 1u << 20))),
-                       dim3(kBlock), 0, stream, vh.d, vh.n_head, g->n, min_tombstones, freed,
-                       v == VF ? g->upd_mark : nullptr);
-    MK_LAUNCH(g, "k_compact");
+  // Tombstones exist only where deletes with seq > clean_seq left them.  When the log still
+  // holds all of those, only their chains are visited, unless they are so many that a sweep
+  // over every chain in memory order costs less.
+  const uint64_t last = g->next_seq - 1;
+  uint64_t ops = 0, heads = 0;
+  for (const BatchRec& b : g->batches)
+    if (b.kind == kDeleteBatch && b.seq > g->clean_seq) ops += b.n;
+  for (const ViewHost& vh : g->view) heads += vh.on ? vh.n_head : 0;
+  const bool by_log = !g->captured_update && g->dropped_seq <= g->clean_seq && kCompactLogRatio * ops <= heads;
+  ChainBits cb{};
+  uint64_t words = 1;
+  for (int v = 0; v < 3; ++v)
+    if (g->view[v].on && by_log && ops) {
+      cb.bits[v] = g->view[v].chain_bits;
+      cb.words[v] = (g->view[v].n_head + 31) / 32;
+      words = std::max(words, cb.words[v]);
+    }
+  hipLaunchKernelGGL(k_compact_begin, dim3(grid_stride_blocks(words, 1024), 3), dim3(kBlock), 0, stream, dv(g, VF),
+                     dv(g, VR), dv(g, VU), g->cfg.views, cb, freed);
+  if (by_log) {
+    for (const BatchRec& b : g->batches)
+      if (b.kind == kDeleteBatch && b.seq > g->clean_seq) {
+        const uint64_t pairs = 4 * b.n;  // <op, table>; 2048 blocks fill the chip
+        const uint32_t rounds =
+            (uint32_t)std::min<uint64_t>(kCompactRound, std::max<uint64_t>(1, pairs / (2048 * kGroupsPerBlock)));
+        hipLaunchKernelGGL(k_compact_log, dim3((uint32_t)((pairs + kGroupsPerBlock * rounds - 1) / (kGroupsPerBlock * rounds))),
+                           dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR), dv(g, VU), g->cfg.views, log_at(g, b.off),
+                           b.n, g->n, min_tombstones, rounds, cb, freed, g->upd_mark);
+      }
+  } else {
+    for (int v = 0; v < 3; ++v) {
+      const ViewHost& vh = g->view[v];
+      if (!vh.on) continue;
+      hipLaunchKernelGGL(k_compact, dim3(std::min<uint32_t>(grid_for_groups(vh.n_head), kSweepBlocks)), dim3(kBlock),
+                         0, stream, vh.d, v, vh.n_head, g->n, min_tombstones, freed,
+                         v == VF ? g->upd_mark : nullptr);
+    }
   }
-  MK_HIP(g, hipMemcpyAsync(g->h_pin + 10, freed, 8, hipMemcpyDeviceToHost, stream));
-  mk_status st = refresh_pool(g, stream);
+  MK_LAUNCH(g, "k_compact");
+  mk_status st = refresh_pool(g, stream, freed, h_freed);
   if (st != MK_OK) return st;
-  *h_freed = g->h_pin[10];
+  if (min_tombstones <= 1) g->clean_seq = last;  // no chain holds a tombstone now
   return MK_OK;
 }
 

@@ -46,6 +46,7 @@ struct ViewHost {
   uint32_t* pair_i = nullptr;
   uint32_t* pair_off = nullptr;
   bool pairs_ok = false;
+  uint32_t* chain_bits = nullptr;  // a bit per head slab: chains claimed by a running compaction
 };
 
 struct AlgoState {
@@ -77,7 +78,8 @@ struct Counters {          // device-side scalars, one 4 KiB block
   double feat[6];          // batch-feature sums
   uint32_t feat_max[2];    // batch-feature maxima
   uint32_t snap[16];       // pool snapshot staging: view v's bump, free-end and free-take
-                           // counters at [4v, 4v+3), the overflow bits at [12]
+                           // counters at [4v, 4v+3), the overflow bits at [12], a 64-bit
+                           // value that a synchronizing call wants as well at [14, 15]
   float mlp_x[16];         // features of an MK_AUTO decision (MK_MLP_IN used)
   float mlp_y[4];          // the cost model's outputs for them (MK_MLP_OUT used)
 };
@@ -109,6 +111,8 @@ struct mk_graph {
   std::deque<mk::BatchRec> batches;
   uint64_t next_seq = 1;      // seq of the next applied batch
   uint64_t dropped_seq = 0;   // batches with seq <= dropped_seq are no longer in the log
+  uint64_t clean_seq = 0;     // deletes with seq <= clean_seq left no tombstone (compacted)
+  bool captured_update = false;  // an update was captured: its replays are not in the log
 
   // traversal scratch
   mk::Counters* ctr = nullptr;

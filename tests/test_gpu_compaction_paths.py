@@ -1,0 +1,72 @@
+"""Compaction by the logged deletes and by a sweep over every chain give the same graph."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_17813_amd import inputs as I
+from paper_2305_17813_amd import native
+from parity import Pair, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("views", [1, 3, 5, 7])
+@pytest.mark.parametrize("load_factor", [0.7, 0.0])
+def test_logged_deletes_and_full_sweep_agree(views, load_factor):
+    """Two copies of a graph take the same batches.  One copy's change log holds every batch
+    (the logged deletes' chains are visited), the other's only the last one (every chain is
+    swept).  Both free the same number of slabs, leave no tombstone behind and hold the
+    oracle's arcs; batches with repeated arcs, absent arcs and both directions of an edge are
+    among them, and thresholds above one come before a threshold of one."""
+    say(f"case: compaction paths, views {views}, load factor {load_factor}")
+    g = I.rmat_s(11)
+    s0, d0, w0 = g.src, g.dst, g.w
+    # both copies build in chunks that fit their logs; chunking does not change what a chain holds
+    a = Pair(g.n, s0, d0, w0, views=views, load_factor=load_factor, log_capacity=1 << 20)
+    b = Pair(g.n, s0, d0, w0, views=views, load_factor=load_factor, log_capacity=4001)
+    rng = np.random.default_rng(5)
+    arcs = np.stack([s0.numpy(), d0.numpy()], 1)
+    for thresholds in ([3, 1], [1, 1], [2, 1]):
+        picks = arcs[rng.permutation(len(arcs))[:3000]]
+        batch1 = np.concatenate([picks[:2000], picks[:500, ::-1], picks[:200]])  # reversed and repeated arcs
+        batch2 = picks[1500:]
+        for p in (a, b):
+            for q in (batch1, batch2):
+                p.delete(torch.as_tensor(q[:, 0].copy()), torch.as_tensor(q[:, 1].copy()), exact_status=False)
+        for t in thresholds:
+            fa, fb = a.g.compact(t), b.g.compact(t)
+            assert fa == fb, (fa, fb)
+            assert a.g.stats()["pool_used"] == b.g.stats()["pool_used"]
+        assert a.g.compact() == 0
+        a.check_structure()
+        b.check_structure()
+        w = torch.as_tensor(I.arc_weight(torch.as_tensor(picks[:, 0].copy()), torch.as_tensor(picks[:, 1].copy()),
+                                         g.wmax, g.wseed))
+        for p in (a, b):
+            p.insert(torch.as_tensor(picks[:, 0].copy()), torch.as_tensor(picks[:, 1].copy()), w)
+    a.check_all(algos=("bfs", "sssp", "wcc"))
+
+
+def test_replayed_deletes_are_reclaimed():
+    """A captured delete that is replayed with other arcs leaves tombstones the log does not
+    name: compaction sweeps every chain then, and reclaims all of them."""
+    say("case: compaction after replayed deletes")
+    n = 2000
+    dst = np.arange(1, 1801)
+    p = Pair(n, np.zeros(1800, np.int64), dst, np.full(1800, 3), load_factor=0.0, views=native.VIEW_FWD)
+    s = torch.zeros(600, dtype=torch.int32, device="cuda")
+    d = torch.as_tensor(dst[:600], dtype=torch.int32, device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        p.g.delete_edges(s, d, status=False, stream=stream)
+    for k in range(2):  # deletes 1..600, then 601..1200
+        d.copy_(torch.as_tensor(dst[600 * k:600 * (k + 1)], dtype=torch.int32))
+        graph.replay()
+        torch.cuda.synchronize()
+        p.o.delete(np.zeros(600, np.uint32), dst[600 * k:600 * (k + 1)].astype(np.uint32))
+    # one chain of 120 slabs keeps 600 arcs: 40 slabs, the head among them
+    assert p.g.compact() == 80
+    p.check_structure()
+    assert p.g.compact() == 0
