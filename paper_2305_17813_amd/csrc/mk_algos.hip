@@ -844,11 +844,6 @@ __global__ void k_pr_final(const Counters* C, const float* a, const float* b, fl
 }
 
 // ================================================================= triangle counting
-__device__ inline bool ranks_before(const uint32_t* deg, uint32_t a, uint32_t b) {
-  const uint32_t da = deg[a], db = deg[b];
-  return da < db || (da == db && a < b);
-}
-
 // |N(a) intersect N(b)| counted by the calling group: walk N(a), each lane probes its
 // neighbour in b's table.  Returns the group total in every lane.
 __device__ inline uint64_t group_intersect(const DView& U, uint32_t a, uint32_t b) {
@@ -859,35 +854,6 @@ __device__ inline uint64_t group_intersect(const DView& U, uint32_t a, uint32_t 
     if (data && valid_key(k) && k != b) c += lane_has(U, tb, k);
   });
   return gsum_u64(c);
-}
-
-// Static count: every undirected edge {u, v} once, from its lower-(degree, id) end.
-__global__ void __launch_bounds__(kBlock) k_tc_static(DView U, uint32_t nv, const uint32_t* heavy,
-                                                      const uint32_t* nheavy,
-                                                      unsigned long long* acc) {
-  uint64_t local = 0;
-  auto per_vertex = [&](uint32_t u, uint32_t b0, uint32_t stride) {
-    for_each_slab_strided(U, u, b0, stride, [&](uint64_t x, bool data) {
-      const uint32_t v = (uint32_t)x;
-      uint32_t todo = gballot(data && valid_key(v) && ranks_before(U.deg, u, v));
-      while (todo) {
-        const int l = __builtin_ctz(todo);
-        todo &= todo - 1;
-        const uint32_t vv = gbcast(v, l);
-        const uint64_t c = group_intersect(U, u, vv);
-        if (glane() == 0) local += c;
-      }
-    });
-  };
-  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
-  const uint32_t ng = gridDim.x * kGroupsPerBlock;
-  for (uint32_t u = g0; u < nv; u += ng) {
-    if (U.nbk[u] > kHeavyBuckets || U.deg[u] < 2) continue;
-    per_vertex(u, 0, 1);
-  }
-  const uint32_t nh = *nheavy, gib = threadIdx.x / kGroup;
-  for (uint32_t j = blockIdx.x; j < nh; j += gridDim.x) per_vertex(heavy[j], gib, kGroupsPerBlock);
-  if (glane() == 0 && local) atomicAdd(acc, (unsigned long long)local);
 }
 
 // Keys of the batch graph: both directions of each effective undirected change, or a
@@ -1563,20 +1529,327 @@ __global__ void __launch_bounds__(HubClass<Small>::kThreads) k_tc_hub(DView U, c
   }
 }
 
+// ---------------------------------------------------------------- static count
+// Every undirected edge is directed from its lower (degree, id) end to its higher one; A(u) are
+// the out-neighbours of u in that orientation (at most sqrt(2 m) of them, however large the
+// degree).  A triangle is counted once, at its lowest vertex u: for every v in A(u), the keys
+// of A(v) that lie in A(u).  k_tc_orient copies the A(u) out of the slabs into packed lists;
+// the counting kernels hold A(u) in an LDS hash set and stream the lists of its members, 64
+// keys to a wave, one bucket read per key.
+//
+// What bounds it: the streamed keys, sum over directed edges of |A(v)| (660M at R-MAT scale 18),
+// which the LDS reads (16 bytes per key) and the vector compares handle at about the rate the
+// caches deliver them.  Walking slabs and probing the other end's slab table, a 128-byte read
+// per key, took 39.5 ms at scale 18 and 1.38 s at scale 22; this takes 1.7 and 59 ms.
+__global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, const uint32_t* heavy, const uint32_t* nheavy,
+                                                      const uint64_t* off, uint32_t* list, uint32_t* dplus) {
+  __shared__ uint32_t cur;
+  const uint32_t ln = threadIdx.x & 63;
+  // u's out-neighbours among the words of one slab: bit j for word j
+  auto higher = [&](uint32_t u, uint32_t du, const Slab& sl, int nd) -> uint32_t {
+    uint32_t dv[kKeysPerSlab], keep = 0;
+#pragma unroll
+    for (int j = 0; j < kKeysPerSlab; ++j) {
+      const uint32_t v = (uint32_t)sl.w[j];
+      dv[j] = j < nd && valid_key(v) ? U.deg[v] : 0u;  // a neighbour has a degree of at least 1
+    }
+#pragma unroll
+    for (int j = 0; j < kKeysPerSlab; ++j)
+      if (dv[j] > du || (dv[j] == du && (uint32_t)sl.w[j] > u)) keep |= 1u << j;
+    return keep;
+  };
+  // vertices of more than kHeavyBuckets buckets first (the longest): a block each, a lane per chain
+  const uint32_t nh = *nheavy;
+  for (uint32_t i = blockIdx.x; i < nh; i += gridDim.x) {
+    const uint32_t u = heavy[i], du = U.deg[u];
+    __syncthreads();
+    if (threadIdx.x == 0) cur = 0;
+    __syncthreads();
+    const uint32_t nb = (uint32_t)(ld_word(slab_ptr(U, u) + 15) >> 32), xb = (uint32_t)ld_word(slab_ptr(U, u) + 14);
+    uint32_t* out = list + off[u];
+    for (uint32_t b0 = 0; b0 < nb; b0 += kBlock) {
+      const uint32_t b = b0 + threadIdx.x;
+      uint32_t s = b >= nb ? kInvalid : b ? xb + b - 1 : u;
+      int nd = b ? kKeysPerSlab : kKeysPerSlab - 1;
+      while (__ballot(s != kInvalid) != 0) {  // wave-uniform
+        Slab sl;
+        uint32_t keep = 0;
+        if (s != kInvalid) {
+          load_slab(U, s, sl);
+          keep = higher(u, du, sl, nd);
+          s = (uint32_t)sl.w[15];
+          nd = kKeysPerSlab;
+        }
+        const uint32_t n = (uint32_t)__popc(keep);
+        uint32_t excl = 0, total = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint64_t m = __ballot((n >> k) & 1u);
+          excl += lanes_below(m) << k;
+          total += (uint32_t)__popcll(m) << k;
+        }
+        uint32_t base = 0;
+        if (ln == 0 && total) base = atomicAdd(&cur, total);
+        base = __shfl(base, 0) + excl;
+#pragma unroll
+        for (int j = 0; j < kKeysPerSlab; ++j)
+          if (keep >> j & 1) out[base++] = (uint32_t)sl.w[j];
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) dplus[u] = cur;
+  }
+  // single-bucket vertices: a lane each
+  for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < nv; u += gridDim.x * kBlock) {
+    if (U.nbk[u] != 1) continue;
+    const uint32_t du = U.deg[u];
+    uint32_t n = 0;
+    if (du) {
+      uint32_t* out = list + off[u];
+      Slab sl;
+      uint32_t s = u;
+      while (true) {
+        load_slab(U, s, sl);
+        const uint32_t keep = higher(u, du, sl, kKeysPerSlab);
+#pragma unroll
+        for (int j = 0; j < kKeysPerSlab; ++j)
+          if (keep >> j & 1) out[n++] = (uint32_t)sl.w[j];
+        s = (uint32_t)sl.w[15];
+        if (s == kInvalid) break;
+      }
+    }
+    dplus[u] = n;
+  }
+  // 2 .. kHeavyBuckets buckets: a 16-lane group each
+  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
+  const uint32_t ng = gridDim.x * kGroupsPerBlock;
+  for (uint32_t u = g0; u < nv; u += ng) {
+    const uint32_t nb = U.nbk[u];
+    if (nb == 1 || nb > kHeavyBuckets) continue;
+    const uint32_t du = U.deg[u];
+    uint32_t* out = list + off[u];
+    uint32_t n = 0;  // the same in every lane of the group
+    for_each_slab(U, u, [&](uint64_t x, bool data) {
+      const uint32_t v = (uint32_t)x;
+      bool keep = false;
+      if (data && valid_key(v)) {
+        const uint32_t dv = U.deg[v];
+        keep = dv > du || (dv == du && v > u);
+      }
+      const uint32_t m = gballot(keep);
+      if (keep) out[n + __popc(m & ((1u << glane()) - 1u))] = v;
+      n += __popc(m);
+    });
+    if (glane() == 0) dplus[u] = n;
+  }
+}
+
+// Classes of vertices by |A(u)| (a vertex with fewer than two out-neighbours closes no
+// triangle): a wave, a 256-thread block or a 1024-thread block to a vertex, with LDS sets that
+// keep the classes at full occupancy; only the last needs several passes for the largest sets.
+// A set has at least 3.2 slots per key, so that a key's first bucket is rarely full.
+constexpr uint32_t kTcWaveKeys = 64, kTcWaveSlots = 256;
+template <bool Mid>
+struct CountClass {
+  static constexpr uint32_t kThreads = Mid ? 256 : 1024;
+  static constexpr uint32_t kSlots = Mid ? 2048 : 16384;
+  static constexpr uint32_t kKeys = kSlots * 5 / 16;
+  static constexpr uint32_t kBlocks = Mid ? 2048 : 512;
+};
+
+__global__ void k_tc_classes(const uint32_t* dplus, uint32_t nv, uint32_t* q0, uint32_t* q1, uint32_t* q2,
+                             uint32_t* cnt) {
+  __shared__ Stage S[3];
+  stage_open(S[0], q0, cnt);
+  stage_open(S[1], q1, cnt + 1);
+  stage_open(S[2], q2, cnt + 2);
+  __syncthreads();
+  const uint32_t stride = gridDim.x * blockDim.x;
+  for (uint32_t base = blockIdx.x * blockDim.x; base < nv; base += stride) {
+    const uint32_t v = base + threadIdx.x;
+    const uint32_t d = v < nv ? dplus[v] : 0u;
+    stage_push(S[0], d >= 2 && d <= kTcWaveKeys, v);
+    stage_push(S[1], d > kTcWaveKeys && d <= CountClass<true>::kKeys, v);
+    stage_push(S[2], d > CountClass<true>::kKeys, v);
+  }
+  stage_close(S);
+}
+
+// The keys of up to 64 packed lists (lane i of the wave holds the start and the length of list i)
+// that lie in the LDS set.  kTcLists lists are read side by side, with loads whose indexes are
+// clamped into the list instead of masked, so that a wave has that many loads and then bucket
+// reads in flight; keys whose first bucket is full are probed further afterwards, together.
+// (8 in the block classes, 4 in the wave class, whose short sets make a longer round waste slots.)
+template <uint32_t kTcLists>
+__device__ inline uint32_t tc_stream(const uint32_t* __restrict__ list, uint64_t poff, uint32_t plen, uint32_t np,
+                                     const uint4* tab4, uint32_t bmask) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t* tab = reinterpret_cast<const uint32_t*>(tab4);
+  uint32_t hits = 0;
+  for (uint32_t j = 0; j < np; j += kTcLists) {
+    const uint32_t* src[kTcLists];
+    uint32_t len[kTcLists], most = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kTcLists; ++k) {
+      const int from = (int)min(j + k, np - 1);
+      const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)poff, from);
+      const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(poff >> 32), from);
+      src[k] = list + (((uint64_t)hi << 32) | lo);
+      len[k] = j + k < np ? __builtin_amdgcn_readlane(plen, from) : 0u;
+      most = max(most, len[k]);
+    }
+    for (uint32_t c = 0; c < most; c += 64) {
+      uint32_t x[kTcLists], h[kTcLists];
+      // an empty list's vertex still has a degree, so its segment has a first entry to read
+#pragma unroll
+      for (uint32_t k = 0; k < kTcLists; ++k) x[k] = src[k][min(c + lane, max(len[k], 1u) - 1u)];
+      uint32_t pend = 0;
+#pragma unroll
+      for (uint32_t k0 = 0; k0 < kTcLists; k0 += 4) {  // four bucket reads at a time (registers)
+        uint4 q[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+          h[k0 + i] = tc_bucket(x[k0 + i], bmask);
+          q[i] = tab4[h[k0 + i]];
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+          const uint32_t k = k0 + i, y = x[k];
+          const bool in = c + lane < len[k];
+          const bool hit = (q[i].x == y) | (q[i].y == y) | (q[i].z == y) | (q[i].w == y);
+          // slots of a bucket fill in order, so a bucket is full when its last slot is taken
+          hits += in & hit;
+          pend |= (uint32_t)(in & !hit & (q[i].w != kInvalid)) << k;
+        }
+      }
+      while (pend) {
+        const uint32_t k = __builtin_ctz(pend);
+        pend &= pend - 1;
+        uint32_t y = x[0], hh = h[0];
+#pragma unroll
+        for (uint32_t i = 1; i < kTcLists; ++i)
+          if (i == k) {
+            y = x[i];
+            hh = h[i];
+          }
+        hits += lds_has_from(tab, bmask, y, (hh + 1) & bmask);
+      }
+    }
+  }
+  return hits;
+}
+
+__device__ inline void tc_total(uint64_t local, unsigned long long* acc) {
+  for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
+  if ((threadIdx.x & 63) == 0 && local) atomicAdd(acc, (unsigned long long)local);
+}
+
+__global__ void __launch_bounds__(kBlock) k_tc_count_wave(const uint32_t* __restrict__ list, const uint64_t* __restrict__ off,
+                                                          const uint32_t* __restrict__ dplus, const uint32_t* q,
+                                                          const uint32_t* nq, unsigned long long* acc) {
+  __shared__ uint4 tabs[kBlock / 64][kTcWaveSlots / 4];
+  static_assert(kTcWaveSlots / 4 == 64 && kTcWaveKeys == 64, "a lane clears a bucket and holds a key");
+  const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63, n = *nq;
+  uint4* tab4 = tabs[w];
+  constexpr uint32_t bmask = kTcWaveSlots / 4 - 1;
+  uint64_t local = 0;
+  for (uint32_t i = blockIdx.x * (kBlock / 64) + w; i < n; i += gridDim.x * (kBlock / 64)) {
+    const uint32_t u = q[i], d = __builtin_amdgcn_readfirstlane(dplus[u]);
+    tab4[lane] = make_uint4(kInvalid, kInvalid, kInvalid, kInvalid);
+    const uint32_t key = lane < d ? list[off[u] + lane] : kInvalid;
+    const uint32_t plen = lane < d ? dplus[key] : 0u;
+    const uint64_t poff = lane < d ? off[key] : 0u;
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+    if (lane < d) lds_insert(reinterpret_cast<uint32_t*>(tab4), bmask, key);  // at most 64 keys in 256 slots
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+    local += tc_stream<4>(list, poff, plen, d, tab4, bmask);
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+  }
+  tc_total(local, acc);
+}
+
+template <bool Mid>
+__global__ void __launch_bounds__(CountClass<Mid>::kThreads) k_tc_count_block(DView U, const uint32_t* __restrict__ list,
+                                                                              const uint64_t* __restrict__ off,
+                                                                              const uint32_t* __restrict__ dplus,
+                                                                              const uint32_t* q, const uint32_t* nq,
+                                                                              unsigned long long* acc) {
+  using H = CountClass<Mid>;
+  constexpr uint32_t kWaves = H::kThreads / 64;
+  __shared__ uint4 tab4[H::kSlots / 4];
+  __shared__ uint32_t full;  // a key found no free slot: this pass looks keys up in u's slabs
+  uint32_t* tab = reinterpret_cast<uint32_t*>(tab4);
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = *nq;
+  uint64_t local = 0;
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const uint32_t u = q[i], d = __builtin_amdgcn_readfirstlane(dplus[u]);
+    const uint32_t* mine = list + off[u];
+    // passes: pass p holds the keys whose partition hash is p, at most kKeys of them on average
+    // (kSlots / kKeys = 3.2 leaves room for an uneven split)
+    const uint32_t P = (d + H::kKeys - 1) / H::kKeys;
+    uint32_t slots = 256;
+    while (slots < H::kSlots && slots * 5 < (d + P - 1) / P * 16) slots <<= 1;
+    const uint32_t bmask = slots / 4 - 1;
+    for (uint32_t p = 0; p < P; ++p) {
+      __syncthreads();  // the last set is no longer read
+      for (uint32_t k = threadIdx.x; k < slots / 4; k += H::kThreads)
+        tab4[k] = make_uint4(kInvalid, kInvalid, kInvalid, kInvalid);
+      if (threadIdx.x == 0) full = 0;
+      __syncthreads();
+      for (uint32_t k = threadIdx.x; k < d; k += H::kThreads) {
+        const uint32_t key = mine[k];
+        if ((P == 1 || tc_part(key, P) == p) && !lds_insert(tab, bmask, key)) full = 1;
+      }
+      __syncthreads();
+      if (full) {  // only an adversarial choice of ids splits this unevenly
+        // a key of A(v) ranks above v and so above u: it lies in A(u) when it is u's neighbour
+        const Table tu = group_table(U, u);
+        for (uint32_t j = 0; j < d; ++j) {
+          const uint32_t v = mine[j], len = dplus[v];
+          for (uint32_t c = threadIdx.x; c < len; c += H::kThreads) {
+            const uint32_t x = list[off[v] + c];
+            if (tc_part(x, P) == p) local += lane_has(U, tu, x);
+          }
+        }
+        continue;
+      }
+      // the lists of A(u)'s members, dealt to the waves in turn: wave w takes members w, w + kWaves ...
+      for (uint32_t j0 = 0; j0 < d; j0 += H::kThreads) {
+        const uint32_t j = j0 + lane * kWaves + w;
+        uint32_t plen = 0;
+        uint64_t poff = 0;
+        if (j < d) {
+          const uint32_t key = mine[j];
+          plen = dplus[key];
+          poff = off[key];
+        }
+        const uint32_t np = d - j0 > w ? min(64u, (d - j0 - w + kWaves - 1) / kWaves) : 0u;
+        local += tc_stream<8>(list, poff, plen, np, tab4, bmask);
+      }
+    }
+  }
+  tc_total(local, acc);
+}
+
 __global__ void k_tc_begin(Counters* C, bool reset_total) {
   if (threadIdx.x != 0) return;
   C->tc_s[0] = C->tc_s[1] = C->tc_s[2] = 0;
   C->u64tmp[0] = 0;
+  C->n_heavy_tc = 0;
+  C->tc_class[0] = C->tc_class[1] = C->tc_class[2] = 0;
   if (reset_total) C->tc_total = 0;
 }
 
-// insert: T += (S1 - S2 + S3/3) / 2;  delete: T -= (S1 + S2 + S3/3) / 2;  static: T = sum / 3
+// insert: T += (S1 - S2 + S3/3) / 2;  delete: T -= (S1 + S2 + S3/3) / 2;  static: T = the sum
 __global__ void k_tc_finish(Counters* C, int kind, unsigned long long* out) {
   if (threadIdx.x != 0) return;
   const unsigned long long s1 = C->tc_s[0], s2 = C->tc_s[1], s3 = C->tc_s[2];
   if (kind == 0) C->tc_total += (s1 - s2 + s3 / 3) / 2;
   else if (kind == 1) C->tc_total -= (s1 + s2 + s3 / 3) / 2;
-  else C->tc_total = C->u64tmp[0] / 3;
+  else if (kind == 2) C->tc_total = C->u64tmp[0];
   if (out) *out = C->tc_total;
 }
 
@@ -1856,12 +2129,24 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
   unsigned long long* out = reinterpret_cast<unsigned long long*>(d_count);
   if (full) {
     uint32_t* nh = &g->ctr->n_heavy_tc;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, nh, 1u);
-    hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U.nbk, N,
-                       g->fq[2], nh);
+    uint32_t *dplus = g->fq[0], *heavy = g->fq[4], *cls = g->ctr->tc_class;  // scratch: the traversal queues
+    uint32_t* q[3] = {g->fq[1], g->fq[2], g->fq[3]};
     hipLaunchKernelGGL(k_tc_begin, dim3(1), dim3(64), 0, stream, g->ctr, true);
-    hipLaunchKernelGGL(k_tc_static, dim3(kWalkBlocks), dim3(kBlock), 0, stream, U, N, g->fq[2], nh,
-                       &g->ctr->u64tmp[0]);
+    hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U.nbk, N, heavy, nh);
+    size_t tb = g->scan_tmp_bytes;
+    if (rocprim::exclusive_scan(g->scan_tmp, tb, U.deg, g->tc_off, (uint64_t)0, (size_t)N, rocprim::plus<uint64_t>(),
+                                stream) != hipSuccess)
+      return MK_ERR_HIP;
+    hipLaunchKernelGGL(k_tc_orient, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U, N, heavy, nh, g->tc_off,
+                       g->tc_list, dplus);
+    hipLaunchKernelGGL(k_tc_classes, dim3(blocks_for(N, 1024)), dim3(kBlock), 0, stream, dplus, N, q[0], q[1], q[2], cls);
+    unsigned long long* sum = &g->ctr->u64tmp[0];
+    hipLaunchKernelGGL(k_tc_count_block<false>, dim3(CountClass<false>::kBlocks), dim3(CountClass<false>::kThreads), 0,
+                       stream, U, g->tc_list, g->tc_off, dplus, q[2], cls + 2, sum);
+    hipLaunchKernelGGL(k_tc_count_block<true>, dim3(CountClass<true>::kBlocks), dim3(CountClass<true>::kThreads), 0,
+                       stream, U, g->tc_list, g->tc_off, dplus, q[1], cls + 1, sum);
+    hipLaunchKernelGGL(k_tc_count_wave, dim3(blocks_for((uint64_t)N * 64)), dim3(kBlock), 0, stream, g->tc_list,
+                       g->tc_off, dplus, q[0], cls, sum);
     hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 2, out);
   } else if (p.list.empty()) {
     hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 3, out);

@@ -65,6 +65,7 @@ struct Counters {          // device-side scalars, one 4 KiB block
   uint32_t n_heavy_pr;     // the same for the PageRank pull (reverse view)
   uint32_t n_heavy_tc;     // the same for the static triangle count (undirected view)
   uint32_t tc_work;        // next hub work item of the triangle batch update
+  uint32_t tc_class[3];    // static triangle count: vertices per class
   uint32_t n_listed_light; // vertices listed for an incremental WCC pass: up to 16 buckets,
   uint32_t n_listed_heavy; //   and more (these two are cleared together)
   uint32_t wcc_big;        // root of the sampled largest component of a static WCC

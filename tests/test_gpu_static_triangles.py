@@ -1,0 +1,45 @@
+"""The static triangle count at the edges of its vertex classes, against closed forms."""
+from math import comb
+
+import pytest
+import torch
+
+from paper_2305_17813_amd import inputs as I
+from paper_2305_17813_amd import native
+from parity import Pair, say
+
+pytestmark = pytest.mark.gpu
+
+
+# K_n has vertices of every out-degree below n in the degree order: around the wave class's 64
+# keys, the 256-thread class's 640 and one pass of the largest class (5,120 keys)
+@pytest.mark.parametrize("n", [3, 64, 65, 66, 67, 640, 641, 642, 5200])
+def test_complete_graph(n):
+    say(f"case: static triangles of K_{n}")
+    u, v = torch.triu_indices(n, n, 1, device="cuda")
+    views = native.VIEW_FWD | native.VIEW_UND
+    g = native.Graph(n + 2, u, v, views=views)  # and two isolated vertices
+    assert int(g.triangles(mode=native.RECOMPUTE).item()) == comb(n, 3)
+    if n <= 642:  # a vertex joined to all, then one edge gone: exact after updates and recounts
+        s = torch.full((n,), n, device="cuda")
+        g.insert_edges(s, torch.arange(n, device="cuda"))
+        assert int(g.triangles().item()) == comb(n + 1, 3)
+        assert int(g.triangles(mode=native.RECOMPUTE).item()) == comb(n + 1, 3)
+        g.delete_edges(s[:1], torch.zeros(1, dtype=torch.int64, device="cuda"))
+        assert int(g.triangles(mode=native.RECOMPUTE).item()) == comb(n + 1, 3) - (n - 1)
+
+
+@pytest.mark.parametrize("load_factor", [0.7, 0.0])
+def test_power_law_graph_with_long_chains(load_factor):
+    """Against the oracle, with hashing on and off (chains of many slabs) and tombstones; a
+    repeated call without a pending batch, with other calls between, repeats its answer."""
+    say(f"case: static triangles, load factor {load_factor}")
+    g = I.rmat_s(11)
+    p = Pair(g.n, g.src, g.dst, g.w, load_factor=load_factor)
+    p.check_tc()
+    s, d = I.Workload(g, 3).delete_batch(2000)
+    p.delete(s, d)
+    p.check_tc()
+    p.g.stats()
+    p.check_tc()
+    p.check_tc(native.RECOMPUTE)
