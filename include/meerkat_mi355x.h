@@ -252,11 +252,10 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
  * list of all <vertex, bucket> pairs (built once from one exclusive scan of the bucket
  * counts, which never change after creation); a per-vertex pass then adds the buckets'
  * partial results in bucket order.
- * PACKED (the default; not in the paper) is SCHEME1 for WCC.  For PageRank its first
- * iteration of a call walks the slabs as SCHEME1 does and also packs every vertex's in-arc
- * keys into one array (segments at the exclusive scan of the in-degrees, room for every
- * data word of the reverse view in the arena); the call's later iterations read those 4-byte
- * keys instead of 128-byte slabs.
+ * PACKED (the default; not in the paper) is SCHEME1 for WCC.  For PageRank a call first packs
+ * every vertex's in-arc sources into one array (segments at the exclusive scan of the
+ * in-degrees, room for every data word of the reverse view in the arena); its iterations read
+ * those 4-byte entries, cut into tiles of equal work, instead of 128-byte slabs.
  * The scheme applies to the PageRank pull over the reverse view and to the union over every
  * arc of a static (or naive incremental) WCC.  Results are the same under every scheme
  * (PageRank within its tolerance).  MK_ERR_INVALID_ARG for an unknown scheme. */

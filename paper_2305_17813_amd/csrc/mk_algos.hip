@@ -22,7 +22,7 @@ constexpr uint32_t kWalkBlocks = 4096;
 constexpr uint32_t kPrContribBlocks = 2048, kPrFinalBlocks = 512;
 static_assert(kPrContribBlocks + kWalkBlocks + kPrFinalBlocks <= kPrParts, "PageRank partial sums");
 constexpr uint32_t kPrChunk = 4;  // buckets per heavy-vertex work item
-constexpr uint32_t kPrBatch = 8;  // head slabs a group loads at once in the PageRank pull
+constexpr uint32_t kPrBatch = 8;  // head slabs a group loads at once in the PageRank kernels
 constexpr int kPrSyncEvery = 4;
 
 inline uint32_t blocks_for(uint64_t n, uint32_t cap = 4096) {
@@ -398,23 +398,17 @@ __global__ void k_pr_fill(float* x, uint32_t nv, float v) {
 
 // Contribution per vertex C[u] = PR[u] / out[u] (the FindContributionPerVertex kernel),
 // plus the FP64 sum of the ranks of zero-out-degree vertices (FindTeleportProb).
-//
-// With `cr` (the packing iteration), the contribution goes beside the vertex's hot-first rank,
-// cr[v] = <rank[v], contribution bits>, so the packing pull reads both with one 8-byte load.
 __global__ void __launch_bounds__(kBlock) k_pr_contrib(const float* __restrict__ x,
                                                        const uint32_t* __restrict__ outdeg,
                                                        float* __restrict__ c, uint32_t nv,
-                                                       double* dpart, const uint32_t* state,
-                                                       const uint32_t* __restrict__ rank, uint2* __restrict__ cr) {
+                                                       double* dpart, const uint32_t* state) {
   __shared__ double lds[kBlock / 64];
   if (state[0]) return;
   double local = 0;
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
     const uint32_t o = outdeg[v];
     const float xv = x[v];
-    const float cv = o ? xv / (float)o : 0.f;
-    if (cr) cr[v] = make_uint2(rank[v], __float_as_uint(cv));
-    else c[v] = cv;
+    c[v] = o ? xv / (float)o : 0.f;
     if (!o) local += xv;
   }
   const double s = block_sum(local, lds);
@@ -441,56 +435,31 @@ __global__ void __launch_bounds__(kBlock) k_pr_sum(const double* part, uint32_t 
 
 // Pull over in-arcs (reverse view): PR'[v] = (1-d)/N + d * (sum C[u] + dangling/N),
 // and the FP64 L1 change sum |PR'[v] - PR[v]|.
-// With `list`, the pull also packs every vertex's in-arc sources, as their ranks in the
-// hot-first order (rank[u]), into list[off[v] .. off[v] + deg[v]) for the packed iterations
-// (k_pr_pull): single-bucket and 2..16-bucket vertices in slab order, heavy vertices in the
-// order their work items reserve room at cur[j] (so their keys' order, and the last bits of
-// their FP64 sums, can vary between runs).
 __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __restrict__ c,
                                                       const float* __restrict__ x,
                                                       float* __restrict__ y, uint32_t nv, float damping,
                                                       const double* dang, double* delta,
                                                       const uint32_t* heavy, const uint32_t* nheavy,
                                                       const uint32_t* hcnt, const uint32_t* hoff,
-                                                      double* hacc, const uint32_t* state,
-                                                      uint32_t* __restrict__ list, const uint32_t* __restrict__ off,
-                                                      uint32_t* cur, const uint2* __restrict__ cr) {
+                                                      double* hacc, const uint32_t* state) {
   __shared__ double lds[kBlock / 64];
   if (state[0]) return;
   const double base = (1.0 - (double)damping) / nv + (double)damping * (*dang) / nv;
   double local = 0;
-  // u's contribution, and with `list` its hot-first rank r (both from one load of cr[u])
-  auto term = [&](uint32_t u, uint32_t& r) -> float {
-    if (list) {
-      const uint2 q = cr[u];
-      r = q.x;
-      return __uint_as_float(q.y);
-    }
-    r = 0;
-    return c[u];
-  };
   // single-bucket vertices (most of a power-law graph): one lane per vertex, so a wave keeps
   // 64 slab reads and their gathers in flight
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
     if (R.nbk[v] != 1) continue;
     double s = 0;
-    const uint32_t dv = R.deg[v];
-    if (dv != 0) {  // vertices without in-arcs need no slab read
+    if (R.deg[v] != 0) {  // vertices without in-arcs need no slab read
       Slab sl;
       uint32_t t = v;
-      uint32_t* out = list ? list + off[v] : nullptr;
-      uint32_t n = 0;
       while (true) {
         load_slab(R, t, sl);
 #pragma unroll
         for (int j = 0; j < kKeysPerSlab; ++j) {
           const uint32_t u = (uint32_t)sl.w[j];
-          if (valid_key(u)) {
-            uint32_t r;
-            s += (double)term(u, r);
-            if (out && n < dv) out[n] = r;
-            ++n;
-          }
+          if (valid_key(u)) s += (double)c[u];
         }
         t = (uint32_t)sl.w[15];
         if (t == kInvalid) break;
@@ -512,15 +481,6 @@ __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __re
     const uint64_t x0 = ld_word(slab_ptr(R, v) + gl);
     const uint32_t xb = gbcast((uint32_t)x0, 14);
     double s = 0;
-    uint32_t* out = list ? list + off[v] : nullptr;
-    const uint32_t dv = list ? R.deg[v] : 0u;
-    uint32_t n = 0;  // keys packed so far (the same in every lane of the group)
-    auto pack = [&](bool valid, uint32_t r) {
-      const uint32_t m = gballot(valid);
-      const uint32_t at = n + (uint32_t)__popc(m & ((1u << gl) - 1u));
-      if (valid && at < dv) out[at] = r;
-      n += (uint32_t)__popc(m);
-    };
     for (uint32_t b0 = 0; b0 < nb; b0 += kPrBatch) {
       uint64_t hw[kPrBatch];
 #pragma unroll
@@ -532,9 +492,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __re
       for (uint32_t j = 0; j < kPrBatch; ++j) {
         const uint32_t u = (uint32_t)hw[j];
         const bool data = gl < (b0 + j == 0 ? kKeysPerSlab - 1 : kKeysPerSlab);
-        uint32_t r = 0;
-        if (data && valid_key(u)) s += (double)term(u, r);
-        if (out) pack(data && valid_key(u), r);
+        if (data && valid_key(u)) s += (double)c[u];
       }
 #pragma unroll
       for (uint32_t j = 0; j < kPrBatch; ++j) {  // chained slabs after a full head slab
@@ -543,9 +501,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __re
         if (next == kInvalid) continue;
         walk_chain(R, next, ld_word(slab_ptr(R, next) + gl), kKeysPerSlab, [&](uint64_t w, bool data) {
           const uint32_t u = (uint32_t)w;
-          uint32_t r = 0;
-          if (data && valid_key(u)) s += (double)term(u, r);
-          if (out) pack(data && valid_key(u), r);
+          if (data && valid_key(u)) s += (double)c[u];
         });
       }
     }
@@ -571,19 +527,9 @@ __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __re
       const uint32_t v = heavy[lo];
       const uint32_t b0 = (it - hoff[lo]) * kPrChunk;
       double s = 0;
-      const uint32_t end = list ? off[v] + R.deg[v] : 0u;
       for_each_bucket_range(R, v, b0, b0 + kPrChunk, [&](uint64_t w, bool data) {
         const uint32_t u = (uint32_t)w;
-        const bool valid = data && valid_key(u);
-        uint32_t r = 0;
-        if (valid) s += (double)term(u, r);
-        if (list) {  // room for this slab's keys in v's segment, one reservation per slab
-          const uint32_t m = gballot(valid);
-          uint32_t at = 0;
-          if (glane() == 0 && m) at = atomicAdd(cur + lo, (uint32_t)__popc(m));
-          at = gbcast(at, 0) + (uint32_t)__popc(m & ((1u << glane()) - 1u));
-          if (valid && at < end) list[at] = r;
-        }
+        if (data && valid_key(u)) s += (double)c[u];
       });
       s = gsum(s);
       if (glane() == 0 && s != 0.0) atomicAdd(hacc + lo, s);
@@ -593,137 +539,411 @@ __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __re
   if (threadIdx.x == 0) delta[blockIdx.x] = s;
 }
 
-// PageRank pull over the packed in-arc lists (iterations after the packing one): the same
-// sums as k_pr_gather, reading 4 bytes per in-arc instead of whole slabs.  Each lane issues
-// kPullRound list loads, then their contribution gathers, before it adds them (in list
-// order), so that many gathers are in flight.  Single-bucket vertices take a lane,
-// 2..16-bucket ones a 16-lane group, heavy ones work items of kPullItem in-arcs (partial sums
-// into hacc, as in k_pr_gather).
-constexpr uint32_t kPullRound = 8;
-constexpr uint32_t kPullItem = kGroup * kPullRound * 4;
+// ---------------------------------------------------------------- packed iterations
+// MK_ITER_PACKED.  A call first packs the graph for its iterations:
+//   * the vertices are ordered by out-degree class, largest first (a stable 6-bit radix sort), so
+//     that the sources of most in-arcs come first; everything below is indexed by a vertex's
+//     rank in that order, so that an iteration reads and writes its vectors in place;
+//   * k_pr_pack copies each vertex's in-arc sources, as ranks, out of the slabs into one list,
+//     segment after segment (off = the exclusive scan of the in-degrees);
+//   * the list and the vertices' segment ends are cut into tiles of kPrTile list entries and
+//     segment ends together (merge path), so that every tile is the same work whatever the
+//     degrees: fv[t] is the first vertex whose end lies in tile t or later, and tile t's entries
+//     start at t * kPrTile - fv[t].
+// An iteration (k_pr_flat) gives each wave a tile at a time: 8 consecutive list entries per
+// lane, their contributions gathered at once, an FP64 prefix sum over the tile, and a vertex's
+// sum as the difference of two prefixes.  A segment that runs over tile borders leaves the
+// sum of its last part in heads[t] and of the earlier ones in tails[], which k_pr_fix adds.
+//
+// What bounds an iteration: the random contribution gathers, one request per in-arc to an L2
+// channel.  So each block keeps the first kPrHot contributions in LDS: half of R-MAT scale 22's
+// arcs start there, two thirds of scale 20's.  Scale 22, per iteration: 240 us and 16 us in the
+// two small kernels (a lane or a group per vertex with all gathers through L2: 411 us and 48 us
+// in four small ones).  Of the 240 us, 94 remain without the cold gathers; 324 us are taken with
+// every gather through L2, 271 with 8,000 contributions in LDS.  The packing takes 1.0 ms a
+// call, half of it the rank reads, which have no hot-first order to help them.
+constexpr uint32_t kPrTile = 512;            // list entries and segment ends per tile
+constexpr uint32_t kPrFlatThreads = 1024;    // one block per CU: 16 waves share its hot contributions
+constexpr uint32_t kPrFlatBlocks = 256;
+constexpr uint32_t kPrHot = 24000;           // contributions in LDS (96,000 of 163,840 bytes)
+constexpr uint32_t kPrFixBlocks = 512;
+static_assert(kPrTile == 64 * 8, "a lane takes 8 entries");
 
-__global__ void k_pull_items(const uint32_t* deg, const uint32_t* heavy, const uint32_t* nheavy,
-                             const uint32_t* off, uint32_t* cnt, uint32_t* cur) {
-  const uint32_t nh = *nheavy;
-  for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < nh; j += gridDim.x * blockDim.x) {
-    const uint32_t v = heavy[j];
-    cnt[j] = (deg[v] + kPullItem - 1) / kPullItem;
-    cur[j] = off[v];
-  }
-}
-
-// off[nv] = off[nv - 1] + deg[nv - 1]: the end of the last segment.
-__global__ void k_pull_end(const uint32_t* deg, uint32_t* off, uint32_t nv) {
-  if (threadIdx.x == 0) off[nv] = off[nv - 1] + deg[nv - 1];
-}
-
-// Hot-first order of the sources for the packed iterations: a stable sort by out-degree class
-// (largest first) puts the sources of most in-arcs in a few MB of the contribution vector,
-// which the L2 of each XCD keeps.  Keys 31 - floor(log2(out + 1)), values the vertex ids.
 __global__ void k_pr_class(const uint32_t* __restrict__ outdeg, uint32_t nv, uint32_t* key, uint32_t* idx) {
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
     key[v] = (uint32_t)__clz(outdeg[v] + 1u);  // 31 - floor(log2(out + 1)), in [0, 31]
     idx[v] = v;
   }
 }
-__global__ void k_pr_rank(const uint32_t* __restrict__ perm, uint32_t nv, uint32_t* __restrict__ rank) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += gridDim.x * blockDim.x) rank[perm[i]] = i;
-}
 
-// k_pr_contrib in the hot-first order: cp[i] = PR[perm[i]] / out[perm[i]], and the FP64 sum of
-// the ranks of zero-out-degree vertices.
-__global__ void __launch_bounds__(kBlock) k_pr_contrib_perm(const float* __restrict__ x,
-                                                            const uint32_t* __restrict__ outdeg,
-                                                            const uint32_t* __restrict__ perm,
-                                                            float* __restrict__ cp, uint32_t nv, double* dpart,
-                                                            const uint32_t* state) {
-  __shared__ double lds[kBlock / 64];
-  if (state[0]) return;
-  double local = 0;
+// In rank order: out- and in-degrees, a zero packing cursor; every vertex's rank; no packing item.
+__global__ void k_pr_order(const uint32_t* __restrict__ perm, const uint32_t* __restrict__ outdeg,
+                           const uint32_t* __restrict__ indeg, uint32_t nv, uint32_t* __restrict__ od,
+                           uint32_t* __restrict__ id, uint32_t* __restrict__ rank, uint32_t* __restrict__ cur,
+                           uint32_t* nitems) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *nitems = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += gridDim.x * blockDim.x) {
     const uint32_t v = perm[i];
-    const uint32_t o = outdeg[v];
-    const float xv = x[v];
-    cp[i] = o ? xv / (float)o : 0.f;
+    od[i] = outdeg[v];
+    id[i] = indeg[v];
+    rank[v] = i;
+    cur[i] = 0;
+  }
+}
+
+// The merge-path tiles: vertex i's segment end sits at off[i + 1] + i among entries and ends.
+// Also off[nv], and the packing items of vertices with more than kHeavyBuckets buckets.
+constexpr uint32_t kPackChunk = 64;  // buckets per packing item (a 16-lane group)
+__global__ void k_pr_tiles(uint32_t* __restrict__ off, const uint32_t* __restrict__ id, uint32_t nv,
+                           uint32_t* __restrict__ fv, const uint32_t* __restrict__ perm,
+                           const uint32_t* __restrict__ nbk, uint32_t* item_i, uint32_t* item_c, uint32_t* nitems) {
+  const uint32_t ln = threadIdx.x & 63;
+  for (uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x - ln; i0 < nv; i0 += gridDim.x * blockDim.x) {
+    const uint32_t i = i0 + ln;
+    uint32_t k = 0;  // packing items of vertex i
+    if (i < nv) {
+      const uint64_t o = off[i], q = o + id[i] + i;  // this end; the tile borders after the previous
+      for (uint64_t t = i ? (o + i - 1) / kPrTile + 1 : 0; t <= q / kPrTile; ++t) fv[t] = i;
+      if (i == nv - 1) {
+        off[nv] = (uint32_t)(o + id[i]);
+        fv[q / kPrTile + 1] = nv;
+      }
+      const uint32_t nb = nbk[perm[i]];
+      if (nb > kHeavyBuckets) k = (nb + kPackChunk - 1) / kPackChunk;
+    }
+    if (!__ballot(k != 0)) continue;
+    uint32_t incl = k;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o);
+      if ((int)ln >= o) incl += y;
+    }
+    uint32_t at = 0;
+    if (ln == 63) at = atomicAdd(nitems, incl);
+    at = __shfl(at, 63) + incl - k;
+    for (uint32_t j = 0; j < k; ++j) {
+      item_i[at + j] = i;
+      item_c[at + j] = j;
+    }
+  }
+}
+
+// Copy the in-arc sources, as ranks, out of the reverse view's slabs: vertex i (rank order) to
+// list[off[i] .. off[i + 1]).  A vertex of more than kHeavyBuckets buckets is several items, whose
+// keys take their places through cur[i] (so their order can vary between runs).
+__global__ void __launch_bounds__(kBlock) k_pr_pack(DView R, const uint32_t* __restrict__ perm,
+                                                    const uint32_t* __restrict__ rank, const uint32_t* __restrict__ off,
+                                                    uint32_t nv, uint32_t* __restrict__ list, uint32_t* cur,
+                                                    const uint32_t* item_i, const uint32_t* item_c,
+                                                    const uint32_t* nitems) {
+  const uint32_t below = (1u << glane()) - 1u;
+  // Head slabs b0 .. b1 - 1 of v (several buckets) and their chains into v's segment [o, o + n), by
+  // the calling group: kPrBatch slabs are read at once, then their ranks.  take(k) is the place
+  // of the next k keys in the segment.
+  auto pack = [&](uint32_t v, uint32_t b0, uint32_t b1, uint32_t o, uint32_t n, auto&& take) {
+    const uint32_t xb = (uint32_t)ld_word(slab_ptr(R, v) + 14);
+    for (; b0 < b1; b0 += kPrBatch) {
+      uint64_t hw[kPrBatch];
+#pragma unroll
+      for (uint32_t j = 0; j < kPrBatch; ++j) {
+        const uint32_t b = b0 + j;
+        hw[j] = b < b1 ? ld_word(slab_ptr(R, b ? xb + b - 1 : v) + glane()) : kNextNone;
+      }
+      uint32_t r[kPrBatch], m[kPrBatch], total = 0;
+#pragma unroll
+      for (uint32_t j = 0; j < kPrBatch; ++j) {
+        const uint32_t u = (uint32_t)hw[j];
+        const bool ok = glane() < (b0 + j ? kKeysPerSlab : kKeysPerSlab - 1) && valid_key(u);
+        r[j] = ok ? rank[u] : kInvalid;
+        m[j] = gballot(ok);
+        total += __popc(m[j]);
+      }
+      uint32_t at = take(total);
+#pragma unroll
+      for (uint32_t j = 0; j < kPrBatch; ++j) {
+        const uint32_t p = at + __popc(m[j] & below);
+        if (r[j] != kInvalid && p < n) list[o + p] = r[j];
+        at += __popc(m[j]);
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < kPrBatch; ++j) {  // chained slabs after a full head slab
+        const uint32_t next = gbcast((uint32_t)hw[j], 15);
+        if (b0 + j >= b1 || next == kInvalid) continue;
+        walk_chain(R, next, ld_word(slab_ptr(R, next) + glane()), kKeysPerSlab, [&](uint64_t w, bool data) {
+          const bool ok = data && valid_key((uint32_t)w);
+          const uint32_t k = gballot(ok), p = take(__popc(k)) + __popc(k & below);
+          if (ok && p < n) list[o + p] = rank[(uint32_t)w];
+        });
+      }
+    }
+  };
+  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
+  const uint32_t ng = gridDim.x * kGroupsPerBlock;
+  const uint32_t items = *nitems;
+  for (uint32_t it = g0; it < items; it += ng) {
+    const uint32_t i = item_i[it], v = perm[i], b0 = item_c[it] * kPackChunk;
+    const uint32_t o = off[i], n = off[i + 1] - o;
+    pack(v, b0, min(R.nbk[v], b0 + kPackChunk), o, n, [&](uint32_t k) {
+      uint32_t at = 0;
+      if (glane() == 0 && k) at = atomicAdd(cur + i, k);
+      return gbcast(at, 0);
+    });
+  }
+  // single-bucket vertices: a lane each
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < nv; i += gridDim.x * kBlock) {
+    const uint32_t o = off[i], n = off[i + 1] - o;
+    if (n == 0) continue;
+    const uint32_t v = perm[i];
+    if (R.nbk[v] != 1) continue;
+    Slab sl;
+    uint32_t s = v, at = 0;
+    while (true) {
+      load_slab(R, s, sl);
+      uint32_t r[kKeysPerSlab];
+#pragma unroll
+      for (int j = 0; j < kKeysPerSlab; ++j) {
+        const uint32_t u = (uint32_t)sl.w[j];
+        r[j] = valid_key(u) ? rank[u] : kInvalid;
+      }
+#pragma unroll
+      for (int j = 0; j < kKeysPerSlab; ++j)
+        if (r[j] != kInvalid) {
+          if (at < n) list[o + at] = r[j];
+          ++at;
+        }
+      s = (uint32_t)sl.w[15];
+      if (s == kInvalid) break;
+    }
+  }
+  // 2 .. kHeavyBuckets buckets: a 16-lane group each
+  for (uint32_t i = g0; i < nv; i += ng) {
+    const uint32_t o = off[i], n = off[i + 1] - o;
+    if (n == 0) continue;
+    const uint32_t v = perm[i], nb = R.nbk[v];
+    if (nb == 1 || nb > kHeavyBuckets) continue;
+    uint32_t at = 0;  // the same in every lane of the group
+    pack(v, 0, nb, o, n, [&](uint32_t k) {
+      at += k;
+      return at - k;
+    });
+  }
+}
+
+// The ranks in rank order, the contributions, and the FP64 mass of the vertices without out-arcs.
+__global__ void __launch_bounds__(kBlock) k_pr_load(const float* __restrict__ keep, const uint32_t* __restrict__ perm,
+                                                    const uint32_t* __restrict__ od, uint32_t nv, float* __restrict__ x,
+                                                    float* __restrict__ c, double* dpart) {
+  __shared__ double lds[kBlock / 64];
+  double local = 0;
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += gridDim.x * blockDim.x) {
+    const float xv = keep[perm[i]];
+    const uint32_t o = od[i];
+    x[i] = xv;
+    c[i] = o ? xv / (float)o : 0.f;
     if (!o) local += xv;
   }
   const double s = block_sum(local, lds);
   if (threadIdx.x == 0) dpart[blockIdx.x] = s;
 }
 
-__global__ void __launch_bounds__(kBlock) k_pr_pull(const uint32_t* __restrict__ nbk,
-                                                    const uint32_t* __restrict__ deg,
-                                                    const uint32_t* __restrict__ off,
-                                                    const uint32_t* __restrict__ list,
-                                                    const float* __restrict__ c, const float* __restrict__ x,
-                                                    float* __restrict__ y, uint32_t nv, float damping,
-                                                    const double* dang, double* delta, const uint32_t* heavy,
-                                                    const uint32_t* nheavy, const uint32_t* pcnt,
-                                                    const uint32_t* poff, double* hacc, const uint32_t* state) {
-  __shared__ double lds[kBlock / 64];
-  if (state[0]) return;
-  const double base = (1.0 - (double)damping) / nv + (double)damping * (*dang) / nv;
-  double local = 0;
-  // in-arcs [a + first + k * stride, for k < kPullRound) below a + n (n >= 1), summed in
-  // order.  Every load is unconditional (indexes clamped into the segment and the vertex
-  // range, out-of-range terms masked afterwards), so a lane has all its loads in flight.
-  auto round = [&](uint32_t a, uint32_t n, uint32_t first, uint32_t stride, double& s) {
-    uint32_t u[kPullRound];
-#pragma unroll
-    for (uint32_t k = 0; k < kPullRound; ++k) u[k] = list[a + min(first + k * stride, n - 1)];
-    float cv[kPullRound];
-#pragma unroll
-    for (uint32_t k = 0; k < kPullRound; ++k) cv[k] = c[min(u[k], nv - 1)];
-#pragma unroll
-    for (uint32_t k = 0; k < kPullRound; ++k)
-      if (first + k * stride < n && u[k] < nv) s += (double)cv[k];
+// What an iteration reads and writes (all in rank order).
+struct PrIter {
+  const uint32_t *off, *list, *fv, *od;
+  const float *c, *x;   // contributions and ranks of this iteration
+  float *cn, *y;        // and of the next
+  double *heads, *tails;  // per tile: the parts of segments that run over tile borders
+  double *ddang, *ddelta;  // per block: dangling mass of y, L1 change
+  const uint32_t* state;
+  const double* dang;   // dangling mass of x
+  uint32_t nv;
+  float damping;
+};
+
+__device__ inline double pr_base(const PrIter& a) {
+  return (1.0 - (double)a.damping) / a.nv + (double)a.damping * (*a.dang) / a.nv;
+}
+// The new rank of vertex i from its in-arc sum, its contribution, and its shares of the L1
+// change and the dangling mass.
+__device__ inline void pr_finish(const PrIter& a, double base, uint32_t i, double s, float x, uint32_t od,
+                                 double& delta, double& dang) {
+  const float r = (float)(base + (double)a.damping * s);
+  a.y[i] = r;
+  a.cn[i] = od ? r / (float)od : 0.f;
+  if (!od) dang += r;
+  delta += fabs((double)r - (double)x);
+}
+
+// Inclusive sum over the lanes of a wave (every lane active): DPP moves within the rows of 16
+// lanes, then row totals broadcast to the rows behind them; a lane without a source adds zero.
+template <int kCtrl, int kRows>
+__device__ inline double dpp_or_zero(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, kRows, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, kRows, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ inline double wave_scan(double v) {
+  v += dpp_or_zero<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);  // lane 15 of a row to the next row, rows 1 and 3
+  v += dpp_or_zero<0x143, 0xC>(v);  // lane 31 to rows 2 and 3
+  return v;
+}
+
+struct __attribute__((packed, aligned(4))) U4 {  // four list entries at any entry's address
+  uint32_t v[4];
+};
+
+__global__ void __launch_bounds__(kPrFlatThreads) k_pr_flat(PrIter a) {
+  constexpr uint32_t kWaves = kPrFlatThreads / 64;
+  __shared__ __align__(16) float hot[kPrHot];
+  __shared__ double pre[kWaves][kPrTile + 1];
+  __shared__ double lds[2][kWaves];
+  if (a.state[0]) return;
+  const uint32_t nv = a.nv, nh = min(nv, kPrHot);
+  for (uint32_t i = threadIdx.x; i < nh; i += kPrFlatThreads) hot[i] = a.c[i];
+  __syncthreads();
+  const double base = pr_base(a);
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t M = a.off[nv];
+  const uint32_t T = (uint32_t)(((uint64_t)M + nv + kPrTile - 1) / kPrTile);
+  double* P = pre[w];
+  // the prefix before entry k of the tile; entry 8 l + j sits at 64 j + l, so that the lanes'
+  // stores do not meet in a bank
+  auto at = [&](uint32_t k) { return P[k == kPrTile ? kPrTile : (k & 7) * 64 + (k >> 3)]; };
+  double delta = 0, dang = 0;
+  constexpr uint32_t kStep = kPrFlatBlocks * kWaves;
+  // While a tile is worked on, the next one's list entries are on their way, and the borders of
+  // the one after it (four waves to a SIMD do not hide a tile's chain of loads by themselves).
+  // The list has a tile of slack behind its last entry, fv two entries.
+  struct Border {
+    uint32_t f0, f1;
   };
-  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
-    if (nbk[v] != 1) continue;
-    const uint32_t a = off[v], n = deg[v];
-    double s = 0;
-    for (uint32_t j0 = 0; j0 < n; j0 += kPullRound) round(a + j0, n - j0, 0, 1, s);
-    const float nvl = (float)(base + (double)damping * s);
-    y[v] = nvl;
-    local += fabs((double)nvl - (double)x[v]);
-  }
-  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
-  const uint32_t ng = gridDim.x * kGroupsPerBlock;
-  const uint32_t gl = (uint32_t)glane();
-  for (uint32_t v = g0; v < nv; v += ng) {
-    const uint32_t nb = nbk[v];
-    if (nb == 1 || nb > kHeavyBuckets) continue;
-    const uint32_t a = off[v], n = deg[v];
-    double s = 0;
-    for (uint32_t j0 = 0; j0 < n; j0 += kGroup * kPullRound) round(a + j0, n - j0, gl, kGroup, s);
-    s = gsum(s);
-    if (gl == 0) {
-      const float nvl = (float)(base + (double)damping * s);
-      y[v] = nvl;
-      local += fabs((double)nvl - (double)x[v]);
+  auto border = [&](uint32_t t) { return t < T ? Border{a.fv[t], a.fv[t + 1]} : Border{nv, nv}; };
+  auto first_entry = [&](uint32_t t, uint32_t f0) { return t < T ? (uint32_t)((uint64_t)t * kPrTile - f0) : M; };
+  uint32_t t = blockIdx.x * kWaves + w;
+  Border cur = border(t), nxt = border(t + kStep);
+  const U4* p = reinterpret_cast<const U4*>(a.list + first_entry(t, cur.f0) + 8 * lane);
+  U4 q0 = p[0], q1 = p[1];
+  for (; t < T; t += kStep) {
+    const uint32_t f0 = cur.f0, f1 = cur.f1;
+    const uint32_t e0 = first_entry(t, f0);
+    const uint32_t e1 = t + 1 == T ? M : (uint32_t)((uint64_t)(t + 1) * kPrTile - f1);
+    const uint32_t ne = e1 - e0;
+    uint32_t u[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) u[k] = min(k < 4 ? q0.v[k] : q1.v[k - 4], nv - 1);
+    // a hot entry's global load goes to one shared line, a cold one's LDS read to the last slot
+    float g[8], l[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) g[k] = a.c[max(u[k], nh - 1)];
+    const Border after = border(t + 2 * kStep);
+    p = reinterpret_cast<const U4*>(a.list + first_entry(t + kStep, nxt.f0) + 8 * lane);
+    q0 = p[0];
+    q1 = p[1];
+    // the segment borders, old ranks and out-degrees of the tile's first 64 vertices
+    uint32_t v = min(f0 + lane, nv - 1);
+    uint32_t o0 = a.off[v], o1 = a.off[v + 1], od = a.od[v];
+    float xv = a.x[v];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) l[k] = hot[min(u[k], nh - 1)];
+    double sum = 0, ex[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      ex[k] = sum;
+      const float cv = u[k] < nh ? l[k] : g[k];
+      sum += 8 * lane + k < ne ? (double)cv : 0.0;
     }
-  }
-  const uint32_t nh = *nheavy;
-  if (nh) {
-    const uint32_t items = poff[nh - 1] + pcnt[nh - 1];
-    for (uint32_t it = g0; it < items; it += ng) {
-      uint32_t lo = 0, hi = nh;  // last j with poff[j] <= it
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (poff[mid] <= it) lo = mid;
-        else hi = mid;
+    const double incl = wave_scan(sum);
+    const double before = incl - sum;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) P[k * 64 + lane] = before + ex[k];
+    if (lane == 63) P[kPrTile] = incl;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t v0 = f0; v0 < f1; v0 += 64) {
+      v = v0 + lane;
+      if (v0 != f0) {
+        const uint32_t vc = min(v, nv - 1);
+        o0 = a.off[vc];
+        o1 = a.off[vc + 1];
+        od = a.od[vc];
+        xv = a.x[vc];
       }
-      const uint32_t v = heavy[lo];
-      const uint32_t j0 = (it - poff[lo]) * kPullItem;
-      const uint32_t n = min(deg[v] - j0, kPullItem);
+      if (v < f1) {
+        const double s = at(o1 - e0) - at(max(o0, e0) - e0);
+        if (o0 < e0) a.heads[t] = s;  // only v == f0: its segment began in an earlier tile
+        else pr_finish(a, base, v, s, xv, od, delta, dang);
+      }
+    }
+    if (lane == 0 && f1 < nv) a.tails[t] = at(ne) - at(min(max(a.off[f1], e0), e1) - e0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    cur = nxt;
+    nxt = after;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    delta += __shfl_xor(delta, o);
+    dang += __shfl_xor(dang, o);
+  }
+  if (lane == 0) {
+    lds[0][w] = delta;
+    lds[1][w] = dang;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double s = 0;
+    for (uint32_t i = 0; i < kWaves; ++i) s += lds[threadIdx.x][i];
+    (threadIdx.x == 0 ? a.ddelta : a.ddang)[blockIdx.x] = s;
+  }
+}
+
+// The vertices whose segment runs over a tile border: a lane per tile adds the parts of the
+// vertex that ends there, a whole wave where there are many.
+__global__ void __launch_bounds__(kBlock) k_pr_fix(PrIter a) {
+  __shared__ double lds[kBlock / 64];
+  if (a.state[0]) return;
+  const double base = pr_base(a);
+  const uint32_t nv = a.nv, lane = threadIdx.x & 63;
+  const uint32_t T = (uint32_t)(((uint64_t)a.off[nv] + nv + kPrTile - 1) / kPrTile);
+  double delta = 0, dang = 0;
+  for (uint32_t t0 = blockIdx.x * kBlock + threadIdx.x - lane; t0 < T; t0 += kPrFixBlocks * kBlock) {
+    const uint32_t t = t0 + lane;
+    uint32_t v = 0, first = t;
+    bool mine = false;
+    if (t > 0 && t < T) {
+      v = a.fv[t];
+      if (v < a.fv[t + 1]) {
+        const uint64_t e0 = (uint64_t)t * kPrTile - v;
+        const uint32_t o0 = a.off[v];
+        if (o0 < e0) {
+          mine = true;
+          first = (uint32_t)(((uint64_t)o0 + v) / kPrTile);  // the tile the segment begins in
+        }
+      }
+    }
+    const uint32_t span = t - first;
+    if (mine && span <= 8) {
       double s = 0;
-      for (uint32_t j = 0; j < n; j += kGroup * kPullRound) round(off[v] + j0 + j, n - j, gl, kGroup, s);
-      s = gsum(s);
-      if (gl == 0 && s != 0.0) atomicAdd(hacc + lo, s);
+      for (uint32_t k = first; k < t; ++k) s += a.tails[k];
+      pr_finish(a, base, v, s + a.heads[t], a.x[v], a.od[v], delta, dang);
+    }
+    for (uint64_t m = __ballot(mine && span > 8); m; m &= m - 1) {
+      const int from = __builtin_ctzll(m);
+      const uint32_t b = __shfl(first, from), e = __shfl(t, from);
+      double s = 0;
+      for (uint32_t k = b + lane; k < e; k += 64) s += a.tails[k];
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if ((int)lane == from) pr_finish(a, base, v, s + a.heads[t], a.x[v], a.od[v], delta, dang);
     }
   }
-  const double s = block_sum(local, lds);
-  if (threadIdx.x == 0) delta[blockIdx.x] = s;
+  const double s0 = block_sum(delta, lds), s1 = block_sum(dang, lds);
+  if (threadIdx.x == 0) {
+    a.ddelta[kPrFlatBlocks + blockIdx.x] = s0;
+    a.ddang[kPrFlatBlocks + blockIdx.x] = s1;
+  }
 }
 
 // PageRank pull under IterationScheme2: the FP64 in-arc sum of every reverse-view bucket
@@ -801,13 +1021,17 @@ __global__ void __launch_bounds__(kBlock) k_pr_heavy_final(const uint32_t* heavy
 
 // Convergence bookkeeping for one iteration (single thread): stop at delta <= tol, when
 // the change has not improved for three iterations (the FP32 noise floor), or at max_iter.
+//
+// With `gpart` (the packed iterations), it also sums the next iteration's dangling mass.
 __global__ void __launch_bounds__(kBlock) k_pr_check(Counters* C, int slot, double tol, uint32_t max_iter,
-                                                     const double* dpart, uint32_t nparts) {
+                                                     const double* dpart, uint32_t nparts, const double* gpart) {
   __shared__ double lds[kBlock / 64];
   uint32_t* st = C->pr_state;
   if (st[0]) return;
   const double d = sum_parts(dpart, nparts, lds);  // the L1 change of this iteration
+  const double next = gpart ? sum_parts(gpart, nparts, lds) : 0.0;
   if (threadIdx.x != 0) return;
+  if (gpart) C->pr_acc[2 * ((slot + 1) & 3)] = next;
   C->pr_acc[2 * slot + 1] = d;
   st[1] += 1;
   C->pr_last = d;
@@ -839,6 +1063,19 @@ __global__ void k_pr_final(const Counters* C, const float* a, const float* b, fl
     const float v = src[i];
     if (keep != src) keep[i] = v;
     out[i] = v;
+  }
+  if (iters_out && blockIdx.x == 0 && threadIdx.x == 0) *iters_out = it;
+}
+
+// The same from the rank order of the packed iterations.
+__global__ void k_pr_store(const Counters* C, const float* a, const float* b, const uint32_t* __restrict__ rank,
+                           float* __restrict__ keep, float* __restrict__ out, uint32_t nv, uint32_t* iters_out) {
+  const uint32_t it = C->pr_state[1];
+  const float* src = (it & 1) ? b : a;
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const float r = src[rank[v]];
+    keep[v] = r;
+    out[v] = r;
   }
   if (iters_out && blockIdx.x == 0 && threadIdx.x == 0) *iters_out = it;
 }
@@ -1883,14 +2120,14 @@ mk_status pagerank_scheme2(mk_graph* g, float damping, double tol_l1, uint32_t m
       float* y = buf[(it + 1) & 1];
       double* dang = &g->ctr->pr_acc[2 * slot];
       hipLaunchKernelGGL(k_pr_contrib, dim3(cb), dim3(kBlock), 0, stream, x, g->view[VF].d.deg, g->pr_c,
-                         N, g->pr_part, g->ctr->pr_state, nullptr, nullptr);
+                         N, g->pr_part, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_sum, dim3(1), dim3(kBlock), 0, stream, g->pr_part, cb, dang, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_gather_s2, dim3(kWalkBlocks), dim3(kBlock), 0, stream, vh.d, g->pr_c,
                          vh.pair_v, vh.pair_i, (uint32_t)vh.n_head, N, g->pr_pair, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_final_s2, dim3(kWalkBlocks), dim3(kBlock), 0, stream, vh.nbk, vh.pair_off,
                          g->pr_pair, x, y, N, damping, dang, dpart, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, dpart,
-                         kWalkBlocks);
+                         kWalkBlocks, nullptr);
       MK_LAUNCH(g, "pagerank iteration (scheme 2)");
     }
     MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->pr_state, 8, hipMemcpyDeviceToHost, stream));
@@ -1899,6 +2136,76 @@ mk_status pagerank_scheme2(mk_graph* g, float damping, double tol_l1, uint32_t m
   }
   hipLaunchKernelGGL(k_pr_final, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->ctr, g->pr_x,
                      g->pr_y, g->pr_x, d_rank, N, d_iters);
+  MK_LAUNCH(g, "pagerank final");
+  g->pr.valid = true;
+  mark_seen(g, g->pr);
+  return MK_OK;
+}
+
+// PageRank by packed iterations from the ranks in g->pr_x.
+mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t max_iter, float* d_rank,
+                          uint32_t* d_iters, hipStream_t stream) {
+  const uint32_t N = g->n;
+  const DView& R = g->view[VR].d;
+  const uint32_t* outdeg = g->view[VF].d.deg;
+  uint32_t *od = g->pr_skey[0], *id = g->pr_skey[1];  // the sort's keys are free after it
+  float* x[2] = {reinterpret_cast<float*>(g->pr_cr), reinterpret_cast<float*>(g->pr_cr) + N};
+  float* c[2] = {g->pr_c, g->pr_cp};
+  uint32_t *cur = g->fq[0], *item_i = g->lv_multi[0], *item_c = g->lv_multi[1];  // traversal scratch
+  uint32_t* nitems = &g->ctr->n_heavy_pr;
+  hipLaunchKernelGGL(k_pr_class, dim3(blocks_for(N)), dim3(kBlock), 0, stream, outdeg, N, g->pr_skey[0], g->pr_sidx);
+  size_t sb = g->pr_sort_bytes;
+  if (rocprim::radix_sort_pairs(g->pr_sort_tmp, sb, g->pr_skey[0], g->pr_skey[1], g->pr_sidx, g->pr_perm,
+                                (size_t)N, 0, 6, stream) != hipSuccess)
+    return MK_ERR_HIP;
+  hipLaunchKernelGGL(k_pr_order, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_perm, outdeg, R.deg, N, od, id,
+                     g->pr_rank, cur, nitems);
+  size_t tb = g->scan_tmp_bytes;
+  if (rocprim::exclusive_scan(g->scan_tmp, tb, id, g->pr_off, 0u, (size_t)N, rocprim::plus<uint32_t>(), stream) !=
+      hipSuccess)
+    return MK_ERR_HIP;
+  hipLaunchKernelGGL(k_pr_start, dim3(1), dim3(64), 0, stream, g->ctr);
+  hipLaunchKernelGGL(k_pr_tiles, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_off, id, N, g->pr_fv, g->pr_perm,
+                     R.nbk, item_i, item_c, nitems);
+  hipLaunchKernelGGL(k_pr_pack, dim3(kWalkBlocks), dim3(kBlock), 0, stream, R, g->pr_perm, g->pr_rank, g->pr_off, N,
+                     g->pr_list, cur, item_i, item_c, nitems);
+  const uint32_t cb = blocks_for(N, kPrContribBlocks);
+  hipLaunchKernelGGL(k_pr_load, dim3(cb), dim3(kBlock), 0, stream, g->pr_x, g->pr_perm, od, N, x[0], c[0], g->pr_part);
+  hipLaunchKernelGGL(k_pr_sum, dim3(1), dim3(kBlock), 0, stream, g->pr_part, cb, &g->ctr->pr_acc[0], g->ctr->pr_state);
+  MK_LAUNCH(g, "pagerank packing");
+  uint32_t it = 0;
+  while (true) {
+    for (int k = 0; k < kPrSyncEvery; ++k, ++it) {
+      const int slot = it & 3;
+      PrIter a;
+      a.off = g->pr_off;
+      a.list = g->pr_list;
+      a.fv = g->pr_fv;
+      a.od = od;
+      a.c = c[it & 1];
+      a.x = x[it & 1];
+      a.cn = c[(it + 1) & 1];
+      a.y = x[(it + 1) & 1];
+      a.heads = g->pr_tile[0];
+      a.tails = g->pr_tile[1];
+      a.ddelta = g->pr_part;
+      a.ddang = g->pr_part + kPrParts / 2;
+      a.state = g->ctr->pr_state;
+      a.dang = &g->ctr->pr_acc[2 * slot];
+      a.nv = N;
+      a.damping = damping;
+      hipLaunchKernelGGL(k_pr_flat, dim3(kPrFlatBlocks), dim3(kPrFlatThreads), 0, stream, a);
+      hipLaunchKernelGGL(k_pr_fix, dim3(kPrFixBlocks), dim3(kBlock), 0, stream, a);
+      hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, a.ddelta,
+                         kPrFlatBlocks + kPrFixBlocks, a.ddang);
+      MK_LAUNCH(g, "pagerank iteration (packed)");
+    }
+    MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->pr_state, 8, hipMemcpyDeviceToHost, stream));
+    MK_HIP(g, hipStreamSynchronize(stream));
+    if (reinterpret_cast<const uint32_t*>(g->h_pin)[0]) break;
+  }
+  hipLaunchKernelGGL(k_pr_store, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->ctr, x[0], x[1], g->pr_rank, g->pr_x,
+                     d_rank, N, d_iters);
   MK_LAUNCH(g, "pagerank final");
   g->pr.valid = true;
   mark_seen(g, g->pr);
@@ -2021,6 +2328,7 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
   if (!warm)
     hipLaunchKernelGGL(k_pr_fill, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, N, 1.f / N);
   if (g->iter_scheme == MK_ITER_SCHEME2) return pagerank_scheme2(g, damping, tol_l1, max_iter, d_rank, d_iters, stream);
+  if (g->iter_scheme == MK_ITER_PACKED) return pagerank_packed(g, damping, tol_l1, max_iter, d_rank, d_iters, stream);
   uint32_t* nh = &g->ctr->n_heavy_pr;
   hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, nh, 1u);
   hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->view[VR].nbk,
@@ -2038,35 +2346,7 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
                                 stream) != hipSuccess)
       return MK_ERR_HIP;
   }
-  // packed iterations: the first one walks the slabs and packs the in-arc keys at the
-  // exclusive scan of the in-degrees; the heavy vertices' pull items and packing cursors
-  // use three more traversal queues
-  const bool packed = g->iter_scheme == MK_ITER_PACKED && g->pr_list;
   const DView& Rd = g->view[VR].d;
-  uint32_t* pcnt = g->fq[2];
-  uint32_t* poff = g->fq[3];
-  uint32_t* pcur = g->fq[4];
-  if (packed) {
-    size_t tb = g->scan_tmp_bytes;
-    if (rocprim::exclusive_scan(g->scan_tmp, tb, Rd.deg, g->pr_off, 0u, (size_t)N, rocprim::plus<uint32_t>(),
-                                stream) != hipSuccess)
-      return MK_ERR_HIP;
-    // hot-first ranks of the sources (out-degrees change with every batch: once per call)
-    hipLaunchKernelGGL(k_pr_class, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->view[VF].d.deg, N,
-                       g->pr_skey[0], g->pr_sidx);
-    size_t sb = g->pr_sort_bytes;
-    if (rocprim::radix_sort_pairs(g->pr_sort_tmp, sb, g->pr_skey[0], g->pr_skey[1], g->pr_sidx, g->pr_perm,
-                                  (size_t)N, 0, 6, stream) != hipSuccess)
-      return MK_ERR_HIP;
-    hipLaunchKernelGGL(k_pr_rank, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_perm, N, g->pr_rank);
-    hipLaunchKernelGGL(k_pull_end, dim3(1), dim3(64), 0, stream, Rd.deg, g->pr_off, N);
-    hipLaunchKernelGGL(k_pull_items, dim3(blocks_for(N)), dim3(kBlock), 0, stream, Rd.deg, g->heavy_rev, nh,
-                       g->pr_off, pcnt, pcur);
-    size_t tb2 = g->scan_tmp_bytes;
-    if (rocprim::exclusive_scan(g->scan_tmp, tb2, pcnt, poff, 0u, (size_t)N, rocprim::plus<uint32_t>(),
-                                stream) != hipSuccess)
-      return MK_ERR_HIP;
-  }
   hipLaunchKernelGGL(k_pr_start, dim3(1), dim3(64), 0, stream, g->ctr);
   MK_LAUNCH(g, "pagerank setup");
   float* buf[2] = {g->pr_x, g->pr_y};
@@ -2081,27 +2361,15 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
       const float* x = buf[it & 1];
       float* y = buf[(it + 1) & 1];
       double* dang = &g->ctr->pr_acc[2 * slot];
-      if (packed && it > 0)
-        hipLaunchKernelGGL(k_pr_contrib_perm, dim3(cb), dim3(kBlock), 0, stream, x, g->view[VF].d.deg,
-                           g->pr_perm, g->pr_cp, N, g->pr_part, g->ctr->pr_state);
-      else  // the first iteration; with packing, <rank, contribution> pairs
-        hipLaunchKernelGGL(k_pr_contrib, dim3(cb), dim3(kBlock), 0, stream, x, g->view[VF].d.deg, g->pr_c,
-                           N, g->pr_part, g->ctr->pr_state, packed ? g->pr_rank : nullptr,
-                           packed ? reinterpret_cast<uint2*>(g->pr_cr) : nullptr);
+      hipLaunchKernelGGL(k_pr_contrib, dim3(cb), dim3(kBlock), 0, stream, x, g->view[VF].d.deg, g->pr_c, N,
+                         g->pr_part, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_sum, dim3(1), dim3(kBlock), 0, stream, g->pr_part, cb, dang, g->ctr->pr_state);
-      if (packed && it > 0)
-        hipLaunchKernelGGL(k_pr_pull, dim3(kWalkBlocks), dim3(kBlock), 0, stream, Rd.nbk, Rd.deg, g->pr_off,
-                           g->pr_list, g->pr_cp, x, y, N, damping, dang, dpart, g->heavy_rev, nh, pcnt, poff,
-                           hacc, g->ctr->pr_state);
-      else
-        hipLaunchKernelGGL(k_pr_gather, dim3(kWalkBlocks), dim3(kBlock), 0, stream, Rd, g->pr_c, x, y, N,
-                           damping, dang, dpart, g->heavy_rev, nh, hcnt, hoff, hacc, g->ctr->pr_state,
-                           packed ? g->pr_list : nullptr, g->pr_off, pcur,
-                           reinterpret_cast<const uint2*>(g->pr_cr));
+      hipLaunchKernelGGL(k_pr_gather, dim3(kWalkBlocks), dim3(kBlock), 0, stream, Rd, g->pr_c, x, y, N, damping, dang,
+                         dpart, g->heavy_rev, nh, hcnt, hoff, hacc, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_heavy_final, dim3(hb), dim3(kBlock), 0, stream, g->heavy_rev, nh, hacc, x, y,
                          N, damping, dang, dpart + kWalkBlocks, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, dpart,
-                         kWalkBlocks + hb);
+                         kWalkBlocks + hb, nullptr);
       MK_LAUNCH(g, "pagerank iteration");
     }
     MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->pr_state, 8, hipMemcpyDeviceToHost, stream));

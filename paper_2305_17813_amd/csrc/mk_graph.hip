@@ -897,7 +897,12 @@ bool layout(const mk_config* c, uint64_t m, char* base, mk_graph* g, size_t* tot
   double* prpair = hb_rev ? cv.take<double>(hb_rev) : nullptr;
   // packed in-arc lists: one u32 per data word of the reverse view's slabs
   const uint64_t rev_words = hb_rev ? (hb_rev + pool_default(c, view_arcs(VR, m))) * kKeysPerSlab : 0;
-  uint32_t* prlist = hb_rev ? cv.take<uint32_t>(rev_words) : nullptr;
+  // (a tile of slack behind the last entry; tiles of 512 list entries and segment ends)
+  const uint64_t rev_tiles = (rev_words + N) / 512 + 4;
+  uint32_t* prlist = hb_rev ? cv.take<uint32_t>(rev_words + 512) : nullptr;
+  uint32_t* prfv = hb_rev ? cv.take<uint32_t>(rev_tiles + 1) : nullptr;
+  double* prtile0 = hb_rev ? cv.take<double>(rev_tiles) : nullptr;
+  double* prtile1 = hb_rev ? cv.take<double>(rev_tiles) : nullptr;
   uint32_t* proff = hb_rev ? cv.take<uint32_t>((uint64_t)N + 1) : nullptr;
   uint32_t *prperm = nullptr, *prrank = nullptr, *prk0 = nullptr, *prk1 = nullptr, *pridx = nullptr;
   float* prcp = nullptr;
@@ -969,6 +974,9 @@ bool layout(const mk_config* c, uint64_t m, char* base, mk_graph* g, size_t* tot
     g->pr_pair = prpair;
     g->pr_list = prlist;
     g->pr_off = proff;
+    g->pr_fv = prfv;
+    g->pr_tile[0] = prtile0;
+    g->pr_tile[1] = prtile1;
     g->pr_perm = prperm;
     g->pr_rank = prrank;
     g->pr_skey[0] = prk0;

@@ -144,20 +144,20 @@ struct mk_graph {
   uint32_t* pr_list = nullptr;    // packed in-arc keys of the reverse view (MK_ITER_PACKED),
                                   // room for every data word of its slabs
   uint32_t* pr_off = nullptr;     // N + 1 segment starts in pr_list (scan of the in-degrees)
+  uint32_t* pr_fv = nullptr;      // first vertex of each tile of the packed iterations
+  double* pr_tile[2] = {};        // per tile: the first and last parts of segments over tile borders
   // hot-first order of the packed iterations: perm[i] = the vertex of rank i (sources sorted
-  // by out-degree class, largest first), rank = its inverse, cp = contributions in rank order
+  // by out-degree class, largest first), rank = its inverse
   uint32_t* pr_perm = nullptr;
   uint32_t* pr_rank = nullptr;
   uint32_t* pr_skey[2] = {};      // sort keys (out-degree classes) and their sorted copy
   uint32_t* pr_sidx = nullptr;    // 0 .. N-1, the sort's values
-  float* pr_cp = nullptr;
-  uint64_t* pr_cr = nullptr;     // packing iteration: <rank, contribution bits> per vertex
+  float* pr_cp = nullptr;        // contributions in rank order (pr_c holds them every other iteration)
+  uint64_t* pr_cr = nullptr;     // ranks in rank order: two vectors of N floats
   void* pr_sort_tmp = nullptr;
   size_t pr_sort_bytes = 0;
   int iter_scheme = MK_ITER_PACKED;   // how all-vertex walks are scheduled
   const float* cm_params = nullptr;   // cost-model parameters for MK_AUTO (device, caller's)
-  uint32_t n_heavy_rev = 0;
-  bool heavy_rev_ok = false;
 
   uint64_t* tc_keys[2] = {nullptr, nullptr};
   // packed neighbour lists of the triangle update: the keys of the vertices whose

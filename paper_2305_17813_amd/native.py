@@ -307,8 +307,8 @@ class Graph:
 
     def set_iteration_scheme(self, scheme: int):
         """ITER_SCHEME1 (a worker per vertex), ITER_SCHEME2 (a group per bucket chain) or
-        ITER_PACKED (the default: SCHEME1, with PageRank's later iterations of a call reading
-        packed in-arc keys) for the PageRank pull and the all-arc WCC walk."""
+        ITER_PACKED (the default: SCHEME1, with PageRank's iterations reading in-arc sources
+        packed once per call) for the PageRank pull and the all-arc WCC walk."""
         _check(self.lib.mk_set_iteration_scheme(self.h, int(scheme)), "mk_set_iteration_scheme")
 
     def pagerank(self, damping: float = 0.85, tol: float = 1e-7, max_iter: int = 500,

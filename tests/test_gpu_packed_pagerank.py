@@ -1,0 +1,63 @@
+"""Packed PageRank iterations where their tiles can go wrong: segments that end on, begin on and
+run over many tile borders (512 list entries and segment ends to a tile), no arcs at all, more
+vertices than the contributions kept in LDS, and sources or targets without arcs."""
+import numpy as np
+import pytest
+
+from paper_2305_17813_amd import native
+from parity import Pair, say
+
+pytestmark = pytest.mark.gpu
+
+
+def star_into(n, leaves):
+    return np.arange(1, leaves + 1), np.zeros(leaves, np.int64), n
+
+
+def ring(n):
+    return np.arange(n), (np.arange(n) + 1) % n, n
+
+
+def many_targets(n, per):
+    """The first n // (per + 1) vertices each get `per` in-arcs; the others have none."""
+    rng = np.random.default_rng(n + per)
+    hubs = n // (per + 1)
+    d = np.repeat(np.arange(hubs), per)
+    s = rng.integers(hubs, n, len(d))
+    return s, d, n
+
+
+CASES = {
+    "no arcs": (np.zeros(0, np.int64), np.zeros(0, np.int64), 700),
+    "one arc": (np.array([600]), np.array([3]), 700),
+    "one vertex": (np.zeros(0, np.int64), np.zeros(0, np.int64), 1),
+    "star 510": star_into(600, 510),
+    "star 511": star_into(600, 511),
+    "star 512": star_into(600, 512),
+    "star 513": star_into(600, 513),
+    "star over 10 tiles": star_into(5200, 5000),
+    "star over 200 tiles": star_into(110_000, 100_000),
+    "ring of 256": ring(256),
+    "ring of 257": ring(257),
+    "ring wider than the LDS copy": ring(24_001),
+    "sixteen in-arcs each": many_targets(60_000, 16),
+    "two hundred in-arcs each": many_targets(60_000, 200),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("load_factor", [0.7, 0.0])
+def test_tiles(name, load_factor):
+    say(f"case: packed PageRank, {name}, load factor {load_factor}")
+    s, d, n = CASES[name]
+    if load_factor == 0.0 and len(s) > 10_000:
+        pytest.skip("one chain of thousands of slabs builds slowly; covered with hashing")
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD | native.VIEW_REV, load_factor=load_factor)
+    p.check_pr()
+    # both ends of the list change; warm start
+    if n > 300:
+        p.insert(np.array([n - 1, n - 2, 1]), np.array([n - 3, 0, n - 1]), np.ones(3, np.int64))
+        p.check_pr()
+        p.delete(np.array([n - 1, n - 2]), np.array([n - 3, 0]))
+        p.check_pr()
+        p.check_pr(native.RECOMPUTE)
