@@ -654,7 +654,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_pack(DView R, const uint32_t* __r
       for (uint32_t j = 0; j < kPrBatch; ++j) {
         const uint32_t u = (uint32_t)hw[j];
         const bool ok = glane() < (b0 + j ? kKeysPerSlab : kKeysPerSlab - 1) && valid_key(u);
-        r[j] = ok ? rank[u] : kInvalid;
+        r[j] = rank[ok ? u : 0u];  // unconditional: the compiler would wait for each otherwise
         m[j] = gballot(ok);
         total += __popc(m[j]);
       }
@@ -662,7 +662,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_pack(DView R, const uint32_t* __r
 #pragma unroll
       for (uint32_t j = 0; j < kPrBatch; ++j) {
         const uint32_t p = at + __popc(m[j] & below);
-        if (r[j] != kInvalid && p < n) list[o + p] = r[j];
+        if ((m[j] >> glane() & 1) && p < n) list[o + p] = r[j];
         at += __popc(m[j]);
       }
 #pragma unroll
@@ -700,14 +700,11 @@ __global__ void __launch_bounds__(kBlock) k_pr_pack(DView R, const uint32_t* __r
     while (true) {
       load_slab(R, s, sl);
       uint32_t r[kKeysPerSlab];
-#pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) {
-        const uint32_t u = (uint32_t)sl.w[j];
-        r[j] = valid_key(u) ? rank[u] : kInvalid;
-      }
+      const uint32_t live = live_words(sl, kKeysPerSlab);
+      load_of_keys<uint32_t>(rank, sl, live, 0u, r);
 #pragma unroll
       for (int j = 0; j < kKeysPerSlab; ++j)
-        if (r[j] != kInvalid) {
+        if (live >> j & 1) {
           if (at < n) list[o + at] = r[j];
           ++at;
         }
@@ -1785,11 +1782,7 @@ __global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, cons
   // u's out-neighbours among the words of one slab: bit j for word j
   auto higher = [&](uint32_t u, uint32_t du, const Slab& sl, int nd) -> uint32_t {
     uint32_t dv[kKeysPerSlab], keep = 0;
-#pragma unroll
-    for (int j = 0; j < kKeysPerSlab; ++j) {
-      const uint32_t v = (uint32_t)sl.w[j];
-      dv[j] = j < nd && valid_key(v) ? U.deg[v] : 0u;  // a neighbour has a degree of at least 1
-    }
+    load_of_keys<uint32_t>(U.deg, sl, live_words(sl, nd), 0u, dv);  // a neighbour's degree is at least 1
 #pragma unroll
     for (int j = 0; j < kKeysPerSlab; ++j)
       if (dv[j] > du || (dv[j] == du && (uint32_t)sl.w[j] > u)) keep |= 1u << j;

@@ -329,6 +329,38 @@ __device__ inline uint32_t lane_head(const DView& V, uint32_t u, uint32_t key, S
   return s;
 }
 
+// Bit j for each of the data words [0, nd) of a slab that holds a live key.
+__device__ inline uint32_t live_words(const Slab& sl, int nd) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int j = 0; j < kKeysPerSlab; ++j) m |= (uint32_t)(j < nd && valid_key((uint32_t)sl.w[j])) << j;
+  return m;
+}
+
+// a[key] for every live word (bits of `live`) of a slab held by one lane, `none` for the others.
+// The loads of four words are issued together and unconditionally, a word without a key reading
+// entry 0: with each load under its own condition the compiler waits for one before it issues the
+// next, and a slab takes 15 round trips.  Four words that no lane of the wave holds are skipped
+// (the vertices of a road network fill a quarter of their slab).
+template <class T>
+__device__ inline void load_of_keys(const T* a, const Slab& sl, uint32_t live, T none, T (&out)[kKeysPerSlab]) {
+#pragma unroll
+  for (int c = 0; c < kKeysPerSlab; c += 4) {
+    if (__ballot((live >> c & 15u) != 0) != 0) {
+#pragma unroll
+      for (int j = c; j < c + 4 && j < kKeysPerSlab; ++j)
+        out[j] = __hip_atomic_load(a + ((live >> j & 1) ? (uint32_t)sl.w[j] : 0u), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
+    } else {
+#pragma unroll
+      for (int j = c; j < c + 4 && j < kKeysPerSlab; ++j) out[j] = none;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kKeysPerSlab; ++j)
+    if (!(live >> j & 1)) out[j] = none;
+}
+
 // Scan the data words [0, nd) of a slab: index and word of `key` (or -1), and the lowest
 // EMPTY word at or above `floor` (or -1).
 __device__ inline void scan_slab(const Slab& sl, int nd, uint32_t key, int floor, int& hit,

@@ -58,7 +58,7 @@ struct AlgoState {
 struct Counters {          // device-side scalars, one 4 KiB block
   uint32_t frontier[16];   // [0..8] rotating frontier sizes (light, heavy and giant
                            // queues), [9..10] far-pile sizes, [11..12] band thresholds,
-                           // [13] smallest far distance
+                           // [13..14] smallest far distance, by band
   uint32_t inval;          // invalidated-vertex list size
   uint32_t overflow;       // bit per view (1 fwd, 2 rev, 4 und): an insert found its pool empty
   uint32_t n_heavy_wcc;    // vertices of more than 16 buckets, all-arc WCC walk
@@ -123,7 +123,8 @@ struct mk_graph {
   uint32_t* far[2] = {};      // far piles of the weighted epilogue
   uint32_t* far_mark = nullptr;
   uint32_t sssp_delta = 0;    // band width of the weighted epilogue
-  uint32_t stamp = 0;
+  uint32_t stamp = 0;         // frontier stamps given out
+  uint32_t bands = 0;         // distance bands numbered (far_mark)
   uint32_t rot = 0;           // frontier counter rotation
 
   uint64_t* bfs_D = nullptr;

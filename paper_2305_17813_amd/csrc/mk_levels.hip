@@ -105,21 +105,27 @@ __device__ inline void push_found(Stage& S, uint32_t found, const Slab& sl) {
 // pushes it and counts its out-arcs).
 __device__ inline uint32_t claim_slab(const Slab& sl, int nd, uint32_t* level, const uint32_t* deg,
                                       uint32_t cur, unsigned long long& arcs) {
-  uint32_t lv[kKeysPerSlab];
+  uint32_t lv[kKeysPerSlab], dv[kKeysPerSlab];
+  load_of_keys<uint32_t>(level, sl, live_words(sl, nd), 0u, lv);
+  // the claims and the claimed vertices' degrees, each in flight together
 #pragma unroll
   for (int j = 0; j < kKeysPerSlab; ++j) {
     const uint32_t v = (uint32_t)sl.w[j];
-    lv[j] = (j < nd && valid_key(v)) ? ld_u32(level + v) : 0u;
+    dv[j] = 0;
+    if (lv[j] == kLevelInf) {
+      lv[j] = atomicCAS(level + v, kLevelInf, cur + 1);
+      dv[j] = deg[v];
+    } else {
+      lv[j] = 0;
+    }
   }
   uint32_t found = 0;
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    const uint32_t v = (uint32_t)sl.w[j];
-    if (lv[j] == kLevelInf && atomicCAS(level + v, kLevelInf, cur + 1) == kLevelInf) {
+  for (int j = 0; j < kKeysPerSlab; ++j)
+    if (lv[j] == kLevelInf) {
       found |= 1u << j;
-      arcs += deg[v];
+      arcs += dv[j];
     }
-  }
   return found;
 }
 
@@ -252,11 +258,7 @@ __device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t*
     }
     while (true) {
       uint32_t lv[kKeysPerSlab];
-#pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) {
-        const uint32_t u = (uint32_t)sl.w[j];
-        lv[j] = (j < nd && valid_key(u)) ? ld_u32(level + u) : kLevelInf;
-      }
+      load_of_keys<uint32_t>(level, sl, live_words(sl, nd), kLevelInf, lv);
       bool hit = false;
 #pragma unroll
       for (int j = 0; j < kKeysPerSlab; ++j) hit |= lv[j] == cur;
@@ -364,11 +366,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_parents(DView R, const uint32_t* 
     while (true) {
       load_slab(R, t, sl);
       uint32_t lu[kKeysPerSlab];
-#pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) {
-        const uint32_t u = (uint32_t)sl.w[j];
-        lu[j] = valid_key(u) ? level[u] : kLevelInf;
-      }
+      load_of_keys<uint32_t>(level, sl, live_words(sl, kKeysPerSlab), kLevelInf, lu);
 #pragma unroll
       for (int j = 0; j < kKeysPerSlab; ++j)
         if (parent_arc<kUnit>(lu[j], sl.w[j], lv)) best = min(best, (uint32_t)sl.w[j]);
@@ -448,27 +446,36 @@ __global__ void k_ds_seed(uint32_t* dist, uint32_t* q0, DsCnt* c, uint32_t src, 
 
 // Relax one slab of u (distance du): a neighbour whose distance drops goes to the near
 // frontier (once per step, by the step stamp) or to the far pile (once per band).
+//
+// A neighbour is marked, and pushed by whoever marks it first, as soon as the new distance beats
+// the one read, without waiting for the minimum to return (if another lane's was smaller still,
+// that lane's drop needs the push as well), so that a slab takes two round trips.
 __device__ inline void relax_ds(const Slab& sl, int nd, uint32_t du, uint32_t* dist, uint32_t* mark,
                                 uint32_t* fmark, uint32_t stamp, uint32_t band, uint32_t T, uint32_t& near,
                                 uint32_t& far) {
-  uint32_t dv[kKeysPerSlab];
-#pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    const uint32_t v = (uint32_t)sl.w[j];
-    dv[j] = (j < nd && valid_key(v)) ? ld_u32(dist + v) : 0u;
-  }
-  near = far = 0;
+  uint32_t dv[kKeysPerSlab], tk[kKeysPerSlab], to_near = 0, to_far = 0;
+  load_of_keys<uint32_t>(dist, sl, live_words(sl, nd), 0u, dv);
 #pragma unroll
   for (int j = 0; j < kKeysPerSlab; ++j) {
     const uint32_t v = (uint32_t)sl.w[j];
     const uint32_t nd_ = (uint32_t)min<uint64_t>((uint64_t)du + (sl.w[j] >> 32), 0xFFFFFFFEull);
-    if (nd_ < dv[j] && nd_ < atomicMin(dist + v, nd_)) {
+    tk[j] = 0;
+    if (nd_ < dv[j]) {
       if (nd_ < T) {
-        if (atomicExch(mark + v, stamp) != stamp) near |= 1u << j;
-      } else if (atomicExch(fmark + v, band) != band) {
-        far |= 1u << j;
+        to_near |= 1u << j;
+        tk[j] = atomicExch(mark + v, stamp);
+      } else {
+        to_far |= 1u << j;
+        tk[j] = atomicExch(fmark + v, band);
       }
+      (void)atomicMin(dist + v, nd_);
     }
+  }
+  near = far = 0;
+#pragma unroll
+  for (int j = 0; j < kKeysPerSlab; ++j) {
+    if ((to_near >> j & 1) && tk[j] != stamp) near |= 1u << j;
+    if ((to_far >> j & 1) && tk[j] != band) far |= 1u << j;
   }
 }
 

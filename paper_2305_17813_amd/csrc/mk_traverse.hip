@@ -102,218 +102,249 @@ __device__ inline void stage_words(Stage& S, uint32_t mask, const Slab& sl) {
     if (mask >> j & 1) stage_put(S, t, pos++, (uint32_t)sl.w[j]);
 }
 
-// Relax the 15 out-arcs of a whole slab held by one lane.  The distance loads, the atomic
-// minima, the frontier marks and the bucket counts are each issued as one independent
-// batch, and the pushes of the wave are appended with one counter atomic per queue.
+// Relax the 15 out-arcs of a whole slab held by one lane: the distance loads, then the atomic
+// minima together with the frontier marks and the bucket counts, each as one independent
+// batch, and the pushes of the wave with one counter atomic per queue.
+//
+// A neighbour is marked, and pushed by whoever marks it first, as soon as the candidate beats
+// the distance read, without waiting for the minimum to return: if another lane's candidate was
+// smaller still, that lane's improvement needs the push as well.  (A vertex whose candidate is far
+// may then wait on the pile in vain; the band step drops it.)  `single`: no vertex of the graph
+// has several buckets, so no bucket count is read.
 template <bool kUnit>
 __device__ inline void relax_slab_lane(const DView& F, uint64_t* D, uint32_t u, uint64_t du, const Slab& sl,
                                        int nd, Stage (&S)[4], const Route& r, uint32_t T, uint32_t* mark,
-                                       uint32_t stamp) {
+                                       uint32_t stamp, bool single) {
   uint64_t cand[kKeysPerSlab], cur[kKeysPerSlab];
+  load_of_keys<uint64_t>(D, sl, live_words(sl, nd), 0ull, cur);
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    const uint32_t v = (uint32_t)sl.w[j];
-    const bool ok = j < nd && valid_key(v);
-    cand[j] = ok ? tree_node(du + (kUnit ? 1ull : (sl.w[j] >> 32)), u) : kTreeNone;
-    cur[j] = ok ? D[v] : 0ull;
-  }
-#pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j)
-    cur[j] = cand[j] < cur[j] ? amin64(D + (uint32_t)sl.w[j], cand[j]) : 0ull;
+  for (int j = 0; j < kKeysPerSlab; ++j) cand[j] = tree_node(du + (kUnit ? 1ull : (sl.w[j] >> 32)), u);
   uint32_t near = 0, far = 0;
 #pragma unroll
   for (int j = 0; j < kKeysPerSlab; ++j) {
-    if (cur[j] > cand[j]) {
-      if ((uint32_t)(cand[j] >> 32) < T) near |= 1u << j;
-      else far |= 1u << j;
-    }
+    if (cand[j] >= cur[j]) continue;
+    if (kUnit || (uint32_t)(cand[j] >> 32) < T) near |= 1u << j;
+    else far |= 1u << j;
   }
-  uint32_t tk[kKeysPerSlab];
+  uint32_t tk[kKeysPerSlab], nb[kKeysPerSlab];
 #pragma unroll
   for (int j = 0; j < kKeysPerSlab; ++j) {
     const uint32_t v = (uint32_t)sl.w[j];
     tk[j] = 0;
-    if (near >> j & 1) tk[j] = atomicExch(mark + v, stamp);
-    else if (far >> j & 1) tk[j] = atomicExch(r.far_mark + v, r.band);
+    nb[j] = 1;
+    if (near >> j & 1) {
+      tk[j] = atomicExch(mark + v, stamp);
+      if (!single) nb[j] = F.nbk[v];
+    } else if (far >> j & 1) {
+      tk[j] = atomicExch(r.far_mark + v, r.band);
+    }
+    if ((near | far) >> j & 1) (void)amin64(D + v, cand[j]);
   }
-  uint32_t tn = 0, tf = 0;
+  uint32_t tn = 0, tf = 0, heavy = 0, giant = 0;
 #pragma unroll
   for (int j = 0; j < kKeysPerSlab; ++j) {
-    if ((near >> j & 1) && tk[j] != stamp) tn |= 1u << j;
+    if ((near >> j & 1) && tk[j] != stamp) {
+      if (nb[j] > kGiantBuckets) giant |= 1u << j;
+      else if (nb[j] > kHeavyBuckets) heavy |= 1u << j;
+      else tn |= 1u << j;
+    }
     if ((far >> j & 1) && tk[j] != r.band) tf |= 1u << j;
   }
-#pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) tk[j] = (tn >> j & 1) ? F.nbk[(uint32_t)sl.w[j]] : 1u;
-  uint32_t heavy = 0, giant = 0;
-#pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    if (tk[j] > kGiantBuckets) giant |= 1u << j;
-    else if (tk[j] > kHeavyBuckets) heavy |= 1u << j;
+  stage_words(S[0], tn, sl);
+  if (!single) {
+    stage_words(S[1], heavy, sl);
+    stage_words(S[2], giant, sl);
   }
-  stage_words(S[0], tn & ~(heavy | giant), sl);
-  stage_words(S[1], heavy, sl);
-  stage_words(S[2], giant, sl);
-  stage_words(S[3], tf, sl);
-}
-
-// Relax every arc in bucket b of u (nb buckets, extra head slabs from xb) with one lane.
-template <bool kUnit>
-__device__ inline void relax_bucket_lane(const DView& F, uint64_t* D, uint32_t u, uint64_t du, uint32_t b,
-                                         uint32_t nb, uint32_t xb, Stage (&S)[4], const Route& r,
-                                         uint32_t T, uint32_t* mark, uint32_t stamp) {
-  uint32_t t = b == 0 ? u : xb + b - 1;
-  int nd = (b == 0 && nb > 1) ? kKeysPerSlab - 1 : kKeysPerSlab;
-  Slab sl;
-  while (true) {
-    load_slab(F, t, sl);
-    relax_slab_lane<kUnit>(F, D, u, du, sl, nd, S, r, T, mark, stamp);
-    t = (uint32_t)sl.w[15];
-    if (t == kInvalid) break;
-    nd = kKeysPerSlab;
-  }
-}
-
-// First extra head slab of a multi-bucket vertex (word 14 of its primary slab).
-__device__ inline uint32_t extra_base(const DView& F, uint32_t u) {
-  return (uint32_t)ld_word(slab_ptr(F, u) + 14);
+  if (!kUnit) stage_words(S[3], tf, sl);
 }
 
 constexpr uint32_t kGiantLanes = kGiantSplit * kGroup;  // lanes sharing one giant vertex
+// A light frontier of at most kInnerMost vertices is expanded by one block, which goes on with
+// the frontiers that follow, up to kInnerSteps of them, while they fit its LDS stage and hold no
+// heavy vertex: a step then costs its own chain of dependent loads (about 5 us) instead of a
+// launch and the reads that find the frontier (about 15 us).
+constexpr uint32_t kInnerMost = 512;
+constexpr uint32_t kInnerSteps = 64;
 
-// Frontier expansion.  Every path gives each lane whole slabs (one bucket chain at a
-// time), so the pushes of a wave cover up to 64 x 15 arcs per counter atomic:
-//   single-bucket vertices: one lane each;
-//   2 .. kHeavyBuckets buckets: one 16-lane group per vertex, a lane per bucket;
-//   heavy: one block per vertex, a lane per bucket;
-//   giant: kGiantLanes lanes per vertex, striding over its buckets.
+// After a step of an inner loop: the frontier staged in S[0] becomes the block's list in LDS, or
+// the loop ends (empty, too large, heavy vertices, or out of steps) and the stages hold the
+// launch's output.  Every thread of the block gets the same answer.
+__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t& n, uint32_t& step) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this step's atomics have been performed
+  __syncthreads();
+  // and the next step reads what they left, not a cache line from before them (a stale distance
+  // of a vertex improved a step ago would push it again)
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const uint32_t k = S[0].n;
+  const bool go = k > 0 && k <= kStage && S[1].n == 0 && S[2].n == 0 && step + 1 < kInnerSteps;
+  if (!go) return false;
+  for (uint32_t i = threadIdx.x; i < k; i += kBlock) list[i] = S[0].buf[i];
+  __syncthreads();
+  if (threadIdx.x == 0) S[0].n = 0;
+  __syncthreads();
+  n = k;
+  ++step;
+  return true;
+}
+
+// Whether a block of a frontier kernel has nothing to do (the same in all its threads).
+__device__ inline bool no_work(uint32_t nl, uint32_t nh, uint32_t ngi) {
+  return (uint64_t)blockIdx.x * kBlock >= nl && blockIdx.x >= nh && blockIdx.x >= ngi * (kGiantLanes / kBlock);
+}
+
+// Slabs of light vertices' further buckets, collected while the block visits the primary slabs.
+constexpr uint32_t kExtras = 1024;
+struct Extras {
+  uint32_t n;
+  uint32_t u[kExtras], s[kExtras];
+};
+
+// Visit every slab of the frontier's vertices, a lane to a bucket chain: the primary slabs of 256
+// light vertices at a time, then those vertices' further buckets (collected in E, so that the
+// lanes share them evenly; a lane walks its own where E is full), a block to a heavy vertex,
+// kGiantLanes lanes to a giant one.  begin(u) is called before a slab of u is read, so that what
+// it loads is on its way together with the slab; body(u, begin's result, slab, data words) once
+// per slab.  There is one call site of body, as its code is long.  Every thread of the block
+// calls this; `list` replaces the light queue (inner steps), `stride` blocks share the work.
+template <class Begin, class Body>
+__device__ inline void walk_frontier(const DView& F, const Queues& q, const uint32_t* list, uint32_t nl, uint32_t nh,
+                                     uint32_t ngi, uint32_t stride, bool single, Extras& E, Begin&& begin,
+                                     Body&& body) {
+  int mode = 0;  // block-uniform: 0 light vertices, 1 their further buckets, 2 heavy, 3 giant
+  uint32_t base = blockIdx.x * kBlock, eb = 0, ne = 0, hb = 0;
+  const uint32_t tid = threadIdx.x;
+  while (true) {
+    uint32_t u = 0, s = kInvalid, own = 0, own_end = 0;  // own: further buckets this lane walks itself
+    int nd = kKeysPerSlab;
+    if (mode == 0) {
+      if (base >= nl) {
+        mode = 2;
+        base = blockIdx.x;
+        continue;
+      }
+      if (base + tid < nl) u = s = list[base + tid];
+    } else if (mode == 1) {
+      if (eb + tid < ne) {
+        u = E.u[eb + tid];
+        s = E.s[eb + tid];
+      }
+    } else {
+      const uint32_t per = mode == 2 ? kBlock : kGiantLanes;  // lanes that share the vertex
+      const uint32_t split = per / kBlock;
+      if (base >= (mode == 2 ? nh : ngi * split)) {
+        if (mode == 3) return;
+        mode = 3;
+        base = blockIdx.x;
+        continue;
+      }
+      u = q.cur[mode - 1][base / split];
+      const uint4 w = reinterpret_cast<const uint4*>(slab_ptr(F, u))[7];  // extra head slabs, bucket count
+      const uint32_t b = hb + (base % split) * kBlock + tid;
+      if (b < w.w) {
+        s = b ? w.x + b - 1 : u;
+        nd = b ? kKeysPerSlab : kKeysPerSlab - 1;
+      }
+      hb += per;
+      if (hb + (base % split) * kBlock >= w.w) {  // the vertex's buckets are dealt out
+        hb = 0;
+        base += stride;
+      }
+    }
+    if (s != kInvalid) {
+      const auto ctx = begin(u);
+      Slab sl;
+      load_slab(F, s, sl);
+      if (mode == 0) {
+        const uint32_t nb = (uint32_t)(sl.w[15] >> 32);
+        if (nb > 1) {
+          nd = kKeysPerSlab - 1;
+          const uint32_t xb = (uint32_t)sl.w[14];
+          const uint32_t at = atomicAdd(&E.n, nb - 1);
+          for (uint32_t k = 0; k < nb - 1; ++k) {
+            if (at + k < kExtras) {
+              E.u[at + k] = u;
+              E.s[at + k] = xb + k;
+            } else {
+              own = xb + k;
+              own_end = xb + nb - 1;
+              break;
+            }
+          }
+        }
+      }
+      while (true) {
+        body(u, ctx, sl, nd);
+        s = (uint32_t)sl.w[15];
+        if (s == kInvalid) {
+          if (own == own_end) break;
+          s = own++;
+        }
+        nd = kKeysPerSlab;
+        load_slab(F, s, sl);
+      }
+    }
+    if (mode == 0) {
+      if (!single) {
+        __syncthreads();
+        ne = min(E.n, kExtras);
+        eb = 0;
+        if (ne) mode = 1;
+      }
+      if (mode == 0) base += stride * kBlock;
+    } else if (mode == 1) {
+      eb += kBlock;
+      if (eb >= ne) {
+        __syncthreads();
+        if (tid == 0) E.n = 0;
+        __syncthreads();
+        mode = 0;
+        base += stride * kBlock;
+      }
+    }
+  }
+}
+
+// Frontier expansion: relax every arc that leaves a frontier vertex.
+//
+// What bounds it where frontiers are small (a road network, a small graph): the chain of
+// dependent memory accesses of one vertex: queue, slab and distance, neighbours' distances,
+// marks, queue counter.  A launch over 50,000 light vertices of the 4096 x 4096 grid takes 13 us
+// (slab 2.2, distances and marks 5.5, staging 1.8, queue counter and copy 1.5; 18-20 us with the
+// bucket counts, the distance and the slab read one after the other and every block opening and
+// closing its stages); an inner step takes 10 us and no launch.
 template <bool kUnit>
 __global__ void __launch_bounds__(kBlock) k_expand(DView F, uint64_t* D, Queues q, Route r, uint32_t* mark,
-                                                   uint32_t stamp) {
-  const uint32_t nl = q.cnt[q.icur], nh = q.cnt[3 + q.icur], ngi = q.cnt[6 + q.icur];
+                                                   uint32_t stamp, bool single) {
+  uint32_t nl = q.cnt[q.icur];
+  const uint32_t nh = q.cnt[3 + q.icur], ngi = q.cnt[6 + q.icur];
   if (blockIdx.x == 0 && threadIdx.x < 3) q.cnt[3 * threadIdx.x + q.iclear] = 0;
-  if (nl == 0 && nh == 0 && ngi == 0) return;  // the same for the whole grid
+  if (no_work(nl, nh, ngi)) return;  // also an empty frontier
+  const bool inner = nl <= kInnerMost && nh == 0 && ngi == 0;
+  if (inner && blockIdx.x != 0) return;
   __shared__ Stage S[4];
+  __shared__ uint32_t list[kStage];
+  __shared__ Extras E;
+  if (threadIdx.x == 0) E.n = 0;
   open_routed(S, q.next, r);
-  const uint32_t T = band_limit(r);
-  const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x, nthreads = gridDim.x * kBlock;
-  const uint32_t ng = gridDim.x * kGroupsPerBlock;
-  if constexpr (kUnit) {  // one loop per path
-    for (uint32_t i = gtid; i < nl; i += nthreads) {
-      const uint32_t u = q.cur[0][i];
-      if (F.nbk[u] != 1) continue;
-      relax_bucket_lane<kUnit>(F, D, u, ld_u64(D + u) >> 32, 0, 1, 0, S, r, T, mark, stamp);
-    }
-    for (uint32_t i = gtid / kGroup; i < nl; i += ng) {
-      const uint32_t u = q.cur[0][i];
-      const uint32_t nb = F.nbk[u];
-      if (nb == 1 || (uint32_t)glane() >= nb) continue;
-      relax_bucket_lane<kUnit>(F, D, u, ld_u64(D + u) >> 32, glane(), nb, extra_base(F, u), S, r, T, mark,
-                               stamp);
-    }
-    for (uint32_t j = blockIdx.x; j < nh; j += gridDim.x) {
-      const uint32_t u = q.cur[1][j];
-      const uint32_t nb = F.nbk[u];
-      const uint64_t du = ld_u64(D + u) >> 32;
-      const uint32_t xb = extra_base(F, u);
-      for (uint32_t b = threadIdx.x; b < nb; b += kBlock)
-        relax_bucket_lane<kUnit>(F, D, u, du, b, nb, xb, S, r, T, mark, stamp);
-    }
-    for (uint32_t it = gtid; it < ngi * kGiantLanes; it += nthreads) {
-      const uint32_t u = q.cur[2][it / kGiantLanes];
-      const uint32_t nb = F.nbk[u];
-      const uint64_t du = ld_u64(D + u) >> 32;
-      const uint32_t xb = extra_base(F, u);
-      for (uint32_t b = it % kGiantLanes; b < nb; b += kGiantLanes)
-        relax_bucket_lane<kUnit>(F, D, u, du, b, nb, xb, S, r, T, mark, stamp);
-    }
-    stage_close(S);
-    return;
-  }
-  // Weighted: each thread walks its (vertex, bucket) work items of the four paths in turn
-  // through a single relaxation call site.  Four inlined copies of the weighted relaxation
-  // need 150 VGPRs (three waves per SIMD), one needs 92 (five).  Lanes in different paths
-  // still relax together.
-  int path = 0;       // 0 single-bucket, 1 group, 2 heavy, 3 giant, 4 done
-  uint32_t i = gtid;  // item index within the path
-  uint32_t b = 0;     // next bucket of the current heavy / giant vertex
-  while (path < 4) {
-    uint32_t u = 0, nb = 1, bk = 0;
-    bool have = false;
-    if (path == 0) {  // one lane per single-bucket vertex
-      if (i < nl) {
-        u = q.cur[0][i];
-        i += nthreads;
-        nb = F.nbk[u];
-        have = nb == 1;
-      } else {
-        path = 1;
-        i = gtid / kGroup;
-      }
-    } else if (path == 1) {  // 2 .. kHeavyBuckets buckets: a 16-lane group, a lane per bucket
-      if (i < nl) {
-        u = q.cur[0][i];
-        i += ng;
-        nb = F.nbk[u];
-        bk = (uint32_t)glane();
-        have = nb > 1 && bk < nb;
-      } else {
-        path = 2;
-        i = blockIdx.x;
-        b = threadIdx.x;
-      }
-    } else if (path == 2) {  // heavy: a block per vertex, a lane per bucket
-      if (i < nh) {
-        u = q.cur[1][i];
-        nb = F.nbk[u];
-        if (b < nb) {
-          bk = b;
-          b += kBlock;
-          have = true;
-        } else {
-          i += gridDim.x;
-          b = threadIdx.x;
-        }
-      } else {
-        path = 3;
-        i = gtid;
-        b = gtid % kGiantLanes;
-      }
-    } else {  // giant: kGiantLanes lanes per vertex
-      if (i < ngi * kGiantLanes) {
-        u = q.cur[2][i / kGiantLanes];
-        nb = F.nbk[u];
-        if (b < nb) {
-          bk = b;
-          b += kGiantLanes;
-          have = true;
-        } else {
-          i += nthreads;
-          b = i % kGiantLanes;
-        }
-      } else {
-        path = 4;
-      }
-    }
-    if (!have) continue;
-    const uint64_t du = ld_u64(D + u) >> 32;
-    relax_bucket_lane<kUnit>(F, D, u, du, bk, nb, nb > 1 ? extra_base(F, u) : 0u, S, r, T, mark, stamp);
-  }
+  const uint32_t T = kUnit ? 0xFFFFFFFFu : band_limit(r);
+  uint32_t step = 0;
+  do {
+    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E,
+                  [&](uint32_t u) { return ld_u64(D + u) >> 32; },
+                  [&](uint32_t u, uint64_t du, const Slab& sl, int nd) {
+                    relax_slab_lane<kUnit>(F, D, u, du, sl, nd, S, r, T, mark, stamp + step, single);
+                  });
+  } while (inner && inner_next(S, list, nl, step));
   stage_close(S);
 }
 
-// Band step, part 1: reset the pile minimum and the size of the pile about to be filled.
-__global__ void k_band_reset(uint32_t* fmin, uint32_t* next_cnt) {
-  if (threadIdx.x == 0) {
-    *fmin = 0xFFFFFFFFu;
-    *next_cnt = 0;
-  }
-}
-
-// Band step, part 2: the smallest distance on the far pile at or above the old threshold
-// (an entry below it was expanded, at its current distance, in an earlier band).
+// Band step, part 1: the smallest distance on the far pile at or above the old threshold
+// (an entry below it was expanded, at its current distance, in an earlier band).  The size of
+// the pile about to be filled is reset here, the minimum by the step before (or the reset).
 __global__ void k_band_min(const uint64_t* D, const uint32_t* far, const uint32_t* far_cnt, const uint32_t* T,
-                           uint32_t* fmin) {
+                           uint32_t* fmin, uint32_t* next_cnt) {
   const uint32_t n = *far_cnt, told = *T;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next_cnt = 0;
   uint32_t m = 0xFFFFFFFFu;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const uint32_t d = (uint32_t)(ld_u64(D + far[i]) >> 32);
@@ -323,21 +354,29 @@ __global__ void k_band_min(const uint64_t* D, const uint32_t* far, const uint32_
   if (lane64() == 0 && m != 0xFFFFFFFFu) atomicMin(fmin, m);
 }
 
-// Band step, part 3: the new threshold is fmin + delta; pile entries in [old T, new T) form
+// Band step, part 2: the new threshold is fmin + delta; pile entries in [old T, new T) form
 // the frontier of the next band, later ones move to the other pile under the new band id.
-__global__ void k_band_split(const uint32_t* nbk, const uint64_t* D, const uint32_t* far, const uint32_t* far_cnt,
-                             const uint32_t* T, const uint32_t* fmin, uint32_t delta, uint32_t* T_next,
-                             PushQ Q, uint32_t* far_next, uint32_t* next_cnt, uint32_t* far_mark,
-                             uint32_t band_next) {
+// Appends are staged per block (with an atomic per wave and output, 700,000 entries took 130 us).
+__global__ void __launch_bounds__(kBlock) k_band_split(const uint32_t* nbk, const uint64_t* D, const uint32_t* far,
+                                                       const uint32_t* far_cnt, const uint32_t* T, const uint32_t* fmin,
+                                                       uint32_t* fmin_next, uint32_t delta, uint32_t* T_next, PushQ Q,
+                                                       uint32_t* far_next, uint32_t* next_cnt, uint32_t* far_mark,
+                                                       uint32_t band_next, bool single) {
   const uint32_t n = *far_cnt, told = *T, fm = *fmin;
   const uint32_t tnew = fm == 0xFFFFFFFFu ? told : (fm >= 0xFFFFFFFFu - delta ? 0xFFFFFFFFu : fm + delta);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *T_next = tnew;
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t base = blockIdx.x * blockDim.x + threadIdx.x - lane; base < n; base += stride) {
-    const uint32_t i = base + lane;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *T_next = tnew;
+    *fmin_next = 0xFFFFFFFFu;
+  }
+  if (blockIdx.x * kBlock >= n) return;
+  __shared__ Stage S[4];
+  for (int k = 0; k < 3; ++k) stage_open(S[k], Q.q[k], Q.c[k]);
+  stage_open(S[3], far_next, next_cnt);
+  __syncthreads();
+  for (uint32_t base = blockIdx.x * kBlock; base < n; base += gridDim.x * kBlock) {
+    const uint32_t i = base + threadIdx.x;
     bool near = false, keep = false;
-    uint32_t v = 0, nb = 0;
+    uint32_t v = 0, nb = 1;
     if (i < n) {
       v = far[i];
       const uint32_t d = (uint32_t)(ld_u64(D + v) >> 32);
@@ -345,12 +384,15 @@ __global__ void k_band_split(const uint32_t* nbk, const uint64_t* D, const uint3
       keep = d >= tnew;
     }
     if (keep) far_mark[v] = band_next;
-    wave_push(far_next, next_cnt, keep, v);
-    if (near) nb = nbk[v];
-    wave_push(Q.q[0], Q.c[0], near && nb <= kHeavyBuckets, v);
-    wave_push(Q.q[1], Q.c[1], near && nb > kHeavyBuckets && nb <= kGiantBuckets, v);
-    wave_push(Q.q[2], Q.c[2], near && nb > kGiantBuckets, v);
+    if (near && !single) nb = nbk[v];
+    stage_push(S[3], keep, v);
+    stage_push(S[0], near && nb <= kHeavyBuckets, v);
+    if (!single) {
+      stage_push(S[1], near && nb > kHeavyBuckets && nb <= kGiantBuckets, v);
+      stage_push(S[2], near && nb > kGiantBuckets, v);
+    }
   }
+  stage_close(S);
 }
 
 __global__ void k_trav_init(uint64_t* D, uint32_t nv, uint32_t src) {
@@ -359,10 +401,11 @@ __global__ void k_trav_init(uint64_t* D, uint32_t nv, uint32_t src) {
 }
 
 // Reset the rotating counters so that slot 0 is the current frontier, empty both far
-// piles and set the first threshold to 0 (every prologue push of a weighted traversal
+// piles, reset their minima and set the first threshold to 0 (every prologue push of a weighted traversal
 // waits on the pile until the first band step).
 __global__ void k_queue_reset(uint32_t* cnt, uint32_t* inval_cnt) {
   if (threadIdx.x < 13) cnt[threadIdx.x] = 0;
+  if (threadIdx.x == 13 || threadIdx.x == 14) cnt[threadIdx.x] = 0xFFFFFFFFu;  // pile minima
   if (threadIdx.x == 0 && inval_cnt) *inval_cnt = 0;
 }
 
@@ -448,86 +491,54 @@ __global__ void k_invalidate(DView F, uint64_t* D, Log lg, uint64_t n, PushQ Q, 
 }
 
 // Delete prologue, step 2: invalidate the subtree below each invalidated vertex x (its
-// tree children are the out-neighbours y whose parent is x).
-__device__ inline void inval_word(const DView& F, uint64_t* D, uint32_t x_parent, uint64_t w,
-                                  bool data, Stage (&S)[4]) {
-  const uint32_t y = (uint32_t)w;
-  bool hit = false;
-  if (data && valid_key(y)) {
-    const uint64_t dy = ld_u64(D + y);
-    if (dy != kTreeNone && (uint32_t)dy == x_parent) hit = cas64(D + y, dy, kTreeNone) == dy;
-  }
-  stage_cut(S, F.nbk, hit, y);
-}
-
+// tree children are the out-neighbours y whose parent is x).  The child tests of a slab are
+// issued together.
 __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queues q, uint32_t* inval,
-                                                      uint32_t* inval_cnt) {
-  const uint32_t nl = q.cnt[q.icur], nh = q.cnt[3 + q.icur], ngi = q.cnt[6 + q.icur];
+                                                      uint32_t* inval_cnt, bool single) {
+  uint32_t nl = q.cnt[q.icur];
+  const uint32_t nh = q.cnt[3 + q.icur], ngi = q.cnt[6 + q.icur];
   if (blockIdx.x == 0 && threadIdx.x < 3) q.cnt[3 * threadIdx.x + q.iclear] = 0;
-  if (nl == 0 && nh == 0 && ngi == 0) return;  // the same for the whole grid
+  if (no_work(nl, nh, ngi)) return;  // also an empty frontier
+  const bool inner = nl <= kInnerMost && nh == 0 && ngi == 0;  // as in k_expand
+  if (inner && blockIdx.x != 0) return;
   __shared__ Stage S[4];
+  __shared__ uint32_t list[kStage];
+  __shared__ Extras E;
+  if (threadIdx.x == 0) E.n = 0;
   for (int k = 0; k < 3; ++k) stage_open(S[k], q.next.q[k], q.next.c[k]);
   stage_open(S[3], inval, inval_cnt);
   __syncthreads();
-  // single-bucket vertices: one lane each; the child tests of a slab are issued together
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nl; i += gridDim.x * blockDim.x) {
-    const uint32_t x = q.cur[0][i];
-    if (F.nbk[x] != 1) continue;
-    Slab sl;
-    uint32_t t = x;
-    while (true) {
-      load_slab(F, t, sl);
-      uint64_t dy[kKeysPerSlab];
+  uint32_t step = 0;
+  do {
+    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E,
+                  [](uint32_t) { return 0; },
+                  [&](uint32_t x, int, const Slab& sl, int nd) {
+                    uint64_t dy[kKeysPerSlab];
+                    load_of_keys<uint64_t>(D, sl, live_words(sl, nd), kTreeNone, dy);
+                    uint32_t nb[kKeysPerSlab];
 #pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) {
-        const uint32_t y = (uint32_t)sl.w[j];
-        dy[j] = valid_key(y) ? ld_u64(D + y) : kTreeNone;
-      }
+                    for (int j = 0; j < kKeysPerSlab; ++j) {
+                      const uint32_t y = (uint32_t)sl.w[j];
+                      const bool child = dy[j] != kTreeNone && (uint32_t)dy[j] == x;
+                      nb[j] = child && !single ? F.nbk[y] : 1u;
+                      dy[j] = child ? cas64(D + y, dy[j], kTreeNone) ^ dy[j] : 1ull;  // 0: this lane cut y
+                    }
+                    uint32_t cut = 0, heavy = 0, giant = 0;
 #pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) {
-        const uint32_t y = (uint32_t)sl.w[j];
-        const bool child = dy[j] != kTreeNone && (uint32_t)dy[j] == x;
-        dy[j] = child ? cas64(D + y, dy[j], kTreeNone) ^ dy[j] : 1ull;  // 0: this lane cut y
-      }
-      uint32_t cut = 0;
-#pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j)
-        if (dy[j] == 0) cut |= 1u << j;
-      uint32_t heavy = 0, giant = 0;
-#pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) {
-        const uint32_t nb = (cut >> j & 1) ? F.nbk[(uint32_t)sl.w[j]] : 1u;
-        if (nb > kGiantBuckets) giant |= 1u << j;
-        else if (nb > kHeavyBuckets) heavy |= 1u << j;
-      }
-      stage_words(S[3], cut, sl);
-      stage_words(S[0], cut & ~(heavy | giant), sl);
-      stage_words(S[1], heavy, sl);
-      stage_words(S[2], giant, sl);
-      t = (uint32_t)sl.w[15];
-      if (t == kInvalid) break;
-    }
-  }
-  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
-  const uint32_t ng = gridDim.x * kGroupsPerBlock;
-  for (uint32_t i = g0; i < nl; i += ng) {
-    const uint32_t x = q.cur[0][i];
-    if (F.nbk[x] == 1) continue;
-    for_each_slab(F, x, [&](uint64_t w, bool data) { inval_word(F, D, x, w, data, S); });
-  }
-  const uint32_t gib = threadIdx.x / kGroup;
-  for (uint32_t j = blockIdx.x; j < nh; j += gridDim.x) {
-    const uint32_t x = q.cur[1][j];
-    for_each_slab_strided(F, x, gib, kGroupsPerBlock, [&](uint64_t w, bool data) {
-      inval_word(F, D, x, w, data, S);
-    });
-  }
-  for (uint32_t it = g0; it < ngi * kGiantSplit; it += ng) {
-    const uint32_t x = q.cur[2][it / kGiantSplit];
-    for_each_slab_strided(F, x, it % kGiantSplit, kGiantSplit, [&](uint64_t w, bool data) {
-      inval_word(F, D, x, w, data, S);
-    });
-  }
+                    for (int j = 0; j < kKeysPerSlab; ++j) {
+                      if (dy[j] != 0) continue;
+                      cut |= 1u << j;
+                      if (nb[j] > kGiantBuckets) giant |= 1u << j;
+                      else if (nb[j] > kHeavyBuckets) heavy |= 1u << j;
+                    }
+                    stage_words(S[3], cut, sl);
+                    stage_words(S[0], cut & ~(heavy | giant), sl);
+                    if (!single) {
+                      stage_words(S[1], heavy, sl);
+                      stage_words(S[2], giant, sl);
+                    }
+                  });
+  } while (inner && inner_next(S, list, nl, step));
   stage_close(S);
 }
 
@@ -536,6 +547,11 @@ __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queu
 // Single-bucket vertices are pulled by one lane, up to kHeavyBuckets buckets by a 16-lane
 // group, larger ones by a whole block (each group offers its own best; the atomic
 // minimum keeps the smallest).
+//
+// A vertex is listed once, so the lane or group that pulls it is the only writer of its node and
+// its mark: plain stores, no exchange.  Its neighbours' loads stay under their own conditions
+// here: the kernel is bound by the random accesses of millions of vertices, and the registers of
+// 15 loads in flight would halve the waves that hide them (1.46 -> 3.26 ms on the grid).
 template <bool kUnit>
 __device__ inline uint64_t pull_word(const uint64_t* D, uint64_t x, bool data) {
   const uint32_t u = (uint32_t)x;
@@ -545,63 +561,81 @@ __device__ inline uint64_t pull_word(const uint64_t* D, uint64_t x, bool data) {
   return tree_node((du >> 32) + (kUnit ? 1ull : (x >> 32)), u);
 }
 
+// A vertex pulled by its only lane or group joins the frontier (distance below T) or the pile.
+__device__ inline void push_pulled(Stage (&S)[4], const uint32_t* nbk, const Route& r, uint32_t T, uint32_t* mark,
+                                   uint32_t stamp, bool single, uint32_t y, uint64_t best) {
+  const bool p = best != kTreeNone, near = p && (uint32_t)(best >> 32) < T;
+  if (near) mark[y] = stamp;
+  else if (p) r.far_mark[y] = r.band;
+  const uint32_t nb = near && !single ? nbk[y] : 1u;
+  stage_push(S[3], p && !near, y);
+  stage_push(S[0], near && nb <= kHeavyBuckets, y);
+  if (!single) {
+    stage_push(S[1], near && nb > kHeavyBuckets && nb <= kGiantBuckets, y);
+    stage_push(S[2], near && nb > kGiantBuckets, y);
+  }
+}
+
 template <bool kUnit>
 __global__ void __launch_bounds__(kBlock) k_dec_pull(DView F, DView R, uint64_t* D,
                                                      const uint32_t* inval, const uint32_t* inval_cnt,
-                                                     PushQ Q, Route r, uint32_t* mark, uint32_t stamp) {
+                                                     PushQ Q, Route r, uint32_t* mark, uint32_t stamp, bool single,
+                                                     bool r_single) {
+  const uint32_t n = *inval_cnt;
+  if ((uint64_t)blockIdx.x * (r_single ? kBlock : 1) >= n) return;
   __shared__ Stage S[4];
   open_routed(S, Q, r);
-  const uint32_t n = *inval_cnt;
-  const uint32_t T = band_limit(r);
+  const uint32_t T = kUnit ? 0xFFFFFFFFu : band_limit(r);
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const uint32_t y = inval[i];
-    if (R.nbk[y] != 1) continue;
     uint64_t best = kTreeNone;
     Slab sl;
-    uint32_t t = y;
+    load_slab(R, y, sl);
+    if ((uint32_t)(sl.w[15] >> 32) != 1) continue;
     while (true) {
-      load_slab(R, t, sl);
       uint64_t c[kKeysPerSlab];
 #pragma unroll
       for (int j = 0; j < kKeysPerSlab; ++j) c[j] = pull_word<kUnit>(D, sl.w[j], true);
 #pragma unroll
       for (int j = 0; j < kKeysPerSlab; ++j) best = c[j] < best ? c[j] : best;
-      t = (uint32_t)sl.w[15];
+      const uint32_t t = (uint32_t)sl.w[15];
       if (t == kInvalid) break;
+      load_slab(R, t, sl);
     }
-    bool improve = false;
-    if (best != kTreeNone) improve = amin64(D + y, best) > best;
-    push_staged(S, F.nbk, r, T, mark, stamp, improve, y, (uint32_t)(best >> 32));
+    if (best != kTreeNone) __hip_atomic_store(D + y, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    push_pulled(S, F.nbk, r, T, mark, stamp, single, y, best);
   }
-  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
-  const uint32_t ng = gridDim.x * kGroupsPerBlock;
-  for (uint32_t i = g0; i < n; i += ng) {
-    const uint32_t y = inval[i];
-    const uint32_t nb = R.nbk[y];
-    if (nb == 1 || nb > kHeavyBuckets) continue;
-    uint64_t best = kTreeNone;
-    for_each_slab(R, y, [&](uint64_t x, bool data) {
-      const uint64_t c = pull_word<kUnit>(D, x, data);
-      best = c < best ? c : best;
-    });
-    best = gmin_u64(best);
-    bool improve = false;
-    if (glane() == 0 && best != kTreeNone) improve = amin64(D + y, best) > best;
-    push_staged(S, F.nbk, r, T, mark, stamp, improve, y, (uint32_t)(best >> 32));
-  }
-  const uint32_t gib = threadIdx.x / kGroup;
-  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
-    const uint32_t y = inval[i];
-    if (R.nbk[y] <= kHeavyBuckets) continue;
-    uint64_t best = kTreeNone;
-    for_each_slab_strided(R, y, gib, kGroupsPerBlock, [&](uint64_t x, bool data) {
-      const uint64_t c = pull_word<kUnit>(D, x, data);
-      best = c < best ? c : best;
-    });
-    best = gmin_u64(best);
-    bool improve = false;
-    if (glane() == 0 && best != kTreeNone) improve = amin64(D + y, best) > best;
-    push_staged(S, F.nbk, r, T, mark, stamp, improve, y, (uint32_t)(best >> 32));
+  if (!r_single) {
+    const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
+    const uint32_t ng = gridDim.x * kGroupsPerBlock;
+    for (uint32_t i = g0; i < n; i += ng) {
+      const uint32_t y = inval[i];
+      const uint32_t nb = R.nbk[y];
+      if (nb == 1 || nb > kHeavyBuckets) continue;
+      uint64_t best = kTreeNone;
+      for_each_slab(R, y, [&](uint64_t x, bool data) {
+        const uint64_t c = pull_word<kUnit>(D, x, data);
+        best = c < best ? c : best;
+      });
+      best = gmin_u64(best);
+      if (glane() != 0) best = kTreeNone;  // lane 0 writes and pushes
+      if (best != kTreeNone) __hip_atomic_store(D + y, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      push_pulled(S, F.nbk, r, T, mark, stamp, single, y, best);
+    }
+    const uint32_t gib = threadIdx.x / kGroup;
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+      const uint32_t y = inval[i];
+      if (R.nbk[y] <= kHeavyBuckets) continue;
+      uint64_t best = kTreeNone;
+      for_each_slab_strided(R, y, gib, kGroupsPerBlock, [&](uint64_t x, bool data) {
+        const uint64_t c = pull_word<kUnit>(D, x, data);
+        best = c < best ? c : best;
+      });
+      best = gmin_u64(best);
+      bool improve = false;
+      if (glane() == 0 && best != kTreeNone) improve = amin64(D + y, best) > best;
+      push_staged(S, F.nbk, r, T, mark, stamp, improve, y, (uint32_t)(best >> 32));
+    }
   }
   stage_close(S);
 }
@@ -632,9 +666,12 @@ struct TravCtx {
   uint32_t* far[2];     // far piles of the weighted epilogue
   uint32_t* far_mark;
   uint32_t* cnt;        // [0..8] rotating frontier sizes, [9..10] pile sizes,
-                        // [11..12] band thresholds, [13] smallest pile distance
+                        // [11..12] band thresholds, [13..14] smallest pile distance, by band
   uint32_t* inval_cnt;  // invalidated-list size
-  uint32_t* stamp;      // host-side stamp counter (also numbers the bands)
+  uint32_t* stamp;      // host-side counter of frontier stamps
+  uint32_t* bands;      // host-side counter that numbers the bands
+  uint32_t n;           // vertices
+  bool single;          // every vertex has one bucket
   uint64_t* h_pin;      // pinned host words for size read-backs
   uint32_t delta;       // band width
 };
@@ -651,6 +688,9 @@ TravCtx graph_ctx(mk_graph* g, uint64_t* D) {
   c.cnt = g->ctr->frontier;
   c.inval_cnt = &g->ctr->inval;
   c.stamp = &g->stamp;
+  c.bands = &g->bands;
+  c.n = g->n;
+  c.single = g->view[VF].n_head == g->n;
   c.h_pin = g->h_pin;
   c.delta = g->sssp_delta;
   return c;
@@ -672,7 +712,7 @@ template <bool kUnit>
 Route first_route(const TravCtx& c, Bands& b) {
   if (kUnit) return Route{nullptr, nullptr, nullptr, nullptr, 0};
   b = Bands{};
-  b.band = ++*c.stamp;
+  b.band = ++*c.bands;
   return route_of(c, b);
 }
 
@@ -701,6 +741,18 @@ Queues queues(const TravCtx& c, uint64_t it) {
   return q;
 }
 
+// The first of `steps` fresh stamps.  Marks only matter within one step, so when the stamps run
+// out the marks are cleared and the count starts again.
+uint32_t next_stamps(const TravCtx& c, uint32_t steps, hipStream_t stream) {
+  if (*c.stamp > 0xFFFFFFFFu - 2 * kInnerSteps) {
+    hipLaunchKernelGGL(k_fill_mark, dim3(blocks_for(c.n)), dim3(kBlock), 0, stream, c.mark, c.n);
+    *c.stamp = 0;
+  }
+  const uint32_t first = *c.stamp + 1;
+  *c.stamp += steps;
+  return first;
+}
+
 // Run frontier iterations (expand or propagate) from iteration *it until the frontier is
 // empty.  Iteration `it` reads slot it%3; the frontier of iteration 0 sits in fq[0] /
 // fq[2] / fq[4] and slot 0.  On return *it is the first iteration with an empty frontier
@@ -712,7 +764,7 @@ mk_status run_frontier(mk_graph* g, const TravCtx& c, hipStream_t stream, Launch
   int every = kSyncFirst;
   for (;; every = every < kSyncMax ? 2 * every : kSyncMax) {
     for (int k = 0; k < every; ++k, ++it) {
-      launch(queues(c, it), ++*c.stamp);
+      launch(queues(c, it), next_stamps(c, kInnerSteps, stream));
       MK_LAUNCH(g, "frontier kernel");
     }
     const int slot = (int)(it % 3);
@@ -737,25 +789,24 @@ mk_status run_expand(mk_graph* g, const TravCtx& c, hipStream_t stream, Bands& b
     const Route r{nullptr, nullptr, nullptr, nullptr, 0};
     return run_frontier(g, c, stream, [&](Queues q, uint32_t stamp) {
       hipLaunchKernelGGL(k_expand<kUnit>, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F, c.D, q, r,
-                         c.mark, stamp);
+                         c.mark, stamp, c.single);
     });
   }
-  uint32_t* fmin = c.cnt + 13;
   uint64_t it = 0;
-  while (true) {
+  for (uint32_t k = 0;; ++k) {
     const int nf = b.fb ^ 1, nt = b.tb ^ 1;
-    const uint32_t band_next = ++*c.stamp;
-    hipLaunchKernelGGL(k_band_reset, dim3(1), dim3(64), 0, stream, fmin, c.cnt + 9 + nf);
+    const uint32_t band_next = ++*c.bands;
+    uint32_t *fmin = c.cnt + 13 + (k & 1), *fmin_next = c.cnt + 13 + (~k & 1);
     hipLaunchKernelGGL(k_band_min, dim3(kBandBlocks), dim3(kBlock), 0, stream, c.D, c.far[b.fb],
-                       c.cnt + 9 + b.fb, c.cnt + 11 + b.tb, fmin);
+                       c.cnt + 9 + b.fb, c.cnt + 11 + b.tb, fmin, c.cnt + 9 + nf);
     PushQ cur;
     for (int k = 0; k < 3; ++k) {
       cur.q[k] = c.fq[2 * k + (int)(it & 1)];
       cur.c[k] = c.cnt + 3 * k + (int)(it % 3);
     }
     hipLaunchKernelGGL(k_band_split, dim3(kBandBlocks), dim3(kBlock), 0, stream, F.nbk, c.D, c.far[b.fb],
-                       c.cnt + 9 + b.fb, c.cnt + 11 + b.tb, fmin, c.delta, c.cnt + 11 + nt, cur, c.far[nf],
-                       c.cnt + 9 + nf, c.far_mark, band_next);
+                       c.cnt + 9 + b.fb, c.cnt + 11 + b.tb, fmin, fmin_next, c.delta, c.cnt + 11 + nt, cur, c.far[nf],
+                       c.cnt + 9 + nf, c.far_mark, band_next, c.single);
     MK_LAUNCH(g, "band step");
     b.fb = nf;
     b.tb = nt;
@@ -763,7 +814,7 @@ mk_status run_expand(mk_graph* g, const TravCtx& c, hipStream_t stream, Bands& b
     const Route r = route_of(c, b);
     mk_status s = run_frontier(g, c, stream, [&](Queues q, uint32_t stamp) {
       hipLaunchKernelGGL(k_expand<kUnit>, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F, c.D, q, r,
-                         c.mark, stamp);
+                         c.mark, stamp, c.single);
     }, &it);
     if (s != MK_OK) return s;
     const uint32_t* h = reinterpret_cast<const uint32_t*>(c.h_pin);
@@ -775,7 +826,7 @@ mk_status run_expand(mk_graph* g, const TravCtx& c, hipStream_t stream, Bands& b
 template <bool kUnit>
 mk_status static_from(mk_graph* g, const TravCtx& c, uint32_t source, hipStream_t stream) {
   const DView F = g->view[VF].d;
-  const uint32_t stamp0 = ++*c.stamp;
+  const uint32_t stamp0 = next_stamps(c, 1, stream);
   hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, stream, c.cnt, c.inval_cnt);
   hipLaunchKernelGGL(k_trav_init, dim3(blocks_for(g->n)), dim3(kBlock), 0, stream, c.D, g->n, source);
   Bands b;
@@ -812,7 +863,7 @@ mk_status traverse(mk_graph* g, AlgoState& st, uint64_t* D, uint32_t source, uin
                            : sssp_tree_by_distances(g, source, d_out, D, stream);
     if (s != MK_OK) return s;
   } else if (!p.list.empty()) {
-    const uint32_t stamp0 = ++g->stamp;
+    const uint32_t stamp0 = next_stamps(c, 1, stream);
     hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, stream, c.cnt, c.inval_cnt);
     Bands bands;
     if (p.kinds == 1) {
@@ -833,14 +884,15 @@ mk_status traverse(mk_graph* g, AlgoState& st, uint64_t* D, uint32_t source, uin
       MK_LAUNCH(g, "k_invalidate");
       mk_status s = run_frontier(g, c, stream, [&](Queues q, uint32_t stamp) {
         hipLaunchKernelGGL(k_propagate, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F, D, q, c.inval,
-                           c.inval_cnt);
+                           c.inval_cnt, c.single);
       });
       if (s != MK_OK) return s;
       hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, stream, c.cnt, nullptr);
-      const uint32_t stamp1 = ++g->stamp;
+      const uint32_t stamp1 = next_stamps(c, 1, stream);
       const Route r0 = first_route<kUnit>(c, bands);
       hipLaunchKernelGGL(k_dec_pull<kUnit>, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F,
-                         g->view[VR].d, D, c.inval, c.inval_cnt, first_push(c), r0, c.mark, stamp1);
+                         g->view[VR].d, D, c.inval, c.inval_cnt, first_push(c), r0, c.mark, stamp1, c.single,
+                         g->view[VR].n_head == N);
     }
     MK_LAUNCH(g, "traversal prologue");
     mk_status s = run_expand<kUnit>(g, c, stream, bands);
@@ -906,8 +958,11 @@ mk_status mk_traverse_from(mk_graph* g, uint32_t source, int weighted, void* d_w
   c.far_mark = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   c.cnt = reinterpret_cast<uint32_t*>(take(128));
   c.inval_cnt = c.cnt + 16;
-  uint32_t stamp = 0;
+  uint32_t stamp = 0, bands = 0;
   c.stamp = &stamp;
+  c.bands = &bands;
+  c.n = N;
+  c.single = g->view[VF].n_head == N;
   c.h_pin = g->slot_pin[slot];
   c.delta = g->sssp_delta;
   hipLaunchKernelGGL(k_fill_mark, dim3(blocks_for(N)), dim3(kBlock), 0, stream, c.mark, N);
