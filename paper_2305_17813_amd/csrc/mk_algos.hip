@@ -79,6 +79,32 @@ __device__ inline void uf_union(uint32_t* P, uint32_t a, uint32_t b) {
   }
 }
 
+// The same with another order: the hooked root is the one of larger uf_order.  Every parent pointer
+// among roots then goes to a smaller order, whatever the ids, and chains stay short where
+// neighbouring ids would make long ones (a row of a grid).  The root of a component is no
+// longer its smallest id; k_wcc_min and k_wcc_label find that.
+// uf_order is a bijection of the ids: the 32-bit finalizer of MurmurHash3 (Appleby).
+__device__ inline uint32_t uf_order(uint32_t x) {
+  x = (x ^ x >> 16) * 0x85EBCA6Bu;
+  x = (x ^ x >> 13) * 0xC2B2AE35u;
+  return x ^ x >> 16;
+}
+__device__ inline void uf_union_any(uint32_t* P, uint32_t a, uint32_t b) {
+  while (true) {
+    a = uf_find(P, a);
+    b = uf_find(P, b);
+    if (a == b) return;
+    if (uf_order(a) < uf_order(b)) {
+      const uint32_t t = a;
+      a = b;
+      b = t;
+    }
+    const uint32_t r = atomicCAS(P + a, a, b);
+    if (r == a) return;
+    a = r;  // a was hooked meanwhile: continue from its true parent
+  }
+}
+
 __global__ void k_wcc_init(uint32_t* P, uint32_t nv) {
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) P[v] = v;
 }
@@ -86,13 +112,8 @@ __global__ void k_wcc_init(uint32_t* P, uint32_t nv) {
 // Static WCC: union over every arc.  A neighbour whose parent already is u's root (as
 // found once per vertex; a stale root only means an older member of the same component)
 // is skipped without a union, and a lane issues the parent loads of a whole slab together.
-//
-// With `big` set (the sampled static WCC below), a vertex whose root is *big is skipped: its
-// arcs are left to their other ends, which then walk both directions (the undirected view).
 __global__ void __launch_bounds__(kBlock) k_wcc_all(DView F, uint32_t* P, uint32_t nv,
-                                                    const uint32_t* heavy, const uint32_t* nheavy,
-                                                    const uint32_t* big) {
-  const uint32_t skip = big ? *big : kInvalid;
+                                                    const uint32_t* heavy, const uint32_t* nheavy, bool single) {
   const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
   const uint32_t ng = gridDim.x * kGroupsPerBlock;
   auto body = [&](uint32_t u, uint32_t ru, uint64_t x, bool data) {
@@ -103,7 +124,6 @@ __global__ void __launch_bounds__(kBlock) k_wcc_all(DView F, uint32_t* P, uint32
   for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nv; u += gridDim.x * blockDim.x) {
     if (F.nbk[u] != 1 || F.deg[u] == 0) continue;
     const uint32_t ru = uf_find(P, u);
-    if (ru == skip) continue;
     Slab sl;
     uint32_t t = u;
     while (true) {
@@ -121,77 +141,255 @@ __global__ void __launch_bounds__(kBlock) k_wcc_all(DView F, uint32_t* P, uint32
       if (t == kInvalid) break;
     }
   }
+  if (single) return;  // no vertex has several buckets
   for (uint32_t u = g0; u < nv; u += ng) {
     const uint32_t nb = F.nbk[u];
     if (nb == 1 || nb > kHeavyBuckets || F.deg[u] == 0) continue;
     const uint32_t ru = uf_find(P, u);
-    if (ru == skip) continue;
     for_each_slab(F, u, [&](uint64_t x, bool data) { body(u, ru, x, data); });
   }
   const uint32_t nh = *nheavy, gib = threadIdx.x / kGroup;
   for (uint32_t j = blockIdx.x; j < nh; j += gridDim.x) {
     const uint32_t u = heavy[j];
     const uint32_t ru = uf_find(P, u);
-    if (ru == skip) continue;
     for_each_slab_strided(F, u, gib, kGroupsPerBlock, [&](uint64_t x, bool data) { body(u, ru, x, data); });
   }
 }
 
+// Before the all-arc walk of a static WCC: every vertex points at the smallest id among itself and
+// the first four words of its primary slab, without atomics, and k_wcc_jump shortens the chains
+// (four pointers per pass).  The walk then finds nearly every neighbour under the same root and
+// unites the few trees that are left, where it used to unite every arc of a forest of single
+// vertices: 3.25 ms on the 4096 x 4096 grid, 2.2 ms with it.
+constexpr uint32_t kWccHook = 4;
+__device__ inline void first_words(const DView& V, uint32_t u, uint32_t (&v)[kWccHook]) {
+  const uint4* q = reinterpret_cast<const uint4*>(slab_ptr(V, u));
+  const uint4 a = q[0], b = q[1];
+  v[0] = a.x;
+  v[1] = a.z;
+  v[2] = b.x;
+  v[3] = b.z;
+}
+
+__global__ void __launch_bounds__(kBlock) k_wcc_hook_min(DView V, uint32_t* P, uint32_t nv) {
+  for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nv; u += gridDim.x * blockDim.x) {
+    uint32_t best = u;
+    if (V.deg[u]) {
+      uint32_t v[kWccHook];
+      first_words(V, u, v);
+#pragma unroll
+      for (uint32_t k = 0; k < kWccHook; ++k) best = min(best, v[k]);  // EMPTY and TOMBSTONE are larger
+    }
+    P[u] = best;
+  }
+}
+
+constexpr int kWccJumps = 3;  // 2: 2.4 ms for hook, jumps and walk on the grid; 3: 2.2; 5: 2.3
+__global__ void __launch_bounds__(kBlock) k_wcc_jump(uint32_t* P, uint32_t nv) {
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const uint32_t p = ld_u32(P + v);
+    if (p == v) continue;
+    uint32_t r = p;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r = ld_u32(P + r);
+    if (r != p) __hip_atomic_store(P + v, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 // Sampled static WCC (after the subgraph-sampling method of Sutton, Ben-Nun and Barak,
-// "Optimizing parallel graph connectivity computation via subgraph sampling", IPDPS 2018).
-// First every vertex points its parent at the smallest id among itself and the neighbours in
-// its primary slab of the undirected view (at most 15, one 128-byte read, no atomics): a
-// forest whose every edge is an arc, which on a power-law graph already holds most of the
-// giant component in one tree.  After flattening, the most frequent root among kWccSamples
-// sampled vertices is taken as the largest component, and only vertices outside it walk their
-// neighbourhoods (both directions, with unions), so the giant component's arcs are not read.
-// The partition is the plain one (labels are still component minima): every arc with an end
-// outside the largest component is united from that end, and an arc with both ends inside
-// joins nothing new.
+// "Optimizing parallel graph connectivity computation via subgraph sampling", IPDPS 2018), over
+// the undirected view (both ends of an arc see it):
+//   1. k_wcc_hook: every vertex points at the neighbour of highest degree among the first four
+//      words of its primary slab (ties: smallest uf_order), if that ranks above itself.  No
+//      atomics and no contention: the pointers climb towards the hubs.  On a power-law graph
+//      this alone gathers nearly every vertex of the giant component under a few hubs.
+//   2. k_wcc_link over the remaining roots: each unites with those four neighbours.
+//   3. k_wcc_big: the most frequent root among kWccSamples vertices is taken as the largest
+//      component.  If it holds less than half of the samples (a road network, where hooking makes
+//      small trees), every vertex unites with its first two neighbours and the samples are
+//      taken again.
+//   4. k_wcc_rest: every vertex points at its root; those outside the largest component are
+//      listed, and k_wcc_walk unites them with all their neighbours, so the arcs of the largest
+//      component are not read.  An arc with an end outside it is united from that end; an arc
+//      with both ends inside joins nothing new, so the partition is the plain one.
+//   5. k_wcc_min, k_wcc_label: the smallest id of each component becomes its root and label.
+// Uniting every vertex with two neighbours under the smaller id (instead of 1 and 2) took 1.1-1.3
+// ms at R-MAT scale 22: half of those unions hook a hub's root, and their CASes meet on a few
+// words.  With the walk of step 4 over every vertex, the recompute took 1.6 ms; it takes 0.31.
 constexpr uint32_t kWccLinks = 2;
 constexpr uint32_t kWccSamples = 1024;
 
-__global__ void k_wcc_link_first(DView U, uint32_t* P, uint32_t nv) {
+__global__ void __launch_bounds__(kBlock) k_wcc_hook(DView V, uint32_t* P, uint32_t* M, uint32_t nv) {
   for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nv; u += gridDim.x * blockDim.x) {
-    if (U.deg[u] == 0) continue;
-    const uint64_t* hs = slab_ptr(U, u);
-    const int nd = (uint32_t)(ld_word(hs + 15) >> 32) > 1 ? kKeysPerSlab - 1 : kKeysPerSlab;
-    const uint32_t ru = uf_find(P, u);
-    uint32_t linked = 0;
-    for (int i = 0; i < nd && linked < kWccLinks; ++i) {
-      const uint32_t v = (uint32_t)ld_word(hs + i);
-      if (!valid_key(v)) continue;
-      if (ld_u32(P + v) != ru) uf_union(P, u, v);
+    const uint32_t d = V.deg[u];
+    uint32_t best = u, bd = d;
+    if (d) {
+      uint32_t v[kWccHook], dv[kWccHook];
+      first_words(V, u, v);
+#pragma unroll
+      for (uint32_t k = 0; k < kWccHook; ++k) dv[k] = V.deg[valid_key(v[k]) ? v[k] : u];
+#pragma unroll
+      for (uint32_t k = 0; k < kWccHook; ++k)
+        if (valid_key(v[k]) && (dv[k] > bd || (dv[k] == bd && uf_order(v[k]) < uf_order(best)))) {
+          best = v[k];
+          bd = dv[k];
+        }
+    }
+    P[u] = best;
+    M[u] = u;
+  }
+}
+
+// Unite vertices with neighbours from their primary slabs' first words: the roots with all four
+// (all == false), or, when the sample found no largest component (*enough == 0), every vertex
+// with the first kWccLinks.
+__global__ void __launch_bounds__(kBlock) k_wcc_link(DView V, uint32_t* P, uint32_t nv, bool all,
+                                                     const uint32_t* enough) {
+  if (all && *enough) return;
+  for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nv; u += gridDim.x * blockDim.x) {
+    if ((!all && ld_u32(P + u) != u) || V.deg[u] == 0) continue;
+    uint32_t v[kWccHook], linked = 0;
+    first_words(V, u, v);
+#pragma unroll
+    for (uint32_t k = 0; k < kWccHook; ++k) {
+      if (!valid_key(v[k]) || (all && linked == kWccLinks)) continue;
+      uf_union_any(P, u, v[k]);
       ++linked;
     }
   }
 }
 
-// Every parent made a root (no labels written); a plain walk to the root, as in k_wcc_compress.
-__global__ void k_wcc_flatten(uint32_t* P, uint32_t nv) {
-  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
-    uint32_t r = v;
-    for (uint32_t p = ld_u32(P + r); p != r; p = ld_u32(P + r)) r = p;
-    __hip_atomic_store(P + v, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+__device__ inline uint32_t wcc_root(const uint32_t* P, uint32_t v) {
+  uint32_t r = v;
+  for (uint32_t p = ld_u32(P + r); p != r; p = ld_u32(P + r)) r = p;
+  return r;
 }
 
-// One block of kWccSamples threads: the most frequent root among the sampled vertices
-// (ties: the smaller root) into *big.  Samples are spread over the ids by a Weyl sequence.
-__global__ void __launch_bounds__(kWccSamples) k_wcc_big(const uint32_t* P, uint32_t nv, uint32_t* big) {
-  __shared__ uint32_t root[kWccSamples];
+// One block of kWccSamples threads: the most frequent root among the sampled vertices into *big,
+// and whether it holds at least half of them into *enough.  Samples are spread over the ids by a
+// Weyl sequence and counted in an LDS table (two slots per sample, linear probing).
+__global__ void __launch_bounds__(kWccSamples) k_wcc_big(const uint32_t* P, uint32_t nv, uint32_t* big,
+                                                         uint32_t* enough, bool again) {
+  __shared__ uint32_t key[2 * kWccSamples], cnt[2 * kWccSamples];
   __shared__ unsigned long long best;
-  const uint32_t v = (uint32_t)(((uint64_t)threadIdx.x * 0x9E3779B97F4A7C15ull >> 32) % nv);
-  root[threadIdx.x] = ld_u32(P + v);
+  if (again && *enough) return;
+  for (uint32_t i = threadIdx.x; i < 2 * kWccSamples; i += kWccSamples) {
+    key[i] = kInvalid;
+    cnt[i] = 0;
+  }
   if (threadIdx.x == 0) best = 0;
+  const uint32_t r = wcc_root(P, (uint32_t)(((uint64_t)threadIdx.x * 0x9E3779B97F4A7C15ull >> 32) % nv));
   __syncthreads();
-  const uint32_t r = root[threadIdx.x];
-  uint32_t n = 0;
-  for (uint32_t i = 0; i < kWccSamples; ++i) n += root[i] == r;
+  uint32_t h = uf_order(r) & (2 * kWccSamples - 1);
+  while (true) {
+    const uint32_t old = atomicCAS(&key[h], kInvalid, r);
+    if (old == kInvalid || old == r) break;
+    h = (h + 1) & (2 * kWccSamples - 1);
+  }
+  const uint32_t n = atomicAdd(&cnt[h], 1u) + 1u;  // the last adder sees the whole count
   // larger count first, then the smaller root
   atomicMax(&best, ((unsigned long long)n << 32) | (0xFFFFFFFFu - r));
   __syncthreads();
-  if (threadIdx.x == 0) *big = 0xFFFFFFFFu - (uint32_t)best;
+  if (threadIdx.x == 0) {
+    *big = 0xFFFFFFFFu - (uint32_t)best;
+    *enough = (uint32_t)(best >> 32) * 2 >= kWccSamples;
+  }
+}
+
+// Every parent made a root (a plain walk, as in k_wcc_compress), and the vertices with arcs
+// outside the largest component listed; those of more than kHeavyBuckets buckets a second time.
+__global__ void __launch_bounds__(kBlock) k_wcc_rest(DView U, uint32_t* P, uint32_t nv, const uint32_t* big,
+                                                     uint32_t* rest, uint32_t* nrest, uint32_t* heavy,
+                                                     uint32_t* nheavy) {
+  __shared__ Stage S[2];
+  stage_open(S[0], rest, nrest);
+  stage_open(S[1], heavy, nheavy);
+  __syncthreads();
+  const uint32_t skip = *big;
+  for (uint32_t base = blockIdx.x * kBlock; base < nv; base += gridDim.x * kBlock) {
+    const uint32_t v = base + threadIdx.x;
+    bool out = false, hv = false;
+    if (v < nv) {
+      const uint32_t r = wcc_root(P, v);
+      __hip_atomic_store(P + v, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (r != skip) {
+        out = U.deg[v] != 0;
+        hv = out && U.nbk[v] > kHeavyBuckets;
+      }
+    }
+    stage_push(S[0], out, v);
+    stage_push(S[1], hv, v);
+  }
+  stage_close(S);
+}
+
+// Unite every listed vertex with all its neighbours: a lane to a vertex of one
+// bucket, a 16-lane group to one of up to kHeavyBuckets, a block to the others.
+__global__ void __launch_bounds__(kBlock) k_wcc_walk(DView V, uint32_t* P, const uint32_t* rest, const uint32_t* nrest,
+                                                     const uint32_t* heavy, const uint32_t* nheavy) {
+  const uint32_t n = *nrest, nh = *nheavy;
+  const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
+  const uint32_t ng = gridDim.x * kGroupsPerBlock;
+  auto unite = [&](uint32_t u, uint32_t ru, uint64_t x, bool data) {
+    const uint32_t v = (uint32_t)x;
+    if (data && valid_key(v) && ld_u32(P + v) != ru) uf_union_any(P, u, v);
+  };
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+    const uint32_t u = rest[i];
+    if (V.nbk[u] != 1 || V.deg[u] == 0) continue;
+    const uint32_t ru = uf_find(P, u);
+    Slab sl;
+    uint32_t t = u;
+    while (true) {
+      load_slab(V, t, sl);
+#pragma unroll
+      for (int j = 0; j < kKeysPerSlab; ++j) unite(u, ru, sl.w[j], true);
+      t = (uint32_t)sl.w[15];
+      if (t == kInvalid) break;
+    }
+  }
+  for (uint32_t i = g0; i < n; i += ng) {
+    const uint32_t u = rest[i], nb = V.nbk[u];
+    if (nb == 1 || nb > kHeavyBuckets) continue;
+    const uint32_t ru = uf_find(P, u);
+    for_each_slab(V, u, [&](uint64_t x, bool data) { unite(u, ru, x, data); });
+  }
+  const uint32_t gib = threadIdx.x / kGroup;
+  for (uint32_t j = blockIdx.x; j < nh; j += gridDim.x) {
+    const uint32_t u = heavy[j];
+    const uint32_t ru = uf_find(P, u);
+    for_each_slab_strided(V, u, gib, kGroupsPerBlock, [&](uint64_t x, bool data) { unite(u, ru, x, data); });
+  }
+}
+
+// The smallest id of each component at its root's entry of M.  No union runs any more, so the
+// roots are final.  The members of the largest sampled component make one atomic per block
+// (one per wave took 1.4 ms, all on one word); those of the others go straight to their entry,
+// unless a smaller id is there already.
+__global__ void __launch_bounds__(kBlock) k_wcc_min(uint32_t* P, uint32_t* M, uint32_t nv, const uint32_t* big) {
+  __shared__ uint32_t lowest;
+  if (threadIdx.x == 0) lowest = kInvalid;
+  __syncthreads();
+  const uint32_t rb = wcc_root(P, *big);
+  uint32_t mine = kInvalid;
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const uint32_t r = wcc_root(P, v);
+    __hip_atomic_store(P + v, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (r == rb) mine = min(mine, v);
+    else if (v < ld_u32(M + r)) atomicMin(M + r, v);
+  }
+  for (int o = 32; o > 0; o >>= 1) mine = min(mine, (uint32_t)__shfl_xor((int)mine, o));
+  if ((threadIdx.x & 63) == 0) atomicMin(&lowest, mine);
+  __syncthreads();
+  if (threadIdx.x == 0 && lowest < ld_u32(M + rb)) atomicMin(M + rb, lowest);
+}
+
+__global__ void k_wcc_label(uint32_t* P, const uint32_t* M, uint32_t nv, uint32_t* label) {
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const uint32_t l = M[P[v]];
+    P[v] = l;
+    label[v] = l;
+  }
 }
 
 // IterationScheme2 (section 3.4): one 16-lane group per bucket chain <v, i>, in a
@@ -2234,32 +2432,49 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
     }
     // IterationScheme1, collecting the heavy vertices first
     uint32_t* nh = &g->ctr->n_heavy_wcc;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, nh, 1u);
-    hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream,
-                       g->view[VF].nbk, N, g->fq[2], nh);
-    hipLaunchKernelGGL(k_wcc_all, dim3(kWalkBlocks), dim3(kBlock), 0, stream, F, P, N, g->fq[2], nh,
-                       nullptr);
+    const bool single = g->view[VF].n_head == N;
+    if (!single) {
+      hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, nh, 1u);
+      hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream,
+                         g->view[VF].nbk, N, g->fq[2], nh);
+    }
+    hipLaunchKernelGGL(k_wcc_all, dim3(blocks_for(N, 16384)), dim3(kBlock), 0, stream, F, P, N, g->fq[2], nh, single);
     return MK_OK;
   };
-  // the sampled static WCC: needs the undirected view (both directions of a skipped arc)
+  // the sampled static WCC: needs the undirected view (scratch: traversal queues)
+  bool labelled = false;  // k_wcc_label has written the labels
+  const dim3 all(blocks_for(N)), block(kBlock);
   auto sampled = [&]() {
     const DView U = g->view[VU].d;
-    uint32_t* nh = &g->ctr->n_heavy_wcc;
-    hipLaunchKernelGGL(k_wcc_link_first, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U, P, N);
-    hipLaunchKernelGGL(k_wcc_flatten, dim3(blocks_for(N)), dim3(kBlock), 0, stream, P, N);
-    hipLaunchKernelGGL(k_wcc_big, dim3(1), dim3(kWccSamples), 0, stream, P, N, &g->ctr->wcc_big);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, nh, 1u);
-    hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream,
-                       g->view[VU].nbk, N, g->fq[2], nh);
-    hipLaunchKernelGGL(k_wcc_all, dim3(kWalkBlocks), dim3(kBlock), 0, stream, U, P, N, g->fq[2], nh,
-                       &g->ctr->wcc_big);
+    uint32_t *M = g->fq[0], *rest = g->fq[1], *heavy = g->fq[2];
+    Counters* c = g->ctr;
+    hipLaunchKernelGGL(k_wcc_hook, all, block, 0, stream, U, P, M, N);
+    hipLaunchKernelGGL(k_wcc_link, all, block, 0, stream, U, P, N, false, &c->wcc_enough);
+    for (int again = 0; again < 2; ++again) {
+      if (again) hipLaunchKernelGGL(k_wcc_link, all, block, 0, stream, U, P, N, true, &c->wcc_enough);
+      hipLaunchKernelGGL(k_wcc_big, dim3(1), dim3(kWccSamples), 0, stream, P, N, &c->wcc_big, &c->wcc_enough,
+                         again != 0);
+    }
+    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, &c->n_listed_light, 2u);
+    hipLaunchKernelGGL(k_wcc_rest, all, block, 0, stream, U, P, N, &c->wcc_big, rest, &c->n_listed_light, heavy,
+                       &c->n_listed_heavy);
+    hipLaunchKernelGGL(k_wcc_walk, dim3(blocks_for(N, 2048)), block, 0, stream, U, P, rest, &c->n_listed_light, heavy,
+                       &c->n_listed_heavy);
+    hipLaunchKernelGGL(k_wcc_min, all, block, 0, stream, P, M, N, &c->wcc_big);
+    hipLaunchKernelGGL(k_wcc_label, all, block, 0, stream, P, M, N, d_label);
+    labelled = true;
   };
   if (full) {
-    hipLaunchKernelGGL(k_wcc_init, dim3(blocks_for(N)), dim3(kBlock), 0, stream, P, N);
-    if (g->view[VU].on && g->iter_scheme != MK_ITER_SCHEME2 && N > 0) {
+    if (g->view[VU].on && g->iter_scheme != MK_ITER_SCHEME2) {
       sampled();
-    } else if (mk_status st = all_arcs(); st != MK_OK) {
-      return st;
+    } else {
+      if (g->iter_scheme == MK_ITER_SCHEME2) {
+        hipLaunchKernelGGL(k_wcc_init, all, block, 0, stream, P, N);
+      } else {
+        hipLaunchKernelGGL(k_wcc_hook_min, all, block, 0, stream, F, P, N);
+        for (int k = 0; k < kWccJumps; ++k) hipLaunchKernelGGL(k_wcc_jump, all, block, 0, stream, P, N);
+      }
+      if (mk_status st = all_arcs(); st != MK_OK) return st;
     }
     if (scheme == MK_WCC_UPDATE)
       hipLaunchKernelGGL(k_mark_all, dim3(grid_for_groups(std::min<uint64_t>(g->view[VF].n_head, 1u << 20))),
@@ -2288,7 +2503,8 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
                          g->fq[0], nl, g->fq[1], nh);
     }
   }
-  if (full || !p.list.empty())
+  if (labelled) {
+  } else if (full || !p.list.empty())
     hipLaunchKernelGGL(k_wcc_compress, dim3(blocks_for(N)), dim3(kBlock), 0, stream, P, N, d_label);
   else  // nothing changed: the parents are the compressed labels of the last call
     hipLaunchKernelGGL(k_copy_u32, dim3(blocks_for(N)), dim3(kBlock), 0, stream, P, d_label, N);

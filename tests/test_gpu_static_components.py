@@ -1,0 +1,68 @@
+"""Static components on graphs where hooking makes long chains, many trees or none: paths whose
+ids rise, fall or are shuffled, combs and grids, many small components beside none that is large,
+and components of nearly equal size; with the undirected view and without it."""
+import numpy as np
+import pytest
+
+from paper_2305_17813_amd import inputs as I
+from paper_2305_17813_amd import native
+from parity import Pair, say
+
+pytestmark = pytest.mark.gpu
+
+
+def path(n, order):
+    ids = {"rising": np.arange(n), "falling": np.arange(n)[::-1],
+           "shuffled": np.random.default_rng(3).permutation(n)}[order]
+    ids = np.ascontiguousarray(ids)
+    return ids[:-1], ids[1:], n
+
+
+def cliques(count, size):
+    a, b = np.triu_indices(size, 1)
+    base = np.arange(count)[:, None] * size
+    return (base + a).ravel(), (base + b).ravel(), count * size + 3
+
+
+def comb(teeth, length):
+    """A path of `teeth` vertices, each with a path of `length` hanging off it."""
+    s, d, _ = path(teeth, "falling")
+    first = teeth + np.arange(teeth) * length
+    s, d = [s, np.arange(teeth)], [d, first]
+    for k in range(length - 1):
+        s.append(first + k)
+        d.append(first + k + 1)
+    return np.concatenate(s), np.concatenate(d), teeth * (length + 1)
+
+
+def grid(side):
+    g = I.grid_graph(side, 5)
+    return g.src.numpy(), g.dst.numpy(), g.n
+
+
+def two_stars(leaves):
+    n = 2 * leaves + 2
+    s = np.concatenate([np.full(leaves, n - 1), np.full(leaves, n - 2)])
+    return s, np.arange(2 * leaves), n
+
+
+CASES = {
+    "rising path": path(5000, "rising"), "falling path": path(5000, "falling"),
+    "shuffled path": path(5000, "shuffled"), "pairs": cliques(3000, 2), "cliques of 5": cliques(700, 5),
+    "comb": comb(300, 20), "grid": grid(70), "two stars": two_stars(2500),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("views", [native.VIEW_FWD, native.VIEW_FWD | native.VIEW_REV, 7])
+def test_components(name, views):
+    say(f"case: components, {name}, views {views}")
+    s, d, n = CASES[name]
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=views)
+    p.check_wcc()
+    cut = np.ascontiguousarray(s[::7]), np.ascontiguousarray(d[::7])
+    p.delete(*cut)  # tombstones in the first words; a recompute
+    p.check_wcc()
+    p.insert(*cut, np.ones(len(cut[0]), np.int64))  # incremental on the recomputed forest
+    p.check_wcc()
+    p.check_wcc(native.RECOMPUTE)
