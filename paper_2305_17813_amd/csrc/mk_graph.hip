@@ -289,6 +289,30 @@ __global__ void __launch_bounds__(kBlock) k_insert_all(DView F, DView R, DView U
   if (r == kPoolEmpty) atomicOr(overflow, task == 1 ? 2u : 4u);
 }
 
+// The initial arcs at creation, without status and change log: a lane per arc, and a row of
+// blocks (blockIdx.y) per table, so that one table is filled after the other.  (A wave serves one
+// table: the lanes that take a slab together share one counter.)  The degree counters already
+// hold the arcs' counts (k_count_deg), so a lane touches its counter only for a copy that was
+// there already: on a list without repeated arcs that saves an atomic per arc and table.
+__global__ void __launch_bounds__(kBlock) k_build_all(DView F, DView R, DView U, uint32_t views,
+                                                      const uint32_t* __restrict__ src,
+                                                      const uint32_t* __restrict__ dst,
+                                                      const uint32_t* __restrict__ w, uint64_t n, uint32_t nv,
+                                                      uint32_t* overflow) {
+  const uint64_t op = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int task = (int)blockIdx.y;
+  const int v = task < 2 ? task : VU;
+  if (op >= n || !(views & (1u << v))) return;
+  const uint32_t s = src[op], d = dst[op];
+  if (bad_arc(s, d, nv)) return;
+  const DView V = v == VF ? F : (v == VR ? R : U);
+  const bool from_s = task == 0 || task == 2;
+  const uint32_t a = from_s ? s : d, b = from_s ? d : s;
+  const int r = insert_key(V, a, b, v != VU && w ? w[op] : 1u);
+  if (r != 1) atomicSub(V.deg + a, 1u);
+  if (r == kPoolEmpty) atomicOr(overflow, 1u << v);
+}
+
 __global__ void __launch_bounds__(kBlock) k_delete_fwd(DView F, const uint32_t* __restrict__ src,
                                                        const uint32_t* __restrict__ dst, uint64_t n,
                                                        uint32_t nv, uint8_t* status, Log log) {
@@ -384,6 +408,11 @@ __global__ void k_count_deg(const uint32_t* __restrict__ src, const uint32_t* __
   }
 }
 
+// Undirected counts where both directions were counted: every arc counts at both its ends.
+__global__ void k_add_u32(const uint32_t* a, const uint32_t* b, uint32_t* out, uint32_t n) {
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) out[i] = a[i] + b[i];
+}
+
 // bucket_count[v] = max(1, ceil(deg0(v) / (load_factor * 15))), 1 when hashing is off;
 // extra[v] = bucket_count[v] - 1 head slabs beyond the primary one.
 __global__ void k_plan(const uint32_t* cnt, uint32_t nv, float keys_per_bucket, uint32_t* nb,
@@ -452,8 +481,13 @@ __global__ void k_sum_u32(const uint32_t* a, uint32_t n, unsigned long long* out
   unsigned long long acc = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     acc += a[i];
+  __shared__ unsigned long long part;  // one atomic per block: they all hit one word
+  if (threadIdx.x == 0) part = 0;
+  __syncthreads();
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-  if (lane64() == 0 && acc) atomicAdd(out, acc);
+  if (lane64() == 0 && acc) atomicAdd(&part, acc);
+  __syncthreads();
+  if (threadIdx.x == 0 && part) atomicAdd(out, part);
 }
 
 // Audit one chain (bucket b of vertex v, head slab s with nd data words).  Returns the
@@ -1189,6 +1223,7 @@ void launch_insert(mk_graph* g, const uint32_t* s, const uint32_t* d, const uint
 // 1M 783 / 1583, 2M 1479 / 1772.  (An atomic per cut chain and words packed by scattered 8-byte
 // stores took 1179 and 2503 us by a sweep at scale 22 with 100K and 1M ops.)
 constexpr uint64_t kCompactLogRatio = 8;
+constexpr uint64_t kBuildChunk = 1ull << 24;  // initial arcs per launch
 // Blocks of a sweep: each then packs many chains between two hand-outs of its cut tails.
 constexpr uint32_t kSweepBlocks = 4096;
 
@@ -1262,10 +1297,15 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
     hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, vh.d.deg, N, 0u);
   }
   (void)hipMemsetAsync(g->ctr, 0, sizeof(Counters), stream);
+  // with the reverse view's counts, the undirected ones are sums: half the atomics
+  const bool add = g->view[VR].on && g->view[VU].on;
   if (m)
     hipLaunchKernelGGL(k_count_deg, dim3(grid_stride_blocks(m)), dim3(kBlock), 0, stream, d_src,
                        d_dst, m, N, g->view[VF].d.deg, g->view[VR].on ? g->view[VR].d.deg : nullptr,
-                       g->view[VU].on ? g->view[VU].d.deg : nullptr);
+                       g->view[VU].on && !add ? g->view[VU].d.deg : nullptr);
+  if (m && add)
+    hipLaunchKernelGGL(k_add_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->view[VF].d.deg, g->view[VR].d.deg,
+                       g->view[VU].d.deg, N);
   const float kpb = cfg->load_factor > 0.f ? cfg->load_factor * kKeysPerSlab : 0.f;
   for (int v = 0; v < 3; ++v) {
     ViewHost& vh = g->view[v];
@@ -1306,7 +1346,6 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
                        dim3(kBlock), 0, stream, vh.d.slab, (vh.n_head + vh.pool_cap) * kGroup);
     hipLaunchKernelGGL(k_init_primary, dim3(nb_blocks), dim3(kBlock), 0, stream, vh.d.slab, vh.nbk,
                        g->fq[1 + v], N);
-    hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, vh.d.deg, N, 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, vh.d.pool_ctr, 64, 0u);
   }
   hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->mark, N, 0u);
@@ -1315,10 +1354,14 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
   // update marks start at the chain heads (encoded 0)
   hipLaunchKernelGGL(k_fill_u32, dim3(grid_stride_blocks(2 * g->view[VF].n_head)), dim3(kBlock), 0,
                      stream, (uint32_t*)g->upd_mark, 2 * g->view[VF].n_head, 0u);
-  // bulk insert, in chunks that fit the change log (used here as scratch)
-  for (uint64_t off = 0; off < m; off += g->log_cap) {
-    const uint64_t k = std::min<uint64_t>(g->log_cap, m - off);
-    launch_insert(g, d_src + off, d_dst + off, d_w ? d_w + off : nullptr, k, nullptr, g->log, stream);
+  // bulk insert, in chunks whose lanes a grid can count
+  for (uint64_t off = 0; off < m; off += kBuildChunk) {
+    const uint64_t k = std::min<uint64_t>(kBuildChunk, m - off);
+    hipLaunchKernelGGL(k_build_all, dim3(grid_for_lanes(k), 4), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR),
+                       dv(g, VU), g->cfg.views, d_src + off, d_dst + off, d_w ? d_w + off : nullptr, k, N,
+                       &g->ctr->overflow);
+    hipLaunchKernelGGL(k_spare_merge, dim3(3), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR), dv(g, VU),
+                       g->cfg.views);
   }
   if (hipGetLastError() != hipSuccess) return fail(MK_ERR_HIP);
   if (refresh_pool(g, stream) != MK_OK) return fail(MK_ERR_HIP);
