@@ -1362,10 +1362,22 @@ __device__ inline bool tc_is_hub(const DView& U, uint32_t b, const uint64_t* key
 // S1, S2 and S3 of the batch identity, one group per batch arc (u, v):
 //   S1 += |N_G(u) & N_G(v)|, S2 += |N_G(u) & N_B(v)|, S3 += |N_B(u) & N_B(v)|
 // with G the graph after the batch and B the graph of the batch alone (S1 and S3 on the
-// canonical direction u < v, counted twice).  The terms k_tc_hub counts are skipped.
+// canonical direction u < v, counted twice).  The terms k_tc_hub counts are skipped, and S1 of an
+// arc whose walked end has more than long_nb buckets is listed for k_tc_long, a block per arc:
+// walked by one group, a vertex of 2,000 neighbours took 200 us, the whole kernel's time after a
+// batch of 1,000 arcs.  A small batch leaves the chip idle, so there long_nb is 16; where the
+// batch fills it, a block per arc of few buckets only idles lanes.  k_tc_batch + k_tc_long, us:
+// scale 16, 997 arcs: 46 at 8, 43 at 16, 67 at 32 or 64 (209 without); scale 20, 100K arcs: 405
+// at 8, 435 at 16 or 32, 340 at 64 (349 without).
+constexpr uint64_t kTcFewKeys = 65536;
+constexpr uint32_t kTcLongFew = 16, kTcLongMany = 64;
 __global__ void __launch_bounds__(kBlock) k_tc_batch(DView U, const uint64_t* keys, uint64_t nk,
                                                      const uint32_t* seg_lo, const uint32_t* seg_hi,
-                                                     uint32_t nv, bool s2in, unsigned long long* S) {
+                                                     uint32_t nv, bool s2in, unsigned long long* S,
+                                                     uint32_t* longs, uint32_t* nlongs, uint32_t long_nb) {
+  __shared__ Stage L[1];
+  stage_open(L[0], longs, nlongs);
+  __syncthreads();
   const uint64_t g0 = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kGroup;
   const uint64_t ng = (uint64_t)gridDim.x * kGroupsPerBlock;
   uint64_t s1 = 0, s2 = 0, s3 = 0;
@@ -1378,7 +1390,9 @@ __global__ void __launch_bounds__(kBlock) k_tc_batch(DView U, const uint64_t* ke
     const uint32_t a = tc_walked(U, u, v), b = a == u ? v : u;
     const bool hub = tc_is_hub(U, b, keys, seg_lo[b], seg_hi[b]);
     uint64_t c1 = 0;
-    if (canon && !hub) c1 = 2 * group_intersect(U, a, b);  // walk the smaller side, probe the other
+    const bool is_long = canon && !hub && U.nbk[a] > long_nb;
+    stage_push(L[0], is_long && gl == 0, (uint32_t)i);
+    if (canon && !hub && !is_long) c1 = 2 * group_intersect(U, a, b);  // walk the smaller side, probe the other
     // batch neighbourhoods: the segments of v and u in the sorted key list
     const uint64_t vlo = seg_lo[v], vhi = seg_hi[v];
     const uint64_t ulo = seg_lo[u], uhi = seg_hi[u];
@@ -1430,7 +1444,29 @@ __global__ void __launch_bounds__(kBlock) k_tc_batch(DView U, const uint64_t* ke
     if (s2) atomicAdd(S + 1, (unsigned long long)s2);
     if (s3) atomicAdd(S + 2, (unsigned long long)s3);
   }
+  stage_close(L);
 }
+
+// S1 of the listed arcs: a block walks the smaller side, its groups striding over the buckets, and
+// probes the other side's table.
+__global__ void __launch_bounds__(kBlock) k_tc_long(DView U, const uint64_t* keys, const uint32_t* longs,
+                                                    const uint32_t* nlongs, unsigned long long* S) {
+  const uint32_t n = *nlongs;
+  uint64_t c = 0;
+  for (uint32_t j = blockIdx.x; j < n; j += gridDim.x) {
+    const uint64_t key = keys[longs[j]];
+    const uint32_t u = (uint32_t)(key >> 32), v = (uint32_t)key;
+    const uint32_t a = tc_walked(U, u, v), b = a == u ? v : u;
+    const Table tb = group_table(U, b);
+    for_each_slab_strided(U, a, threadIdx.x / kGroup, kGroupsPerBlock, [&](uint64_t x, bool data) {
+      const uint32_t k = (uint32_t)x;
+      if (data && valid_key(k) && k != b) c += lane_has(U, tb, k);
+    });
+  }
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+  if (lane64() == 0 && c) atomicAdd(S, 2ull * c);
+}
+
 
 // ---------------------------------------------------------------- hub edges through LDS sets
 // A hub b (tc_is_hub, with its segment in the sorted batch keys) owns the batch edges {a, b}
@@ -2268,6 +2304,7 @@ __global__ void k_tc_begin(Counters* C, bool reset_total) {
   C->u64tmp[0] = 0;
   C->n_heavy_tc = 0;
   C->tc_class[0] = C->tc_class[1] = C->tc_class[2] = 0;
+  C->tc_work = 0;
   if (reset_total) C->tc_total = 0;
 }
 
@@ -2648,9 +2685,12 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
                        g->fq[4], g->fq[5]);
     // S2 of arcs into hubs goes through the hubs' sets when ids leave the tag bit free
     const bool s2in = N <= 0x7FFFFFFFu;
+    uint32_t* longs = reinterpret_cast<uint32_t*>(g->tc_keys[0]);  // free after the sort
     hipLaunchKernelGGL(k_tc_batch, dim3(grid_for_groups(std::min<uint64_t>(nk, 1u << 20))),
                        dim3(kBlock), 0, stream, U, g->tc_keys[1], nk, g->fq[4], g->fq[5], N, s2in,
-                       g->ctr->tc_s);
+                       g->ctr->tc_s, longs, &g->ctr->tc_work, nk < kTcFewKeys ? kTcLongFew : kTcLongMany);
+    hipLaunchKernelGGL(k_tc_long, dim3((uint32_t)std::min<uint64_t>(nk, 4096)), dim3(kBlock), 0, stream, U,
+                       g->tc_keys[1], longs, &g->ctr->tc_work, g->ctr->tc_s);
     // hub edges: work items numbered by an exclusive scan over the key
     // positions, in the sort's input buffer (free after the sort; 2 * nk u32 fit in it)
     uint32_t* hcnt = reinterpret_cast<uint32_t*>(g->tc_keys[0]);

@@ -64,7 +64,8 @@ struct Counters {          // device-side scalars, one 4 KiB block
   uint32_t n_heavy_wcc;    // vertices of more than 16 buckets, all-arc WCC walk
   uint32_t n_heavy_pr;     // the same for the PageRank pull (reverse view)
   uint32_t n_heavy_tc;     // the same for the static triangle count (undirected view)
-  uint32_t tc_work;        // next hub work item of the triangle batch update
+  uint32_t tc_work;        // triangle batch update: arcs listed for k_tc_long, then the next hub
+                           // work item
   uint32_t tc_class[3];    // static triangle count: vertices per class
   uint32_t n_listed_light; // vertices listed for an incremental WCC pass: up to 16 buckets,
   uint32_t n_listed_heavy; //   and more (these two are cleared together)
