@@ -18,7 +18,7 @@ def test_pairs_of_large_vertices(degree, extra):
     big = np.arange(8)
     s = np.repeat(big, degree)
     d = np.concatenate([100 + rng.choice(3 * degree, degree, replace=False) for _ in big])
-    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD | native.VIEW_UND)
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD | native.VIEW_UND, pool_slabs=200_000)
     p.check_tc()
     # an edge per pair (a vertex has too few batch edges to be a hub), and sparse edges elsewhere
     bs, bd = [big[0::2]], [big[1::2]]
