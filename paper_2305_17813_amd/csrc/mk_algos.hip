@@ -590,6 +590,9 @@ __device__ inline double block_sum(double v, double* lds) {
   return s;  // valid in thread 0
 }
 
+__global__ void k_copy_f32(const float* a, float* b, uint32_t n) {
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) b[i] = a[i];
+}
 __global__ void k_pr_fill(float* x, uint32_t nv, float v) {
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += gridDim.x * blockDim.x) x[i] = v;
 }
@@ -765,6 +768,7 @@ constexpr uint32_t kPrFlatThreads = 1024;    // one block per CU: 16 waves share
 constexpr uint32_t kPrFlatBlocks = 256;
 constexpr uint32_t kPrHot = 24000;           // contributions in LDS (96,000 of 163,840 bytes)
 constexpr uint32_t kPrFixBlocks = 512;
+constexpr uint32_t kPrFixOne = 8192;         // up to this many tiles one block fixes and checks
 static_assert(kPrTile == 64 * 8, "a lane takes 8 entries");
 
 __global__ void k_pr_class(const uint32_t* __restrict__ outdeg, uint32_t nv, uint32_t* key, uint32_t* idx) {
@@ -785,6 +789,19 @@ __global__ void k_pr_order(const uint32_t* __restrict__ perm, const uint32_t* __
     od[i] = outdeg[v];
     id[i] = indeg[v];
     rank[v] = i;
+    cur[i] = 0;
+  }
+}
+
+// The identity order, for graphs whose contributions all fit the LDS copy anyway.
+__global__ void k_pr_identity(const uint32_t* __restrict__ outdeg, const uint32_t* __restrict__ indeg, uint32_t nv,
+                              uint32_t* __restrict__ perm, uint32_t* __restrict__ od, uint32_t* __restrict__ id,
+                              uint32_t* __restrict__ rank, uint32_t* __restrict__ cur, uint32_t* nitems) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *nitems = 0;
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += gridDim.x * blockDim.x) {
+    perm[i] = rank[i] = i;
+    od[i] = outdeg[i];
+    id[i] = indeg[i];
     cur[i] = 0;
   }
 }
@@ -941,6 +958,8 @@ __global__ void __launch_bounds__(kBlock) k_pr_load(const float* __restrict__ ke
   if (threadIdx.x == 0) dpart[blockIdx.x] = s;
 }
 
+__device__ inline bool pr_check_step(Counters* C, int slot, double tol, uint32_t max_iter, double d, uint32_t* pin);
+
 // What an iteration reads and writes (all in rank order).
 struct PrIter {
   const uint32_t *off, *list, *fv, *od;
@@ -1003,7 +1022,7 @@ __global__ void __launch_bounds__(kPrFlatThreads) k_pr_flat(PrIter a) {
   const double base = pr_base(a);
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const uint32_t M = a.off[nv];
-  const uint32_t T = (uint32_t)(((uint64_t)M + nv + kPrTile - 1) / kPrTile);
+  const uint32_t T = (uint32_t)(((uint64_t)M + nv + kPrTile - 1) / kPrTile);  // pr_tiles
   double* P = pre[w];
   // the prefix before entry k of the tile; entry 8 l + j sits at 64 j + l, so that the lanes'
   // stores do not meet in a bank
@@ -1095,16 +1114,13 @@ __global__ void __launch_bounds__(kPrFlatThreads) k_pr_flat(PrIter a) {
   }
 }
 
-// The vertices whose segment runs over a tile border: a lane per tile adds the parts of the
-// vertex that ends there, a whole wave where there are many.
-__global__ void __launch_bounds__(kBlock) k_pr_fix(PrIter a) {
-  __shared__ double lds[kBlock / 64];
-  if (a.state[0]) return;
-  const double base = pr_base(a);
-  const uint32_t nv = a.nv, lane = threadIdx.x & 63;
-  const uint32_t T = (uint32_t)(((uint64_t)a.off[nv] + nv + kPrTile - 1) / kPrTile);
-  double delta = 0, dang = 0;
-  for (uint32_t t0 = blockIdx.x * kBlock + threadIdx.x - lane; t0 < T; t0 += kPrFixBlocks * kBlock) {
+// The vertices whose segment runs over a tile border, tiles [t0, T) by steps of `stride` (a wave
+// takes 64 consecutive tiles): a lane per tile adds the parts of the vertex that ends there, the
+// whole wave where there are many.  finish(v, sum) is called by one lane per such vertex.
+template <class Finish>
+__device__ inline void pr_fix_tiles(const PrIter& a, uint32_t t0, uint32_t T, uint32_t stride, Finish&& finish) {
+  const uint32_t lane = threadIdx.x & 63;
+  for (; t0 < T; t0 += stride) {
     const uint32_t t = t0 + lane;
     uint32_t v = 0, first = t;
     bool mine = false;
@@ -1123,7 +1139,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_fix(PrIter a) {
     if (mine && span <= 8) {
       double s = 0;
       for (uint32_t k = first; k < t; ++k) s += a.tails[k];
-      pr_finish(a, base, v, s + a.heads[t], a.x[v], a.od[v], delta, dang);
+      finish(v, s + a.heads[t]);
     }
     for (uint64_t m = __ballot(mine && span > 8); m; m &= m - 1) {
       const int from = __builtin_ctzll(m);
@@ -1131,13 +1147,121 @@ __global__ void __launch_bounds__(kBlock) k_pr_fix(PrIter a) {
       double s = 0;
       for (uint32_t k = b + lane; k < e; k += 64) s += a.tails[k];
       for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      if ((int)lane == from) pr_finish(a, base, v, s + a.heads[t], a.x[v], a.od[v], delta, dang);
+      if ((int)lane == from) finish(v, s + a.heads[t]);
     }
   }
+}
+
+__device__ inline uint32_t pr_tiles(const PrIter& a) {
+  return (uint32_t)(((uint64_t)a.off[a.nv] + a.nv + kPrTile - 1) / kPrTile);
+}
+
+__global__ void __launch_bounds__(kBlock) k_pr_fix(PrIter a) {
+  __shared__ double lds[kBlock / 64];
+  if (a.state[0]) return;
+  const double base = pr_base(a);
+  double delta = 0, dang = 0;
+  pr_fix_tiles(a, (blockIdx.x * kBlock + threadIdx.x) & ~63u, pr_tiles(a), kPrFixBlocks * kBlock,
+               [&](uint32_t v, double s) { pr_finish(a, base, v, s, a.x[v], a.od[v], delta, dang); });
   const double s0 = block_sum(delta, lds), s1 = block_sum(dang, lds);
   if (threadIdx.x == 0) {
     a.ddelta[kPrFlatBlocks + blockIdx.x] = s0;
     a.ddang[kPrFlatBlocks + blockIdx.x] = s1;
+  }
+}
+
+// The same and the convergence check in one block, for graphs of few tiles (kPrFixOne).
+__global__ void __launch_bounds__(1024) k_pr_fix_check(PrIter a, Counters* C, int slot, double tol, uint32_t max_iter,
+                                                       uint32_t* pin) {
+  __shared__ double lds[1024 / 64];
+  if (a.state[0]) return;
+  const double base = pr_base(a);
+  double delta = 0, dang = 0;
+  pr_fix_tiles(a, threadIdx.x & ~63u, pr_tiles(a), 1024,
+               [&](uint32_t v, double s) { pr_finish(a, base, v, s, a.x[v], a.od[v], delta, dang); });
+  if (threadIdx.x < kPrFlatBlocks) {
+    delta += a.ddelta[threadIdx.x];
+    dang += a.ddang[threadIdx.x];
+  }
+  const double d = block_sum(delta, lds), next = block_sum(dang, lds);
+  if (threadIdx.x != 0) return;
+  C->pr_acc[2 * ((slot + 1) & 3)] = next;
+  pr_check_step(C, slot, tol, max_iter, d, pin);
+}
+
+// Every iteration of a small graph in one launch of one block (at most kPrSmallN vertices, and
+// about kPrSmallTiles tiles before one block takes longer than the launches): the contributions of this and the next iteration are in LDS, the waves
+// meet at barriers, and the check decides whether to go on.  An iteration of the 4,096-vertex
+// random graph takes 10 us; as three launches, with a read-back every fourth time, 20 us.
+constexpr uint32_t kPrSmallN = 11800, kPrSmallTiles = 256;
+__global__ void __launch_bounds__(kPrFlatThreads) k_pr_small(PrIter a, float* x1, Counters* C, double tol,
+                                                             uint32_t max_iter, uint32_t* pin) {
+  constexpr uint32_t kWaves = kPrFlatThreads / 64;
+  __shared__ float cl[2][kPrSmallN];
+  __shared__ double pre[kWaves][kPrTile + 1], lds[kWaves];
+  __shared__ double dang_s;
+  __shared__ uint32_t go;
+  const uint32_t nv = a.nv, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t M = a.off[nv], T = pr_tiles(a);
+  float* x[2] = {const_cast<float*>(a.x), x1};
+  double* P = pre[w];
+  auto at = [&](uint32_t k) { return P[k == kPrTile ? kPrTile : (k & 7) * 64 + (k >> 3)]; };
+  double d0 = 0;
+  for (uint32_t i = threadIdx.x; i < nv; i += kPrFlatThreads) {
+    const uint32_t o = a.od[i];
+    const float xv = x[0][i];
+    cl[0][i] = o ? xv / (float)o : 0.f;
+    if (!o) d0 += xv;
+  }
+  d0 = block_sum(d0, lds);
+  if (threadIdx.x == 0) dang_s = d0;
+  a.dang = &dang_s;
+  for (uint32_t it = 0;; ++it) {
+    __syncthreads();
+    const float* c = cl[it & 1];
+    a.x = x[it & 1];
+    a.y = x[(it + 1) & 1];
+    a.cn = cl[(it + 1) & 1];
+    const double base = pr_base(a);
+    double delta = 0, dang = 0;
+    for (uint32_t t = w; t < T; t += kWaves) {
+      const uint32_t f0 = a.fv[t], f1 = a.fv[t + 1];
+      const uint32_t e0 = t * kPrTile - f0, e1 = t + 1 == T ? M : (t + 1) * kPrTile - f1, ne = e1 - e0;
+      const U4* p = reinterpret_cast<const U4*>(a.list + e0 + 8 * lane);
+      const U4 q0 = p[0], q1 = p[1];
+      double sum = 0, ex[8];
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) {
+        const float cv = c[min(k < 4 ? q0.v[k] : q1.v[k - 4], nv - 1)];
+        ex[k] = sum;
+        sum += 8 * lane + k < ne ? (double)cv : 0.0;
+      }
+      const double incl = wave_scan(sum), before = incl - sum;
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) P[k * 64 + lane] = before + ex[k];
+      if (lane == 63) P[kPrTile] = incl;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (uint32_t v = f0 + lane; v < f1; v += 64) {
+        const uint32_t o0 = a.off[v], o1 = a.off[v + 1];
+        const double s = at(o1 - e0) - at(max(o0, e0) - e0);
+        if (o0 < e0) a.heads[t] = s;
+        else pr_finish(a, base, v, s, a.x[v], a.od[v], delta, dang);
+      }
+      if (lane == 0 && f1 < nv) a.tails[t] = at(ne) - at(min(max(a.off[f1], e0), e1) - e0);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    pr_fix_tiles(a, threadIdx.x & ~63u, T, kPrFlatThreads,
+                 [&](uint32_t v, double s) { pr_finish(a, base, v, s, a.x[v], a.od[v], delta, dang); });
+    const double d = block_sum(delta, lds), next = block_sum(dang, lds);
+    if (threadIdx.x == 0) {
+      dang_s = next;
+      go = !pr_check_step(C, (int)(it & 3), tol, max_iter, d, pin);
+    }
+    __syncthreads();
+    if (!go) return;  // the same in every thread
   }
 }
 
@@ -1214,19 +1338,12 @@ __global__ void __launch_bounds__(kBlock) k_pr_heavy_final(const uint32_t* heavy
   if (threadIdx.x == 0) delta[blockIdx.x] = s;
 }
 
-// Convergence bookkeeping for one iteration (single thread): stop at delta <= tol, when
-// the change has not improved for three iterations (the FP32 noise floor), or at max_iter.
-//
-// With `gpart` (the packed iterations), it also sums the next iteration's dangling mass.
-__global__ void __launch_bounds__(kBlock) k_pr_check(Counters* C, int slot, double tol, uint32_t max_iter,
-                                                     const double* dpart, uint32_t nparts, const double* gpart) {
-  __shared__ double lds[kBlock / 64];
+// Convergence bookkeeping for one iteration (one thread): d is its L1 change.  Stop at d <= tol,
+// when the change has not improved for three iterations (the FP32 noise floor), or at max_iter.
+// The done flag and the iteration count also go to `pin`, two words of pinned host memory, so
+// that the host needs a synchronization and no copy to read them.
+__device__ inline bool pr_check_step(Counters* C, int slot, double tol, uint32_t max_iter, double d, uint32_t* pin) {
   uint32_t* st = C->pr_state;
-  if (st[0]) return;
-  const double d = sum_parts(dpart, nparts, lds);  // the L1 change of this iteration
-  const double next = gpart ? sum_parts(gpart, nparts, lds) : 0.0;
-  if (threadIdx.x != 0) return;
-  if (gpart) C->pr_acc[2 * ((slot + 1) & 3)] = next;
   C->pr_acc[2 * slot + 1] = d;
   st[1] += 1;
   C->pr_last = d;
@@ -1236,7 +1353,25 @@ __global__ void __launch_bounds__(kBlock) k_pr_check(Counters* C, int slot, doub
   } else {
     st[2] += 1;
   }
-  if (d <= tol || st[2] >= 3 || st[1] >= max_iter) st[0] = 1;
+  const bool done = d <= tol || st[2] >= 3 || st[1] >= max_iter;
+  if (done) st[0] = 1;
+  pin[0] = done ? 1u : 0u;
+  pin[1] = st[1];
+  return done;
+}
+
+// The check over per-block partial sums.  With `gpart` (the packed iterations), it also sums the
+// next iteration's dangling mass.
+__global__ void __launch_bounds__(kBlock) k_pr_check(Counters* C, int slot, double tol, uint32_t max_iter,
+                                                     const double* dpart, uint32_t nparts, const double* gpart,
+                                                     uint32_t* pin) {
+  __shared__ double lds[kBlock / 64];
+  if (C->pr_state[0]) return;
+  const double d = sum_parts(dpart, nparts, lds);
+  const double next = gpart ? sum_parts(gpart, nparts, lds) : 0.0;
+  if (threadIdx.x != 0) return;
+  if (gpart) C->pr_acc[2 * ((slot + 1) & 3)] = next;
+  pr_check_step(C, slot, tol, max_iter, d, pin);
 }
 
 __global__ void k_pr_start(Counters* C) {
@@ -2355,12 +2490,11 @@ mk_status pagerank_scheme2(mk_graph* g, float damping, double tol_l1, uint32_t m
       hipLaunchKernelGGL(k_pr_final_s2, dim3(kWalkBlocks), dim3(kBlock), 0, stream, vh.nbk, vh.pair_off,
                          g->pr_pair, x, y, N, damping, dang, dpart, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, dpart,
-                         kWalkBlocks, nullptr);
+                         kWalkBlocks, nullptr, reinterpret_cast<uint32_t*>(g->h_pin));
       MK_LAUNCH(g, "pagerank iteration (scheme 2)");
     }
-    MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->pr_state, 8, hipMemcpyDeviceToHost, stream));
     MK_HIP(g, hipStreamSynchronize(stream));
-    if (reinterpret_cast<const uint32_t*>(g->h_pin)[0]) break;
+    if (*(volatile uint32_t*)g->h_pin) break;
   }
   hipLaunchKernelGGL(k_pr_final, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->ctr, g->pr_x,
                      g->pr_y, g->pr_x, d_rank, N, d_iters);
@@ -2381,13 +2515,18 @@ mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t ma
   float* c[2] = {g->pr_c, g->pr_cp};
   uint32_t *cur = g->fq[0], *item_i = g->lv_multi[0], *item_c = g->lv_multi[1];  // traversal scratch
   uint32_t* nitems = &g->ctr->n_heavy_pr;
-  hipLaunchKernelGGL(k_pr_class, dim3(blocks_for(N)), dim3(kBlock), 0, stream, outdeg, N, g->pr_skey[0], g->pr_sidx);
-  size_t sb = g->pr_sort_bytes;
-  if (rocprim::radix_sort_pairs(g->pr_sort_tmp, sb, g->pr_skey[0], g->pr_skey[1], g->pr_sidx, g->pr_perm,
-                                (size_t)N, 0, 6, stream) != hipSuccess)
-    return MK_ERR_HIP;
-  hipLaunchKernelGGL(k_pr_order, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_perm, outdeg, R.deg, N, od, id,
-                     g->pr_rank, cur, nitems);
+  if (N <= kPrHot) {
+    hipLaunchKernelGGL(k_pr_identity, dim3(blocks_for(N)), dim3(kBlock), 0, stream, outdeg, R.deg, N, g->pr_perm, od,
+                       id, g->pr_rank, cur, nitems);
+  } else {
+    hipLaunchKernelGGL(k_pr_class, dim3(blocks_for(N)), dim3(kBlock), 0, stream, outdeg, N, g->pr_skey[0], g->pr_sidx);
+    size_t sb = g->pr_sort_bytes;
+    if (rocprim::radix_sort_pairs(g->pr_sort_tmp, sb, g->pr_skey[0], g->pr_skey[1], g->pr_sidx, g->pr_perm,
+                                  (size_t)N, 0, 6, stream) != hipSuccess)
+      return MK_ERR_HIP;
+    hipLaunchKernelGGL(k_pr_order, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_perm, outdeg, R.deg, N, od, id,
+                       g->pr_rank, cur, nitems);
+  }
   size_t tb = g->scan_tmp_bytes;
   if (rocprim::exclusive_scan(g->scan_tmp, tb, id, g->pr_off, 0u, (size_t)N, rocprim::plus<uint32_t>(), stream) !=
       hipSuccess)
@@ -2397,40 +2536,52 @@ mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t ma
                      R.nbk, item_i, item_c, nitems);
   hipLaunchKernelGGL(k_pr_pack, dim3(kWalkBlocks), dim3(kBlock), 0, stream, R, g->pr_perm, g->pr_rank, g->pr_off, N,
                      g->pr_list, cur, item_i, item_c, nitems);
-  const uint32_t cb = blocks_for(N, kPrContribBlocks);
-  hipLaunchKernelGGL(k_pr_load, dim3(cb), dim3(kBlock), 0, stream, g->pr_x, g->pr_perm, od, N, x[0], c[0], g->pr_part);
-  hipLaunchKernelGGL(k_pr_sum, dim3(1), dim3(kBlock), 0, stream, g->pr_part, cb, &g->ctr->pr_acc[0], g->ctr->pr_state);
-  MK_LAUNCH(g, "pagerank packing");
-  uint32_t it = 0;
-  while (true) {
-    for (int k = 0; k < kPrSyncEvery; ++k, ++it) {
-      const int slot = it & 3;
-      PrIter a;
-      a.off = g->pr_off;
-      a.list = g->pr_list;
-      a.fv = g->pr_fv;
-      a.od = od;
-      a.c = c[it & 1];
-      a.x = x[it & 1];
-      a.cn = c[(it + 1) & 1];
-      a.y = x[(it + 1) & 1];
-      a.heads = g->pr_tile[0];
-      a.tails = g->pr_tile[1];
-      a.ddelta = g->pr_part;
-      a.ddang = g->pr_part + kPrParts / 2;
-      a.state = g->ctr->pr_state;
-      a.dang = &g->ctr->pr_acc[2 * slot];
-      a.nv = N;
-      a.damping = damping;
-      hipLaunchKernelGGL(k_pr_flat, dim3(kPrFlatBlocks), dim3(kPrFlatThreads), 0, stream, a);
-      hipLaunchKernelGGL(k_pr_fix, dim3(kPrFixBlocks), dim3(kBlock), 0, stream, a);
-      hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, a.ddelta,
-                         kPrFlatBlocks + kPrFixBlocks, a.ddang);
-      MK_LAUNCH(g, "pagerank iteration (packed)");
+  uint32_t* pin = reinterpret_cast<uint32_t*>(g->h_pin);
+  PrIter a;
+  a.off = g->pr_off;
+  a.list = g->pr_list;
+  a.fv = g->pr_fv;
+  a.od = od;
+  a.heads = g->pr_tile[0];
+  a.tails = g->pr_tile[1];
+  a.ddelta = g->pr_part;
+  a.ddang = g->pr_part + kPrParts / 2;
+  a.state = g->ctr->pr_state;
+  a.nv = N;
+  a.damping = damping;
+  // the host does not know the in-arcs; their head slabs' words bound them well enough to choose
+  const uint64_t tiles = (g->view[VR].n_head * kKeysPerSlab + N) / kPrTile;
+  if (N <= kPrSmallN && tiles <= kPrSmallTiles) {
+    hipLaunchKernelGGL(k_copy_f32, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, x[0], N);
+    a.x = x[0];
+    hipLaunchKernelGGL(k_pr_small, dim3(1), dim3(kPrFlatThreads), 0, stream, a, x[1], g->ctr, tol_l1, max_iter, pin);
+  } else {
+    const uint32_t cb = blocks_for(N, kPrContribBlocks);
+    hipLaunchKernelGGL(k_pr_load, dim3(cb), dim3(kBlock), 0, stream, g->pr_x, g->pr_perm, od, N, x[0], c[0], g->pr_part);
+    hipLaunchKernelGGL(k_pr_sum, dim3(1), dim3(kBlock), 0, stream, g->pr_part, cb, &g->ctr->pr_acc[0], g->ctr->pr_state);
+    MK_LAUNCH(g, "pagerank packing");
+    uint32_t it = 0;
+    while (true) {
+      for (int k = 0; k < kPrSyncEvery; ++k, ++it) {
+        const int slot = it & 3;
+        a.c = c[it & 1];
+        a.x = x[it & 1];
+        a.cn = c[(it + 1) & 1];
+        a.y = x[(it + 1) & 1];
+        a.dang = &g->ctr->pr_acc[2 * slot];
+        hipLaunchKernelGGL(k_pr_flat, dim3(kPrFlatBlocks), dim3(kPrFlatThreads), 0, stream, a);
+        if (tiles <= kPrFixOne) {
+          hipLaunchKernelGGL(k_pr_fix_check, dim3(1), dim3(1024), 0, stream, a, g->ctr, slot, tol_l1, max_iter, pin);
+        } else {
+          hipLaunchKernelGGL(k_pr_fix, dim3(kPrFixBlocks), dim3(kBlock), 0, stream, a);
+          hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, a.ddelta,
+                             kPrFlatBlocks + kPrFixBlocks, a.ddang, pin);
+        }
+        MK_LAUNCH(g, "pagerank iteration (packed)");
+      }
+      MK_HIP(g, hipStreamSynchronize(stream));
+      if (*(volatile uint32_t*)pin) break;
     }
-    MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->pr_state, 8, hipMemcpyDeviceToHost, stream));
-    MK_HIP(g, hipStreamSynchronize(stream));
-    if (reinterpret_cast<const uint32_t*>(g->h_pin)[0]) break;
   }
   hipLaunchKernelGGL(k_pr_store, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->ctr, x[0], x[1], g->pr_rank, g->pr_x,
                      d_rank, N, d_iters);
@@ -2615,12 +2766,11 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
       hipLaunchKernelGGL(k_pr_heavy_final, dim3(hb), dim3(kBlock), 0, stream, g->heavy_rev, nh, hacc, x, y,
                          N, damping, dang, dpart + kWalkBlocks, g->ctr->pr_state);
       hipLaunchKernelGGL(k_pr_check, dim3(1), dim3(kBlock), 0, stream, g->ctr, slot, tol_l1, max_iter, dpart,
-                         kWalkBlocks + hb, nullptr);
+                         kWalkBlocks + hb, nullptr, reinterpret_cast<uint32_t*>(g->h_pin));
       MK_LAUNCH(g, "pagerank iteration");
     }
-    MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->pr_state, 8, hipMemcpyDeviceToHost, stream));
     MK_HIP(g, hipStreamSynchronize(stream));
-    if (reinterpret_cast<const uint32_t*>(g->h_pin)[0]) break;
+    if (*(volatile uint32_t*)g->h_pin) break;
   }
   hipLaunchKernelGGL(k_pr_final, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->ctr, g->pr_x,
                      g->pr_y, g->pr_x, d_rank, N, d_iters);

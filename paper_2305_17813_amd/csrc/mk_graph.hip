@@ -182,6 +182,10 @@ __global__ void k_pool_snapshot(const uint32_t* f, const uint32_t* r, const uint
   }
 }
 
+__global__ void k_read_back(const uint32_t* src, uint32_t* pin, uint32_t words) {
+  if (threadIdx.x < words) pin[threadIdx.x] = src[threadIdx.x];
+}
+
 // Delete key from u's table (one lane).  Returns 1 deleted, 0 absent; *w_out gets the weight.
 __device__ int delete_key(const DView& V, uint32_t u, uint32_t key, uint32_t* w_out) {
   Slab sl;
@@ -1066,20 +1070,19 @@ uint64_t used_from(const ViewHost& vh, const uint32_t* c) {
   return hw - std::min<uint64_t>((uint64_t)avail, hw);
 }
 
-// Gather the pool counters, the overflow bits and the 64-bit value at `extra` into ctr->snap.
-void launch_snapshot(mk_graph* g, const void* extra, hipStream_t stream) {
+// Gather the pool counters, the overflow bits and the 64-bit value at `extra` into `out`.
+void launch_snapshot(mk_graph* g, const void* extra, uint32_t* out, hipStream_t stream) {
   const auto ctr_of = [&](int v) -> const uint32_t* { return g->view[v].on ? g->view[v].d.pool_ctr : nullptr; };
   hipLaunchKernelGGL(k_pool_snapshot, dim3(1), dim3(64), 0, stream, ctr_of(VF), ctr_of(VR), ctr_of(VU),
-                     &g->ctr->overflow, g->ctr->snap, (const uint32_t*)extra);
+                     &g->ctr->overflow, out, (const uint32_t*)extra);
 }
 
-// Exact pool figures and the overflow bits (synchronizes the stream): one kernel and one copy,
-// where a copy per view and one for the bits cost about 5 us each.  *h_extra (nullable)
+// Exact pool figures and the overflow bits (synchronizes the stream): one kernel writes them to
+// pinned memory, where a copy per view and one for the bits cost about 5 us each.  *h_extra (nullable)
 // receives the 64-bit device value at `extra`.
 mk_status refresh_pool(mk_graph* g, hipStream_t stream, const void* extra = nullptr, uint64_t* h_extra = nullptr) {
-  launch_snapshot(g, extra, stream);
+  launch_snapshot(g, extra, reinterpret_cast<uint32_t*>(g->h_pin), stream);
   MK_LAUNCH(g, "k_pool_snapshot");
-  MK_HIP(g, hipMemcpyAsync(g->h_pin, g->ctr->snap, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
   MK_HIP(g, hipStreamSynchronize(stream));
   const uint32_t* h = reinterpret_cast<const uint32_t*>(g->h_pin);
   g->overflowed.fetch_or(h[12]);
@@ -1135,7 +1138,7 @@ void poll_snapshots(mk_graph* g) {
 void enqueue_snapshot(mk_graph* g, hipStream_t stream) {
   PoolSnap& sn = g->snap[g->snap_next];
   if (sn.pending && hipEventQuery(sn.ev) != hipSuccess) return;  // ring slot still in flight
-  launch_snapshot(g, nullptr, stream);
+  launch_snapshot(g, nullptr, g->ctr->snap, stream);
   if (hipMemcpyAsync(sn.pin, g->ctr->snap, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream) != hipSuccess ||
       hipEventRecord(sn.ev, stream) != hipSuccess) {
     (void)hipGetLastError();
@@ -1230,6 +1233,10 @@ constexpr uint32_t kSweepBlocks = 4096;
 }  // namespace
 
 namespace mk {
+void read_back(const void* d_src, void* h_pin, uint32_t words, hipStream_t stream) {
+  hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, stream, (const uint32_t*)d_src, (uint32_t*)h_pin, words);
+}
+
 mk_status ensure_pairs(mk_graph* g, int v, hipStream_t stream) {
   ViewHost& vh = g->view[v];
   if (!vh.on || !vh.pair_v) return MK_ERR_STATE;

@@ -46,7 +46,7 @@ struct LvCnt {
   uint32_t pad[5];
   unsigned long long arcs[4];   // out-arcs of each frontier
 };
-static_assert(sizeof(LvCnt) <= 256, "counter block");
+static_assert(sizeof(LvCnt) <= 256, "counter block (and at most 64 pinned words of 8 bytes)");
 
 __global__ void k_lv_fill(uint32_t* level, uint32_t nv) {
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x)
@@ -672,13 +672,12 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
     if (L + 1 == next_sync || L + 1 >= N) {
       if (next_sync >= 2 * kSyncFirst) every = std::min<uint64_t>(2 * every, kSyncMax);
       next_sync += every;
-      MK_HIP(g, hipMemcpyAsync(pin, &c->n[(L + 1) & 3], 4, hipMemcpyDeviceToHost, stream));
-      MK_HIP(g, hipMemcpyAsync(pin + 1, &c->bu_steps, 4, hipMemcpyDeviceToHost, stream));
+      read_back(c, pin, sizeof(LvCnt) / 4, stream);
       MK_HIP(g, hipStreamSynchronize(stream));
-      if ((uint32_t)pin[0] == 0 || L + 1 >= N) break;
+      if (reinterpret_cast<const volatile LvCnt*>(pin)->n[(L + 1) & 3] == 0 || L + 1 >= N) break;
     }
   }
-  if (h_bottom_up_steps) *h_bottom_up_steps = (uint32_t)pin[1];
+  if (h_bottom_up_steps) *h_bottom_up_steps = reinterpret_cast<const volatile LvCnt*>(pin)->bu_steps;
   return MK_OK;
 }
 
@@ -746,11 +745,10 @@ mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2]
     if (S + 1 == next_sync) {
       if (next_sync >= 2 * kSyncFirst) every = std::min<uint64_t>(2 * every, kSyncMax);
       next_sync += every;
-      MK_HIP(g, hipMemcpyAsync(pin, &c->n[(S + 1) & 3], 4, hipMemcpyDeviceToHost, stream));
-      MK_HIP(g, hipMemcpyAsync(pin + 1, &c->nfar[0], 8, hipMemcpyDeviceToHost, stream));
+      read_back(c, pin, sizeof(DsCnt) / 4, stream);
       MK_HIP(g, hipStreamSynchronize(stream));
-      const uint32_t* h = reinterpret_cast<const uint32_t*>(pin + 1);
-      if ((uint32_t)pin[0] == 0 && h[0] == 0 && h[1] == 0) break;
+      const volatile DsCnt* h = reinterpret_cast<const volatile DsCnt*>(pin);
+      if (h->n[(S + 1) & 3] == 0 && h->nfar[0] == 0 && h->nfar[1] == 0) break;
       if (S > cap) return MK_ERR_HIP;
     }
   }

@@ -34,6 +34,7 @@ namespace {
 constexpr uint32_t kExpandBlocks = 2048;  // 256 CUs x 8 resident blocks
 constexpr int kSyncFirst = 4, kSyncMax = 16;  // frontier launches between size read-backs: 4,
                                               // then doubling while the frontier lasts
+constexpr uint32_t kSmallGraph = 1u << 17;    // vertices of a graph whose loops start with 2
 
 __device__ inline uint64_t tree_node(uint64_t dist, uint32_t parent) {
   if (dist >= 0xFFFFFFFFull) dist = 0xFFFFFFFEull;  // saturate below INF
@@ -761,16 +762,17 @@ template <class Launch>
 mk_status run_frontier(mk_graph* g, const TravCtx& c, hipStream_t stream, Launch&& launch,
                        uint64_t* it_io = nullptr) {
   uint64_t it = it_io ? *it_io : 0;
-  int every = kSyncFirst;
+  // a small graph's frontiers mostly end inside one launch (kInnerSteps)
+  int every = c.n <= kSmallGraph ? kSyncFirst / 2 : kSyncFirst;
   for (;; every = every < kSyncMax ? 2 * every : kSyncMax) {
     for (int k = 0; k < every; ++k, ++it) {
       launch(queues(c, it), next_stamps(c, kInnerSteps, stream));
       MK_LAUNCH(g, "frontier kernel");
     }
     const int slot = (int)(it % 3);
-    MK_HIP(g, hipMemcpyAsync(c.h_pin, c.cnt, 14 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+    read_back(c.cnt, c.h_pin, 14, stream);
     MK_HIP(g, hipStreamSynchronize(stream));
-    const uint32_t* h = reinterpret_cast<const uint32_t*>(c.h_pin);
+    const volatile uint32_t* h = reinterpret_cast<const volatile uint32_t*>(c.h_pin);
     if (h[slot] == 0 && h[3 + slot] == 0 && h[6 + slot] == 0) break;
   }
   if (it_io) *it_io = it;
@@ -817,7 +819,7 @@ mk_status run_expand(mk_graph* g, const TravCtx& c, hipStream_t stream, Bands& b
                          c.mark, stamp, c.single);
     }, &it);
     if (s != MK_OK) return s;
-    const uint32_t* h = reinterpret_cast<const uint32_t*>(c.h_pin);
+    const volatile uint32_t* h = reinterpret_cast<const volatile uint32_t*>(c.h_pin);
     if (h[9 + b.fb] == 0) break;  // the frontier and the pile are both empty
   }
   return MK_OK;
