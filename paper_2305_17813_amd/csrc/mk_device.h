@@ -182,6 +182,68 @@ __device__ inline void stage_push(Stage& S, bool p, uint32_t v) {
   if (p) stage_put(S, t, t.pos, v);
 }
 
+// The same for kernels that push as much as they read: a buffer per wave, written out by one
+// atomic when the next push would not fit (64 x 15 entries at most, which fit after that), so that a counter sees an atomic per several hundred entries however many a block pushes.
+// What is left at the end is written by the block together.
+constexpr uint32_t kWaveStage = 64 * 16;
+struct WaveStage {
+  uint32_t n[kBlock / 64], base;
+  uint32_t buf[kBlock / 64][kWaveStage];
+};
+
+struct WaveOut {
+  WaveStage* S;
+  uint32_t *buf, *q, *ctr;
+  uint32_t n;  // entries of this wave's buffer (the same in every lane)
+};
+
+__device__ inline WaveOut wave_out(WaveStage& S, uint32_t* q, uint32_t* ctr) {
+  return WaveOut{&S, S.buf[threadIdx.x / 64], q, ctr, 0};
+}
+
+__device__ inline void wave_write(const WaveOut& o, uint32_t base) {
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t i = threadIdx.x & 63; i < o.n; i += 64) o.q[base + i] = o.buf[i];
+  __builtin_amdgcn_wave_barrier();
+}
+
+// This lane's first slot for `cnt` (0..15) entries; every lane of the wave calls it.
+__device__ inline uint32_t wave_slots(WaveOut& o, uint32_t cnt, bool& any) {
+  uint32_t excl = 0, total = 0;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const uint64_t m = __ballot((cnt >> b) & 1u);
+    excl += lanes_below(m) << b;
+    total += (uint32_t)__popcll(m) << b;
+  }
+  any = total != 0;
+  if (o.n + total > kWaveStage) {
+    uint32_t base = 0;
+    if ((threadIdx.x & 63) == 0) base = atomicAdd(o.ctr, o.n);
+    wave_write(o, __shfl(base, 0));
+    o.n = 0;
+  }
+  const uint32_t pos = o.n + excl;
+  o.n += total;
+  return pos;
+}
+
+// Every thread of the block calls it once, at the end.
+__device__ inline void wave_out_close(WaveOut& o) {
+  const uint32_t w = threadIdx.x / 64;
+  if ((threadIdx.x & 63) == 0) o.S->n[w] = o.n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (uint32_t i = 0; i < kBlock / 64; ++i) total += o.S->n[i];
+    o.S->base = total ? atomicAdd(o.ctr, total) : 0u;
+  }
+  __syncthreads();
+  uint32_t base = o.S->base;
+  for (uint32_t i = 0; i < w; ++i) base += o.S->n[i];
+  wave_write(o, base);
+}
+
 template <int K>
 __device__ inline void stage_close(Stage (&S)[K]) {
   __syncthreads();

@@ -239,11 +239,13 @@ void read_back(const void* d_src, void* h_pin, uint32_t words, hipStream_t strea
 mk_status ensure_pairs(mk_graph* g, int v, hipStream_t stream);
 
 // Buffers of one level-synchronous BFS (mk_levels.hip): a 256-byte counter block, two
-// frontier queues of N entries and two work-item arrays of levels_multi_cap(g) entries.
+// frontier queues of N entries, two work-item arrays of levels_multi_cap(g) entries and the reached
+// set (a byte per vertex).
 struct LevelBufs {
   void* cnt = nullptr;
   uint32_t* q[2] = {};
   uint32_t *multi_v = nullptr, *multi_c = nullptr;
+  uint8_t* seen = nullptr;
 };
 size_t levels_multi_cap(const mk_graph* g);
 mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBufs& b, uint32_t* level,

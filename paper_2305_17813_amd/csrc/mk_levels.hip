@@ -4,8 +4,9 @@
 // The experimental section runs BFS in two variants: a vanilla one with 32-bit atomics that
 // computes only distances, and the tree variant (64-bit <distance, parent> nodes) that the
 // dynamic algorithms need; its static BFS is level-based.  This file is the vanilla variant:
-// one u32 level per vertex, one level per step.  A step is either top-down (the frontier's
-// out-arcs claim unreached vertices by CAS) or bottom-up (every unreached vertex scans its
+// one u32 level per vertex, one level per step, and a byte per vertex for the reached set.  A step
+// is either top-down (the frontier's out-arcs claim unreached vertices by CAS, or, when there are
+// many, mark their bytes for a sweep over the vertices) or bottom-up (every unreached vertex scans its
 // in-arcs, through the reverse view, for a vertex of the current level and stops at the
 // first one).  A one-thread kernel picks the direction of each step on the device from the
 // frontier's size and out-arc count against the number of unreached vertices, so the host
@@ -36,6 +37,17 @@ constexpr uint32_t kChunk = kGroup;       // buckets of a multi-bucket vertex pe
 constexpr uint32_t kSyncFirst = 4, kSyncMax = 16;  // steps between size read-backs: 4, 4,
                                                     // then doubling while the traversal lasts
 
+// How a step reaches vertices.  Top-down steps test a byte per vertex of the reached set: at scale
+// 22 the levels are 16 MB and 20 M reads of them brought 16 M lines into the L2s, while the bytes
+// mostly stay there.  With few arcs the unreached neighbours are claimed by CAS, which go to memory
+// at 5.7 G/s whatever else the step does.  Past N / kMarkShare arcs the step only stores bytes, and
+// a sweep over all vertices, 14 ps a vertex, collects what has a byte and no level: as much as the
+// CAS of an N / 13th of the vertices, and on a road-like network about a quarter of the arcs reach
+// something new (1,048,576 vertices, levels of up to 80,000 arcs: 1.69 ms with a share of 16, 1.23
+// with this one).  The great step of an R-MAT graph at scale 22: 456 us claiming, 365 marking and
+// sweeping.
+constexpr uint32_t kClaim = 0, kBottomUp = 1, kMark = 2, kMarkShare = 2;
+
 // Device counters of one call (in the caller's workspace).  Level L uses slot L mod 4.
 struct LvCnt {
   uint32_t n[4];                // frontier sizes
@@ -48,15 +60,11 @@ struct LvCnt {
 };
 static_assert(sizeof(LvCnt) <= 256, "counter block (and at most 64 pinned words of 8 bytes)");
 
-__global__ void k_lv_fill(uint32_t* level, uint32_t nv) {
-  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x)
-    level[v] = kLevelInf;
-}
-
-__global__ void k_zero_marks(uint32_t* a, uint32_t* b, uint32_t nv) {
+// Every vertex unreached: no level, no byte of the reached set.
+__global__ void k_lv_fill(uint32_t* level, uint8_t* seen, uint32_t nv) {
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
-    a[v] = 0;
-    b[v] = 0;
+    level[v] = kLevelInf;
+    seen[v] = 0;
   }
 }
 
@@ -65,9 +73,11 @@ __global__ void k_lv_clear(LvCnt* c) {
   for (uint32_t i = threadIdx.x; i < sizeof(LvCnt) / 4; i += blockDim.x) w[i] = 0;
 }
 
-__global__ void k_lv_seed(uint32_t* level, uint32_t* q0, LvCnt* c, const uint32_t* deg, uint32_t src) {
+__global__ void k_lv_seed(uint32_t* level, uint8_t* seen, uint32_t* q0, LvCnt* c, const uint32_t* deg,
+                          uint32_t src) {
   if (threadIdx.x != 0) return;
   level[src] = 0;
+  seen[src] = 1;
   q0[0] = src;
   c->n[0] = 1;
   c->arcs[0] = deg[src];
@@ -85,63 +95,198 @@ __global__ void k_lv_decide(LvCnt* c, uint32_t L, uint32_t nv, int allow_bu) {
   const uint64_t nf = c->n[s], mf = c->arcs[s];
   if (L > 0) c->reached += c->n[(L - 1) & 3];
   const uint64_t nu = (uint64_t)nv - c->reached - nf;
-  const uint32_t mode = allow_bu && nu > 0 && 2 * nf + mf > 6 * nu + nv / 2 ? 1u : 0u;
+  const uint32_t mode = allow_bu && nu > 0 && 2 * nf + mf > 6 * nu + nv / 2 ? kBottomUp
+                        : mf > nv / kMarkShare                               ? kMark
+                                                                             : kClaim;
   c->mode = mode;
-  if (nf) c->bu_steps += mode;
+  if (nf) c->bu_steps += mode == kBottomUp;
 }
 
-// Append the words of `sl` flagged in `found` (<= 15) to the staged next frontier.
-__device__ inline void push_found(Stage& S, uint32_t found, const Slab& sl) {
+// Slab chains, sixteen to a group of 16 lanes: lane i holds the head of chain i (kInvalid: none)
+// and the value that goes with it.  A round takes K of the group's chains one slab further, a
+// word per lane: body(key words, live, values), where live[k] says that this lane's word of slab k
+// holds a key.  `short0`: the head held by this lane has a word less (it names the extra heads).
+//
+// Every step below is bound by its instructions and by the rate at which a CU's address unit takes
+// the lanes' lines.  A lane per slab reads 128 bytes as eight loads of 64 lines each and repeats the
+// work on a word fifteen times under as many branches (160 registers, three waves on a SIMD); a
+// group reads a slab as one line and does the work on its words once, at 54 to 121 registers.
+// Distances at scale 22, the multi-bucket rounds of one run: 2.42 ms with a lane per slab, 2.20 with
+// a group and eight slabs a round, 2.38 with four, 2.64 with two; marking prefers four (0.35 ms a
+// run, 0.37 with eight).
+constexpr int kRoundClaim = 4, kRoundRelax = 8;
+template <int K, class Body>
+__device__ inline void walk_chains(const DView& F, uint32_t head, uint32_t value, bool short0, Body body) {
+  const int gl = glane(), g0 = lane64() - gl;
+  uint32_t short_heads = (uint32_t)(__ballot(short0) >> g0) & 0xFFFFu;
+  while (true) {
+    const uint64_t all = __ballot(head != kInvalid);
+    if (all == 0) break;
+    uint32_t m = (uint32_t)(all >> g0) & 0xFFFFu;
+    uint64_t w[K];
+    uint32_t val[K], at[K];
+    bool live[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      live[k] = m != 0;
+      at[k] = m ? (uint32_t)__builtin_ctz(m) : 0u;
+      m &= m - 1;
+      const uint32_t t = __shfl(head, g0 + (int)at[k]);
+      val[k] = __shfl(value, g0 + (int)at[k]);
+      w[k] = live[k] ? slab_ptr(F, t)[gl] : kEmptyWord;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t next = __shfl((uint32_t)w[k], g0 + kKeysPerSlab);
+      if (live[k] && gl == (int)at[k]) head = next;
+      const int nd = kKeysPerSlab - (int)(short_heads >> at[k] & 1u);
+      if (live[k]) short_heads &= ~(1u << at[k]);
+      live[k] = live[k] && gl < nd && valid_key((uint32_t)w[k]);
+    }
+    body(w, live, val);
+  }
+}
+
+// Append the words flagged in `found` (a bit per word) to the staged next frontier.
+template <int K>
+__device__ inline void push_found(WaveOut& o, uint32_t found, const uint64_t (&w)[K]) {
   bool any;
-  const StageSlots t = stage_reserve(S, (uint32_t)__popc(found), any);
+  uint32_t pos = wave_slots(o, (uint32_t)__popc(found), any);
   if (!any) return;
-  uint32_t k = 0;
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j)
-    if (found >> j & 1) stage_put(S, t, t.pos + k++, (uint32_t)sl.w[j]);
+  for (int k = 0; k < K; ++k)
+    if (found >> k & 1) o.buf[pos++] = (uint32_t)w[k];
 }
 
-// Top-down on one slab: claim every unreached neighbour for level cur + 1 (the CAS winner
-// pushes it and counts its out-arcs).
-__device__ inline uint32_t claim_slab(const Slab& sl, int nd, uint32_t* level, const uint32_t* deg,
-                                      uint32_t cur, unsigned long long& arcs) {
-  uint32_t lv[kKeysPerSlab], dv[kKeysPerSlab];
-  load_of_keys<uint32_t>(level, sl, live_words(sl, nd), 0u, lv);
-  // the claims and the claimed vertices' degrees, each in flight together
+// Block-wide exclusive prefix of k and one atomic per block on *ctr: this thread's first slot.
+__device__ inline uint32_t block_reserve(uint32_t* ctr, uint32_t k, uint32_t* sh) {
+  const int lane = lane64();
+  const uint32_t w = threadIdx.x / 64;
+  uint32_t incl = k;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t below = __shfl_up(incl, o);
+    if (lane >= o) incl += below;
+  }
+  if (lane == 63) sh[w] = incl;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (uint32_t i = 0; i < kBlock / 64; ++i) {
+      const uint32_t x = sh[i];
+      sh[i] = total;
+      total += x;
+    }
+    const uint32_t base = total ? atomicAdd(ctr, total) : 0u;
+    for (uint32_t i = 0; i < kBlock / 64; ++i) sh[i] += base;
+  }
+  __syncthreads();
+  const uint32_t first = sh[w] + incl - k;
+  __syncthreads();
+  return first;
+}
+
+// A step's frontier, 16 vertices to a group of lanes (four while there are groups to spare) and up
+// to kTileRows a lane: the multi-bucket vertices of a block's tile become work items of 16 buckets,
+// reserved by one atomic a tile (one a wave bounded the step: 37,000 on one address for 2.4 M
+// vertices), then each(u) is called for the single-bucket ones, by whole waves (u = kInvalid:
+// nothing).
+constexpr uint32_t kTileRows = 4;
+template <class Each>
+__device__ inline void for_each_frontier(const DView& F, const uint32_t* fin, uint32_t n, uint32_t* nm,
+                                         uint32_t* mu, uint32_t* mc, Each each) {
+  __shared__ uint32_t sh[kBlock / 64];
+  const uint32_t groups = gridDim.x * kGroupsPerBlock;
+  const uint32_t per = n <= groups * kRoundClaim ? (uint32_t)kRoundClaim : (uint32_t)kGroup;
+  const uint32_t rows = min(kTileRows, (n + groups * per - 1) / (groups * per));
+  const uint32_t tile = kGroupsPerBlock * per * rows;
+  for (uint32_t base = blockIdx.x * tile; base < n; base += gridDim.x * tile) {
+    uint32_t u[kTileRows], nb[kTileRows], k = 0;
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    const uint32_t v = (uint32_t)sl.w[j];
-    dv[j] = 0;
-    if (lv[j] == kLevelInf) {
-      lv[j] = atomicCAS(level + v, kLevelInf, cur + 1);
-      dv[j] = deg[v];
-    } else {
-      lv[j] = 0;
+    for (uint32_t r = 0; r < kTileRows; ++r) {
+      const uint32_t i = base + (r * kGroupsPerBlock + threadIdx.x / kGroup) * per + glane();
+      u[r] = r < rows && (uint32_t)glane() < per && i < n ? fin[i] : kInvalid;
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kTileRows; ++r) {
+      nb[r] = u[r] != kInvalid ? F.nbk[u[r]] : 0u;
+      k += nb[r] > 1 ? (nb[r] + kChunk - 1) / kChunk : 0u;
+    }
+    uint32_t pos = block_reserve(nm, k, sh);
+#pragma unroll
+    for (uint32_t r = 0; r < kTileRows; ++r) {
+      if (nb[r] <= 1) continue;
+      for (uint32_t j = 0; j * kChunk < nb[r]; ++j) {
+        mu[pos] = u[r];
+        mc[pos++] = j;
+      }
+      u[r] = kInvalid;
+    }
+    for (uint32_t r = 0; r < rows; ++r) {
+      const uint32_t x = r == 0 ? u[0] : r == 1 ? u[1] : r == 2 ? u[2] : u[3];
+      each(x != kInvalid && F.deg[x] > 0 ? x : kInvalid);
     }
   }
-  uint32_t found = 0;
+}
+static_assert(kTileRows == 4, "rows are picked by name");
+
+// The work items of a step, one to a group of 16 lanes: each(u, head, short0) by whole waves, head
+// being this lane's bucket of the item (kInvalid: none).
+template <class Each>
+__device__ inline void for_each_item(const DView& F, uint32_t nm, const uint32_t* mu, const uint32_t* mc, Each each) {
+  for (uint32_t base = blockIdx.x * kGroupsPerBlock; base < nm; base += gridDim.x * kGroupsPerBlock) {
+    const uint32_t it = base + threadIdx.x / kGroup;
+    uint32_t u = kInvalid, head = kInvalid, b = 1;
+    if (it < nm) {
+      u = mu[it];
+      b = mc[it] * kChunk + glane();
+      const uint64_t* h = slab_ptr(F, u);
+      const uint32_t nb = (uint32_t)(h[kKeysPerSlab] >> 32), xb = (uint32_t)h[kKeysPerSlab - 1];
+      if (b < nb) head = b == 0 ? u : xb + b - 1;
+    }
+    each(u, head, b == 0);
+  }
+}
+
+
+
+// Top-down on a round of slabs, claiming: every unreached neighbour gets level cur + 1 (the CAS
+// winner pushes it and counts its out-arcs).
+template <int K>
+__device__ inline uint32_t claim_round(const uint64_t (&w)[K], const bool (&live)[K], uint32_t* level,
+                                       uint8_t* seen, const uint32_t* deg, uint32_t cur, unsigned long long& arcs) {
+  uint32_t was[K], dv[K], found = 0;
+  uint8_t sv[K];
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j)
-    if (lv[j] == kLevelInf) {
-      found |= 1u << j;
-      arcs += dv[j];
+  for (int k = 0; k < K; ++k) sv[k] = seen[live[k] ? (uint32_t)w[k] : 0u];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint32_t v = (uint32_t)w[k];
+    was[k] = dv[k] = 0;
+    if (live[k] && !sv[k]) {
+      was[k] = atomicCAS(level + v, kLevelInf, cur + 1);
+      dv[k] = deg[v];
+      seen[v] = 1;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (was[k] == kLevelInf) {
+      found |= 1u << k;
+      arcs += dv[k];
     }
   return found;
 }
 
-// Wave-wide exclusive prefix of k and one atomic per wave on *ctr: this lane's first slot.
-__device__ inline uint32_t wave_reserve(uint32_t* ctr, uint32_t k) {
-  const int lane = lane64();
-  uint32_t incl = k;
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  const uint32_t total = __shfl(incl, 63);
-  uint32_t base = 0;
-  if (lane == 63 && total) base = atomicAdd(ctr, total);
-  base = __shfl(base, 63);
-  return base + incl - k;
+// Top-down on a round of slabs, marking: every unreached neighbour's byte is set by plain stores,
+// and the sweep over the vertices afterwards finds them.
+template <int K>
+__device__ inline void mark_round(const uint64_t (&w)[K], const bool (&live)[K], uint8_t* seen) {
+  uint8_t sv[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) sv[k] = seen[live[k] ? (uint32_t)w[k] : 0u];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (live[k] && !sv[k]) seen[(uint32_t)w[k]] = 1;
 }
 
 __device__ inline void block_add(unsigned long long* acc, unsigned long long v, unsigned long long* out) {
@@ -154,98 +299,60 @@ __device__ inline void block_add(unsigned long long* acc, unsigned long long v, 
 // Top-down step, single-bucket frontier vertices: a lane walks its vertex's chain.  A vertex
 // with several buckets becomes ceil(nb / 16) work items for k_lv_td_multi.
 __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L, uint32_t* level,
-                                                  const uint32_t* fin, uint32_t* fout, uint32_t* mu_,
+                                                  uint8_t* seen, const uint32_t* fin, uint32_t* fout, uint32_t* mu_,
                                                   uint32_t* mc_) {
   const uint32_t s = L & 3;
-  if (c->mode != 0) return;
+  const uint32_t mode = c->mode;
+  if (mode == kBottomUp) return;
   const uint32_t n = c->n[s];
   if (n == 0) return;
-  __shared__ Stage S[1];
+  __shared__ WaveStage S;
   __shared__ unsigned long long acc;
-  stage_open(S[0], fout, &c->n[(L + 1) & 3]);
+  WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t base = blockIdx.x * blockDim.x; base < n; base += stride) {
-    const uint32_t i = base + threadIdx.x;
-    uint32_t u = 0, nb = 0;
-    if (i < n) {
-      u = fin[i];
-      nb = F.nbk[u];
-    }
-    const uint32_t k = nb > 1 ? (nb + kChunk - 1) / kChunk : 0u;
-    const uint32_t pos = wave_reserve(&c->nm[s], k);
-    for (uint32_t j = 0; j < k; ++j) {
-      mu_[pos + j] = u;
-      mc_[pos + j] = j;
-    }
-    bool active = i < n && nb == 1 && F.deg[u] > 0;
-    uint32_t t = u;
-    while (__ballot(active)) {
-      Slab sl;
-      uint32_t found = 0;
-      if (active) {
-        load_slab(F, t, sl);
-        found = claim_slab(sl, kKeysPerSlab, level, F.deg, L, arcs);
-        t = (uint32_t)sl.w[15];
-        active = t != kInvalid;
-      }
-      push_found(S[0], found, sl);
-    }
-  }
-  stage_close(S);
+  for_each_frontier(F, fin, n, &c->nm[s], mu_, mc_, [&](uint32_t u) {
+    walk_chains<kRoundClaim>(F, u, 0u, false, [&](const auto& w, const auto& live, const auto&) {
+      if (mode == kMark) mark_round(w, live, seen);
+      else push_found(out, claim_round(w, live, level, seen, F.deg, L, arcs), w);
+    });
+  });
+  wave_out_close(out);
   block_add(&acc, arcs, &c->arcs[(L + 1) & 3]);
 }
 
 // Top-down step, multi-bucket frontier vertices: a 16-lane group per work item (16 buckets),
 // a lane per bucket chain.
 __global__ void __launch_bounds__(kBlock) k_lv_td_multi(DView F, LvCnt* c, uint32_t L, uint32_t* level,
-                                                        uint32_t* fout, const uint32_t* mu_,
+                                                        uint8_t* seen, uint32_t* fout, const uint32_t* mu_,
                                                         const uint32_t* mc_) {
   const uint32_t s = L & 3;
-  if (c->mode != 0) return;
+  const uint32_t mode = c->mode;
+  if (mode == kBottomUp) return;
   const uint32_t nm = c->nm[s];
   if (nm == 0) return;
-  __shared__ Stage S[1];
+  __shared__ WaveStage S;
   __shared__ unsigned long long acc;
-  stage_open(S[0], fout, &c->n[(L + 1) & 3]);
+  WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
-  const uint32_t gib = threadIdx.x / kGroup;
-  for (uint32_t base = blockIdx.x * kGroupsPerBlock; base < nm; base += gridDim.x * kGroupsPerBlock) {
-    const uint32_t it = base + gib;  // one item per 16-lane group, a lane per bucket
-    uint32_t u = 0, nb = 0, xb = 0, b = 0;
-    if (it < nm) {
-      u = mu_[it];
-      nb = (uint32_t)(slab_ptr(F, u)[15] >> 32);
-      xb = (uint32_t)slab_ptr(F, u)[14];
-      b = mc_[it] * kChunk + glane();
-    }
-    bool active = it < nm && b < nb;
-    uint32_t t = b == 0 ? u : xb + b - 1;
-    int nd = b == 0 ? kKeysPerSlab - 1 : kKeysPerSlab;
-    while (__ballot(active)) {
-      Slab sl;
-      uint32_t found = 0;
-      if (active) {
-        load_slab(F, t, sl);
-        found = claim_slab(sl, nd, level, F.deg, L, arcs);
-        t = (uint32_t)sl.w[15];
-        nd = kKeysPerSlab;
-        active = t != kInvalid;
-      }
-      push_found(S[0], found, sl);
-    }
-  }
-  stage_close(S);
+  for_each_item(F, nm, mu_, mc_, [&](uint32_t, uint32_t head, bool short0) {
+    walk_chains<kRoundClaim>(F, head, 0u, short0, [&](const auto& w, const auto& live, const auto&) {
+      if (mode == kMark) mark_round(w, live, seen);
+      else push_found(out, claim_round(w, live, level, seen, F.deg, L, arcs), w);
+    });
+  });
+  wave_out_close(out);
   block_add(&acc, arcs, &c->arcs[(L + 1) & 3]);
 }
 
 // Does some in-neighbour of v (reverse view) sit on level cur?  A lane walks v's buckets
-// and stops at the first slab that holds one.
-__device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t* level, uint32_t cur) {
+// and stops at the first slab that holds one.  v is unreached, so an in-neighbour of the reached
+// set is on level cur or was reached in this step: the set's bits say which levels to read.
+__device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t* level, const uint8_t* seen,
+                                     uint32_t cur) {
   Slab sl;
   load_slab(R, v, sl);
   const uint32_t nb = (uint32_t)(sl.w[15] >> 32);
@@ -257,11 +364,12 @@ __device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t*
       nd = kKeysPerSlab;
     }
     while (true) {
-      uint32_t lv[kKeysPerSlab];
-      load_of_keys<uint32_t>(level, sl, live_words(sl, nd), kLevelInf, lv);
+      uint8_t sv[kKeysPerSlab];
+      load_of_keys<uint8_t>(seen, sl, live_words(sl, nd), (uint8_t)0, sv);
       bool hit = false;
 #pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j) hit |= lv[j] == cur;
+      for (int j = 0; j < kKeysPerSlab; ++j)
+        if (!hit && sv[j]) hit = ld_u32(level + (uint32_t)sl.w[j]) == cur;
       if (hit) return true;
       const uint32_t t = (uint32_t)sl.w[15];
       if (t == kInvalid) break;
@@ -273,14 +381,17 @@ __device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t*
 }
 
 // Bottom-up step: every unreached vertex with in-arcs looks for a parent on level L.  Only
-// the vertex's own lane writes its level, and no level changes to L during the step.
+// the vertex's own lane writes its level, and no level changes to L during the step.  After a
+// marking step the same sweep collects the vertices with a byte and no level.  (A block adds to two
+// counters at its end; 8,192 blocks took 123 us for that at scale 22, these 2,048 take 55.)
 __global__ void __launch_bounds__(kBlock) k_lv_bu(DView F, DView R, LvCnt* c, uint32_t L, uint32_t* level,
-                                                  uint32_t* fout, uint32_t nv) {
+                                                  uint8_t* seen, uint32_t* fout, uint32_t nv) {
   const uint32_t s = L & 3;
-  if (c->mode != 1 || c->n[s] == 0) return;
-  __shared__ Stage S[1];
+  const uint32_t mode = c->mode;
+  if (mode == kClaim || c->n[s] == 0) return;
+  __shared__ WaveStage S;
   __shared__ unsigned long long acc;
-  stage_open(S[0], fout, &c->n[(L + 1) & 3]);
+  WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
@@ -288,14 +399,18 @@ __global__ void __launch_bounds__(kBlock) k_lv_bu(DView F, DView R, LvCnt* c, ui
   for (uint32_t base = blockIdx.x * blockDim.x; base < nv; base += stride) {
     const uint32_t v = base + threadIdx.x;
     bool found = false;
-    if (v < nv && ld_u32(level + v) == kLevelInf && R.deg[v] > 0 && has_parent_at(R, v, level, L)) {
+    if (v < nv && ld_u32(level + v) == kLevelInf &&
+        (mode == kMark ? seen[v] != 0 : R.deg[v] > 0 && has_parent_at(R, v, level, seen, L))) {
       level[v] = L + 1;
+      seen[v] = 1;
       arcs += F.deg[v];
       found = true;
     }
-    stage_push(S[0], found, v);
+    bool any;
+    const uint32_t pos = wave_slots(out, found ? 1u : 0u, any);
+    if (found) out.buf[pos] = v;
   }
-  stage_close(S);
+  wave_out_close(out);
   block_add(&acc, arcs, &c->arcs[(L + 1) & 3]);
 }
 
@@ -304,7 +419,8 @@ inline uint32_t blocks_for(uint64_t n, uint32_t cap) {
 }
 
 size_t levels_ws_bytes(const mk_graph* g) {
-  return 256 + 2 * ((size_t)g->n * 4 + 256) + 2 * (levels_multi_cap(g) * 4 + 256) + 256;
+  return 256 + 2 * ((size_t)g->n * 4 + 256) + 2 * (levels_multi_cap(g) * 4 + 256) +
+         ((size_t)g->n + 256) + 256;
 }
 
 // ----------------------------------------------------------------- tree nodes from levels
@@ -434,9 +550,46 @@ struct DsCnt {
 };
 static_assert(sizeof(DsCnt) <= 256, "counter block");
 
-__global__ void k_ds_seed(uint32_t* dist, uint32_t* q0, DsCnt* c, uint32_t src, uint32_t delta) {
+// A vertex's word holds its distance above the stamp of its last push, so that one 64-bit atomic
+// minimum lowers the distance and says whether the vertex is queued already: near pushes are
+// stamped kNear | step + 1, far ones with the band.  A distance below the band limit is on no far
+// pile that the band will push to again, so one stamp serves both.  A minimum that only ties
+// leaves the word alone: within a band a distance is always near or always far, and the stamps of
+// each kind grow (a split stamps what it keeps).
+//
+// What a relaxation reads first is one byte per vertex, a distance that the vertex had, rounded up
+// to kDsMant + 1 significant bits: an arc that does not beat it is dropped.  Four bytes a vertex
+// brought 103 M lines into the L2s in a run at scale 22, the bytes bring half of that, and what
+// they let through by rounding costs fewer atomics (10.8 M for all) than the second one that a stamp
+// array takes (15.5 M).  The bytes are written without order among the lanes; any of them is a
+// distance the vertex had, so none is too low.
+//
+// One run at scale 22: 4.0 ms with u32 distances, a stamp array for each queue and a lane per slab;
+// 2.9 now.  What is left is slab reads: a round over most of the graph takes 0.9 ms for 20 M lines.
+constexpr uint32_t kNear = 1u << 31;
+constexpr int kDsMant = 3;
+using DsByte = uint8_t;
+constexpr DsByte kDsFar = 255;  // no distance yet: above every code
+
+// d to its kDsMant + 1 leading bits, rounded down, as a code in the order of the values.
+__device__ inline uint32_t ds_code(uint32_t d, uint32_t& exact) {
+  const int e = max(0, 31 - __clz((int)(d | 1u)) - kDsMant);
+  exact = (d & ((1u << e) - 1)) == 0;
+  return ((uint32_t)e << kDsMant) + (d >> e);
+}
+
+__global__ void k_ds_fill(unsigned long long* word, DsByte* bound, uint32_t nv) {
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    word[v] = (unsigned long long)kLevelInf << 32;
+    bound[v] = kDsFar;
+  }
+}
+
+__global__ void k_ds_seed(unsigned long long* word, DsByte* bound, uint32_t* q0, DsCnt* c, uint32_t src,
+                          uint32_t delta) {
   if (threadIdx.x != 0) return;
-  dist[src] = 0;
+  word[src] = 0;
+  bound[src] = 0;
   q0[0] = src;
   c->n[0] = 1;
   c->T = delta;
@@ -444,49 +597,57 @@ __global__ void k_ds_seed(uint32_t* dist, uint32_t* q0, DsCnt* c, uint32_t src, 
   c->fmin = kLevelInf;
 }
 
-// Relax one slab of u (distance du): a neighbour whose distance drops goes to the near
-// frontier (once per step, by the step stamp) or to the far pile (once per band).
-//
-// A neighbour is marked, and pushed by whoever marks it first, as soon as the new distance beats
-// the one read, without waiting for the minimum to return (if another lane's was smaller still,
-// that lane's drop needs the push as well), so that a slab takes two round trips.
-__device__ inline void relax_ds(const Slab& sl, int nd, uint32_t du, uint32_t* dist, uint32_t* mark,
-                                uint32_t* fmark, uint32_t stamp, uint32_t band, uint32_t T, uint32_t& near,
-                                uint32_t& far) {
-  uint32_t dv[kKeysPerSlab], tk[kKeysPerSlab], to_near = 0, to_far = 0;
-  load_of_keys<uint32_t>(dist, sl, live_words(sl, nd), 0u, dv);
+__global__ void k_ds_store(const unsigned long long* word, uint32_t* dist, uint32_t nv) {
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x)
+    dist[v] = (uint32_t)(word[v] >> 32);
+}
+
+struct DsArgs {
+  unsigned long long* word;
+  DsByte* bound;
+  uint32_t *far[2], *multi_v, *multi_c;
+};
+
+__device__ inline uint32_t ds_dist(const DsArgs& a, uint32_t v) {
+  return ld_u32(reinterpret_cast<const uint32_t*>(a.word + v) + 1);
+}
+
+// Relax a round of slabs (val: the distances they are reached from): a neighbour whose distance
+// drops goes to the near frontier (once per step, by the step stamp) or to the far pile (once per
+// band).
+template <int K>
+__device__ inline void relax_round(const uint64_t (&w)[K], const bool (&live)[K],
+                                   const uint32_t (&val)[K], const DsArgs& a, uint32_t step, uint32_t band,
+                                   uint32_t T, uint32_t& near, uint32_t& far) {
+  DsByte bv[K];
+  unsigned long long old[K];
+  uint32_t d[K], tried = 0, exact;
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    const uint32_t v = (uint32_t)sl.w[j];
-    const uint32_t nd_ = (uint32_t)min<uint64_t>((uint64_t)du + (sl.w[j] >> 32), 0xFFFFFFFEull);
-    tk[j] = 0;
-    if (nd_ < dv[j]) {
-      if (nd_ < T) {
-        to_near |= 1u << j;
-        tk[j] = atomicExch(mark + v, stamp);
-      } else {
-        to_far |= 1u << j;
-        tk[j] = atomicExch(fmark + v, band);
-      }
-      (void)atomicMin(dist + v, nd_);
+  for (int k = 0; k < K; ++k) bv[k] = a.bound[live[k] ? (uint32_t)w[k] : 0u];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    d[k] = (uint32_t)min<uint64_t>((uint64_t)val[k] + (w[k] >> 32), 0xFFFFFFFEull);
+    old[k] = 0;
+    if (live[k] && ds_code(d[k], exact) < bv[k]) {
+      tried |= 1u << k;
+      old[k] = atomicMin(a.word + (uint32_t)w[k], (unsigned long long)d[k] << 32 | (d[k] < T ? step : band));
     }
   }
   near = far = 0;
 #pragma unroll
-  for (int j = 0; j < kKeysPerSlab; ++j) {
-    if ((to_near >> j & 1) && tk[j] != stamp) near |= 1u << j;
-    if ((to_far >> j & 1) && tk[j] != band) far |= 1u << j;
-  }
+  for (int k = 0; k < K; ++k)
+    if ((tried >> k & 1) && d[k] < (uint32_t)(old[k] >> 32)) {
+      const uint32_t code = ds_code(d[k], exact);
+      a.bound[(uint32_t)w[k]] = (DsByte)(code + (exact ? 0u : 1u));
+      if (d[k] < T) near |= (uint32_t)((uint32_t)old[k] != step) << k;
+      else far |= (uint32_t)((uint32_t)old[k] != band) << k;
+    }
 }
 
 __device__ inline void wave_min_to(uint32_t* out, uint32_t m) {
   for (int o = 32; o > 0; o >>= 1) m = min(m, (uint32_t)__shfl_xor(m, o));
   if ((threadIdx.x & 63) == 0 && m != kLevelInf) atomicMin(out, m);
 }
-
-struct DsArgs {
-  uint32_t *dist, *mark, *fmark, *far[2], *multi_v, *multi_c;
-};
 
 // Near step, single-bucket frontier vertices (a lane each); others become 16-bucket items.
 __global__ void __launch_bounds__(kBlock) k_ds_relax(DView F, DsCnt* c, uint32_t S, DsArgs a, const uint32_t* fin,
@@ -498,42 +659,21 @@ __global__ void __launch_bounds__(kBlock) k_ds_relax(DView F, DsCnt* c, uint32_t
   }
   const uint32_t n = c->n[s];
   if (n == 0) return;
-  const uint32_t T = c->T, band = c->band, fp = c->fpar, stamp = S + 1;
-  __shared__ Stage St[2];
-  stage_open(St[0], fout, &c->n[(S + 1) & 3]);
-  stage_open(St[1], a.far[fp], &c->nfar[fp]);
-  __syncthreads();
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t base = blockIdx.x * blockDim.x; base < n; base += stride) {
-    const uint32_t i = base + threadIdx.x;
-    uint32_t u = 0, nb = 0, du = 0;
-    if (i < n) {
-      u = fin[i];
-      nb = F.nbk[u];
-      du = ld_u32(a.dist + u);
-    }
-    const uint32_t k = nb > 1 ? (nb + kChunk - 1) / kChunk : 0u;
-    const uint32_t pos = wave_reserve(&c->nm[s], k);
-    for (uint32_t j = 0; j < k; ++j) {
-      a.multi_v[pos + j] = u;
-      a.multi_c[pos + j] = j;
-    }
-    bool active = i < n && nb == 1 && F.deg[u] > 0;
-    uint32_t t = u;
-    while (__ballot(active)) {
-      Slab sl;
-      uint32_t nr = 0, fr = 0;
-      if (active) {
-        load_slab(F, t, sl);
-        relax_ds(sl, kKeysPerSlab, du, a.dist, a.mark, a.fmark, stamp, band, T, nr, fr);
-        t = (uint32_t)sl.w[15];
-        active = t != kInvalid;
-      }
-      push_found(St[0], nr, sl);
-      push_found(St[1], fr, sl);
-    }
-  }
-  stage_close(St);
+  const uint32_t T = c->T, band = c->band, fp = c->fpar, step = kNear | (S + 1);
+  __shared__ WaveStage St[2];
+  WaveOut near = wave_out(St[0], fout, &c->n[(S + 1) & 3]);
+  WaveOut far = wave_out(St[1], a.far[fp], &c->nfar[fp]);
+  for_each_frontier(F, fin, n, &c->nm[s], a.multi_v, a.multi_c, [&](uint32_t u) {
+    const uint32_t du = u != kInvalid ? ds_dist(a, u) : 0u;
+    walk_chains<kRoundRelax>(F, u, du, false, [&](const auto& w, const auto& live, const auto& val) {
+      uint32_t nr, fr;
+      relax_round(w, live, val, a, step, band, T, nr, fr);
+      push_found(near, nr, w);
+      push_found(far, fr, w);
+    });
+  });
+  wave_out_close(near);
+  wave_out_close(far);
 }
 
 // Near step, multi-bucket frontier vertices: a 16-lane group per item, a lane per bucket.
@@ -542,53 +682,37 @@ __global__ void __launch_bounds__(kBlock) k_ds_relax_multi(DView F, DsCnt* c, ui
   const uint32_t s = S & 3;
   const uint32_t nm = c->nm[s];
   if (nm == 0) return;
-  const uint32_t T = c->T, band = c->band, fp = c->fpar, stamp = S + 1;
-  __shared__ Stage St[2];
-  stage_open(St[0], fout, &c->n[(S + 1) & 3]);
-  stage_open(St[1], a.far[fp], &c->nfar[fp]);
-  __syncthreads();
-  const uint32_t gib = threadIdx.x / kGroup;
-  for (uint32_t base = blockIdx.x * kGroupsPerBlock; base < nm; base += gridDim.x * kGroupsPerBlock) {
-    const uint32_t it = base + gib;  // one item per 16-lane group, a lane per bucket
-    uint32_t u = 0, du = 0, nb = 0, xb = 0, b = 0;
-    if (it < nm) {
-      u = a.multi_v[it];
-      du = ld_u32(a.dist + u);
-      nb = (uint32_t)(slab_ptr(F, u)[15] >> 32);
-      xb = (uint32_t)slab_ptr(F, u)[14];
-      b = a.multi_c[it] * kChunk + glane();
-    }
-    bool active = it < nm && b < nb;
-    uint32_t t = b == 0 ? u : xb + b - 1;
-    int nd = b == 0 ? kKeysPerSlab - 1 : kKeysPerSlab;
-    while (__ballot(active)) {
-      Slab sl;
-      uint32_t nr = 0, fr = 0;
-      if (active) {
-        load_slab(F, t, sl);
-        relax_ds(sl, nd, du, a.dist, a.mark, a.fmark, stamp, band, T, nr, fr);
-        t = (uint32_t)sl.w[15];
-        nd = kKeysPerSlab;
-        active = t != kInvalid;
-      }
-      push_found(St[0], nr, sl);
-      push_found(St[1], fr, sl);
-    }
-  }
-  stage_close(St);
+  const uint32_t T = c->T, band = c->band, fp = c->fpar, step = kNear | (S + 1);
+  __shared__ WaveStage St[2];
+  WaveOut near = wave_out(St[0], fout, &c->n[(S + 1) & 3]);
+  WaveOut far = wave_out(St[1], a.far[fp], &c->nfar[fp]);
+  for_each_item(F, nm, a.multi_v, a.multi_c, [&](uint32_t u, uint32_t head, bool short0) {
+    const uint32_t du = u != kInvalid ? ds_dist(a, u) : 0u;
+    walk_chains<kRoundRelax>(F, head, du, short0, [&](const auto& w, const auto& live, const auto& val) {
+      uint32_t nr, fr;
+      relax_round(w, live, val, a, step, band, T, nr, fr);
+      push_found(near, nr, w);
+      push_found(far, fr, w);
+    });
+  });
+  wave_out_close(near);
+  wave_out_close(far);
 }
 
-// When a step leaves the near frontier empty: the smallest distance on the far pile ...
+// When a step leaves the near frontier empty: the smallest distance on the far pile at or past the
+// band limit (a vertex below it has joined the near frontier since) ...
 __global__ void k_ds_far_min(DsCnt* c, uint32_t S, DsArgs a) {
   if (c->n[(S + 1) & 3] != 0) return;
-  const uint32_t fp = c->fpar, nf = c->nfar[fp];
+  const uint32_t fp = c->fpar, nf = c->nfar[fp], T = c->T;
   uint32_t m = kLevelInf;
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nf; i += gridDim.x * blockDim.x)
-    m = min(m, ld_u32(a.dist + a.far[fp][i]));
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nf; i += gridDim.x * blockDim.x) {
+    const uint32_t d = ds_dist(a, a.far[fp][i]);
+    if (d >= T) m = min(m, d);
+  }
   wave_min_to(&c->fmin, m);
 }
 
-// ... and the split at T' = fmin + delta: vertices below T' start the next near frontier,
+// ... and the split at T' = fmin + delta: those below T' start the next near frontier,
 // the others move to the other pile, stamped with the next band.  The last block to finish
 // commits the new band limit, band number and pile (no block waits for another).
 __global__ void k_ds_split(DsCnt* c, uint32_t S, DsArgs a, uint32_t* fout, uint32_t delta) {
@@ -596,7 +720,7 @@ __global__ void k_ds_split(DsCnt* c, uint32_t S, DsArgs a, uint32_t* fout, uint3
   const uint32_t fp = c->fpar, nf = c->nfar[fp];
   if (nf == 0) return;
   const uint32_t T2 = (uint32_t)min<uint64_t>((uint64_t)c->fmin + delta, 0xFFFFFFFFull);
-  const uint32_t nb = c->band + 1;
+  const uint32_t T = c->T, nb = c->band + 1;
   __shared__ Stage St[2];
   __shared__ bool last;
   stage_open(St[0], fout, &c->n[(S + 1) & 3]);
@@ -609,10 +733,10 @@ __global__ void k_ds_split(DsCnt* c, uint32_t S, DsArgs a, uint32_t* fout, uint3
     uint32_t v = 0;
     if (i < nf) {
       v = a.far[fp][i];
-      const uint32_t d = ld_u32(a.dist + v);
-      to_near = d < T2;
-      keep = !to_near;
-      if (keep) a.fmark[v] = nb;
+      const uint32_t d = ds_dist(a, v);
+      to_near = d >= T && d < T2;
+      keep = d >= T2;
+      if (keep) *reinterpret_cast<uint32_t*>(a.word + v) = nb;
     }
     stage_push(St[0], to_near, v);
     stage_push(St[1], keep, v);
@@ -636,7 +760,9 @@ __global__ void k_ds_split(DsCnt* c, uint32_t S, DsArgs a, uint32_t* fout, uint3
 }
 
 size_t dist_ws_bytes(const mk_graph* g) {
-  return 256 + 6 * ((size_t)g->n * 4 + 256) + 2 * (levels_multi_cap(g) * 4 + 256) + 256;
+  return 256 + ((size_t)g->n * 8 + 256) + ((size_t)g->n * sizeof(DsByte) + 256) +
+         4 * ((size_t)g->n * 4 + 256) +
+         2 * (levels_multi_cap(g) * 4 + 256) + 256;
 }
 
 }  // namespace
@@ -653,21 +779,20 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
   const DView R = g->view[VR].on ? g->view[VR].d : F;
   allow_bu = allow_bu && g->view[VR].on;
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, c);
-  hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, level, N);
-  hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.q[0], c, F.deg, source);
+  hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, level, b.seen, N);
+  hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.seen, b.q[0], c, F.deg, source);
   MK_LAUNCH(g, "k_lv_seed");
   uint64_t every = kSyncFirst, next_sync = kSyncFirst;
   for (uint32_t L = 0;; ++L) {
     uint32_t* fin = b.q[L & 1];
     uint32_t* fout = b.q[(L + 1) & 1];
     hipLaunchKernelGGL(k_lv_decide, dim3(1), dim3(64), 0, stream, c, L, N, (int)allow_bu);
-    hipLaunchKernelGGL(k_lv_td, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, L, level, fin,
-                       fout, b.multi_v, b.multi_c);
-    hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, fout, b.multi_v,
-                       b.multi_c);
-    if (allow_bu)
-      hipLaunchKernelGGL(k_lv_bu, dim3(blocks_for(N, 8192)), dim3(kBlock), 0, stream, F, R, c, L, level,
-                         fout, N);
+    hipLaunchKernelGGL(k_lv_td, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, L, level, b.seen,
+                       fin, fout, b.multi_v, b.multi_c);
+    hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, b.seen, fout,
+                       b.multi_v, b.multi_c);
+    hipLaunchKernelGGL(k_lv_bu, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, R, c, L, level,
+                       b.seen, fout, N);
     MK_LAUNCH(g, "k_lv step");
     if (L + 1 == next_sync || L + 1 >= N) {
       if (next_sync >= 2 * kSyncFirst) every = std::min<uint64_t>(2 * every, kSyncMax);
@@ -712,6 +837,7 @@ mk_status bfs_tree_by_levels(mk_graph* g, uint32_t source, uint32_t* level, uint
   b.q[1] = g->fq[1];
   b.multi_v = g->lv_multi[0];
   b.multi_c = g->lv_multi[1];
+  b.seen = reinterpret_cast<uint8_t*>(g->fq[2]);
   mk_status s = levels_run(g, source, true, b, level, g->h_pin, nullptr, stream);
   if (s != MK_OK) return s;
   return tree_from_dist<true>(g, source, level, D, stream);
@@ -721,15 +847,14 @@ mk_status bfs_tree_by_levels(mk_graph* g, uint32_t source, uint32_t* level, uint
 // positive weights bound the number of distance drops, so the loop ends; the cap is a guard
 // (and keeps the step stamps unique).
 mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2], const DsArgs& a,
-                   uint64_t* pin, hipStream_t stream) {
+                   uint32_t* dist, uint64_t* pin, hipStream_t stream) {
   const uint32_t N = g->n;
   DsCnt* c = reinterpret_cast<DsCnt*>(cnt);
   const DView F = g->view[VF].d;
   const uint32_t delta = std::max<uint32_t>(1u, g->sssp_delta);
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, reinterpret_cast<LvCnt*>(c));
-  hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, a.dist, N);
-  hipLaunchKernelGGL(k_zero_marks, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, a.mark, a.fmark, N);
-  hipLaunchKernelGGL(k_ds_seed, dim3(1), dim3(64), 0, stream, a.dist, q[0], c, source, delta);
+  hipLaunchKernelGGL(k_ds_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, a.word, a.bound, N);
+  hipLaunchKernelGGL(k_ds_seed, dim3(1), dim3(64), 0, stream, a.word, a.bound, q[0], c, source, delta);
   MK_LAUNCH(g, "k_ds_seed");
   const uint64_t cap = std::min<uint64_t>(64ull * N + 1024, 1ull << 31);
   uint64_t every = kSyncFirst, next_sync = kSyncFirst;
@@ -752,20 +877,21 @@ mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2]
       if (S > cap) return MK_ERR_HIP;
     }
   }
+  hipLaunchKernelGGL(k_ds_store, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, a.word, dist, N);
+  MK_LAUNCH(g, "k_ds_store");
   return MK_OK;
 }
 
 mk_status sssp_tree_by_distances(mk_graph* g, uint32_t source, uint32_t* dist, uint64_t* D, hipStream_t stream) {
   uint32_t* q[2] = {g->fq[0], g->fq[1]};
   DsArgs a;
-  a.dist = dist;
-  a.mark = g->fq[2];  // scratch here; the maintained traversals' stamps stay untouched
-  a.fmark = g->fq[3];
+  a.word = reinterpret_cast<unsigned long long*>(D);  // the nodes are written afterwards
+  a.bound = reinterpret_cast<DsByte*>(g->fq[2]);
   a.far[0] = g->far[0];
   a.far[1] = g->far[1];
   a.multi_v = g->lv_multi[0];
   a.multi_c = g->lv_multi[1];
-  mk_status s = dist_run(g, source, g->lv_cnt, q, a, g->h_pin, stream);
+  mk_status s = dist_run(g, source, g->lv_cnt, q, a, dist, g->h_pin, stream);
   if (s != MK_OK) return s;
   return tree_from_dist<false>(g, source, dist, D, stream);
 }
@@ -797,6 +923,7 @@ mk_status mk_bfs_levels(mk_graph* g, uint32_t source, uint32_t flags, void* d_ws
   b.q[1] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   b.multi_v = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));
   b.multi_c = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));
+  b.seen = reinterpret_cast<uint8_t*>(take((size_t)N));
   return levels_run(g, source, !(flags & MK_BFS_TOP_DOWN_ONLY), b, d_level, g->slot_pin[slot],
                     h_bottom_up_steps, stream);
 }
@@ -824,14 +951,13 @@ mk_status mk_sssp_distances(mk_graph* g, uint32_t source, void* d_ws, size_t ws_
   q[0] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   q[1] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   DsArgs a;
-  a.dist = d_dist;
-  a.mark = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
-  a.fmark = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
+  a.word = reinterpret_cast<unsigned long long*>(take((size_t)N * 8));
+  a.bound = reinterpret_cast<DsByte*>(take((size_t)N));
   a.far[0] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   a.far[1] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   a.multi_v = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));
   a.multi_c = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));
-  return dist_run(g, source, c, q, a, g->slot_pin[slot], stream);
+  return dist_run(g, source, c, q, a, d_dist, g->slot_pin[slot], stream);
 }
 
 size_t mk_sssp_distances_workspace_bytes(const mk_graph* g) { return g ? dist_ws_bytes(g) : 0; }

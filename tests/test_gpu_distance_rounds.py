@@ -1,0 +1,88 @@
+"""Distance-only traversals, the paths that depend on sizes: steps that claim against steps that
+mark and sweep, single-bucket chains against items of 16 buckets, frontiers of a few vertices
+against several rows a lane, and the rounded distance bound over the whole range of distances."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_17813_amd import inputs as I
+from paper_2305_17813_amd import native
+
+from parity import say
+
+pytestmark = pytest.mark.gpu
+INF = 0xFFFFFFFF
+
+
+def reference(n, src, dst, w, source):
+    """Levels by whole-edge-list relaxation, distances the same way with the saturating sum."""
+    lv = np.full(n, INF, np.uint64)
+    di = np.full(n, INF, np.uint64)
+    lv[source] = di[source] = 0
+    src, dst, w = src.astype(np.int64), dst.astype(np.int64), w.astype(np.uint64)
+    for a, step in ((lv, np.ones_like(w)), (di, w)):
+        while True:
+            old = a.copy()
+            m = a[src] != INF
+            np.minimum.at(a, dst[m], np.minimum(a[src[m]] + step[m], INF - 1))
+            if (a == old).all():
+                break
+    return lv.astype(np.uint32), di.astype(np.uint32)
+
+
+def compare(n, src, dst, w, sources, **cfg):
+    src, dst, w = (np.asarray(x, np.uint32) for x in (src, dst, w))
+    t = [torch.from_numpy(x.view(np.int32).copy()).cuda() for x in (src, dst, w)]
+    G = native.Graph(n, *t, views=native.VIEW_FWD | native.VIEW_REV, **cfg)
+    for s in sources:
+        lv, di = reference(n, src, dst, w, s)
+        for kw in ({}, {"top_down_only": True}):
+            got, _ = G.bfs_levels(s, **kw)
+            assert np.array_equal(got.cpu().numpy().view(np.uint32), lv), (s, kw)
+        assert np.array_equal(G.sssp_distances(s).cpu().numpy().view(np.uint32), di), s
+
+
+def arcs(rng, n, m, weights):
+    key = np.unique(rng.integers(0, n * n, m, dtype=np.int64))
+    rng.shuffle(key)
+    src, dst = key // n, key % n
+    keep = src != dst
+    return src[keep], dst[keep], weights(keep.sum())
+
+
+# one vertex short of, exactly at and past a wave, a block and a row of them; a hub of several
+# items of 16 buckets whose arcs reach every vertex
+@pytest.mark.parametrize("n", [1, 2, 15, 17, 63, 64, 65, 255, 257, 4099])
+@pytest.mark.parametrize("delta", [0, 7])
+def test_hub_and_ring(n, delta):
+    say(f"case: hub and ring, {n} vertices, band {delta}")
+    v = np.arange(n)
+    ring = v if n > 1 else v[:0]
+    hub = v[1:]
+    src = np.concatenate([ring, np.zeros(len(hub), np.int64)])
+    dst = np.concatenate([(ring + 1) % max(n, 1), hub])
+    key, first = np.unique(src * n + dst, return_index=True)
+    w = (np.arange(len(src)) * 2654435761 % 97 + 1).astype(np.uint32)
+    compare(n, src[first], dst[first], w[first], sorted({0, n // 2, n - 1}), sssp_delta=delta)
+
+
+# weights from one to the saturation of the sums: every exponent of the rounded bound
+@pytest.mark.parametrize("bits", [1, 3, 4, 5, 9, 16, 24, 31, 32])
+def test_weight_ranges(bits):
+    say(f"case: weights of up to {bits} bits")
+    rng = np.random.default_rng(100 + bits)
+    hi = (1 << bits) - 1
+    weights = lambda k: np.maximum(1, rng.integers(max(1, hi // 3), hi + 1, k)).astype(np.uint32)
+    src, dst, w = arcs(rng, 700, 4000, weights)
+    compare(700, src, dst, w, [int(src[0]), 3])
+    compare(700, src, dst, w, [5], sssp_delta=max(1, hi // 2))
+
+
+# power-law graphs: dense steps, many repeated relaxations of the same vertices
+@pytest.mark.parametrize("scale,ef", [(9, 16), (13, 8), (14, 4)])
+def test_power_law(scale, ef):
+    say(f"case: power-law graph, scale {scale}, edge factor {ef}")
+    g = I.rmat_graph(scale, ef, 7 + scale)
+    a = [np.asarray(x.cpu()).view(np.uint32) if torch.is_tensor(x) else np.asarray(x) for x in g.u32()]
+    deg = np.bincount(a[0].astype(np.int64), minlength=g.n)
+    compare(g.n, *a, [int(deg.argmax()), int(np.nonzero(deg == 1)[0][0])])
