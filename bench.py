@@ -300,17 +300,16 @@ def main():
                          "traffic": roof["traffic"],
                          "slabs_per_op": {k: slabs[k] / (K * B) for k in ("i_fwd", "i_rev", "i_und")}},
     }
-    # PageRank (packed iterations, the default scheme): the first iteration of a call reads the
-    # reverse view's slabs (128 B each; vertices without in-arcs are skipped, so this
-    # over-counts), gathers a 4 B contribution and writes a 4 B packed key per in-arc, and
-    # streams ranks, contributions and out-degrees (12 B per vertex); every later iteration
-    # reads the 4 B packed key and gathers the 4 B contribution per in-arc, and streams 16 B per
-    # vertex (segment start, rank, contribution, out-degree).  The figure is the mean over the
-    # iterations of the timed calls.
+    # PageRank (packed iterations, the default scheme): a call first reads the reverse view's slabs
+    # (128 B each; vertices without in-arcs are skipped, so this over-counts), reads a 4 B rank and
+    # writes a 4 B packed source per in-arc, and streams degrees, ranks and offsets (12 B per
+    # vertex); every iteration then reads the 4 B packed source and gathers the 4 B contribution
+    # per in-arc, and streams 16 B per vertex (segment start, rank, contribution, out-degree).  The
+    # figure is the mean over the iterations of the timed calls.
     rev_slabs = st_after["head_slabs"][1] + st_after["pool_used"][1]
     n_in = st_after["n_arcs"]
-    first_bytes = 128 * rev_slabs + 8 * n_in + 12 * g_in.n
     packed_bytes = 8 * n_in + 16 * g_in.n
+    first_bytes = 128 * rev_slabs + 8 * n_in + 12 * g_in.n + packed_bytes
     n_iter = sum(sum(x) for x in pr_iters)
     n_calls = sum(len(x) for x in pr_iters)
     pr_iter_bytes = (n_calls * first_bytes + (n_iter - n_calls) * packed_bytes) / n_iter

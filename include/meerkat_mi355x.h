@@ -185,10 +185,11 @@ mk_status mk_traverse_from(mk_graph* g, uint32_t source, int weighted, void* d_w
 
 /* Distance-only BFS levels from `source` (the "vanilla" BFS of the experimental section:
  * 32-bit levels, no parents, against the tree variant that the maintained BFS/SSSP keep).
- * Level-synchronous; each step is top-down (the frontier's out-arcs claim unreached vertices)
- * or, with MK_VIEW_REV, bottom-up (each unreached vertex scans its in-arcs and stops at the
- * first one on the current level), chosen on the device per step by direction optimization
- * (Beamer et al.) recast for slabs: bottom-up when 2 nf + mf > 6 nu + N/2, with nf and mf
+ * Level-synchronous; each step is top-down (the frontier's out-arcs claim unreached vertices,
+ * or mark them for a sweep when there are more than N/2 of these arcs) or, with MK_VIEW_REV,
+ * bottom-up (each unreached vertex scans its in-arcs and stops at the first one on the current
+ * level), chosen on the device per step by direction optimization (Beamer et al.) recast for
+ * slabs: bottom-up when 2 nf + mf > 6 nu + N/2, with nf and mf
  * the frontier's vertices and out-arcs and nu the unreached vertices.
  * Reads the graph only; state lives in the caller's workspace, so it may overlap other reads
  * (not updates) on other streams.
@@ -275,7 +276,7 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
  * insertions T += (S1 - S2 + S3/3)/2 and after deletions T -= (S1 + S2 + S3/3)/2 with
  * S1 = Count(G, G, B), S2 = Count(G, U, B), S3 = Count(U, U, B) over both directions of
  * the effective batch B, G the graph after the batch and U the graph of the batch alone;
- * a recompute counts every edge once from its lower-(degree, id) end.  Needs MK_VIEW_UND.
+ * a recompute counts every triangle once, at its end of lowest (degree, id).  Needs MK_VIEW_UND.
  *   d_count : 1 uint64 (device). */
 mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipStream_t stream);
 

@@ -1190,9 +1190,10 @@ __global__ void __launch_bounds__(1024) k_pr_fix_check(PrIter a, Counters* C, in
 }
 
 // Every iteration of a small graph in one launch of one block (at most kPrSmallN vertices, and
-// about kPrSmallTiles tiles before one block takes longer than the launches): the contributions of this and the next iteration are in LDS, the waves
-// meet at barriers, and the check decides whether to go on.  An iteration of the 4,096-vertex
-// random graph takes 10 us; as three launches, with a read-back every fourth time, 20 us.
+// about kPrSmallTiles tiles before one block takes longer than the launches): the contributions
+// of this and the next iteration are in LDS, the waves meet at barriers, and the check decides
+// whether to go on.  An iteration of the 4,096-vertex random graph takes 10 us; as three launches,
+// with a read-back every fourth time, 20 us.
 constexpr uint32_t kPrSmallN = 11800, kPrSmallTiles = 256;
 __global__ void __launch_bounds__(kPrFlatThreads) k_pr_small(PrIter a, float* x1, Counters* C, double tol,
                                                              uint32_t max_iter, uint32_t* pin) {

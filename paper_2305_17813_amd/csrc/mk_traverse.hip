@@ -162,8 +162,8 @@ __device__ inline void relax_slab_lane(const DView& F, uint64_t* D, uint32_t u, 
 constexpr uint32_t kGiantLanes = kGiantSplit * kGroup;  // lanes sharing one giant vertex
 // A light frontier of at most kInnerMost vertices is expanded by one block, which goes on with
 // the frontiers that follow, up to kInnerSteps of them, while they fit its LDS stage and hold no
-// heavy vertex: a step then costs its own chain of dependent loads (about 5 us) instead of a
-// launch and the reads that find the frontier (about 15 us).
+// heavy vertex: a step then costs its own chain of dependent loads (about 10 us) instead of a
+// launch and the reads that find the frontier as well (about 16 us).
 constexpr uint32_t kInnerMost = 512;
 constexpr uint32_t kInnerSteps = 64;
 
