@@ -1498,22 +1498,26 @@ __device__ inline bool tc_is_hub(const DView& U, uint32_t b, const uint64_t* key
 // S1, S2 and S3 of the batch identity, one group per batch arc (u, v):
 //   S1 += |N_G(u) & N_G(v)|, S2 += |N_G(u) & N_B(v)|, S3 += |N_B(u) & N_B(v)|
 // with G the graph after the batch and B the graph of the batch alone (S1 and S3 on the
-// canonical direction u < v, counted twice).  The terms k_tc_hub counts are skipped, and S1 of an
-// arc whose walked end has more than long_nb buckets is listed for k_tc_long, a block per arc:
-// walked by one group, a vertex of 2,000 neighbours took 200 us, the whole kernel's time after a
-// batch of 1,000 arcs.  A small batch leaves the chip idle, so there long_nb is 16; where the
-// batch fills it, a block per arc of few buckets only idles lanes.  k_tc_batch + k_tc_long, us:
-// scale 16, 997 arcs: 46 at 8, 43 at 16, 67 at 32 or 64 (209 without); scale 20, 100K arcs: 405
-// at 8, 435 at 16 or 32, 340 at 64 (349 without).
+// canonical direction u < v, counted twice).  The terms k_tc_hub counts are skipped, and with
+// kList S1 of an arc whose walked end has more than kTcLong buckets is listed for k_tc_long, a block
+// per arc: walked by one group, a vertex of 2,000 neighbours took 200 us, the whole kernel's time
+// after a batch of 1,000 arcs.  That pays where the batch leaves the chip idle; where it fills it, a
+// block per arc only idles lanes.  k_tc_batch + k_tc_long, us: scale 16, 997 arcs: 46 with more than
+// 8 buckets listed, 43 with 16, 67 with 32 or 64 (209 without); scale 20, 100K arcs: 405 at 8, 435
+// at 16 or 32, 340 at 64 (349 without); scale 22, 1M deleted arcs: 1,739 at 64
+// (1,400 without).
 constexpr uint64_t kTcFewKeys = 65536;
-constexpr uint32_t kTcLongFew = 16, kTcLongMany = 64;
+constexpr uint32_t kTcLong = 16;
+template <bool kList>
 __global__ void __launch_bounds__(kBlock) k_tc_batch(DView U, const uint64_t* keys, uint64_t nk,
                                                      const uint32_t* seg_lo, const uint32_t* seg_hi,
                                                      uint32_t nv, bool s2in, unsigned long long* S,
-                                                     uint32_t* longs, uint32_t* nlongs, uint32_t long_nb) {
+                                                     uint32_t* longs, uint32_t* nlongs) {
   __shared__ Stage L[1];
-  stage_open(L[0], longs, nlongs);
-  __syncthreads();
+  if (kList) {
+    stage_open(L[0], longs, nlongs);
+    __syncthreads();
+  }
   const uint64_t g0 = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kGroup;
   const uint64_t ng = (uint64_t)gridDim.x * kGroupsPerBlock;
   uint64_t s1 = 0, s2 = 0, s3 = 0;
@@ -1526,8 +1530,8 @@ __global__ void __launch_bounds__(kBlock) k_tc_batch(DView U, const uint64_t* ke
     const uint32_t a = tc_walked(U, u, v), b = a == u ? v : u;
     const bool hub = tc_is_hub(U, b, keys, seg_lo[b], seg_hi[b]);
     uint64_t c1 = 0;
-    const bool is_long = canon && !hub && U.nbk[a] > long_nb;
-    stage_push(L[0], is_long && gl == 0, (uint32_t)i);
+    const bool is_long = kList && canon && !hub && U.nbk[a] > kTcLong;
+    if (kList) stage_push(L[0], is_long && gl == 0, (uint32_t)i);
     if (canon && !hub && !is_long) c1 = 2 * group_intersect(U, a, b);  // walk the smaller side, probe the other
     // batch neighbourhoods: the segments of v and u in the sorted key list
     const uint64_t vlo = seg_lo[v], vhi = seg_hi[v];
@@ -1580,7 +1584,7 @@ __global__ void __launch_bounds__(kBlock) k_tc_batch(DView U, const uint64_t* ke
     if (s2) atomicAdd(S + 1, (unsigned long long)s2);
     if (s3) atomicAdd(S + 2, (unsigned long long)s3);
   }
-  stage_close(L);
+  if (kList) stage_close(L);
 }
 
 // S1 of the listed arcs: a block walks the smaller side, its groups striding over the buckets, and
@@ -2837,11 +2841,16 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
     // S2 of arcs into hubs goes through the hubs' sets when ids leave the tag bit free
     const bool s2in = N <= 0x7FFFFFFFu;
     uint32_t* longs = reinterpret_cast<uint32_t*>(g->tc_keys[0]);  // free after the sort
-    hipLaunchKernelGGL(k_tc_batch, dim3(grid_for_groups(std::min<uint64_t>(nk, 1u << 20))),
-                       dim3(kBlock), 0, stream, U, g->tc_keys[1], nk, g->fq[4], g->fq[5], N, s2in,
-                       g->ctr->tc_s, longs, &g->ctr->tc_work, nk < kTcFewKeys ? kTcLongFew : kTcLongMany);
-    hipLaunchKernelGGL(k_tc_long, dim3((uint32_t)std::min<uint64_t>(nk, 4096)), dim3(kBlock), 0, stream, U,
-                       g->tc_keys[1], longs, &g->ctr->tc_work, g->ctr->tc_s);
+    const dim3 groups(grid_for_groups(std::min<uint64_t>(nk, 1u << 20)));
+    if (nk < kTcFewKeys) {
+      hipLaunchKernelGGL(k_tc_batch<true>, groups, dim3(kBlock), 0, stream, U, g->tc_keys[1], nk, g->fq[4], g->fq[5],
+                         N, s2in, g->ctr->tc_s, longs, &g->ctr->tc_work);
+      hipLaunchKernelGGL(k_tc_long, dim3((uint32_t)std::min<uint64_t>(nk, 4096)), dim3(kBlock), 0, stream, U,
+                         g->tc_keys[1], longs, &g->ctr->tc_work, g->ctr->tc_s);
+    } else {
+      hipLaunchKernelGGL(k_tc_batch<false>, groups, dim3(kBlock), 0, stream, U, g->tc_keys[1], nk, g->fq[4],
+                         g->fq[5], N, s2in, g->ctr->tc_s, longs, &g->ctr->tc_work);
+    }
     // hub edges: work items numbered by an exclusive scan over the key
     // positions, in the sort's input buffer (free after the sort; 2 * nk u32 fit in it)
     uint32_t* hcnt = reinterpret_cast<uint32_t*>(g->tc_keys[0]);
