@@ -4,7 +4,7 @@
 // The experimental section runs BFS in two variants: a vanilla one with 32-bit atomics that
 // computes only distances, and the tree variant (64-bit <distance, parent> nodes) that the
 // dynamic algorithms need; its static BFS is level-based.  This file is the vanilla variant:
-// one u32 level per vertex, one level per step, and a byte per vertex for the reached set.  A step
+// one u32 level per vertex, one level per step, and a byte per vertex for marks.  A step
 // is either top-down (the frontier's out-arcs claim unreached vertices by CAS, or, when there are
 // many, mark their bytes for a sweep over the vertices) or bottom-up (every unreached vertex scans its
 // in-arcs, through the reverse view, for a vertex of the current level and stops at the
@@ -37,30 +37,30 @@ constexpr uint32_t kChunk = kGroup;       // buckets of a multi-bucket vertex pe
 constexpr uint32_t kSyncFirst = 4, kSyncMax = 16;  // steps between size read-backs: 4, 4,
                                                     // then doubling while the traversal lasts
 
-// How a step reaches vertices.  Top-down steps test a byte per vertex of the reached set: at scale
-// 22 the levels are 16 MB and 20 M reads of them brought 16 M lines into the L2s, while the bytes
-// mostly stay there.  With few arcs the unreached neighbours are claimed by CAS, which go to memory
-// at 5.7 G/s whatever else the step does.  Past N / kMarkShare arcs the step only stores bytes, and
-// a sweep over all vertices, 14 ps a vertex, collects what has a byte and no level: as much as the
-// CAS of an N / 13th of the vertices, and on a road-like network about a quarter of the arcs reach
-// something new (1,048,576 vertices, levels of up to 80,000 arcs: 1.69 ms with a share of 16, 1.23
-// with this one).  The great step of an R-MAT graph at scale 22: 456 us claiming, 365 marking and
-// sweeping.
+// How a step reaches vertices.  With few arcs the unreached neighbours are claimed by CAS, which go
+// to memory at 5.7 G/s whatever else the step does.  Past N / kMarkShare arcs the step only sets a
+// byte per neighbour, and a sweep over all vertices, 14 ps a vertex, collects what has a byte and
+// no level: as much as the CAS of an N / 13th of the vertices, and on a road-like network about a
+// quarter of the arcs reach something new (1,048,576 vertices, levels of up to 80,000 arcs: 1.69 ms
+// with a share of 16, 1.23 with this one).  The great step of an R-MAT graph at scale 22: 456 us
+// claiming, 365 marking and sweeping; 20 M reads of its 16 MB of levels brought 16 M lines into the
+// L2s, the bytes mostly stay there.  A claiming step leaves the bytes alone: testing and setting them
+// as well cost the road-like grid of 16.8 M vertices a line more per vertex (36 to 42 us a level).
 constexpr uint32_t kClaim = 0, kBottomUp = 1, kMark = 2, kMarkShare = 2;
 
 // Device counters of one call (in the caller's workspace).  Level L uses slot L mod 4.
 struct LvCnt {
   uint32_t n[4];                // frontier sizes
   uint32_t nm[4];               // multi-bucket work items of the level's top-down step
-  uint32_t mode;                // direction of the current step: 0 top-down, 1 bottom-up
+  uint32_t mode, last;          // how the current step and the one before it reach vertices
   uint32_t bu_steps;            // bottom-up steps taken
   uint32_t reached;             // vertices reached before the current frontier
-  uint32_t pad[5];
+  uint32_t pad[4];
   unsigned long long arcs[4];   // out-arcs of each frontier
 };
 static_assert(sizeof(LvCnt) <= 256, "counter block (and at most 64 pinned words of 8 bytes)");
 
-// Every vertex unreached: no level, no byte of the reached set.
+// Every vertex unreached: no level, no mark.
 __global__ void k_lv_fill(uint32_t* level, uint8_t* seen, uint32_t nv) {
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
     level[v] = kLevelInf;
@@ -98,6 +98,7 @@ __global__ void k_lv_decide(LvCnt* c, uint32_t L, uint32_t nv, int allow_bu) {
   const uint32_t mode = allow_bu && nu > 0 && 2 * nf + mf > 6 * nu + nv / 2 ? kBottomUp
                         : mf > nv / kMarkShare                               ? kMark
                                                                              : kClaim;
+  c->last = L > 0 ? c->mode : kClaim;
   c->mode = mode;
   if (nf) c->bu_steps += mode == kBottomUp;
 }
@@ -253,32 +254,31 @@ __device__ inline void for_each_item(const DView& F, uint32_t nm, const uint32_t
 // winner pushes it and counts its out-arcs).
 template <int K>
 __device__ inline uint32_t claim_round(const uint64_t (&w)[K], const bool (&live)[K], uint32_t* level,
-                                       uint8_t* seen, const uint32_t* deg, uint32_t cur, unsigned long long& arcs) {
-  uint32_t was[K], dv[K], found = 0;
-  uint8_t sv[K];
+                                       const uint32_t* deg, uint32_t cur, unsigned long long& arcs) {
+  uint32_t lv[K], dv[K], found = 0;
 #pragma unroll
-  for (int k = 0; k < K; ++k) sv[k] = seen[live[k] ? (uint32_t)w[k] : 0u];
+  for (int k = 0; k < K; ++k) lv[k] = ld_u32(level + (live[k] ? (uint32_t)w[k] : 0u));
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const uint32_t v = (uint32_t)w[k];
-    was[k] = dv[k] = 0;
-    if (live[k] && !sv[k]) {
-      was[k] = atomicCAS(level + v, kLevelInf, cur + 1);
+    const bool open = live[k] && lv[k] == kLevelInf;
+    lv[k] = dv[k] = 0;
+    if (open) {
+      lv[k] = atomicCAS(level + v, kLevelInf, cur + 1);
       dv[k] = deg[v];
-      seen[v] = 1;
     }
   }
 #pragma unroll
   for (int k = 0; k < K; ++k)
-    if (was[k] == kLevelInf) {
+    if (lv[k] == kLevelInf) {
       found |= 1u << k;
       arcs += dv[k];
     }
   return found;
 }
 
-// Top-down on a round of slabs, marking: every unreached neighbour's byte is set by plain stores,
-// and the sweep over the vertices afterwards finds them.
+// Top-down on a round of slabs, marking: every neighbour's byte is set by plain stores, if it does
+// not look set, and the sweep over the vertices afterwards finds those without a level.
 template <int K>
 __device__ inline void mark_round(const uint64_t (&w)[K], const bool (&live)[K], uint8_t* seen) {
   uint8_t sv[K];
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L,
   for_each_frontier(F, fin, n, &c->nm[s], mu_, mc_, [&](uint32_t u) {
     walk_chains<kRoundClaim>(F, u, 0u, false, [&](const auto& w, const auto& live, const auto&) {
       if (mode == kMark) mark_round(w, live, seen);
-      else push_found(out, claim_round(w, live, level, seen, F.deg, L, arcs), w);
+      else push_found(out, claim_round(w, live, level, F.deg, L, arcs), w);
     });
   });
   wave_out_close(out);
@@ -341,7 +341,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_td_multi(DView F, LvCnt* c, uint3
   for_each_item(F, nm, mu_, mc_, [&](uint32_t, uint32_t head, bool short0) {
     walk_chains<kRoundClaim>(F, head, 0u, short0, [&](const auto& w, const auto& live, const auto&) {
       if (mode == kMark) mark_round(w, live, seen);
-      else push_found(out, claim_round(w, live, level, seen, F.deg, L, arcs), w);
+      else push_found(out, claim_round(w, live, level, F.deg, L, arcs), w);
     });
   });
   wave_out_close(out);
@@ -349,10 +349,10 @@ __global__ void __launch_bounds__(kBlock) k_lv_td_multi(DView F, LvCnt* c, uint3
 }
 
 // Does some in-neighbour of v (reverse view) sit on level cur?  A lane walks v's buckets
-// and stops at the first slab that holds one.  v is unreached, so an in-neighbour of the reached
-// set is on level cur or was reached in this step: the set's bits say which levels to read.
+// and stops at the first slab that holds one.  With `bytes` every vertex on level cur has its byte
+// set, and the bytes say which levels to read.
 __device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t* level, const uint8_t* seen,
-                                     uint32_t cur) {
+                                     bool bytes, uint32_t cur) {
   Slab sl;
   load_slab(R, v, sl);
   const uint32_t nb = (uint32_t)(sl.w[15] >> 32);
@@ -364,12 +364,19 @@ __device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t*
       nd = kKeysPerSlab;
     }
     while (true) {
-      uint8_t sv[kKeysPerSlab];
-      load_of_keys<uint8_t>(seen, sl, live_words(sl, nd), (uint8_t)0, sv);
       bool hit = false;
+      if (bytes) {
+        uint8_t sv[kKeysPerSlab];
+        load_of_keys<uint8_t>(seen, sl, live_words(sl, nd), (uint8_t)0, sv);
 #pragma unroll
-      for (int j = 0; j < kKeysPerSlab; ++j)
-        if (!hit && sv[j]) hit = ld_u32(level + (uint32_t)sl.w[j]) == cur;
+        for (int j = 0; j < kKeysPerSlab; ++j)
+          if (!hit && sv[j]) hit = ld_u32(level + (uint32_t)sl.w[j]) == cur;
+      } else {
+        uint32_t lv[kKeysPerSlab];
+        load_of_keys<uint32_t>(level, sl, live_words(sl, nd), kLevelInf, lv);
+#pragma unroll
+        for (int j = 0; j < kKeysPerSlab; ++j) hit |= lv[j] == cur;
+      }
       if (hit) return true;
       const uint32_t t = (uint32_t)sl.w[15];
       if (t == kInvalid) break;
@@ -389,6 +396,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_bu(DView F, DView R, LvCnt* c, ui
   const uint32_t s = L & 3;
   const uint32_t mode = c->mode;
   if (mode == kClaim || c->n[s] == 0) return;
+  const bool bytes = c->last != kClaim;  // the frontier came from a sweep
   __shared__ WaveStage S;
   __shared__ unsigned long long acc;
   WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
@@ -400,7 +408,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_bu(DView F, DView R, LvCnt* c, ui
     const uint32_t v = base + threadIdx.x;
     bool found = false;
     if (v < nv && ld_u32(level + v) == kLevelInf &&
-        (mode == kMark ? seen[v] != 0 : R.deg[v] > 0 && has_parent_at(R, v, level, seen, L))) {
+        (mode == kMark ? seen[v] != 0 : R.deg[v] > 0 && has_parent_at(R, v, level, seen, bytes, L))) {
       level[v] = L + 1;
       seen[v] = 1;
       arcs += F.deg[v];
