@@ -2155,12 +2155,13 @@ __global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, cons
   const uint32_t ln = threadIdx.x & 63;
   // u's out-neighbours among the words of one slab: bit j for word j
   auto higher = [&](uint32_t u, uint32_t du, const Slab& sl, int nd) -> uint32_t {
+    const uint32_t live = live_words(sl, nd);
     uint32_t dv[kKeysPerSlab], keep = 0;
-    load_of_keys<uint32_t>(U.deg, sl, live_words(sl, nd), 0u, dv);  // a neighbour's degree is at least 1
+    load_of_keys<uint32_t>(U.deg, sl, live, 0u, dv);
 #pragma unroll
     for (int j = 0; j < kKeysPerSlab; ++j)
       if (dv[j] > du || (dv[j] == du && (uint32_t)sl.w[j] > u)) keep |= 1u << j;
-    return keep;
+    return keep & live;  // a word without a key passes the test when u has lost all its arcs (du == 0)
   };
   // vertices of more than kHeavyBuckets buckets first (the longest): a block each, a lane per chain
   const uint32_t nh = *nheavy;

@@ -1,6 +1,7 @@
 """The static triangle count at the edges of its vertex classes, against closed forms."""
 from math import comb
 
+import numpy as np
 import pytest
 import torch
 
@@ -41,5 +42,34 @@ def test_power_law_graph_with_long_chains(load_factor):
     p.delete(s, d)
     p.check_tc()
     p.g.stats()
+    p.check_tc()
+    p.check_tc(native.RECOMPUTE)
+
+
+# vertices whose buckets outlive their arcs: a lane's, a group's, a block's (17 buckets) and several
+# rounds of a block's chains; their lists must stay empty and leave their neighbours' lists alone
+@pytest.mark.parametrize("degree", [1, 60, 160, 190, 1000, 4000])
+@pytest.mark.parametrize("everything", [False, True])
+def test_vertices_that_lost_all_their_arcs(degree, everything):
+    """Every arc of three such vertices is deleted, once one by one and once with all others of
+    the graph; the vertices with neighbouring ids keep their triangles."""
+    say(f"case: static triangles, {degree} deleted arcs of a vertex, everything {everything}")
+    n = degree + 40
+    hubs = [4, 5, 20]
+    u, v = np.triu_indices(24, 1)  # K_24 on the first vertices, the hubs among them
+    s, d = [u], [v]
+    for h in hubs:
+        leaf = 24 + np.arange(degree)
+        s.append(np.full(degree, h))
+        d.append(leaf)
+    s, d = np.concatenate(s), np.concatenate(d)
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD | native.VIEW_UND)
+    p.check_tc(native.RECOMPUTE)
+    gone = np.isin(s, hubs) | np.isin(d, hubs) | everything
+    p.delete(np.ascontiguousarray(s[gone]), np.ascontiguousarray(d[gone]))
+    p.check_tc(native.RECOMPUTE)  # among tombstones
+    p.g.compact()
+    p.check_tc(native.RECOMPUTE)  # among empty words
+    p.insert(np.ascontiguousarray(s[gone]), np.ascontiguousarray(d[gone]), np.ones(int(gone.sum()), np.int64))
     p.check_tc()
     p.check_tc(native.RECOMPUTE)
