@@ -194,11 +194,19 @@ __device__ inline bool no_work(uint32_t nl, uint32_t nh, uint32_t ngi) {
 }
 
 // Slabs of light vertices' further buckets, collected while the block visits the primary slabs.
+// Each round of 256 vertices counts in its turn's word of n, which is zero when the round begins.
+// One word would not do: after a round that collected nothing, a wave that is ahead adds for the next
+// round while another has yet to read this round's count.  The word of the next turn is cleared
+// before this round's barrier; it was read last two rounds ago, before the barrier of the round
+// between, so no wave can still want it.
 constexpr uint32_t kExtras = 1024;
 struct Extras {
-  uint32_t n;
+  uint32_t n[3];
   uint32_t u[kExtras], s[kExtras];
 };
+__device__ inline void open_extras(Extras& E) {  // the caller then synchronizes the block
+  if (threadIdx.x < 3) E.n[threadIdx.x] = 0;
+}
 
 // Visit every slab of the frontier's vertices, a lane to a bucket chain: the primary slabs of 256
 // light vertices at a time, then those vertices' further buckets (collected in E, so that the
@@ -206,11 +214,12 @@ struct Extras {
 // kGiantLanes lanes to a giant one.  begin(u) is called before a slab of u is read, so that what
 // it loads is on its way together with the slab; body(u, begin's result, slab, data words) once
 // per slab.  There is one call site of body, as its code is long.  Every thread of the block
-// calls this; `list` replaces the light queue (inner steps), `stride` blocks share the work.
+// calls this; `list` replaces the light queue (inner steps), `stride` blocks share the work, `turn`
+// (0 before the first call) goes from one call to the next.
 template <class Begin, class Body>
 __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint32_t* list, uint32_t nl, uint32_t nh,
-                                     uint32_t ngi, uint32_t stride, bool single, Extras& E, Begin&& begin,
-                                     Body&& body) {
+                                     uint32_t ngi, uint32_t stride, bool single, Extras& E, uint32_t& turn,
+                                     Begin&& begin, Body&& body) {
   int mode = 0;  // block-uniform: 0 light vertices, 1 their further buckets, 2 heavy, 3 giant
   uint32_t base = blockIdx.x * kBlock, eb = 0, ne = 0, hb = 0;
   const uint32_t tid = threadIdx.x;
@@ -260,7 +269,7 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
         if (nb > 1) {
           nd = kKeysPerSlab - 1;
           const uint32_t xb = (uint32_t)sl.w[14];
-          const uint32_t at = atomicAdd(&E.n, nb - 1);
+          const uint32_t at = atomicAdd(&E.n[turn], nb - 1);
           for (uint32_t k = 0; k < nb - 1; ++k) {
             if (at + k < kExtras) {
               E.u[at + k] = u;
@@ -286,8 +295,11 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
     }
     if (mode == 0) {
       if (!single) {
+        const uint32_t after = turn == 2 ? 0u : turn + 1;
+        if (tid == 0) E.n[after] = 0;
         __syncthreads();
-        ne = min(E.n, kExtras);
+        ne = min(E.n[turn], kExtras);
+        turn = after;
         eb = 0;
         if (ne) mode = 1;
       }
@@ -295,9 +307,7 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
     } else if (mode == 1) {
       eb += kBlock;
       if (eb >= ne) {
-        __syncthreads();
-        if (tid == 0) E.n = 0;
-        __syncthreads();
+        __syncthreads();  // the next round writes E.u and E.s
         mode = 0;
         base += stride * kBlock;
       }
@@ -325,12 +335,12 @@ __global__ void __launch_bounds__(kBlock) k_expand(DView F, uint64_t* D, Queues 
   __shared__ Stage S[4];
   __shared__ uint32_t list[kStage];
   __shared__ Extras E;
-  if (threadIdx.x == 0) E.n = 0;
+  open_extras(E);
   open_routed(S, q.next, r);
   const uint32_t T = kUnit ? 0xFFFFFFFFu : band_limit(r);
-  uint32_t step = 0;
+  uint32_t step = 0, turn = 0;
   do {
-    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E,
+    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E, turn,
                   [&](uint32_t u) { return ld_u64(D + u) >> 32; },
                   [&](uint32_t u, uint64_t du, const Slab& sl, int nd) {
                     relax_slab_lane<kUnit>(F, D, u, du, sl, nd, S, r, T, mark, stamp + step, single);
@@ -505,13 +515,13 @@ __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queu
   __shared__ Stage S[4];
   __shared__ uint32_t list[kStage];
   __shared__ Extras E;
-  if (threadIdx.x == 0) E.n = 0;
+  open_extras(E);
   for (int k = 0; k < 3; ++k) stage_open(S[k], q.next.q[k], q.next.c[k]);
   stage_open(S[3], inval, inval_cnt);
   __syncthreads();
-  uint32_t step = 0;
+  uint32_t step = 0, turn = 0;
   do {
-    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E,
+    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E, turn,
                   [](uint32_t) { return 0; },
                   [&](uint32_t x, int, const Slab& sl, int nd) {
                     uint64_t dy[kKeysPerSlab];

@@ -67,3 +67,38 @@ def test_inserts_and_deletes_through_small_frontiers(name, views):
         di, pa = p.g.traverse_from(0, weighted, ws)
         assert np.array_equal(di.cpu().numpy().view(np.uint32), want[0])
         assert np.array_equal(pa.cpu().numpy().view(np.uint32), want[1])
+
+
+def rare_fans(width, every, fan, layers):
+    """`layers` layers of `width` vertices: each vertex has one arc into the next layer, every
+    `every`-th one `fan` more (several buckets among many single ones)."""
+    rng = np.random.default_rng(width + every + fan)
+    s, d = [np.zeros(width, np.int64)], [1 + np.arange(width)]
+    for k in range(layers - 1):
+        base = 1 + k * width
+        s.append(base + np.arange(width))
+        d.append(base + width + rng.permutation(width))
+        big = base + np.arange(0, width, every)
+        s.append(np.repeat(big, fan))
+        d.append(base + width + rng.integers(0, width, len(big) * fan))
+    s, d = np.concatenate(s), np.concatenate(d)
+    key = np.unique(s * (2 * width * layers) + d)
+    s, d = key // (2 * width * layers), key % (2 * width * layers)
+    return s, d, rng.integers(1, 30, len(s)), 1 + width * layers
+
+
+# several rounds of 256 vertices in one block, of which some collect further buckets and some do
+# not: inner frontiers of up to 1,024 vertices, and frontiers of more rounds than there are blocks
+@pytest.mark.parametrize("width,every,fan,layers", [(257, 256, 30, 5), (512, 300, 150, 5), (900, 400, 100, 4),
+                                                    (1024, 1, 20, 4), (1024, 511, 160, 4), (700_000, 5000, 120, 2)])
+def test_rounds_with_and_without_further_buckets(width, every, fan, layers):
+    say(f"case: frontier rounds, {width} wide, {fan} more arcs every {every}")
+    s, d, w, n = rare_fans(width, every, fan, layers)
+    p = Pair(n, s, d, w, views=VIEWS, sssp_delta=25)
+    p.check_all(algos=("bfs", "sssp"))
+    cut = np.nonzero(s == 0)[0]
+    for part in (cut, cut[::3], cut[:300]):
+        p.delete(s[part], d[part])
+        p.check_all(algos=("bfs", "sssp"))
+        p.insert(s[part], d[part], w[part])
+        p.check_all(algos=("bfs", "sssp"))
