@@ -554,7 +554,8 @@ struct DsCnt {
   uint32_t band;     // band number (far-pile duplicate stamps)
   uint32_t fmin;     // smallest distance on the far pile (before a split)
   uint32_t done;     // blocks of the running split that have finished
-  uint32_t pad[5];
+  uint32_t dry;      // the last step left the near frontier empty: the far pile is to be split
+  uint32_t pad[4];
 };
 static_assert(sizeof(DsCnt) <= 256, "counter block");
 
@@ -708,9 +709,13 @@ __global__ void __launch_bounds__(kBlock) k_ds_relax_multi(DView F, DsCnt* c, ui
 }
 
 // When a step leaves the near frontier empty: the smallest distance on the far pile at or past the
-// band limit (a vertex below it has joined the near frontier since) ...
+// band limit (a vertex below it has joined the near frontier since) ...  It also settles for the
+// split whether the frontier is empty: the blocks of the split fill that frontier, so one that
+// starts late would see it filled and leave out its share of the pile.
 __global__ void k_ds_far_min(DsCnt* c, uint32_t S, DsArgs a) {
-  if (c->n[(S + 1) & 3] != 0) return;
+  const bool dry = c->n[(S + 1) & 3] == 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) c->dry = dry;
+  if (!dry) return;
   const uint32_t fp = c->fpar, nf = c->nfar[fp], T = c->T;
   uint32_t m = kLevelInf;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nf; i += gridDim.x * blockDim.x) {
@@ -724,7 +729,7 @@ __global__ void k_ds_far_min(DsCnt* c, uint32_t S, DsArgs a) {
 // the others move to the other pile, stamped with the next band.  The last block to finish
 // commits the new band limit, band number and pile (no block waits for another).
 __global__ void k_ds_split(DsCnt* c, uint32_t S, DsArgs a, uint32_t* fout, uint32_t delta) {
-  if (c->n[(S + 1) & 3] != 0) return;
+  if (!c->dry) return;
   const uint32_t fp = c->fpar, nf = c->nfar[fp];
   if (nf == 0) return;
   const uint32_t T2 = (uint32_t)min<uint64_t>((uint64_t)c->fmin + delta, 0xFFFFFFFFull);

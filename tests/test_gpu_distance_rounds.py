@@ -86,3 +86,22 @@ def test_power_law(scale, ef):
     a = [np.asarray(x.cpu()).view(np.uint32) if torch.is_tensor(x) else np.asarray(x) for x in g.u32()]
     deg = np.bincount(a[0].astype(np.int64), minlength=g.n)
     compare(g.n, *a, [int(deg.argmax()), int(np.nonzero(deg == 1)[0][0])])
+
+
+# bands of a fraction of a weight on a graph of many blocks: many splits, of piles that most blocks
+# have a share in
+@pytest.mark.parametrize("scale,ef,delta", [(16, 8, 3), (17, 4, 20), (18, 8, 200)])
+def test_many_splits_of_large_piles(scale, ef, delta, orc):
+    say(f"case: far-pile splits, scale {scale}, edge factor {ef}, band {delta}")
+    g = I.rmat_graph(scale, ef, 3)
+    s, d, w = (np.asarray(x.cpu()).view(np.uint32) for x in g.u32())
+    O = orc.OracleGraph(g.n, s, d, w)
+    G = native.Graph(g.n, *g.u32(), views=native.VIEW_FWD | native.VIEW_REV, sssp_delta=delta)
+    for u in (int(np.bincount(s).argmax()), int(s[len(s) // 2])):
+        want, parent = O.sssp(u)
+        ws = torch.empty(native.load().mk_sssp_distances_workspace_bytes(G.h), dtype=torch.uint8, device="cuda")
+        for _ in range(3):
+            assert np.array_equal(G.sssp_distances(u, ws=ws).cpu().numpy().view(np.uint32), want)
+        di, pa = G.sssp(u, mode=native.RECOMPUTE)
+        assert np.array_equal(di.cpu().numpy().view(np.uint32), want)
+        assert np.array_equal(pa.cpu().numpy().view(np.uint32), parent)
