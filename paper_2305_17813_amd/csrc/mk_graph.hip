@@ -1246,7 +1246,16 @@ void launch_insert(mk_graph* g, const uint32_t* s, const uint32_t* d, const uint
 // 1M 783 / 1583, 2M 1479 / 1772.  (An atomic per cut chain and words packed by scattered 8-byte
 // stores took 1179 and 2503 us by a sweep at scale 22 with 100K and 1M ops.)
 constexpr uint64_t kCompactLogRatio = 8;
-constexpr uint64_t kBuildChunk = 1ull << 24;  // initial arcs per launch
+// Creation fills one table after the other (k_build_all) while a chain mostly fits its head slab.
+// Where chains are longer (load factors above 1, hashing off), lanes race to extend them: each that
+// loses holds the slab it took until the launch is over, and the more arcs a launch has for one
+// table, the more slabs wait and the longer the races take.  So batches of the change log's size
+// then go to all tables at once.  All views, tables / batches, ms: scale 18, edge factor 4: load
+// factor 0.7: 0.86 / 1.18, 1: 1.32 / 1.35, 1.25: 1.72 / 1.54, 2: 2.35 / 1.78, 64: 5.5 / 3.9; edge
+// factor 16: 0.7: 2.0 / 3.1, 1: 3.2 / 3.5, 1.25: 3.9 / 4.0, 64: 19.0 / 11.2; 20,000 vertices of
+// degree 150: 1: 2.78 / 2.82, 1.25: 3.4 / 3.2.
+constexpr float kBuildLoad = 1.f;
+constexpr uint64_t kBuildChunk = 1ull << 24;  // initial arcs per launch of k_build_all
 // Blocks of a sweep: each then packs many chains between two hand-outs of its cut tails.
 constexpr uint32_t kSweepBlocks = 4096;
 
@@ -1380,27 +1389,58 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
     vh.n_head = (uint64_t)N + g->h_pin[v];
     if (vh.n_head > vh.head_reserved) return fail(MK_ERR_CAPACITY);
     vh.d.pool_base = (uint32_t)vh.n_head;
-    hipLaunchKernelGGL(k_init_primary, dim3(nb_blocks), dim3(kBlock), 0, stream, vh.d.slab, vh.nbk,
-                       g->fq[1 + v], N);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, vh.d.pool_ctr, 64, 0u);
   }
+  const auto empty_tables = [&] {  // every slab holds EMPTY words already
+    for (int v = 0; v < 3; ++v) {
+      const ViewHost& vh = g->view[v];
+      if (!vh.on) continue;
+      hipLaunchKernelGGL(k_init_primary, dim3(nb_blocks), dim3(kBlock), 0, stream, vh.d.slab, vh.nbk,
+                         g->fq[1 + v], N);
+      hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, vh.d.pool_ctr, 64, 0u);
+    }
+  };
+  empty_tables();
   hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->mark, N, 0u);
   hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->far_mark, N, 0u);
   hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->wcc_flag, N, 0u);
   // update marks start at the chain heads (encoded 0)
   hipLaunchKernelGGL(k_fill_u32, dim3(grid_stride_blocks(2 * g->view[VF].n_head)), dim3(kBlock), 0,
                      stream, (uint32_t*)g->upd_mark, 2 * g->view[VF].n_head, 0u);
-  // bulk insert, in chunks whose lanes a grid can count
-  for (uint64_t off = 0; off < m; off += kBuildChunk) {
-    const uint64_t k = std::min<uint64_t>(kBuildChunk, m - off);
-    hipLaunchKernelGGL(k_build_all, dim3(grid_for_lanes(k), 4), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR),
-                       dv(g, VU), g->cfg.views, d_src + off, d_dst + off, d_w ? d_w + off : nullptr, k, N,
-                       &g->ctr->overflow);
-    hipLaunchKernelGGL(k_spare_merge, dim3(3), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR), dv(g, VU),
-                       g->cfg.views);
-  }
+  // bulk insert by tables, in chunks whose lanes a grid can count
+  const auto build_by_tables = [&] {
+    for (uint64_t off = 0; off < m; off += kBuildChunk) {
+      const uint64_t k = std::min<uint64_t>(kBuildChunk, m - off);
+      hipLaunchKernelGGL(k_build_all, dim3(grid_for_lanes(k), 4), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR),
+                         dv(g, VU), g->cfg.views, d_src + off, d_dst + off, d_w ? d_w + off : nullptr, k, N,
+                         &g->ctr->overflow);
+      hipLaunchKernelGGL(k_spare_merge, dim3(3), dim3(kBlock), 0, stream, dv(g, VF), dv(g, VR), dv(g, VU),
+                         g->cfg.views);
+    }
+  };
+  // or by batches that fit the change log (used here as scratch)
+  const auto build_by_batches = [&] {
+    for (int v = 0; v < 3; ++v)
+      if (g->view[v].on)
+        hipLaunchKernelGGL(k_fill_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->view[v].d.deg, N, 0u);
+    for (uint64_t off = 0; off < m; off += g->log_cap) {
+      const uint64_t k = std::min<uint64_t>(g->log_cap, m - off);
+      launch_insert(g, d_src + off, d_dst + off, d_w ? d_w + off : nullptr, k, nullptr, g->log, stream);
+    }
+  };
+  const bool by_tables = cfg->load_factor > 0.f && cfg->load_factor <= kBuildLoad;
+  if (by_tables) build_by_tables();
+  else build_by_batches();
   if (hipGetLastError() != hipSuccess) return fail(MK_ERR_HIP);
   if (refresh_pool(g, stream) != MK_OK) return fail(MK_ERR_HIP);
+  if (by_tables && g->overflowed.load()) {  // the spares of a whole chunk left too few slabs: again, by batches
+    g->overflowed = 0;
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, &g->ctr->overflow, 1, 0u);
+    hipLaunchKernelGGL(k_fill_slabs, dim3(grid_stride_blocks(most * kGroup)), dim3(kBlock), 0, stream, slabs);
+    empty_tables();
+    build_by_batches();
+    if (hipGetLastError() != hipSuccess) return fail(MK_ERR_HIP);
+    if (refresh_pool(g, stream) != MK_OK) return fail(MK_ERR_HIP);
+  }
   // the initial arcs did not fit the pool (only an explicit, too small pool_slabs can do this)
   if (g->overflowed.load()) return fail(MK_ERR_OUT_OF_SLABS);
   *out = g;

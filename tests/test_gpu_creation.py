@@ -1,0 +1,75 @@
+"""Creation where chains are long: large load factors, hashing off, and slab pools with little room
+beyond the slabs that the initial arcs fill."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_17813_amd import inputs as I
+from paper_2305_17813_amd import native
+from parity import Pair, say, u32
+
+pytestmark = pytest.mark.gpu
+
+
+def dense(n, m, seed):
+    """About m arcs between n vertices, in random order."""
+    rng = np.random.default_rng(seed)
+    s = rng.integers(0, n, m)
+    d = (s + 1 + rng.integers(0, n - 1, m)) % n
+    key = rng.permutation(np.unique(s * n + d))
+    return key // n, key % n, rng.integers(1, 100, len(key))
+
+
+# the default pool: a slab per 15 arcs and half a slab per arc on top, while lanes racing to extend
+# one chain each hold a slab until their launch is over
+@pytest.mark.parametrize("m,load_factor,log_capacity", [(1_000_000, 8.0, 0), (1_000_000, 64.0, 1 << 12)])
+def test_long_chains_build_within_the_default_pool(m, load_factor, log_capacity):
+    say(f"case: creation, {m} arcs of 2,000 vertices, load factor {load_factor}")
+    s, d, w = dense(2000, m, 7)
+    p = Pair(2000, s, d, w, views=native.VIEW_FWD | native.VIEW_REV, load_factor=load_factor,
+             log_capacity=log_capacity)
+    p.check_structure()
+
+
+@pytest.mark.parametrize("views", [1, 3, 7])
+@pytest.mark.parametrize("load_factor", [0.0, 0.7, 1.0, 1.25, 8.0])
+def test_pool_with_room_for_one_chunk_of_racing_lanes(views, load_factor):
+    """A pool of the slabs that the chains need and two per arc of one log's worth is enough."""
+    say(f"case: creation with a small pool, views {views}, load factor {load_factor}")
+    s, d, w = dense(600, 100_000, 3)
+    log = 256
+    roomy = native.Graph(600, s, d, w, views=views, load_factor=load_factor, pool_slabs=1 << 20)
+    need = max(roomy.stats()["pool_used"])
+    roomy.close()
+    p = Pair(600, s, d, w, views=views, load_factor=load_factor, pool_slabs=need + 2 * log, log_capacity=log)
+    assert max(p.g.stats()["pool_used"]) == need
+    p.check_structure()
+    p.delete(s[:200], d[:200])
+    p.g.compact()
+    p.insert(s[:100], d[:100], w[:100])
+    p.check_structure()
+
+
+@pytest.mark.parametrize("load_factor", [0.0, 0.7, 8.0])
+def test_pool_without_room_is_refused(load_factor):
+    say(f"case: creation without room, load factor {load_factor}")
+    s, d, w = dense(600, 100_000, 3)
+    roomy = native.Graph(600, s, d, w, load_factor=load_factor, pool_slabs=1 << 20)
+    need = max(roomy.stats()["pool_used"])
+    roomy.close()
+    with pytest.raises(native.MkError) as e:
+        native.Graph(600, s, d, w, load_factor=load_factor, pool_slabs=need - 1)
+    assert e.value.status == 2  # MK_ERR_OUT_OF_SLABS
+
+
+# repeated and invalid arcs on either way of building
+@pytest.mark.parametrize("load_factor", [0.0, 0.7, 2.0])
+def test_repeated_and_invalid_arcs(load_factor):
+    say(f"case: creation with repeated arcs, load factor {load_factor}")
+    g = I.rmat_s(10)
+    s, d, w = (np.concatenate([u32(x)] * 3) for x in (g.src, g.dst, g.w))
+    s[5], d[9], s[11] = g.n + 3, 0xFFFFFFFE, d[11]
+    p = Pair(g.n, torch.as_tensor(s.astype(np.int64)), torch.as_tensor(d.astype(np.int64)),
+             torch.as_tensor(w.astype(np.int64)), load_factor=load_factor)
+    p.check_structure()
+    p.check_all(algos=("wcc", "tc"))
