@@ -1344,8 +1344,9 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
     slabs.slabs[v] = vh.head_reserved + vh.pool_cap;
     most = std::max(most, slabs.slabs[v]);
   }
-  if (m)
-    hipLaunchKernelGGL(k_count_deg, dim3(2 * grid_stride_blocks(m)), dim3(kBlock), 0, stream, d_src,
+  if (m)  // as many blocks as either half needs: a graph to be filled later has few arcs and many slabs
+    hipLaunchKernelGGL(k_count_deg, dim3(2 * std::max(grid_stride_blocks(m), grid_stride_blocks(most * kGroup))),
+                       dim3(kBlock), 0, stream, d_src,
                        d_dst, m, N, g->view[VF].d.deg, g->view[VR].on ? g->view[VR].d.deg : nullptr,
                        g->view[VU].on && !add ? g->view[VU].d.deg : nullptr, slabs);
   else
