@@ -2561,6 +2561,8 @@ mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t ma
     hipLaunchKernelGGL(k_copy_f32, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, x[0], N);
     a.x = x[0];
     hipLaunchKernelGGL(k_pr_small, dim3(1), dim3(kPrFlatThreads), 0, stream, a, x[1], g->ctr, tol_l1, max_iter, pin);
+    MK_LAUNCH(g, "pagerank of a small graph");
+    MK_HIP(g, hipStreamSynchronize(stream));  // converged when the call returns, whatever the size
   } else {
     const uint32_t cb = blocks_for(N, kPrContribBlocks);
     hipLaunchKernelGGL(k_pr_load, dim3(cb), dim3(kBlock), 0, stream, g->pr_x, g->pr_perm, od, N, x[0], c[0], g->pr_part);
@@ -2728,6 +2730,8 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
     MK_LAUNCH(g, "pagerank copy");
     return MK_OK;
   }
+  // every scheme waits for its iterations to converge, which a capturing stream cannot
+  if (stream_capturing(stream)) return hip_fail(g, hipErrorStreamCaptureUnsupported, "mk_incr_pagerank");
   if (!warm)
     hipLaunchKernelGGL(k_pr_fill, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, N, 1.f / N);
   if (g->iter_scheme == MK_ITER_SCHEME2) return pagerank_scheme2(g, damping, tol_l1, max_iter, d_rank, d_iters, stream);

@@ -41,6 +41,13 @@ void mark_seen(mk_graph* g, AlgoState& st) { st.seen_seq = g->next_seq - 1; }
 
 }  // namespace mk
 
+namespace mk {
+bool stream_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+}  // namespace mk
+
 namespace {
 void poll_snapshots(mk_graph* g);
 }
@@ -1117,11 +1124,6 @@ mk_status refresh_pool(mk_graph* g, hipStream_t stream, const void* extra = null
   // every snapshot still in flight is older than these figures
   for (auto& sn : g->snap) sn.pending = false;
   return MK_OK;
-}
-
-bool stream_capturing(hipStream_t stream) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
 }
 
 // A captured update may be replayed, with other arcs and over log entries that later batches took

@@ -230,6 +230,8 @@ void mlp_forward_launch(const float* params, const float* x, uint32_t n, float* 
 // faster than applying the pending batches `p` incrementally (synchronizes).
 mk_status auto_prefers_recompute(mk_graph* g, int algo, const Pending& p, hipStream_t stream, bool* out);
 
+bool stream_capturing(hipStream_t stream);
+
 // Write `words` u32 device words to pinned host memory from a kernel (at most 64): what a loop on
 // the host reads after it synchronizes.  A copy of a few bytes costs the host and the stream
 // about three times as much.

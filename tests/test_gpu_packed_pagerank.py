@@ -1,8 +1,11 @@
 """Packed PageRank iterations where their tiles can go wrong: segments that end on, begin on and
 run over many tile borders (512 list entries and segment ends to a tile), no arcs at all, more
 vertices than the contributions kept in LDS, and sources or targets without arcs."""
+import time
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2305_17813_amd import native
 from parity import Pair, say
@@ -61,3 +64,49 @@ def test_tiles(name, load_factor):
         p.delete(np.array([n - 1, n - 2]), np.array([n - 3, 0]))
         p.check_pr()
         p.check_pr(native.RECOMPUTE)
+
+
+# small graphs iterate in one launch, larger ones in a loop of launches
+@pytest.mark.parametrize("n", [600, 40_000])
+@pytest.mark.parametrize("scheme", [native.ITER_SCHEME1, native.ITER_SCHEME2, native.ITER_PACKED])
+def test_refused_under_capture(n, scheme):
+    """The call waits for convergence, on graphs of any size, so a stream capture is refused, and
+    what it did not compute is not taken for a result."""
+    say(f"case: PageRank under capture, {n} vertices, scheme {scheme}")
+    s, d, n = ring(n)
+    p = Pair(n, s, d, np.ones(n, np.int64), views=native.VIEW_FWD | native.VIEW_REV)
+    p.g.set_iteration_scheme(scheme)
+    p.check_pr()
+    p.insert(np.array([5, 6]), np.array([300, 300]), np.ones(2, np.int64))
+    one = torch.ones(8, device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        one.add_(1)
+        with pytest.raises(native.MkError) as e:
+            p.g.pagerank(stream=stream)
+    assert e.value.status == 5  # MK_ERR_HIP
+    graph.replay()
+    torch.cuda.synchronize()
+    assert float(one.sum()) == 16
+    p.check_pr()
+
+
+def test_returns_with_the_ranks_computed():
+    say("case: PageRank of a small graph, its stream is idle afterwards")
+    s, d, n = ring(8000)
+    s, d = np.append(s, 0), np.append(d, 4000)  # converges slowly
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD | native.VIEW_REV)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    left = []
+    for _ in range(5):
+        _, it = p.g.pagerank(damping=0.99, mode=native.RECOMPUTE, tol=0.0, stream=stream)
+        t = time.perf_counter()
+        stream.synchronize()
+        left.append(time.perf_counter() - t)
+        assert int(it.item()) > 300
+    # only the copy of the ranks may be left; the iterations take milliseconds
+    assert min(left) < 2e-4, left
