@@ -2555,8 +2555,17 @@ mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t ma
   a.state = g->ctr->pr_state;
   a.nv = N;
   a.damping = damping;
-  // the host does not know the in-arcs; their head slabs' words bound them well enough to choose
-  const uint64_t tiles = (g->view[VR].n_head * kKeysPerSlab + N) / kPrTile;
+  // The host does not know the in-arcs.  The words of all slabs in use bound them, but the pool's share
+  // is itself a bound (a slab per inserted arc, until the next exact figures), so a graph of few
+  // vertices that it would send to the launches below has its list's length read back: a graph
+  // created empty and filled by inserts has nearly all its words in the pool.
+  uint64_t tiles = ((g->view[VR].n_head + g->view[VR].pool_used_est) * kKeysPerSlab + N) / kPrTile + 1;
+  if (N <= kPrSmallN && tiles > kPrSmallTiles) {
+    read_back(g->pr_off + N, pin, 1, stream);
+    MK_LAUNCH(g, "pagerank tiles");
+    MK_HIP(g, hipStreamSynchronize(stream));
+    tiles = ((uint64_t)*(volatile uint32_t*)pin + N + kPrTile - 1) / kPrTile;
+  }
   if (N <= kPrSmallN && tiles <= kPrSmallTiles) {
     hipLaunchKernelGGL(k_copy_f32, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, x[0], N);
     a.x = x[0];

@@ -110,3 +110,34 @@ def test_returns_with_the_ranks_computed():
         assert int(it.item()) > 300
     # only the copy of the ranks may be left; the iterations take milliseconds
     assert min(left) < 2e-4, left
+
+
+# created empty, so that nearly every in-arc lies in a chained slab, then filled by inserts: few tiles
+# (one launch), just above and far above the 256 tiles that one block iterates over
+@pytest.mark.parametrize("n,m", [(500, 3000), (5000, 100_000), (5000, 140_000), (8000, 2_000_000)])
+def test_graph_filled_by_inserts(n, m):
+    say(f"case: packed PageRank, {n} vertices filled with {m} arcs")
+    rng = np.random.default_rng(m)
+    key = np.unique(rng.integers(0, n * n, m))
+    s, d = key // n, key % n
+    s, d = s[s != d], d[s != d]
+    none = np.zeros(0, np.int64)
+    p = Pair(n, none, none, none, views=native.VIEW_FWD | native.VIEW_REV, pool_slabs=2 * m, log_capacity=m)
+    p.check_pr()
+    p.insert(s, d, np.ones(len(s), np.int64))
+    p.check_pr()
+    p.check_pr(native.RECOMPUTE)
+    if m < 1_000_000:
+        return
+    # the same arcs known at creation: an iteration must not cost several times as much here
+    us = []
+    for g in (p.g, native.Graph(n, s, d, views=native.VIEW_FWD | native.VIEW_REV)):
+        best = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g.pagerank(mode=native.RECOMPUTE)
+            torch.cuda.synchronize()
+            best.append(time.perf_counter() - t)
+        us.append(min(best))
+    assert us[0] <= 3 * us[1], us
