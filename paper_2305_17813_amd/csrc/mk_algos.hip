@@ -1190,11 +1190,13 @@ __global__ void __launch_bounds__(1024) k_pr_fix_check(PrIter a, Counters* C, in
 }
 
 // Every iteration of a small graph in one launch of one block (at most kPrSmallN vertices, and
-// about kPrSmallTiles tiles before one block takes longer than the launches): the contributions
+// kPrSmallTiles tiles before one block takes longer than the launches): the contributions
 // of this and the next iteration are in LDS, the waves meet at barriers, and the check decides
 // whether to go on.  An iteration of the 4,096-vertex random graph takes 10 us; as three launches,
-// with a read-back every fourth time, 20 us.
-constexpr uint32_t kPrSmallN = 11800, kPrSmallTiles = 256;
+// with a read-back every fourth time, 20 us.  A call, one launch / launches, us: 2,000 vertices at 35
+// tiles 172 / 344, at 121 210 / 257, at 160 234 / 208, at 238 296 / 208; 8,000 at 78 396 / 466, at 140
+// 342 / 339; R-MAT of 4,096 at 112 273 / 277, of 8,192 at 130 371 / 355.
+constexpr uint32_t kPrSmallN = 11800, kPrSmallTiles = 128;
 __global__ void __launch_bounds__(kPrFlatThreads) k_pr_small(PrIter a, float* x1, Counters* C, double tol,
                                                              uint32_t max_iter, uint32_t* pin) {
   constexpr uint32_t kWaves = kPrFlatThreads / 64;
@@ -2555,11 +2557,14 @@ mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t ma
   a.state = g->ctr->pr_state;
   a.nv = N;
   a.damping = damping;
-  // The host does not know the in-arcs.  The words of all slabs in use bound them, but the pool's share
-  // is itself a bound (a slab per inserted arc, until the next exact figures), so a graph of few
-  // vertices that it would send to the launches below has its list's length read back: a graph
-  // created empty and filled by inserts has nearly all its words in the pool.
-  uint64_t tiles = ((g->view[VR].n_head + g->view[VR].pool_used_est) * kKeysPerSlab + N) / kPrTile + 1;
+  // The host does not know the in-arcs.  The arcs ever passed in bound them, and so do the words of all
+  // slabs in use, with the chained ones: a graph created empty and filled by inserts has nearly all
+  // its words there.  Both drift upwards over a stream of batches (the pool's figure counts a slab
+  // per inserted arc until it is read back), so a graph of few vertices that they would send
+  // to the launches below has its list's length read back first.
+  const ViewHost& rv = g->view[VR];
+  uint64_t tiles =
+      (std::min((rv.n_head + rv.pool_used_est) * kKeysPerSlab, g->m0 + rv.added) + N) / kPrTile + 1;
   if (N <= kPrSmallN && tiles > kPrSmallTiles) {
     read_back(g->pr_off + N, pin, 1, stream);
     MK_LAUNCH(g, "pagerank tiles");

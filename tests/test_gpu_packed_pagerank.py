@@ -113,8 +113,8 @@ def test_returns_with_the_ranks_computed():
 
 
 # created empty, so that nearly every in-arc lies in a chained slab, then filled by inserts: few tiles
-# (one launch), just above and far above the 256 tiles that one block iterates over
-@pytest.mark.parametrize("n,m", [(500, 3000), (5000, 100_000), (5000, 140_000), (8000, 2_000_000)])
+# (one launch), just below, just above and far above the 128 tiles that one block iterates over
+@pytest.mark.parametrize("n,m", [(500, 3000), (5000, 60_000), (5000, 63_000), (8000, 2_000_000)])
 def test_graph_filled_by_inserts(n, m):
     say(f"case: packed PageRank, {n} vertices filled with {m} arcs")
     rng = np.random.default_rng(m)
@@ -122,11 +122,15 @@ def test_graph_filled_by_inserts(n, m):
     s, d = key // n, key % n
     s, d = s[s != d], d[s != d]
     none = np.zeros(0, np.int64)
-    p = Pair(n, none, none, none, views=native.VIEW_FWD | native.VIEW_REV, pool_slabs=2 * m, log_capacity=m)
+    p = Pair(n, none, none, none, views=native.VIEW_FWD | native.VIEW_REV, pool_slabs=4 * m, log_capacity=m)
     p.check_pr()
     p.insert(s, d, np.ones(len(s), np.int64))
     p.check_pr()
     p.check_pr(native.RECOMPUTE)
+    for _ in range(4):  # arcs taken out and put back: the host's bounds drift, the list does not
+        p.delete(s[: m // 2], d[: m // 2])
+        p.insert(s[: m // 2], d[: m // 2], np.ones(len(s[: m // 2]), np.int64))
+    p.check_pr()
     if m < 1_000_000:
         return
     # the same arcs known at creation: an iteration must not cost several times as much here
