@@ -111,11 +111,12 @@ __device__ inline void stage_words(Stage& S, uint32_t mask, const Slab& sl) {
 // the distance read, without waiting for the minimum to return: if another lane's candidate was
 // smaller still, that lane's improvement needs the push as well.  (A vertex whose candidate is far
 // may then wait on the pile in vain; the band step drops it.)  `single`: no vertex of the graph
-// has several buckets, so no bucket count is read.
+// has several buckets, so no bucket count is read.  *more counts the further buckets of the light
+// vertices pushed (inner steps).
 template <bool kUnit>
 __device__ inline void relax_slab_lane(const DView& F, uint64_t* D, uint32_t u, uint64_t du, const Slab& sl,
                                        int nd, Stage (&S)[4], const Route& r, uint32_t T, uint32_t* mark,
-                                       uint32_t stamp, bool single) {
+                                       uint32_t stamp, bool single, uint32_t* more) {
   uint64_t cand[kKeysPerSlab], cur[kKeysPerSlab];
   load_of_keys<uint64_t>(D, sl, live_words(sl, nd), 0ull, cur);
 #pragma unroll
@@ -141,18 +142,22 @@ __device__ inline void relax_slab_lane(const DView& F, uint64_t* D, uint32_t u, 
     }
     if ((near | far) >> j & 1) (void)amin64(D + v, cand[j]);
   }
-  uint32_t tn = 0, tf = 0, heavy = 0, giant = 0;
+  uint32_t tn = 0, tf = 0, heavy = 0, giant = 0, further = 0;
 #pragma unroll
   for (int j = 0; j < kKeysPerSlab; ++j) {
     if ((near >> j & 1) && tk[j] != stamp) {
       if (nb[j] > kGiantBuckets) giant |= 1u << j;
       else if (nb[j] > kHeavyBuckets) heavy |= 1u << j;
-      else tn |= 1u << j;
+      else {
+        tn |= 1u << j;
+        further += nb[j] - 1;
+      }
     }
     if ((far >> j & 1) && tk[j] != r.band) tf |= 1u << j;
   }
   stage_words(S[0], tn, sl);
   if (!single) {
+    if (further) atomicAdd(more, further);
     stage_words(S[1], heavy, sl);
     stage_words(S[2], giant, sl);
   }
@@ -163,34 +168,76 @@ constexpr uint32_t kGiantLanes = kGiantSplit * kGroup;  // lanes sharing one gia
 // A light frontier of at most kInnerMost vertices is expanded by one block, which goes on with
 // the frontiers that follow, up to kInnerSteps of them, while they fit its LDS stage and hold no
 // heavy vertex: a step then costs its own chain of dependent loads (about 10 us) instead of a
-// launch and the reads that find the frontier as well (about 16 us).
-constexpr uint32_t kInnerMost = 512;
+// launch and the reads that find the frontier as well (about 16 us).  Where vertices have several
+// buckets, at most kInnerBuckets buckets, a round of the block: 512 vertices of 15 buckets are 30
+// rounds, and took 100 us where the whole chip takes 20.
+constexpr uint32_t kInnerMost = 512, kInnerBuckets = 256;
 constexpr uint32_t kInnerSteps = 64;
 
 // After a step of an inner loop: the frontier staged in S[0] becomes the block's list in LDS, or
 // the loop ends (empty, too large, heavy vertices, or out of steps) and the stages hold the
 // launch's output.  Every thread of the block gets the same answer.
-__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t& n, uint32_t& step) {
+__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t* more, bool single, uint32_t& n, uint32_t& step) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this step's atomics have been performed
   __syncthreads();
   // and the next step reads what they left, not a cache line from before them (a stale distance
   // of a vertex improved a step ago would push it again)
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   const uint32_t k = S[0].n;
-  const bool go = k > 0 && k <= kStage && S[1].n == 0 && S[2].n == 0 && step + 1 < kInnerSteps;
+  const bool go = k > 0 && k + *more <= (single ? kStage : kInnerBuckets) && S[1].n == 0 && S[2].n == 0 && step + 1 < kInnerSteps;
   if (!go) return false;
   for (uint32_t i = threadIdx.x; i < k; i += kBlock) list[i] = S[0].buf[i];
   __syncthreads();
-  if (threadIdx.x == 0) S[0].n = 0;
+  if (threadIdx.x == 0) S[0].n = *more = 0;
   __syncthreads();
   n = k;
   ++step;
   return true;
 }
 
+// How a launch's blocks share the light vertices.  Where no vertex has several buckets: a lane each.
+// Else 16 lanes each, a lane to a bucket, when there are lanes enough (kWideMost vertices) or the
+// vertices have many buckets (kManyBuckets on average).  Else a lane each again, with kShareBlocks
+// blocks to spread them over, whose other lanes take the further buckets.  One-off traversals, us, BFS
+// and SSSP, with 256 vertices to a block always / with 32 to 256 / so: 20,000 vertices of degree 150
+// 560, 2,113 / 235, 747 / 243, 714; 4,096 of degree 16 175, 596 / 139, 480 / 125, 386; 100,000 of degree
+// 30 419, 1,436 / 218, 884 / 201, 796; R-MAT scale 16 336, 922 / 206, 594 / 198, 535, scale 18 414, 983 /
+// 276, 726 / 264, 704.  With 16 lanes each whatever the number, R-MAT scale 20 takes 752, 1,684 instead
+// of 657, 1,463.
+struct Share {
+  uint32_t n;  // light vertices to a block and round
+  bool wide;   // 16 lanes each
+};
+constexpr uint32_t kWideMost = 16384, kShareBlocks = 512, kManyBuckets = 4;
+__device__ inline Share light_share(uint32_t nl, bool single, bool many) {
+  if (single) return Share{kBlock, false};
+  if (many || nl <= kWideMost) return Share{kGroupsPerBlock, true};
+  return Share{min((uint32_t)kBlock, (nl + kShareBlocks - 1) / kShareBlocks), false};
+}
+
 // Whether a block of a frontier kernel has nothing to do (the same in all its threads).
-__device__ inline bool no_work(uint32_t nl, uint32_t nh, uint32_t ngi) {
-  return (uint64_t)blockIdx.x * kBlock >= nl && blockIdx.x >= nh && blockIdx.x >= ngi * (kGiantLanes / kBlock);
+__device__ inline bool no_work(uint32_t nl, uint32_t nh, uint32_t ngi, uint32_t share) {
+  return (uint64_t)blockIdx.x * share >= nl && blockIdx.x >= nh && blockIdx.x >= ngi * (kGiantLanes / kBlock);
+}
+
+// Whether one block takes this frontier (and those that follow): every block with work finds the
+// same answer.  *more is zero before the call and after it, when the block has synchronized.
+__device__ inline bool inner_first(const DView& F, const uint32_t* light, uint32_t nl, uint32_t nh, uint32_t ngi,
+                                   bool single, uint32_t* more) {
+  if (nl > kInnerMost || nh || ngi) return false;
+  if (single) return true;
+  if (nl > kInnerBuckets) return false;
+  if (nl * kHeavyBuckets <= kInnerBuckets) return true;
+  uint32_t b = 0;
+  for (uint32_t i = threadIdx.x; i < nl; i += kBlock) b += F.nbk[light[i]];
+  for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o);
+  if (threadIdx.x == 0) *more = 0;
+  __syncthreads();
+  if (lane64() == 0) atomicAdd(more, b);
+  __syncthreads();
+  const uint32_t total = *more;
+  __syncthreads();
+  return total <= kInnerBuckets;
 }
 
 // Slabs of light vertices' further buckets, collected while the block visits the primary slabs.
@@ -208,7 +255,7 @@ __device__ inline void open_extras(Extras& E) {  // the caller then synchronizes
   if (threadIdx.x < 3) E.n[threadIdx.x] = 0;
 }
 
-// Visit every slab of the frontier's vertices, a lane to a bucket chain: the primary slabs of 256
+// Visit every slab of the frontier's vertices, a lane to a bucket chain: the primary slabs of `share`
 // light vertices at a time, then those vertices' further buckets (collected in E, so that the
 // lanes share them evenly; a lane walks its own where E is full), a block to a heavy vertex,
 // kGiantLanes lanes to a giant one.  begin(u) is called before a slab of u is read, so that what
@@ -218,10 +265,12 @@ __device__ inline void open_extras(Extras& E) {  // the caller then synchronizes
 // (0 before the first call) goes from one call to the next.
 template <class Begin, class Body>
 __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint32_t* list, uint32_t nl, uint32_t nh,
-                                     uint32_t ngi, uint32_t stride, bool single, Extras& E, uint32_t& turn,
+                                     uint32_t ngi, uint32_t stride, const Share& share, bool single, Extras& E,
+                                     uint32_t& turn,
                                      Begin&& begin, Body&& body) {
   int mode = 0;  // block-uniform: 0 light vertices, 1 their further buckets, 2 heavy, 3 giant
-  uint32_t base = blockIdx.x * kBlock, eb = 0, ne = 0, hb = 0;
+  const bool wide = share.wide;
+  uint32_t base = blockIdx.x * share.n, eb = 0, ne = 0, hb = 0;
   const uint32_t tid = threadIdx.x;
   while (true) {
     uint32_t u = 0, s = kInvalid, own = 0, own_end = 0;  // own: further buckets this lane walks itself
@@ -232,7 +281,17 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
         base = blockIdx.x;
         continue;
       }
-      if (base + tid < nl) u = s = list[base + tid];
+      if (wide) {
+        const uint32_t i = base + tid / kGroup, b = tid % kGroup;
+        if (i < nl) {
+          u = list[i];
+          const uint4 w = reinterpret_cast<const uint4*>(slab_ptr(F, u))[7];
+          if (b < w.w) s = b ? w.x + b - 1 : u;
+          if (b == 0 && w.w > 1) nd = kKeysPerSlab - 1;
+        }
+      } else if (tid < share.n && base + tid < nl) {
+        u = s = list[base + tid];
+      }
     } else if (mode == 1) {
       if (eb + tid < ne) {
         u = E.u[eb + tid];
@@ -264,7 +323,7 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
       const auto ctx = begin(u);
       Slab sl;
       load_slab(F, s, sl);
-      if (mode == 0) {
+      if (mode == 0 && !wide) {
         const uint32_t nb = (uint32_t)(sl.w[15] >> 32);
         if (nb > 1) {
           nd = kKeysPerSlab - 1;
@@ -294,7 +353,7 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
       }
     }
     if (mode == 0) {
-      if (!single) {
+      if (!single && !wide) {
         const uint32_t after = turn == 2 ? 0u : turn + 1;
         if (tid == 0) E.n[after] = 0;
         __syncthreads();
@@ -303,13 +362,13 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
         eb = 0;
         if (ne) mode = 1;
       }
-      if (mode == 0) base += stride * kBlock;
+      if (mode == 0) base += stride * share.n;
     } else if (mode == 1) {
       eb += kBlock;
       if (eb >= ne) {
         __syncthreads();  // the next round writes E.u and E.s
         mode = 0;
-        base += stride * kBlock;
+        base += stride * share.n;
       }
     }
   }
@@ -325,27 +384,31 @@ __device__ inline void walk_frontier(const DView& F, const Queues& q, const uint
 // closing its stages); an inner step takes 10 us and no launch.
 template <bool kUnit>
 __global__ void __launch_bounds__(kBlock) k_expand(DView F, uint64_t* D, Queues q, Route r, uint32_t* mark,
-                                                   uint32_t stamp, bool single) {
+                                                   uint32_t stamp, bool single, bool many) {
   uint32_t nl = q.cnt[q.icur];
   const uint32_t nh = q.cnt[3 + q.icur], ngi = q.cnt[6 + q.icur];
   if (blockIdx.x == 0 && threadIdx.x < 3) q.cnt[3 * threadIdx.x + q.iclear] = 0;
-  if (no_work(nl, nh, ngi)) return;  // also an empty frontier
-  const bool inner = nl <= kInnerMost && nh == 0 && ngi == 0;
+  Share share = light_share(nl, single, many);
+  if (no_work(nl, nh, ngi, share.n)) return;  // also an empty frontier
+  __shared__ uint32_t more;
+  const bool inner = inner_first(F, q.cur[0], nl, nh, ngi, single, &more);
   if (inner && blockIdx.x != 0) return;
+  if (inner) share = Share{kBlock, false};
   __shared__ Stage S[4];
   __shared__ uint32_t list[kStage];
   __shared__ Extras E;
   open_extras(E);
+  if (threadIdx.x == 0) more = 0;
   open_routed(S, q.next, r);
   const uint32_t T = kUnit ? 0xFFFFFFFFu : band_limit(r);
   uint32_t step = 0, turn = 0;
   do {
-    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E, turn,
+    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, share, single, E, turn,
                   [&](uint32_t u) { return ld_u64(D + u) >> 32; },
                   [&](uint32_t u, uint64_t du, const Slab& sl, int nd) {
-                    relax_slab_lane<kUnit>(F, D, u, du, sl, nd, S, r, T, mark, stamp + step, single);
+                    relax_slab_lane<kUnit>(F, D, u, du, sl, nd, S, r, T, mark, stamp + step, single, &more);
                   });
-  } while (inner && inner_next(S, list, nl, step));
+  } while (inner && inner_next(S, list, &more, single, nl, step));
   stage_close(S);
 }
 
@@ -505,23 +568,27 @@ __global__ void k_invalidate(DView F, uint64_t* D, Log lg, uint64_t n, PushQ Q, 
 // tree children are the out-neighbours y whose parent is x).  The child tests of a slab are
 // issued together.
 __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queues q, uint32_t* inval,
-                                                      uint32_t* inval_cnt, bool single) {
+                                                      uint32_t* inval_cnt, bool single, bool many) {
   uint32_t nl = q.cnt[q.icur];
   const uint32_t nh = q.cnt[3 + q.icur], ngi = q.cnt[6 + q.icur];
   if (blockIdx.x == 0 && threadIdx.x < 3) q.cnt[3 * threadIdx.x + q.iclear] = 0;
-  if (no_work(nl, nh, ngi)) return;  // also an empty frontier
-  const bool inner = nl <= kInnerMost && nh == 0 && ngi == 0;  // as in k_expand
+  Share share = light_share(nl, single, many);
+  if (no_work(nl, nh, ngi, share.n)) return;  // also an empty frontier
+  __shared__ uint32_t more;
+  const bool inner = inner_first(F, q.cur[0], nl, nh, ngi, single, &more);
   if (inner && blockIdx.x != 0) return;
+  if (inner) share = Share{kBlock, false};
   __shared__ Stage S[4];
   __shared__ uint32_t list[kStage];
   __shared__ Extras E;
   open_extras(E);
+  if (threadIdx.x == 0) more = 0;
   for (int k = 0; k < 3; ++k) stage_open(S[k], q.next.q[k], q.next.c[k]);
   stage_open(S[3], inval, inval_cnt);
   __syncthreads();
   uint32_t step = 0, turn = 0;
   do {
-    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, single, E, turn,
+    walk_frontier(F, q, step ? list : q.cur[0], nl, nh, ngi, inner ? 1u : gridDim.x, share, single, E, turn,
                   [](uint32_t) { return 0; },
                   [&](uint32_t x, int, const Slab& sl, int nd) {
                     uint64_t dy[kKeysPerSlab];
@@ -534,22 +601,24 @@ __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queu
                       nb[j] = child && !single ? F.nbk[y] : 1u;
                       dy[j] = child ? cas64(D + y, dy[j], kTreeNone) ^ dy[j] : 1ull;  // 0: this lane cut y
                     }
-                    uint32_t cut = 0, heavy = 0, giant = 0;
+                    uint32_t cut = 0, heavy = 0, giant = 0, further = 0;
 #pragma unroll
                     for (int j = 0; j < kKeysPerSlab; ++j) {
                       if (dy[j] != 0) continue;
                       cut |= 1u << j;
                       if (nb[j] > kGiantBuckets) giant |= 1u << j;
                       else if (nb[j] > kHeavyBuckets) heavy |= 1u << j;
+                      else further += nb[j] - 1;
                     }
                     stage_words(S[3], cut, sl);
                     stage_words(S[0], cut & ~(heavy | giant), sl);
                     if (!single) {
+                      if (further) atomicAdd(&more, further);
                       stage_words(S[1], heavy, sl);
                       stage_words(S[2], giant, sl);
                     }
                   });
-  } while (inner && inner_next(S, list, nl, step));
+  } while (inner && inner_next(S, list, &more, single, nl, step));
   stage_close(S);
 }
 
@@ -683,6 +752,7 @@ struct TravCtx {
   uint32_t* bands;      // host-side counter that numbers the bands
   uint32_t n;           // vertices
   bool single;          // every vertex has one bucket
+  bool many;            // the vertices have kManyBuckets or more on average
   uint64_t* h_pin;      // pinned host words for size read-backs
   uint32_t delta;       // band width
 };
@@ -702,6 +772,7 @@ TravCtx graph_ctx(mk_graph* g, uint64_t* D) {
   c.bands = &g->bands;
   c.n = g->n;
   c.single = g->view[VF].n_head == g->n;
+  c.many = g->view[VF].n_head >= (uint64_t)kManyBuckets * g->n;
   c.h_pin = g->h_pin;
   c.delta = g->sssp_delta;
   return c;
@@ -772,8 +843,8 @@ template <class Launch>
 mk_status run_frontier(mk_graph* g, const TravCtx& c, hipStream_t stream, Launch&& launch,
                        uint64_t* it_io = nullptr) {
   uint64_t it = it_io ? *it_io : 0;
-  // a small graph's frontiers mostly end inside one launch (kInnerSteps)
-  int every = c.n <= kSmallGraph ? kSyncFirst / 2 : kSyncFirst;
+  // a small graph's frontiers mostly end inside one launch (kInnerSteps), unless they hold many buckets
+  int every = c.n <= kSmallGraph && !c.many ? kSyncFirst / 2 : kSyncFirst;
   for (;; every = every < kSyncMax ? 2 * every : kSyncMax) {
     for (int k = 0; k < every; ++k, ++it) {
       launch(queues(c, it), next_stamps(c, kInnerSteps, stream));
@@ -801,7 +872,7 @@ mk_status run_expand(mk_graph* g, const TravCtx& c, hipStream_t stream, Bands& b
     const Route r{nullptr, nullptr, nullptr, nullptr, 0};
     return run_frontier(g, c, stream, [&](Queues q, uint32_t stamp) {
       hipLaunchKernelGGL(k_expand<kUnit>, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F, c.D, q, r,
-                         c.mark, stamp, c.single);
+                         c.mark, stamp, c.single, c.many);
     });
   }
   uint64_t it = 0;
@@ -826,7 +897,7 @@ mk_status run_expand(mk_graph* g, const TravCtx& c, hipStream_t stream, Bands& b
     const Route r = route_of(c, b);
     mk_status s = run_frontier(g, c, stream, [&](Queues q, uint32_t stamp) {
       hipLaunchKernelGGL(k_expand<kUnit>, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F, c.D, q, r,
-                         c.mark, stamp, c.single);
+                         c.mark, stamp, c.single, c.many);
     }, &it);
     if (s != MK_OK) return s;
     const volatile uint32_t* h = reinterpret_cast<const volatile uint32_t*>(c.h_pin);
@@ -896,7 +967,7 @@ mk_status traverse(mk_graph* g, AlgoState& st, uint64_t* D, uint32_t source, uin
       MK_LAUNCH(g, "k_invalidate");
       mk_status s = run_frontier(g, c, stream, [&](Queues q, uint32_t stamp) {
         hipLaunchKernelGGL(k_propagate, dim3(kExpandBlocks), dim3(kBlock), 0, stream, F, D, q, c.inval,
-                           c.inval_cnt, c.single);
+                           c.inval_cnt, c.single, c.many);
       });
       if (s != MK_OK) return s;
       hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, stream, c.cnt, nullptr);
@@ -975,6 +1046,7 @@ mk_status mk_traverse_from(mk_graph* g, uint32_t source, int weighted, void* d_w
   c.bands = &bands;
   c.n = N;
   c.single = g->view[VF].n_head == N;
+  c.many = g->view[VF].n_head >= (uint64_t)kManyBuckets * N;
   c.h_pin = g->slot_pin[slot];
   c.delta = g->sssp_delta;
   hipLaunchKernelGGL(k_fill_mark, dim3(blocks_for(N)), dim3(kBlock), 0, stream, c.mark, N);

@@ -1,8 +1,11 @@
 """Frontier kernels at the sizes where one block goes on by itself: frontiers around the 512
 vertices it starts with and the 1,024 it can stage, depths around the 64 steps of one launch, and
 vertices with many buckets (more than a block collects) in such a frontier."""
+import time
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2305_17813_amd import native
 from parity import Pair, say
@@ -102,3 +105,66 @@ def test_rounds_with_and_without_further_buckets(width, every, fan, layers):
         p.check_all(algos=("bfs", "sssp"))
         p.insert(s[part], d[part], w[part])
         p.check_all(algos=("bfs", "sssp"))
+
+
+def even_layers(width, fan, layers):
+    """`layers` layers; every vertex has about `fan` arcs into the next one."""
+    rng = np.random.default_rng(width * 31 + fan)
+    s, d = [np.zeros(width, np.int64)], [1 + np.arange(width)]
+    for k in range(layers - 1):
+        base = 1 + k * width
+        s.append(np.repeat(base + np.arange(width), fan))
+        d.append(base + width + rng.integers(0, width, width * fan))
+    s, d = np.concatenate(s), np.concatenate(d)
+    n = 1 + width * layers
+    key = np.unique(s * n + d)
+    return key // n, key % n, rng.integers(1, 60, len(key)), n
+
+
+# how a launch's blocks share the light vertices: 256 buckets in one block and one more; 16 lanes a
+# vertex where there are many buckets on average (fans of 60 and 150) and up to 16,384 vertices; beyond
+# that blocks of 32 to 256 vertices (fan 14, two buckets each, one bucket under a larger load factor)
+@pytest.mark.parametrize("width,fan,layers", [(31, 80, 5), (32, 80, 4), (33, 80, 4), (128, 20, 4), (129, 20, 4),
+                                              (2000, 60, 4), (6000, 150, 3), (16_384, 14, 3), (16_385, 14, 3),
+                                              (60_000, 14, 3)])
+@pytest.mark.parametrize("load_factor", [0.7, 3.0])
+def test_shares_of_the_blocks(width, fan, layers, load_factor):
+    say(f"case: frontier shares, {width} wide, fan {fan}, load factor {load_factor}")
+    s, d, w, n = even_layers(width, fan, layers)
+    p = Pair(n, s, d, w, views=VIEWS, sssp_delta=20, load_factor=load_factor)
+    p.check_all(algos=("bfs", "sssp"))
+    cut = np.nonzero(s == 0)[0]
+    for part in (cut, cut[::2]):
+        p.delete(s[part], d[part])
+        p.check_all(algos=("bfs", "sssp"))
+        p.insert(s[part], d[part], w[part])
+        p.check_all(algos=("bfs", "sssp"))
+    ws = p.g.traversal_workspace()
+    for weighted, want in ((False, p.o.bfs(0)), (True, p.o.sssp(0))):
+        di, pa = p.g.traverse_from(0, weighted, ws)
+        assert np.array_equal(di.cpu().numpy().view(np.uint32), want[0])
+        assert np.array_equal(pa.cpu().numpy().view(np.uint32), want[1])
+
+
+def test_dense_graph_fills_the_chip():
+    """20,000 vertices of 15 buckets: far more lanes than one block's share of 256 vertices keeps
+    busy.  Against the levels of the same graph, whose kernels share the slabs differently."""
+    say("case: traversal of a dense graph, time")
+    rng = np.random.default_rng(2)
+    key = np.unique(rng.integers(0, 20_000 ** 2, 3_000_000))
+    s, d = key // 20_000, key % 20_000
+    g = native.Graph(20_000, s, d, views=VIEWS)
+    ws = g.traversal_workspace()
+
+    def fastest(call):
+        us = []
+        for _ in range(9):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            call()
+            torch.cuda.synchronize()
+            us.append(time.perf_counter() - t)
+        return min(us)
+
+    # 245 us against 126 top down; it was 560
+    assert fastest(lambda: g.traverse_from(0, False, ws)) <= 3.2 * fastest(lambda: g.bfs_levels(0, top_down_only=True))
