@@ -160,7 +160,14 @@ __global__ void __launch_bounds__(kBlock) k_wcc_all(DView F, uint32_t* P, uint32
 // the first four words of its primary slab, without atomics, and k_wcc_jump shortens the chains
 // (four pointers per pass).  The walk then finds nearly every neighbour under the same root and
 // unites the few trees that are left, where it used to unite every arc of a forest of single
-// vertices: 3.25 ms on the 4096 x 4096 grid, 2.2 ms with it.
+// vertices: 3.25 ms on the 4096 x 4096 grid, 2.2 ms with it.  It pays where no vertex has several
+// buckets, and on graphs of kHookLeast to kHookMost vertices, whose unions otherwise meet on few words
+// (without / with it, us: R-MAT scale 16, edge factors 4 and 16: 256, 356 / 177, 256; scale 18: 640,
+// 1,140 / 540, 650; scale 19: 1,070, 1,960 / 910, 1,380).  Smaller graphs only have more launches (scale
+// 12: 78, 103 / 103, 134), on larger ones the passes cost more than they save (scale 20: 1,040, 1,220 /
+// 1,330, 1,310; scale 22: 1,290, 2,220 / 1,250, 2,990; a million vertices, uniform, degree 8: 1,020 /
+// 1,570).
+constexpr uint32_t kHookLeast = 1u << 15, kHookMost = 1u << 19;
 constexpr uint32_t kWccHook = 4;
 __device__ inline void first_words(const DView& V, uint32_t u, uint32_t (&v)[kWccHook]) {
   const uint4* q = reinterpret_cast<const uint4*>(slab_ptr(V, u));
@@ -2648,7 +2655,12 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
       hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream,
                          g->view[VF].nbk, N, g->fq[2], nh);
     }
-    hipLaunchKernelGGL(k_wcc_all, dim3(blocks_for(N, 16384)), dim3(kBlock), 0, stream, F, P, N, g->fq[2], nh, single);
+    // A lane per vertex; where some have several buckets, at least 256 blocks for the groups and blocks
+    // that take those (R-MAT scale 10, edge factor 4: 98 us with 4 blocks, 64 with 256).  More
+    // than the lanes need make a middling graph's unions meet: scale 16, edge factor 16, with 256,
+    // 1,024 and 4,096 blocks: 355, 640 and 1,115 us.
+    const uint32_t blocks = std::max(blocks_for(N, 16384), single ? 1u : 256u);
+    hipLaunchKernelGGL(k_wcc_all, dim3(blocks), dim3(kBlock), 0, stream, F, P, N, g->fq[2], nh, single);
     return MK_OK;
   };
   // the sampled static WCC: needs the undirected view (scratch: traversal queues)
@@ -2678,7 +2690,8 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
     if (g->view[VU].on && g->iter_scheme != MK_ITER_SCHEME2) {
       sampled();
     } else {
-      if (g->iter_scheme == MK_ITER_SCHEME2) {
+      const bool hook = g->view[VF].n_head == N || (N >= kHookLeast && N <= kHookMost);
+      if (g->iter_scheme == MK_ITER_SCHEME2 || !hook) {
         hipLaunchKernelGGL(k_wcc_init, all, block, 0, stream, P, N);
       } else {
         hipLaunchKernelGGL(k_wcc_hook_min, all, block, 0, stream, F, P, N);

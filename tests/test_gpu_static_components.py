@@ -66,3 +66,24 @@ def test_components(name, views):
     p.insert(*cut, np.ones(len(cut[0]), np.int64))  # incremental on the recomputed forest
     p.check_wcc()
     p.check_wcc(native.RECOMPUTE)
+
+
+# without the undirected view: vertices of several buckets on either side of the sizes from and to
+# which trees are hooked before the walk (2^15 and 2^19 vertices), and the smallest sizes
+@pytest.mark.parametrize("n,extra", [(900, 40), (32_767, 30), (32_768, 30), (524_288, 12), (524_289, 12)])
+def test_all_arc_walk(n, extra):
+    say(f"case: components by the all-arc walk, {n} vertices")
+    rng = np.random.default_rng(n)
+    hubs = rng.choice(n, 50, replace=False)
+    s = np.concatenate([rng.integers(0, n, n // 3), np.repeat(hubs, extra)])
+    d = rng.integers(0, n, len(s))
+    key = np.unique(s * n + d)
+    s, d = key // n, key % n
+    s, d = s[s != d], d[s != d]
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD)
+    p.check_wcc()
+    p.check_wcc(native.RECOMPUTE)
+    p.delete(s[::5], d[::5])
+    p.check_wcc()
+    p.insert(s[::5], d[::5], np.ones(len(s[::5]), np.int64))
+    p.check_wcc()
