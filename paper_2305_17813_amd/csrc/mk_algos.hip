@@ -2686,8 +2686,15 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
     hipLaunchKernelGGL(k_wcc_label, all, block, 0, stream, P, M, N, d_label);
     labelled = true;
   };
+  // Where next to no vertex has many neighbours (its arcs at creation fit its primary slabs, and most
+  // arcs are from creation), there is no largest component to find early, and the unions meet on few
+  // words: hooks by id, jumps and the walk over the forward view do better.  Sampled / so, us: grids
+  // of side 64: 89 / 46, 256: 106 / 107, 1,024: 878 / 450, 2,048: 831 / 820.
+  const bool few = g->view[VU].on && g->view[VF].n_head == N && g->view[VU].n_head - N <= N / 512 &&
+                   g->cfg.load_factor > 0.f && g->cfg.load_factor <= 1.f && g->m0 >= N &&
+                   g->view[VF].added <= g->m0;
   if (full) {
-    if (g->view[VU].on && g->iter_scheme != MK_ITER_SCHEME2) {
+    if (g->view[VU].on && !few && g->iter_scheme != MK_ITER_SCHEME2) {
       sampled();
     } else {
       const bool hook = g->view[VF].n_head == N || (N >= kHookLeast && N <= kHookMost);

@@ -87,3 +87,24 @@ def test_all_arc_walk(n, extra):
     p.check_wcc()
     p.insert(s[::5], d[::5], np.ones(len(s[::5]), np.int64))
     p.check_wcc()
+
+
+# graphs of few neighbours a vertex take the all-arc walk; with long chains allowed, or filled by
+# inserts, they are sampled like any other
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("filled", [False, True])
+def test_sampled_components_of_the_same_graphs(name, filled):
+    say(f"case: components, {name}, sampled, filled by inserts {filled}")
+    s, d, n = CASES[name]
+    w = np.ones(len(s), np.int64)
+    k = 0 if filled else len(s)
+    p = Pair(n, s[:k], d[:k], w[:k], load_factor=0.7 if filled else 2.0)
+    if filled:
+        p.insert(s, d, w, exact_status=False)
+    p.check_wcc()
+    cut = np.ascontiguousarray(s[::7]), np.ascontiguousarray(d[::7])
+    p.delete(*cut, exact_status=False)
+    p.check_wcc()
+    p.insert(*cut, np.ones(len(cut[0]), np.int64), exact_status=False)
+    p.check_wcc()
+    p.check_wcc(native.RECOMPUTE)
