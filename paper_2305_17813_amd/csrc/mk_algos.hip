@@ -2158,10 +2158,96 @@ __global__ void __launch_bounds__(HubClass<Small>::kThreads) k_tc_hub(DView U, c
 // which the LDS reads (16 bytes per key) and the vector compares handle at about the rate the
 // caches deliver them.  Walking slabs and probing the other end's slab table, a 128-byte read
 // per key, took 39.5 ms at scale 18 and 1.38 s at scale 22; this takes 1.7 and 59 ms.
+//
+// A count of a small graph is its launches (the random graph of 4,096 vertices of degree 8: 84 us with
+// ten of them, 65 with five), so the first kernel makes room for the lists and collects the large
+// vertices, and the second puts the vertices into their classes.
+
+// A list segment of its degree for every vertex (in no order), and the vertices of more than kHeavyBuckets
+// buckets.  The next kernels' counters are zeroed here; tc_alloc and n_heavy_tc, which this kernel
+// counts in, by k_tc_finish.
+constexpr uint32_t kTcRoom = 4;  // vertices a thread
+__global__ void __launch_bounds__(kBlock) k_tc_room(DView U, uint32_t nv, uint64_t* off, uint32_t* heavy, Counters* C) {
+  __shared__ Stage S[1];
+  __shared__ uint64_t first[kBlock / 64 + 1];
+  stage_open(S[0], heavy, &C->n_heavy_tc);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    C->u64tmp[0] = 0;
+    C->tc_class[0] = C->tc_class[1] = C->tc_class[2] = 0;
+  }
+  const uint32_t w = threadIdx.x >> 6, ln = threadIdx.x & 63;
+  for (uint32_t base = blockIdx.x * kBlock * kTcRoom; base < nv; base += gridDim.x * kBlock * kTcRoom) {
+    uint32_t d[kTcRoom];
+    uint64_t sum = 0;
+    __syncthreads();  // the stage is open; first[] has been read
+#pragma unroll
+    for (uint32_t k = 0; k < kTcRoom; ++k) {
+      const uint32_t v = base + k * kBlock + threadIdx.x;
+      d[k] = v < nv ? U.deg[v] : 0u;
+      sum += d[k];
+      stage_push(S[0], v < nv && U.nbk[v] > kHeavyBuckets, v);
+    }
+    uint64_t incl = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint64_t below = ((uint64_t)__shfl_up((uint32_t)(incl >> 32), o) << 32) | __shfl_up((uint32_t)incl, o);
+      if ((int)ln >= o) incl += below;
+    }
+    if (ln == 63) first[w] = incl;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint64_t total = 0;
+      for (uint32_t i = 0; i < kBlock / 64; ++i) {
+        const uint64_t x = first[i];
+        first[i] = total;
+        total += x;
+      }
+      const uint64_t at = total ? atomicAdd(&C->tc_alloc, (unsigned long long)total) : 0u;
+      for (uint32_t i = 0; i < kBlock / 64; ++i) first[i] += at;
+    }
+    __syncthreads();
+    uint64_t o = first[w] + incl - sum;
+#pragma unroll
+    for (uint32_t k = 0; k < kTcRoom; ++k) {
+      const uint32_t v = base + k * kBlock + threadIdx.x;
+      if (v < nv) off[v] = o;
+      o += d[k];
+    }
+  }
+  stage_close(S);
+}
+
+// Classes of vertices by |A(u)| (a vertex with fewer than two out-neighbours closes no
+// triangle): a wave, a 256-thread block or a 1024-thread block to a vertex, with LDS sets that
+// keep the classes at full occupancy; only the last needs several passes for the largest sets.
+// A set has at least 3.2 slots per key, so that a key's first bucket is rarely full.
+constexpr uint32_t kTcWaveKeys = 64, kTcWaveSlots = 256;
+template <bool Mid>
+struct CountClass {
+  static constexpr uint32_t kThreads = Mid ? 256 : 1024;
+  static constexpr uint32_t kSlots = Mid ? 2048 : 16384;
+  static constexpr uint32_t kKeys = kSlots * 5 / 16;
+  static constexpr uint32_t kBlocks = Mid ? 2048 : 512;
+};
+
+// The vertices of each class (q[0] wave, q[1] small block, q[2] large block) and their numbers.
+struct TcClasses {
+  uint32_t *q[3], *n;
+};
+
 __global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, const uint32_t* heavy, const uint32_t* nheavy,
-                                                      const uint64_t* off, uint32_t* list, uint32_t* dplus) {
+                                                      const uint64_t* off, uint32_t* list, uint32_t* dplus, TcClasses cls) {
+  __shared__ Stage S[3];
   __shared__ uint32_t cur;
   const uint32_t ln = threadIdx.x & 63;
+  for (int k = 0; k < 3; ++k) stage_open(S[k], cls.q[k], cls.n + k);
+  __syncthreads();
+  // |A(u)| = d, by one lane of those that found it
+  auto store = [&](bool mine, uint32_t u, uint32_t d) {
+    if (mine) dplus[u] = d;
+    stage_push(S[0], mine && d >= 2 && d <= kTcWaveKeys, u);
+    stage_push(S[1], mine && d > kTcWaveKeys && d <= CountClass<true>::kKeys, u);
+    stage_push(S[2], mine && d > CountClass<true>::kKeys, u);
+  };
   // u's out-neighbours among the words of one slab: bit j for word j
   auto higher = [&](uint32_t u, uint32_t du, const Slab& sl, int nd) -> uint32_t {
     const uint32_t live = live_words(sl, nd);
@@ -2211,7 +2297,7 @@ __global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, cons
       }
     }
     __syncthreads();
-    if (threadIdx.x == 0) dplus[u] = cur;
+    store(threadIdx.x == 0, u, cur);
   }
   // single-bucket vertices: a lane each
   for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < nv; u += gridDim.x * kBlock) {
@@ -2232,7 +2318,7 @@ __global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, cons
         if (s == kInvalid) break;
       }
     }
-    dplus[u] = n;
+    store(true, u, n);
   }
   // 2 .. kHeavyBuckets buckets: a 16-lane group each
   const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) / kGroup;
@@ -2254,37 +2340,7 @@ __global__ void __launch_bounds__(kBlock) k_tc_orient(DView U, uint32_t nv, cons
       if (keep) out[n + __popc(m & ((1u << glane()) - 1u))] = v;
       n += __popc(m);
     });
-    if (glane() == 0) dplus[u] = n;
-  }
-}
-
-// Classes of vertices by |A(u)| (a vertex with fewer than two out-neighbours closes no
-// triangle): a wave, a 256-thread block or a 1024-thread block to a vertex, with LDS sets that
-// keep the classes at full occupancy; only the last needs several passes for the largest sets.
-// A set has at least 3.2 slots per key, so that a key's first bucket is rarely full.
-constexpr uint32_t kTcWaveKeys = 64, kTcWaveSlots = 256;
-template <bool Mid>
-struct CountClass {
-  static constexpr uint32_t kThreads = Mid ? 256 : 1024;
-  static constexpr uint32_t kSlots = Mid ? 2048 : 16384;
-  static constexpr uint32_t kKeys = kSlots * 5 / 16;
-  static constexpr uint32_t kBlocks = Mid ? 2048 : 512;
-};
-
-__global__ void k_tc_classes(const uint32_t* dplus, uint32_t nv, uint32_t* q0, uint32_t* q1, uint32_t* q2,
-                             uint32_t* cnt) {
-  __shared__ Stage S[3];
-  stage_open(S[0], q0, cnt);
-  stage_open(S[1], q1, cnt + 1);
-  stage_open(S[2], q2, cnt + 2);
-  __syncthreads();
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t base = blockIdx.x * blockDim.x; base < nv; base += stride) {
-    const uint32_t v = base + threadIdx.x;
-    const uint32_t d = v < nv ? dplus[v] : 0u;
-    stage_push(S[0], d >= 2 && d <= kTcWaveKeys, v);
-    stage_push(S[1], d > kTcWaveKeys && d <= CountClass<true>::kKeys, v);
-    stage_push(S[2], d > CountClass<true>::kKeys, v);
+    store(glane() == 0, u, n);
   }
   stage_close(S);
 }
@@ -2356,6 +2412,33 @@ __device__ inline uint32_t tc_stream(const uint32_t* __restrict__ list, uint64_t
 __device__ inline void tc_total(uint64_t local, unsigned long long* acc) {
   for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
   if ((threadIdx.x & 63) == 0 && local) atomicAdd(acc, (unsigned long long)local);
+}
+
+// Where every vertex has a few neighbours in one or two buckets, lists and sets do not pay: a group
+// per vertex walks its table and, for every edge to a higher vertex, probes that vertex's table with
+// its neighbours (each triangle is met at its three edges).  Three launches, by lists in six / so, us:
+// grids of side 64: 69 / 26, 256: 75 / 41, 1,024: 387 / 317, 2,048: 1,905 / 1,377; the random graph of 500
+// vertices of degree 8, whose vertices have up to three buckets: 58 / 64.
+__global__ void __launch_bounds__(kBlock) k_tc_few(DView U, uint32_t nv, unsigned long long* acc) {
+  uint64_t local = 0;
+  const uint32_t ng = gridDim.x * kGroupsPerBlock;
+  for (uint32_t u = (blockIdx.x * kBlock + threadIdx.x) / kGroup; u < nv; u += ng) {
+    const uint32_t du = U.deg[u];
+    if (du < 2) continue;
+    for_each_slab(U, u, [&](uint64_t x, bool data) {
+      const uint32_t v = (uint32_t)x;
+      bool higher = false;
+      if (data && valid_key(v)) {
+        const uint32_t dv = U.deg[v];
+        higher = dv > du || (dv == du && v > u);
+      }
+      for (uint32_t todo = gballot(higher); todo; todo &= todo - 1) {
+        const uint64_t c = group_intersect(U, u, gbcast(v, __builtin_ctz(todo)));
+        if (glane() == 0) local += c;
+      }
+    });
+  }
+  tc_total(local, acc);
 }
 
 __global__ void __launch_bounds__(kBlock) k_tc_count_wave(const uint32_t* __restrict__ list, const uint64_t* __restrict__ off,
@@ -2448,23 +2531,24 @@ __global__ void __launch_bounds__(CountClass<Mid>::kThreads) k_tc_count_block(DV
   tc_total(local, acc);
 }
 
-__global__ void k_tc_begin(Counters* C, bool reset_total) {
+__global__ void k_tc_begin(Counters* C) {
   if (threadIdx.x != 0) return;
   C->tc_s[0] = C->tc_s[1] = C->tc_s[2] = 0;
-  C->u64tmp[0] = 0;
-  C->n_heavy_tc = 0;
-  C->tc_class[0] = C->tc_class[1] = C->tc_class[2] = 0;
   C->tc_work = 0;
-  if (reset_total) C->tc_total = 0;
 }
 
 // insert: T += (S1 - S2 + S3/3) / 2;  delete: T -= (S1 + S2 + S3/3) / 2;  static: T = the sum
+// (kind 4: a third of it), and k_tc_room's counters go back to zero for the next count
 __global__ void k_tc_finish(Counters* C, int kind, unsigned long long* out) {
   if (threadIdx.x != 0) return;
   const unsigned long long s1 = C->tc_s[0], s2 = C->tc_s[1], s3 = C->tc_s[2];
   if (kind == 0) C->tc_total += (s1 - s2 + s3 / 3) / 2;
   else if (kind == 1) C->tc_total -= (s1 + s2 + s3 / 3) / 2;
-  else if (kind == 2) C->tc_total = C->u64tmp[0];
+  else if (kind == 2 || kind == 4) {
+    C->tc_total = kind == 4 ? C->u64tmp[0] / 3 : C->u64tmp[0];
+    C->tc_alloc = 0;
+    C->n_heavy_tc = 0;
+  }
   if (out) *out = C->tc_total;
 }
 
@@ -2836,26 +2920,44 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
     if (mk_status s = auto_prefers_recompute(g, MK_ALGO_TC, p, stream, &full); s != MK_OK) return s;
   unsigned long long* out = reinterpret_cast<unsigned long long*>(d_count);
   if (full) {
-    uint32_t* nh = &g->ctr->n_heavy_tc;
-    uint32_t *dplus = g->fq[0], *heavy = g->fq[4], *cls = g->ctr->tc_class;  // scratch: the traversal queues
-    uint32_t* q[3] = {g->fq[1], g->fq[2], g->fq[3]};
-    hipLaunchKernelGGL(k_tc_begin, dim3(1), dim3(64), 0, stream, g->ctr, true);
-    hipLaunchKernelGGL(k_collect_heavy, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U.nbk, N, heavy, nh);
-    size_t tb = g->scan_tmp_bytes;
-    if (rocprim::exclusive_scan(g->scan_tmp, tb, U.deg, g->tc_off, (uint64_t)0, (size_t)N, rocprim::plus<uint64_t>(),
-                                stream) != hipSuccess)
-      return MK_ERR_HIP;
-    hipLaunchKernelGGL(k_tc_orient, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U, N, heavy, nh, g->tc_off,
-                       g->tc_list, dplus);
-    hipLaunchKernelGGL(k_tc_classes, dim3(blocks_for(N, 1024)), dim3(kBlock), 0, stream, dplus, N, q[0], q[1], q[2], cls);
-    unsigned long long* sum = &g->ctr->u64tmp[0];
-    hipLaunchKernelGGL(k_tc_count_block<false>, dim3(CountClass<false>::kBlocks), dim3(CountClass<false>::kThreads), 0,
-                       stream, U, g->tc_list, g->tc_off, dplus, q[2], cls + 2, sum);
-    hipLaunchKernelGGL(k_tc_count_block<true>, dim3(CountClass<true>::kBlocks), dim3(CountClass<true>::kThreads), 0,
-                       stream, U, g->tc_list, g->tc_off, dplus, q[1], cls + 1, sum);
-    hipLaunchKernelGGL(k_tc_count_wave, dim3(blocks_for((uint64_t)N * 64)), dim3(kBlock), 0, stream, g->tc_list,
-                       g->tc_off, dplus, q[0], cls, sum);
-    hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 2, out);
+    Counters* C = g->ctr;
+    uint32_t *dplus = g->fq[0], *heavy = g->fq[4];  // scratch: the traversal queues
+    const TcClasses cls = {{g->fq[1], g->fq[2], g->fq[3]}, C->tc_class};
+    unsigned long long* sum = &C->u64tmp[0];
+    // |A(u)| = k takes k neighbours of degree k or more, so k^2 <= 2 m, and u's own degree is at most
+    // what its buckets were sized for and the arcs inserted since: a class that cannot have a vertex
+    // is not launched, and one that can gets no more blocks than vertices.  (The host does not
+    // know what replays of a captured insert added, nor the graph that replays of this count meet.)
+    const uint64_t added = g->captured_update || stream_capturing(stream) ? UINT64_MAX / 4 : g->view[VF].added;
+    const uint64_t m = g->m0 + added;
+    const uint64_t degree =
+        g->cfg.load_factor > 0.f
+            ? (uint64_t)((double)g->cfg.load_factor * kKeysPerSlab * g->view[VU].nb_max) + 1 + added
+            : m;
+    const auto blocks = [&](uint64_t keys, uint32_t most) -> uint32_t {
+      return degree <= keys || 2 * m < (keys + 1) * (keys + 1) ? 0u : (uint32_t)std::min<uint64_t>(most, m / keys + 1);
+    };
+    const uint32_t mid = blocks(kTcWaveKeys, CountClass<true>::kBlocks);
+    const uint32_t large = blocks(CountClass<true>::kKeys, CountClass<false>::kBlocks);
+    if (g->view[VU].nb_max <= 2 && degree <= kTcWaveKeys) {
+      hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(sum), 2u);
+      hipLaunchKernelGGL(k_tc_few, dim3(blocks_for((uint64_t)N * kGroup)), dim3(kBlock), 0, stream, U, N, sum);
+      hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 4, out);
+    } else {
+      hipLaunchKernelGGL(k_tc_room, dim3(blocks_for((N + kTcRoom - 1) / kTcRoom)), dim3(kBlock), 0, stream, U, N, g->tc_off,
+                         heavy, C);
+      hipLaunchKernelGGL(k_tc_orient, dim3(blocks_for(N)), dim3(kBlock), 0, stream, U, N, heavy, &C->n_heavy_tc,
+                         g->tc_off, g->tc_list, dplus, cls);
+      if (large)
+        hipLaunchKernelGGL(k_tc_count_block<false>, dim3(large), dim3(CountClass<false>::kThreads), 0, stream, U,
+                           g->tc_list, g->tc_off, dplus, cls.q[2], cls.n + 2, sum);
+      if (mid)
+        hipLaunchKernelGGL(k_tc_count_block<true>, dim3(mid), dim3(CountClass<true>::kThreads), 0, stream, U, g->tc_list,
+                           g->tc_off, dplus, cls.q[1], cls.n + 1, sum);
+      hipLaunchKernelGGL(k_tc_count_wave, dim3(blocks_for((uint64_t)N * 64)), dim3(kBlock), 0, stream, g->tc_list,
+                         g->tc_off, dplus, cls.q[0], cls.n, sum);
+      hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 2, out);
+    }
   } else if (p.list.empty()) {
     hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 3, out);
   } else {
@@ -2873,7 +2975,7 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
     if (rocprim::radix_sort_keys(g->sort_tmp, tb, g->tc_keys[0], g->tc_keys[1], (size_t)nk, 0,
                                  end_bit, stream) != hipSuccess)
       return MK_ERR_HIP;
-    hipLaunchKernelGGL(k_tc_begin, dim3(1), dim3(64), 0, stream, g->ctr, false);
+    hipLaunchKernelGGL(k_tc_begin, dim3(1), dim3(64), 0, stream, g->ctr);
     // segment bounds per source vertex (scratch: two traversal queues, unused here)
     hipLaunchKernelGGL(k_tc_segs, dim3(blocks_for(nk)), dim3(kBlock), 0, stream, g->tc_keys[1], nk, N,
                        g->fq[4], g->fq[5]);
@@ -2881,7 +2983,7 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
     const bool s2in = N <= 0x7FFFFFFFu;
     uint32_t* longs = reinterpret_cast<uint32_t*>(g->tc_keys[0]);  // free after the sort
     const dim3 groups(grid_for_groups(std::min<uint64_t>(nk, 1u << 20)));
-    if (nk < kTcFewKeys) {
+    if (nk < kTcFewKeys && g->view[VU].nb_max > kTcLong) {
       hipLaunchKernelGGL(k_tc_batch<true>, groups, dim3(kBlock), 0, stream, U, g->tc_keys[1], nk, g->fq[4], g->fq[5],
                          N, s2in, g->ctr->tc_s, longs, &g->ctr->tc_work);
       hipLaunchKernelGGL(k_tc_long, dim3((uint32_t)std::min<uint64_t>(nk, 4096)), dim3(kBlock), 0, stream, U,

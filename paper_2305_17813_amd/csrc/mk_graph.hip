@@ -446,14 +446,24 @@ __global__ void k_add_u32(const uint32_t* a, const uint32_t* b, uint32_t* out, u
 
 // bucket_count[v] = max(1, ceil(deg0(v) / (load_factor * 15))), 1 when hashing is off;
 // extra[v] = bucket_count[v] - 1 head slabs beyond the primary one.
+// most[block]: the largest bucket count that the block met.
 __global__ void k_plan(const uint32_t* cnt, uint32_t nv, float keys_per_bucket, uint32_t* nb,
-                       uint32_t* extra) {
+                       uint32_t* extra, uint32_t* most) {
+  __shared__ uint32_t block_most;
+  if (threadIdx.x == 0) block_most = 0;
+  __syncthreads();
+  uint32_t mine = 0;
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
     uint32_t b = 1;
     if (keys_per_bucket > 0.f) b = max(1u, (uint32_t)ceilf((float)cnt[v] / keys_per_bucket));
     nb[v] = b;
     extra[v] = b - 1;
+    mine = max(mine, b);
   }
+  for (int o = 32; o > 0; o >>= 1) mine = max(mine, (uint32_t)__shfl_xor((int)mine, o));
+  if (lane64() == 0) atomicMax(&block_most, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) most[blockIdx.x] = block_most;
 }
 
 // Primary slab v: word 15 = <INVALID next, nb>; with several buckets, word 14 holds the
@@ -466,9 +476,20 @@ __global__ void k_init_primary(uint64_t* slab, const uint32_t* nb, const uint32_
   }
 }
 
-__global__ void k_extra_total(const uint32_t* nb, const uint32_t* xrel, uint32_t nv,
-                              unsigned long long* total) {
-  if (threadIdx.x == 0) *total = (unsigned long long)xrel[nv - 1] + nb[nv - 1] - 1;
+// The extra head slabs of all vertices, and the largest bucket count (one block).
+__global__ void k_extra_total(const uint32_t* nb, const uint32_t* xrel, uint32_t nv, const uint32_t* most,
+                              uint32_t n_most, unsigned long long* total, uint32_t* nb_max) {
+  __shared__ uint32_t all;
+  if (threadIdx.x == 0) all = 1;
+  __syncthreads();
+  uint32_t m = 1;
+  for (uint32_t i = threadIdx.x; i < n_most; i += blockDim.x) m = max(m, most[i]);
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+  if (lane64() == 0) atomicMax(&all, m);
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  *total = (unsigned long long)xrel[nv - 1] + nb[nv - 1] - 1;
+  *nb_max = all;
 }
 
 // IterationScheme2 pairs: bucket k = off[v] + i of vertex v becomes <v, i>.
@@ -1347,7 +1368,7 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
     most = std::max(most, slabs.slabs[v]);
   }
   if (m)  // as many blocks as either half needs: a graph to be filled later has few arcs and many slabs
-    hipLaunchKernelGGL(k_count_deg, dim3(2 * std::max(grid_stride_blocks(m), grid_stride_blocks(most * kGroup))),
+    hipLaunchKernelGGL(k_count_deg, dim3(2 * std::max(grid_stride_blocks(m), grid_stride_blocks(most * kGroup, 4096))),
                        dim3(kBlock), 0, stream, d_src,
                        d_dst, m, N, g->view[VF].d.deg, g->view[VR].on ? g->view[VR].d.deg : nullptr,
                        g->view[VU].on && !add ? g->view[VU].d.deg : nullptr, slabs);
@@ -1356,12 +1377,14 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
   if (m && add)
     hipLaunchKernelGGL(k_add_u32, dim3(nb_blocks), dim3(kBlock), 0, stream, g->view[VF].d.deg, g->view[VR].d.deg,
                        g->view[VU].d.deg, N);
+  const uint32_t plan_blocks = grid_stride_blocks(N);
+  uint32_t* const plan_most[3] = {g->far[0], g->far[1], g->inval};  // scratch: no traversal has run yet
   const float kpb = cfg->load_factor > 0.f ? cfg->load_factor * kKeysPerSlab : 0.f;
   for (int v = 0; v < 3; ++v) {
     ViewHost& vh = g->view[v];
     if (!vh.on) continue;
-    hipLaunchKernelGGL(k_plan, dim3(nb_blocks), dim3(kBlock), 0, stream, vh.d.deg, N, kpb, vh.nbk,
-                       g->fq[0]);
+    hipLaunchKernelGGL(k_plan, dim3(plan_blocks), dim3(kBlock), 0, stream, vh.d.deg, N, kpb, vh.nbk,
+                       g->fq[0], plan_most[v]);
     size_t tb = g->scan_tmp_bytes;
     if (rocprim::exclusive_scan(g->scan_tmp, tb, g->fq[0], g->fq[1 + v], 0u, (size_t)N,
                                 rocprim::plus<uint32_t>(), stream) != hipSuccess)
@@ -1372,15 +1395,16 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
     ViewHost& vh = g->view[v];
     if (!vh.on) continue;
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, (uint32_t*)&g->ctr->u64tmp[v], 2, 0u);
-    hipLaunchKernelGGL(k_extra_total, dim3(1), dim3(64), 0, stream, vh.nbk, g->fq[1 + v], N,
-                       &g->ctr->u64tmp[v]);
+    hipLaunchKernelGGL(k_extra_total, dim3(1), dim3(1024), 0, stream, vh.nbk, g->fq[1 + v], N, plan_most[v],
+                       plan_blocks, &g->ctr->u64tmp[v], &g->ctr->nb_max[v]);
   }
   // the initial weight sum sets the default band width of the weighted epilogue
   hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, (uint32_t*)&g->ctr->u64tmp[3], 2, 0u);
   if (m && d_w)
     hipLaunchKernelGGL(k_sum_u32, dim3(grid_stride_blocks(m, 1024)), dim3(kBlock), 0, stream, d_w,
                        (uint32_t)std::min<uint64_t>(m, 0xFFFFFFFFu), &g->ctr->u64tmp[3]);
-  if (hipMemcpyAsync(g->h_pin, g->ctr->u64tmp, 4 * sizeof(uint64_t), hipMemcpyDeviceToHost,
+  static_assert(offsetof(Counters, nb_max) == offsetof(Counters, u64tmp) + 32, "one copy reads both");
+  if (hipMemcpyAsync(g->h_pin, g->ctr->u64tmp, 6 * sizeof(uint64_t), hipMemcpyDeviceToHost,
                      stream) != hipSuccess ||
       hipStreamSynchronize(stream) != hipSuccess)
     return fail(MK_ERR_HIP);
@@ -1392,6 +1416,7 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
     vh.n_head = (uint64_t)N + g->h_pin[v];
     if (vh.n_head > vh.head_reserved) return fail(MK_ERR_CAPACITY);
     vh.d.pool_base = (uint32_t)vh.n_head;
+    vh.nb_max = reinterpret_cast<const uint32_t*>(g->h_pin + 4)[v];
   }
   const auto empty_tables = [&] {  // every slab holds EMPTY words already
     for (int v = 0; v < 3; ++v) {

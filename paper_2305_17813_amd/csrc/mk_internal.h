@@ -34,6 +34,7 @@ struct ViewHost {
   uint32_t* nbk = nullptr;     // bucket count per vertex
   uint64_t head_reserved = 0;  // head slabs the arena reserves (upper bound)
   uint64_t n_head = 0;         // head slabs in use (N primary + extra)
+  uint32_t nb_max = 1;         // largest bucket count of a vertex (fixed at creation)
   uint64_t pool_cap = 0;       // chained slabs
   uint64_t pool_used_est = 0;  // host-side upper bound of the pool slabs in use
   uint64_t pool_hw = 0;        // bump-pointer high-water mark read back last
@@ -73,7 +74,10 @@ struct Counters {          // device-side scalars, one 4 KiB block
   uint32_t wcc_enough;     // whether it holds half of the samples
   unsigned long long tc_s[3];  // S1, S2, S3 of the triangle batch identity
   unsigned long long tc_total; // current triangle count
+  unsigned long long tc_alloc; // static triangle count: list entries given out (0 between calls,
+                               // like n_heavy_tc)
   unsigned long long u64tmp[4];
+  uint32_t nb_max[4];      // creation: largest bucket count per view
   double pr_acc[8];        // PageRank sums: [2i] dangling, [2i+1] L1 change (rotating)
   uint32_t pr_state[8];    // [0] done flag, [1] iterations run, [2] stall count
   double pr_last;          // last L1 change

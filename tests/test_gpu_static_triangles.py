@@ -73,3 +73,66 @@ def test_vertices_that_lost_all_their_arcs(degree, everything):
     p.insert(np.ascontiguousarray(s[gone]), np.ascontiguousarray(d[gone]), np.ones(int(gone.sum()), np.int64))
     p.check_tc()
     p.check_tc(native.RECOMPUTE)
+
+
+@pytest.mark.parametrize("n", [3, 66, 642])
+def test_complete_graph_filled_by_inserts(n):
+    """Classes that the arcs of creation alone could not fill."""
+    say(f"case: static triangles of K_{n}, filled by inserts")
+    u, v = torch.triu_indices(n, n, 1, device="cuda")
+    none = torch.zeros(0, dtype=torch.int32, device="cuda")
+    g = native.Graph(n + 2, none, none, views=native.VIEW_FWD | native.VIEW_UND, pool_slabs=1 << 20)
+    assert int(g.triangles(mode=native.RECOMPUTE).item()) == 0
+    g.insert_edges(u, v)
+    assert int(g.triangles(mode=native.RECOMPUTE).item()) == comb(n, 3)
+    g.delete_edges(u, v)
+    assert int(g.triangles(mode=native.RECOMPUTE).item()) == 0
+
+
+def test_replayed_recount_follows_the_graph():
+    """A captured recount is replayed on a graph that grows out of the classes it was captured with,
+    with eager work between the replays."""
+    say("case: static triangles, captured")
+    n = 700
+    u, v = torch.triu_indices(n, n, 1, device="cuda")
+    order = torch.randperm(len(u), generator=torch.Generator().manual_seed(3)).cuda()
+    u, v = u[order], v[order]
+    g = native.Graph(n, u[:100], v[:100], views=native.VIEW_FWD | native.VIEW_UND, pool_slabs=1 << 20)
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        count.copy_(g.triangles(mode=native.RECOMPUTE, stream=stream))
+    done = 100
+    for k in (100, 1200, 40_000, len(u), len(u)):
+        if k > done:
+            g.insert_edges(u[done:k], v[done:k])
+            done = k
+        graph.replay()
+        torch.cuda.synchronize()
+        got = int(count.item())
+        assert got == int(g.triangles(mode=native.RECOMPUTE).item())
+        assert int(g.stats()["n_und_edges"]) == done
+    assert got == comb(n, 3)
+
+
+# degrees that buckets and arcs inserted since keep at 64 or below are counted without lists
+@pytest.mark.parametrize("inserted", [0, 30, 200])
+def test_lattice(inserted):
+    say(f"case: static triangles of a lattice, {inserted} arcs inserted")
+    side = 45
+    v = np.arange(side * side).reshape(side, side)
+    s = np.concatenate([v[:, :-1].ravel(), v[:-1].ravel(), v[:-1, :-1].ravel()])
+    d = np.concatenate([v[:, 1:].ravel(), v[1:].ravel(), v[1:, 1:].ravel()])
+    p = Pair(side * side, s, d, np.ones(len(s), np.int64))
+    p.check_tc()
+    p.delete(s[::9], d[::9])
+    p.check_tc(native.RECOMPUTE)
+    if inserted:  # a hub beside the lattice
+        p.insert(np.full(inserted, 3), 100 + np.arange(inserted), np.ones(inserted, np.int64), exact_status=False)
+        p.check_tc(native.RECOMPUTE)
+    p.g.compact()
+    p.check_tc(native.RECOMPUTE)
+    p.delete(s, d)
+    p.check_tc(native.RECOMPUTE)
