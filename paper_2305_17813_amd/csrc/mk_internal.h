@@ -244,12 +244,11 @@ void read_back(const void* d_src, void* h_pin, uint32_t words, hipStream_t strea
 // IterationScheme2 work list of view v (built on first use; see ViewHost::pair_v).
 mk_status ensure_pairs(mk_graph* g, int v, hipStream_t stream);
 
-// Buffers of one level-synchronous BFS (mk_levels.hip): a 256-byte counter block, two
-// frontier queues of N entries, two work-item arrays of levels_multi_cap(g) entries and the reached
-// set (a byte per vertex).
+// Buffers of one level-synchronous BFS (mk_levels.hip): a 256-byte counter block, a queue of N
+// entries, two work-item arrays of levels_multi_cap(g) entries and the marks (a byte per vertex).
 struct LevelBufs {
   void* cnt = nullptr;
-  uint32_t* q[2] = {};
+  uint32_t* q = nullptr;
   uint32_t *multi_v = nullptr, *multi_c = nullptr;
   uint8_t* seen = nullptr;
 };

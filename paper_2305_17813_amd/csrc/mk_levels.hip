@@ -54,7 +54,8 @@ struct LvCnt {
   uint32_t nm[4];               // multi-bucket work items of the level's top-down step
   uint32_t mode, last;          // how the current step and the one before it reach vertices
   uint32_t bu_steps;            // bottom-up steps taken
-  uint32_t reached;             // vertices reached before the current frontier
+  uint32_t reached;             // vertices reached before the current frontier, and its place in the
+                                // queue: every vertex is queued once, frontier after frontier
   uint32_t pad[4];
   unsigned long long arcs[4];   // out-arcs of each frontier
 };
@@ -299,16 +300,17 @@ __device__ inline void block_add(unsigned long long* acc, unsigned long long v, 
 // Top-down step, single-bucket frontier vertices: a lane walks its vertex's chain.  A vertex
 // with several buckets becomes ceil(nb / 16) work items for k_lv_td_multi.
 __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L, uint32_t* level,
-                                                  uint8_t* seen, const uint32_t* fin, uint32_t* fout, uint32_t* mu_,
+                                                  uint8_t* seen, uint32_t* queue, uint32_t* mu_,
                                                   uint32_t* mc_) {
   const uint32_t s = L & 3;
   const uint32_t mode = c->mode;
   if (mode == kBottomUp) return;
   const uint32_t n = c->n[s];
   if (n == 0) return;
+  const uint32_t* fin = queue + c->reached;
   __shared__ WaveStage S;
   __shared__ unsigned long long acc;
-  WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
+  WaveOut out = wave_out(S, queue + c->reached + n, &c->n[(L + 1) & 3]);
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
@@ -325,7 +327,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L,
 // Top-down step, multi-bucket frontier vertices: a 16-lane group per work item (16 buckets),
 // a lane per bucket chain.
 __global__ void __launch_bounds__(kBlock) k_lv_td_multi(DView F, LvCnt* c, uint32_t L, uint32_t* level,
-                                                        uint8_t* seen, uint32_t* fout, const uint32_t* mu_,
+                                                        uint8_t* seen, uint32_t* queue, const uint32_t* mu_,
                                                         const uint32_t* mc_) {
   const uint32_t s = L & 3;
   const uint32_t mode = c->mode;
@@ -334,7 +336,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_td_multi(DView F, LvCnt* c, uint3
   if (nm == 0) return;
   __shared__ WaveStage S;
   __shared__ unsigned long long acc;
-  WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
+  WaveOut out = wave_out(S, queue + c->reached + c->n[s], &c->n[(L + 1) & 3]);
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
@@ -392,14 +394,14 @@ __device__ inline bool has_parent_at(const DView& R, uint32_t v, const uint32_t*
 // marking step the same sweep collects the vertices with a byte and no level.  (A block adds to two
 // counters at its end; 8,192 blocks took 123 us for that at scale 22, these 2,048 take 55.)
 __global__ void __launch_bounds__(kBlock) k_lv_bu(DView F, DView R, LvCnt* c, uint32_t L, uint32_t* level,
-                                                  uint8_t* seen, uint32_t* fout, uint32_t nv) {
+                                                  uint8_t* seen, uint32_t* queue, uint32_t nv) {
   const uint32_t s = L & 3;
   const uint32_t mode = c->mode;
   if (mode == kClaim || c->n[s] == 0) return;
   const bool bytes = c->last != kClaim;  // the frontier came from a sweep
   __shared__ WaveStage S;
   __shared__ unsigned long long acc;
-  WaveOut out = wave_out(S, fout, &c->n[(L + 1) & 3]);
+  WaveOut out = wave_out(S, queue + c->reached + c->n[s], &c->n[(L + 1) & 3]);
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
@@ -427,8 +429,7 @@ inline uint32_t blocks_for(uint64_t n, uint32_t cap) {
 }
 
 size_t levels_ws_bytes(const mk_graph* g) {
-  return 256 + 2 * ((size_t)g->n * 4 + 256) + 2 * (levels_multi_cap(g) * 4 + 256) +
-         ((size_t)g->n + 256) + 256;
+  return 256 + ((size_t)g->n * 4 + 256) + 2 * (levels_multi_cap(g) * 4 + 256) + ((size_t)g->n + 256) + 256;
 }
 
 // ----------------------------------------------------------------- tree nodes from levels
@@ -773,9 +774,7 @@ __global__ void k_ds_split(DsCnt* c, uint32_t S, DsArgs a, uint32_t* fout, uint3
 }
 
 size_t dist_ws_bytes(const mk_graph* g) {
-  return 256 + ((size_t)g->n * 8 + 256) + ((size_t)g->n * sizeof(DsByte) + 256) +
-         4 * ((size_t)g->n * 4 + 256) +
-         2 * (levels_multi_cap(g) * 4 + 256) + 256;
+  return 256 + ((size_t)g->n * 8 + 256) + 4 * ((size_t)g->n * 4 + 256) + 2 * (levels_multi_cap(g) * 4 + 256) + 256;
 }
 
 }  // namespace
@@ -793,19 +792,17 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
   allow_bu = allow_bu && g->view[VR].on;
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, c);
   hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, level, b.seen, N);
-  hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.seen, b.q[0], c, F.deg, source);
+  hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.seen, b.q, c, F.deg, source);
   MK_LAUNCH(g, "k_lv_seed");
   uint64_t every = kSyncFirst, next_sync = kSyncFirst;
   for (uint32_t L = 0;; ++L) {
-    uint32_t* fin = b.q[L & 1];
-    uint32_t* fout = b.q[(L + 1) & 1];
     hipLaunchKernelGGL(k_lv_decide, dim3(1), dim3(64), 0, stream, c, L, N, (int)allow_bu);
     hipLaunchKernelGGL(k_lv_td, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, L, level, b.seen,
-                       fin, fout, b.multi_v, b.multi_c);
-    hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, b.seen, fout,
+                       b.q, b.multi_v, b.multi_c);
+    hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, b.seen, b.q,
                        b.multi_v, b.multi_c);
     hipLaunchKernelGGL(k_lv_bu, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, R, c, L, level,
-                       b.seen, fout, N);
+                       b.seen, b.q, N);
     MK_LAUNCH(g, "k_lv step");
     if (L + 1 == next_sync || L + 1 >= N) {
       if (next_sync >= 2 * kSyncFirst) every = std::min<uint64_t>(2 * every, kSyncMax);
@@ -846,11 +843,10 @@ mk_status tree_from_dist(mk_graph* g, uint32_t source, const uint32_t* dist, uin
 mk_status bfs_tree_by_levels(mk_graph* g, uint32_t source, uint32_t* level, uint64_t* D, hipStream_t stream) {
   LevelBufs b;
   b.cnt = g->lv_cnt;
-  b.q[0] = g->fq[0];
-  b.q[1] = g->fq[1];
+  b.q = g->fq[0];
   b.multi_v = g->lv_multi[0];
   b.multi_c = g->lv_multi[1];
-  b.seen = reinterpret_cast<uint8_t*>(g->fq[2]);
+  b.seen = reinterpret_cast<uint8_t*>(g->fq[1]);
   mk_status s = levels_run(g, source, true, b, level, g->h_pin, nullptr, stream);
   if (s != MK_OK) return s;
   return tree_from_dist<true>(g, source, level, D, stream);
@@ -859,8 +855,11 @@ mk_status bfs_tree_by_levels(mk_graph* g, uint32_t source, uint32_t* level, uint
 // Every step either relaxes a non-empty near frontier or splits a non-empty far pile, and
 // positive weights bound the number of distance drops, so the loop ends; the cap is a guard
 // (and keeps the step stamps unique).
-mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2], const DsArgs& a,
+//
+// The bounds (a byte per vertex) lie in `dist`, which takes the distances when they are final.
+mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2], DsArgs a,
                    uint32_t* dist, uint64_t* pin, hipStream_t stream) {
+  a.bound = reinterpret_cast<DsByte*>(dist);
   const uint32_t N = g->n;
   DsCnt* c = reinterpret_cast<DsCnt*>(cnt);
   const DView F = g->view[VF].d;
@@ -899,7 +898,6 @@ mk_status sssp_tree_by_distances(mk_graph* g, uint32_t source, uint32_t* dist, u
   uint32_t* q[2] = {g->fq[0], g->fq[1]};
   DsArgs a;
   a.word = reinterpret_cast<unsigned long long*>(D);  // the nodes are written afterwards
-  a.bound = reinterpret_cast<DsByte*>(g->fq[2]);
   a.far[0] = g->far[0];
   a.far[1] = g->far[1];
   a.multi_v = g->lv_multi[0];
@@ -932,8 +930,7 @@ mk_status mk_bfs_levels(mk_graph* g, uint32_t source, uint32_t flags, void* d_ws
   };
   LevelBufs b;
   b.cnt = take(256);
-  b.q[0] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
-  b.q[1] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
+  b.q = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   b.multi_v = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));
   b.multi_c = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));
   b.seen = reinterpret_cast<uint8_t*>(take((size_t)N));
@@ -965,7 +962,6 @@ mk_status mk_sssp_distances(mk_graph* g, uint32_t source, void* d_ws, size_t ws_
   q[1] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   DsArgs a;
   a.word = reinterpret_cast<unsigned long long*>(take((size_t)N * 8));
-  a.bound = reinterpret_cast<DsByte*>(take((size_t)N));
   a.far[0] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   a.far[1] = reinterpret_cast<uint32_t*>(take((size_t)N * 4));
   a.multi_v = reinterpret_cast<uint32_t*>(take(levels_multi_cap(g) * 4));

@@ -105,3 +105,26 @@ def test_many_splits_of_large_piles(scale, ef, delta, orc):
         di, pa = G.sssp(u, mode=native.RECOMPUTE)
         assert np.array_equal(di.cpu().numpy().view(np.uint32), want)
         assert np.array_equal(pa.cpu().numpy().view(np.uint32), parent)
+
+
+@pytest.mark.parametrize("n", [1, 63, 257, 5000])
+def test_workspaces_fit_where_they_did(n):
+    """The sizes that programs may have noted down: two queues of n words for the levels, six arrays of
+    n words for the distances, and the work items."""
+    say(f"case: workspace sizes, {n} vertices")
+    rng = np.random.default_rng(n)
+    src, dst, w = arcs(rng, n, 40 * n, lambda k: rng.integers(1, 90, k))
+    G = native.Graph(n, src, dst, w, views=native.VIEW_FWD | native.VIEW_REV)
+    items = 2 * ((n + G.stats()["head_slabs"][0] // 16 + 64) * 4 + 256)
+    lib = native.load()
+    lv_bytes, di_bytes = 256 + 2 * (4 * n + 256) + items + 256, 256 + 6 * (4 * n + 256) + items + 256
+    assert lib.mk_bfs_levels_workspace_bytes(G.h) <= lv_bytes
+    assert lib.mk_sssp_distances_workspace_bytes(G.h) <= di_bytes
+    lv, di = reference(n, np.asarray(src, np.uint32), np.asarray(dst, np.uint32), np.asarray(w, np.uint32), 0)
+    # the workspace ends where the last of the needed bytes does, and what lies behind it stays as it was
+    for need, call, want in ((lib.mk_bfs_levels_workspace_bytes(G.h), lambda ws: G.bfs_levels(0, ws=ws)[0], lv),
+                             (lib.mk_sssp_distances_workspace_bytes(G.h), lambda ws: G.sssp_distances(0, ws=ws), di)):
+        room = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        got = call(room[:need])
+        assert np.array_equal(got.cpu().numpy().view(np.uint32), want)
+        assert bool((room[need:] == 0xA5).all())
