@@ -169,22 +169,25 @@ constexpr uint32_t kGiantLanes = kGiantSplit * kGroup;  // lanes sharing one gia
 // the frontiers that follow, up to kInnerSteps of them, while they fit its LDS stage and hold no
 // heavy vertex: a step then costs its own chain of dependent loads (about 10 us) instead of a
 // launch and the reads that find the frontier as well (about 16 us).  Where vertices have several
-// buckets, at most kInnerBuckets buckets, a round of the block: 512 vertices of 15 buckets are 30
-// rounds, and took 100 us where the whole chip takes 20.
-constexpr uint32_t kInnerMost = 512, kInnerBuckets = 256;
+// buckets, the buckets count: at most kInnerMixed to begin with and kInnerOn to go on, kInnerMany where
+// they have many (kManyBuckets).  512 vertices of 15 buckets are 30 rounds of a block, and took 100 us
+// where the whole chip takes 20.  Bounds of 256, of 384 and 512, and of 512 and 1,024, us: 4,096 vertices of
+// degree 8, 1,000 arcs deleted 196, 190, 190, inserted back 114, 106, 106, one-off BFS 135, 131, 164;
+// degree 16 one-off SSSP 392, 385, 445.
+constexpr uint32_t kInnerMost = 512, kInnerMixed = 384, kInnerOn = 512, kInnerMany = 256;
 constexpr uint32_t kInnerSteps = 64;
 
 // After a step of an inner loop: the frontier staged in S[0] becomes the block's list in LDS, or
 // the loop ends (empty, too large, heavy vertices, or out of steps) and the stages hold the
 // launch's output.  Every thread of the block gets the same answer.
-__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t* more, bool single, uint32_t& n, uint32_t& step) {
+__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t* more, bool single, bool many, uint32_t& n, uint32_t& step) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this step's atomics have been performed
   __syncthreads();
   // and the next step reads what they left, not a cache line from before them (a stale distance
   // of a vertex improved a step ago would push it again)
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   const uint32_t k = S[0].n;
-  const bool go = k > 0 && k + *more <= (single ? kStage : kInnerBuckets) && S[1].n == 0 && S[2].n == 0 && step + 1 < kInnerSteps;
+  const bool go = k > 0 && k + *more <= (single ? kStage : many ? kInnerMany : kInnerOn) && S[1].n == 0 && S[2].n == 0 && step + 1 < kInnerSteps;
   if (!go) return false;
   for (uint32_t i = threadIdx.x; i < k; i += kBlock) list[i] = S[0].buf[i];
   __syncthreads();
@@ -223,11 +226,12 @@ __device__ inline bool no_work(uint32_t nl, uint32_t nh, uint32_t ngi, uint32_t 
 // Whether one block takes this frontier (and those that follow): every block with work finds the
 // same answer.  *more is zero before the call and after it, when the block has synchronized.
 __device__ inline bool inner_first(const DView& F, const uint32_t* light, uint32_t nl, uint32_t nh, uint32_t ngi,
-                                   bool single, uint32_t* more) {
+                                   bool single, bool many, uint32_t* more) {
   if (nl > kInnerMost || nh || ngi) return false;
   if (single) return true;
-  if (nl > kInnerBuckets) return false;
-  if (nl * kHeavyBuckets <= kInnerBuckets) return true;
+  const uint32_t lim = many ? kInnerMany : kInnerMixed;
+  if (nl > lim) return false;
+  if (nl * kHeavyBuckets <= lim) return true;
   uint32_t b = 0;
   for (uint32_t i = threadIdx.x; i < nl; i += kBlock) b += F.nbk[light[i]];
   for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o);
@@ -237,7 +241,7 @@ __device__ inline bool inner_first(const DView& F, const uint32_t* light, uint32
   __syncthreads();
   const uint32_t total = *more;
   __syncthreads();
-  return total <= kInnerBuckets;
+  return total <= lim;
 }
 
 // Slabs of light vertices' further buckets, collected while the block visits the primary slabs.
@@ -391,7 +395,7 @@ __global__ void __launch_bounds__(kBlock) k_expand(DView F, uint64_t* D, Queues 
   Share share = light_share(nl, single, many);
   if (no_work(nl, nh, ngi, share.n)) return;  // also an empty frontier
   __shared__ uint32_t more;
-  const bool inner = inner_first(F, q.cur[0], nl, nh, ngi, single, &more);
+  const bool inner = inner_first(F, q.cur[0], nl, nh, ngi, single, many, &more);
   if (inner && blockIdx.x != 0) return;
   if (inner) share = Share{kBlock, false};
   __shared__ Stage S[4];
@@ -408,7 +412,7 @@ __global__ void __launch_bounds__(kBlock) k_expand(DView F, uint64_t* D, Queues 
                   [&](uint32_t u, uint64_t du, const Slab& sl, int nd) {
                     relax_slab_lane<kUnit>(F, D, u, du, sl, nd, S, r, T, mark, stamp + step, single, &more);
                   });
-  } while (inner && inner_next(S, list, &more, single, nl, step));
+  } while (inner && inner_next(S, list, &more, single, many, nl, step));
   stage_close(S);
 }
 
@@ -575,7 +579,7 @@ __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queu
   Share share = light_share(nl, single, many);
   if (no_work(nl, nh, ngi, share.n)) return;  // also an empty frontier
   __shared__ uint32_t more;
-  const bool inner = inner_first(F, q.cur[0], nl, nh, ngi, single, &more);
+  const bool inner = inner_first(F, q.cur[0], nl, nh, ngi, single, many, &more);
   if (inner && blockIdx.x != 0) return;
   if (inner) share = Share{kBlock, false};
   __shared__ Stage S[4];
@@ -618,7 +622,7 @@ __global__ void __launch_bounds__(kBlock) k_propagate(DView F, uint64_t* D, Queu
                       stage_words(S[2], giant, sl);
                     }
                   });
-  } while (inner && inner_next(S, list, &more, single, nl, step));
+  } while (inner && inner_next(S, list, &more, single, many, nl, step));
   stage_close(S);
 }
 

@@ -121,10 +121,11 @@ def even_layers(width, fan, layers):
     return key // n, key % n, rng.integers(1, 60, len(key)), n
 
 
-# how a launch's blocks share the light vertices: 256 buckets in one block and one more; 16 lanes a
-# vertex where there are many buckets on average (fans of 60 and 150) and up to 16,384 vertices; beyond
+# how a launch's blocks share the light vertices: 256 buckets in one block and one more, 384 and 512
+# where there are two a vertex; 16 lanes a vertex where there are many buckets on average (fans of 60 and 150) and up to 16,384 vertices; beyond
 # that blocks of 32 to 256 vertices (fan 14, two buckets each, one bucket under a larger load factor)
 @pytest.mark.parametrize("width,fan,layers", [(31, 80, 5), (32, 80, 4), (33, 80, 4), (128, 20, 4), (129, 20, 4),
+                                              (192, 14, 4), (193, 14, 4), (256, 14, 5), (257, 14, 5),
                                               (2000, 60, 4), (6000, 150, 3), (16_384, 14, 3), (16_385, 14, 3),
                                               (60_000, 14, 3)])
 @pytest.mark.parametrize("load_factor", [0.7, 3.0])
