@@ -12,8 +12,9 @@
  *     byte it uses lives in the caller's arena passed to mk_graph_create.  It allocates a
  *     few pinned host words per graph (hipHostMalloc) for size read-backs.
  *   - Every call is ordered on the given HIP stream.  Calls that must read a size back
- *     (traversal frontier sizes, PageRank convergence, mk_graph_stats) synchronize that
- *     stream.  Delete and query calls never synchronize.  An insert call synchronizes only
+ *     (traversal frontier sizes, PageRank convergence on all but small graphs, mk_graph_stats)
+ *     synchronize that stream, but outputs in device memory are in stream order only.  Delete
+ *     and query calls never synchronize.  An insert call synchronizes only
  *     when the host cannot otherwise show that the slab pools hold the batch: the host keeps
  *     an upper bound of the slabs in use (one per inserted arc and view), tightened without
  *     waiting by pool snapshots that earlier inserts left behind events; only when both fall
@@ -267,6 +268,7 @@ mk_status mk_set_iteration_scheme(mk_graph* g, mk_iter_scheme scheme);
  * + sum over zero-out-degree z of PR(z)/N), iterated from 1/N (first call, RECOMPUTE) or
  * from the previous vector (incremental and decremental batches) until the L1 change of
  * one iteration is <= tol_l1, stops decreasing for three iterations, or max_iter is hit.
+ * A capturing stream is refused (MK_ERR_HIP, nothing launched) unless no batch is pending.
  * Needs MK_VIEW_REV.  Ranks are stored in FP32; sums and the L1 change use FP64.
  *   d_rank  : N float (device).   d_iters : NULL or 1 uint32 (device): iterations run. */
 mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t max_iter,

@@ -1351,7 +1351,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_heavy_final(const uint32_t* heavy
 // Convergence bookkeeping for one iteration (one thread): d is its L1 change.  Stop at d <= tol,
 // when the change has not improved for three iterations (the FP32 noise floor), or at max_iter.
 // The done flag and the iteration count also go to `pin`, two words of pinned host memory, so
-// that the host needs a synchronization and no copy to read them.
+// that the host needs a synchronization and no copy to read them (null where it does not read them).
 __device__ inline bool pr_check_step(Counters* C, int slot, double tol, uint32_t max_iter, double d, uint32_t* pin) {
   uint32_t* st = C->pr_state;
   C->pr_acc[2 * slot + 1] = d;
@@ -1365,8 +1365,10 @@ __device__ inline bool pr_check_step(Counters* C, int slot, double tol, uint32_t
   }
   const bool done = d <= tol || st[2] >= 3 || st[1] >= max_iter;
   if (done) st[0] = 1;
-  pin[0] = done ? 1u : 0u;
-  pin[1] = st[1];
+  if (pin) {
+    pin[0] = done ? 1u : 0u;
+    pin[1] = st[1];
+  }
   return done;
 }
 
@@ -2665,9 +2667,10 @@ mk_status pagerank_packed(mk_graph* g, float damping, double tol_l1, uint32_t ma
   if (N <= kPrSmallN && tiles <= kPrSmallTiles) {
     hipLaunchKernelGGL(k_copy_f32, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, x[0], N);
     a.x = x[0];
-    hipLaunchKernelGGL(k_pr_small, dim3(1), dim3(kPrFlatThreads), 0, stream, a, x[1], g->ctr, tol_l1, max_iter, pin);
-    MK_LAUNCH(g, "pagerank of a small graph");
-    MK_HIP(g, hipStreamSynchronize(stream));  // converged when the call returns, whatever the size
+    // nothing is read back: the ranks are in stream order like any other call's (a wait here took 40 us
+    // of the launches that follow out of its shadow)
+    hipLaunchKernelGGL(k_pr_small, dim3(1), dim3(kPrFlatThreads), 0, stream, a, x[1], g->ctr, tol_l1, max_iter,
+                       (uint32_t*)nullptr);
   } else {
     const uint32_t cb = blocks_for(N, kPrContribBlocks);
     hipLaunchKernelGGL(k_pr_load, dim3(cb), dim3(kBlock), 0, stream, g->pr_x, g->pr_perm, od, N, x[0], c[0], g->pr_part);
@@ -2848,7 +2851,8 @@ mk_status mk_incr_pagerank(mk_graph* g, float damping, double tol_l1, uint32_t m
     MK_LAUNCH(g, "pagerank copy");
     return MK_OK;
   }
-  // every scheme waits for its iterations to converge, which a capturing stream cannot
+  // The iterations' number is not known beforehand: the loops wait for convergence, which a capturing
+  // stream cannot, and the sizes that choose between them are read now, not at a replay.
   if (stream_capturing(stream)) return hip_fail(g, hipErrorStreamCaptureUnsupported, "mk_incr_pagerank");
   if (!warm)
     hipLaunchKernelGGL(k_pr_fill, dim3(blocks_for(N)), dim3(kBlock), 0, stream, g->pr_x, N, 1.f / N);
