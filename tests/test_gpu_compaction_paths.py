@@ -5,7 +5,7 @@ import torch
 
 from paper_2305_17813_amd import inputs as I
 from paper_2305_17813_amd import native
-from parity import Pair, say
+from parity import Pair, say, u32
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +70,68 @@ def test_replayed_deletes_are_reclaimed():
     assert p.g.compact() == 80
     p.check_structure()
     assert p.g.compact() == 0
+
+
+# ops per batch (two batches, among them repeated, reversed and absent arcs) on graphs of 2^scale
+# vertices; from 16,384 ops on, a block takes several chains a group
+@pytest.mark.parametrize("views,scale,ops,load_factor", [
+    (1, 14, 1, 0.7), (1, 14, 900, 0.7), (3, 14, 1500, 0.7), (5, 14, 1900, 0.7), (7, 14, 2500, 0.7),
+    (1, 14, 1, 0.0), (1, 14, 900, 0.0), (3, 14, 1500, 0.0), (5, 14, 1900, 0.0), (7, 14, 2500, 0.0),
+    (7, 18, 16_000, 0.7), (7, 18, 40_000, 0.7)])
+def test_chains_of_logged_deletes(views, scale, ops, load_factor):
+    """A copy whose log holds every delete, few enough of them, against one whose log lost the first
+    batch (a sweep) and against the oracle."""
+    say(f"case: logged compaction, views {views}, {ops} ops, load factor {load_factor}")
+    g = I.rmat_graph(scale, 8, 31)
+    s0, d0, w0 = (np.asarray(x.cpu()).view(np.uint32).astype(np.int64) for x in g.u32())
+    a = Pair(g.n, s0, d0, w0, views=views, load_factor=load_factor)
+    b = Pair(g.n, s0, d0, w0, views=views, load_factor=load_factor, log_capacity=max(2, ops))
+    rng = np.random.default_rng(ops)
+    arcs = np.stack([s0, d0], 1)
+    for thresholds in ([1], [3, 2, 1]):
+        picks = arcs[rng.permutation(len(arcs))[:ops]]
+        batch1 = np.concatenate([picks[: ops // 2], picks[: ops // 5, ::-1], picks[: ops // 9]])
+        batch2 = picks[ops // 3:]
+        logged = len(batch1) + len(batch2)
+        assert 8 * logged <= sum(a.g.stats()["head_slabs"]), "the first copy must go by its log"
+        for p in (a, b):
+            for q in (batch1, batch2):
+                p.delete(q[:, 0].copy(), q[:, 1].copy(), exact_status=False)
+            if logged <= max(2, ops):  # one more batch takes the first one's place in the second copy's log
+                for _ in range(3):
+                    p.delete(batch2[:1, 0].copy(), batch2[:1, 1].copy(), exact_status=False)
+        for t in thresholds:
+            fa, fb = a.g.compact(t), b.g.compact(t)
+            assert fa == fb, (fa, fb)
+            assert a.g.stats()["pool_used"] == b.g.stats()["pool_used"]
+        assert a.g.compact() == 0 and b.g.compact() == 0
+        a.check_structure()
+        b.check_structure()
+        for p in (a, b):
+            p.insert(s0[:0], d0[:0], w0[:0])
+            p.insert(picks[:, 0].copy(), picks[:, 1].copy(),
+                     u32(I.arc_weight(torch.as_tensor(picks[:, 0].copy()), torch.as_tensor(picks[:, 1].copy()), g.wmax,
+                                      g.wseed)).astype(np.int64))
+        a.check_structure()
+    a.check_all(algos=("wcc", "tc"))
+
+
+@pytest.mark.parametrize("more", [0, 1])
+def test_either_side_of_the_ratio(more):
+    """As many deletes as head slabs / 8, and one more: by the log, by the sweep."""
+    say(f"case: compaction at the ratio, {more} more")
+    n = 1 << 12
+    v = np.arange(n)
+    s = np.concatenate([v, v, v[: n // 2]])
+    d = np.concatenate([(v + 1) % n, (v + 2) % n, (v[: n // 2] + 3) % n])
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD)
+    assert p.g.stats()["head_slabs"][0] == n
+    k = n // 8 + more
+    p.delete(s[:k], d[:k])
+    assert p.g.compact() == 0  # one slab a chain: nothing to free, but every tombstone packed away
+    p.check_structure()
+    p.delete(s[k:3 * k:2], d[k:3 * k:2])
+    p.g.compact()
+    p.insert(s[:k], d[:k], np.ones(k, np.int64))
+    p.check_structure()
+    p.check_all(algos=("wcc",))
