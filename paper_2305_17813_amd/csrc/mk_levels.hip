@@ -191,10 +191,11 @@ __device__ inline uint32_t block_reserve(uint32_t* ctr, uint32_t k, uint32_t* sh
 // to kTileRows a lane: the multi-bucket vertices of a block's tile become work items of 16 buckets,
 // reserved by one atomic a tile (one a wave bounded the step: 37,000 on one address for 2.4 M
 // vertices), then each(u) is called for the single-bucket ones, by whole waves (u = kInvalid:
-// nothing).
+// nothing).  `single`: no vertex of the graph has several buckets, so no count is read and no item made,
+// and the step needs no second launch (the grid of side 1,024: 1.13 ms a run with both, 0.92 without).
 constexpr uint32_t kTileRows = 4;
 template <class Each>
-__device__ inline void for_each_frontier(const DView& F, const uint32_t* fin, uint32_t n, uint32_t* nm,
+__device__ inline void for_each_frontier(const DView& F, const uint32_t* fin, uint32_t n, bool single, uint32_t* nm,
                                          uint32_t* mu, uint32_t* mc, Each each) {
   __shared__ uint32_t sh[kBlock / 64];
   const uint32_t groups = gridDim.x * kGroupsPerBlock;
@@ -208,20 +209,22 @@ __device__ inline void for_each_frontier(const DView& F, const uint32_t* fin, ui
       const uint32_t i = base + (r * kGroupsPerBlock + threadIdx.x / kGroup) * per + glane();
       u[r] = r < rows && (uint32_t)glane() < per && i < n ? fin[i] : kInvalid;
     }
+    if (!single) {
 #pragma unroll
-    for (uint32_t r = 0; r < kTileRows; ++r) {
-      nb[r] = u[r] != kInvalid ? F.nbk[u[r]] : 0u;
-      k += nb[r] > 1 ? (nb[r] + kChunk - 1) / kChunk : 0u;
-    }
-    uint32_t pos = block_reserve(nm, k, sh);
-#pragma unroll
-    for (uint32_t r = 0; r < kTileRows; ++r) {
-      if (nb[r] <= 1) continue;
-      for (uint32_t j = 0; j * kChunk < nb[r]; ++j) {
-        mu[pos] = u[r];
-        mc[pos++] = j;
+      for (uint32_t r = 0; r < kTileRows; ++r) {
+        nb[r] = u[r] != kInvalid ? F.nbk[u[r]] : 0u;
+        k += nb[r] > 1 ? (nb[r] + kChunk - 1) / kChunk : 0u;
       }
-      u[r] = kInvalid;
+      uint32_t pos = block_reserve(nm, k, sh);
+#pragma unroll
+      for (uint32_t r = 0; r < kTileRows; ++r) {
+        if (nb[r] <= 1) continue;
+        for (uint32_t j = 0; j * kChunk < nb[r]; ++j) {
+          mu[pos] = u[r];
+          mc[pos++] = j;
+        }
+        u[r] = kInvalid;
+      }
     }
     for (uint32_t r = 0; r < rows; ++r) {
       const uint32_t x = r == 0 ? u[0] : r == 1 ? u[1] : r == 2 ? u[2] : u[3];
@@ -301,7 +304,7 @@ __device__ inline void block_add(unsigned long long* acc, unsigned long long v, 
 // with several buckets becomes ceil(nb / 16) work items for k_lv_td_multi.
 __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L, uint32_t* level,
                                                   uint8_t* seen, uint32_t* queue, uint32_t* mu_,
-                                                  uint32_t* mc_) {
+                                                  uint32_t* mc_, bool single) {
   const uint32_t s = L & 3;
   const uint32_t mode = c->mode;
   if (mode == kBottomUp) return;
@@ -314,7 +317,7 @@ __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L,
   if (threadIdx.x == 0) acc = 0;
   __syncthreads();
   unsigned long long arcs = 0;
-  for_each_frontier(F, fin, n, &c->nm[s], mu_, mc_, [&](uint32_t u) {
+  for_each_frontier(F, fin, n, single, &c->nm[s], mu_, mc_, [&](uint32_t u) {
     walk_chains<kRoundClaim>(F, u, 0u, false, [&](const auto& w, const auto& live, const auto&) {
       if (mode == kMark) mark_round(w, live, seen);
       else push_found(out, claim_round(w, live, level, F.deg, L, arcs), w);
@@ -661,7 +664,7 @@ __device__ inline void wave_min_to(uint32_t* out, uint32_t m) {
 
 // Near step, single-bucket frontier vertices (a lane each); others become 16-bucket items.
 __global__ void __launch_bounds__(kBlock) k_ds_relax(DView F, DsCnt* c, uint32_t S, DsArgs a, const uint32_t* fin,
-                                                     uint32_t* fout) {
+                                                     uint32_t* fout, bool single) {
   const uint32_t s = S & 3;
   if (blockIdx.x == 0 && threadIdx.x == 0) {  // counters of the next step (unused in this one)
     c->n[(S + 2) & 3] = 0;
@@ -673,7 +676,7 @@ __global__ void __launch_bounds__(kBlock) k_ds_relax(DView F, DsCnt* c, uint32_t
   __shared__ WaveStage St[2];
   WaveOut near = wave_out(St[0], fout, &c->n[(S + 1) & 3]);
   WaveOut far = wave_out(St[1], a.far[fp], &c->nfar[fp]);
-  for_each_frontier(F, fin, n, &c->nm[s], a.multi_v, a.multi_c, [&](uint32_t u) {
+  for_each_frontier(F, fin, n, single, &c->nm[s], a.multi_v, a.multi_c, [&](uint32_t u) {
     const uint32_t du = u != kInvalid ? ds_dist(a, u) : 0u;
     walk_chains<kRoundRelax>(F, u, du, false, [&](const auto& w, const auto& live, const auto& val) {
       uint32_t nr, fr;
@@ -790,6 +793,7 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
   const DView F = g->view[VF].d;
   const DView R = g->view[VR].on ? g->view[VR].d : F;
   allow_bu = allow_bu && g->view[VR].on;
+  const bool single = g->view[VF].n_head == N;
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, c);
   hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, level, b.seen, N);
   hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.seen, b.q, c, F.deg, source);
@@ -798,9 +802,10 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
   for (uint32_t L = 0;; ++L) {
     hipLaunchKernelGGL(k_lv_decide, dim3(1), dim3(64), 0, stream, c, L, N, (int)allow_bu);
     hipLaunchKernelGGL(k_lv_td, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, L, level, b.seen,
-                       b.q, b.multi_v, b.multi_c);
-    hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, b.seen, b.q,
-                       b.multi_v, b.multi_c);
+                       b.q, b.multi_v, b.multi_c, single);
+    if (!single)
+      hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, b.seen, b.q,
+                         b.multi_v, b.multi_c);
     hipLaunchKernelGGL(k_lv_bu, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, R, c, L, level,
                        b.seen, b.q, N);
     MK_LAUNCH(g, "k_lv step");
@@ -864,6 +869,7 @@ mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2]
   DsCnt* c = reinterpret_cast<DsCnt*>(cnt);
   const DView F = g->view[VF].d;
   const uint32_t delta = std::max<uint32_t>(1u, g->sssp_delta);
+  const bool single = g->view[VF].n_head == N;
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, reinterpret_cast<LvCnt*>(c));
   hipLaunchKernelGGL(k_ds_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, a.word, a.bound, N);
   hipLaunchKernelGGL(k_ds_seed, dim3(1), dim3(64), 0, stream, a.word, a.bound, q[0], c, source, delta);
@@ -874,8 +880,10 @@ mk_status dist_run(mk_graph* g, uint32_t source, void* cnt, uint32_t* const q[2]
     const uint32_t s32 = (uint32_t)S;
     uint32_t* fin = q[S & 1];
     uint32_t* fout = q[(S + 1) & 1];
-    hipLaunchKernelGGL(k_ds_relax, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, s32, a, fin, fout);
-    hipLaunchKernelGGL(k_ds_relax_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, s32, a, fout);
+    hipLaunchKernelGGL(k_ds_relax, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, s32, a, fin, fout,
+                       single);
+    if (!single)
+      hipLaunchKernelGGL(k_ds_relax_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, s32, a, fout);
     hipLaunchKernelGGL(k_ds_far_min, dim3(blocks_for(N, 1024)), dim3(kBlock), 0, stream, c, s32, a);
     hipLaunchKernelGGL(k_ds_split, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, c, s32, a, fout, delta);
     MK_LAUNCH(g, "k_ds step");

@@ -128,3 +128,37 @@ def test_workspaces_fit_where_they_did(n):
         got = call(room[:need])
         assert np.array_equal(got.cpu().numpy().view(np.uint32), want)
         assert bool((room[need:] == 0xA5).all())
+
+
+# no vertex with several buckets: no work items, one launch less a step; long chains, rows of vertices a
+# lane, and a frontier of one vertex for many steps
+@pytest.mark.parametrize("name,load_factor", [("power law", 0.0), ("wide", 0.0), ("wide", 0.7), ("grid", 0.7)])
+def test_single_bucket_graphs(name, load_factor):
+    say(f"case: distances on single-bucket graphs, {name}, load factor {load_factor}")
+    rng = np.random.default_rng(5)
+    if name == "grid":
+        g = I.grid_graph(60, 3)
+        src, dst, w = (np.asarray(x.cpu()).view(np.uint32) for x in g.u32())
+        n = g.n
+    elif name == "power law":
+        g = I.rmat_graph(11, 8, 3)
+        src, dst, w = (np.asarray(x.cpu()).view(np.uint32) for x in g.u32())
+        n = g.n
+    else:  # 0 -> 300 -> 90,000 -> 90,000, three arcs a vertex at most
+        n = 1 + 300 + 180_000
+        a = 301 + np.arange(90_000)
+        src = np.concatenate([np.zeros(300, np.int64), 1 + np.arange(90_000) % 300, a, a])
+        dst = np.concatenate([1 + np.arange(300), a, 90_000 + rng.permutation(a), 90_000 + rng.permutation(a)])
+        key = np.unique(src * n + dst)
+        src, dst = key // n, key % n
+        w = rng.integers(1, 40, len(src))
+        if load_factor:  # the first vertices' arcs fill several buckets: only the rest as a graph of its own
+            keep = src > 300
+            src, dst, w = src[keep] - 301, dst[keep] - 301, w[keep]
+            n -= 301
+    w = np.asarray(w, np.uint32)
+    G = native.Graph(n, np.asarray(src, np.int64), np.asarray(dst, np.int64), w.astype(np.int64),
+                     views=native.VIEW_FWD, load_factor=load_factor)
+    assert G.stats()["head_slabs"][0] == n
+    G.close()
+    compare(n, src, dst, w, [int(src[0]), int(src[-1])], load_factor=load_factor)
