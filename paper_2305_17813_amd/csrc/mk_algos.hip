@@ -274,8 +274,13 @@ __device__ inline uint32_t wcc_root(const uint32_t* P, uint32_t v) {
 
 // One block of kWccSamples threads: the most frequent root among the sampled vertices into *big,
 // and whether it holds at least half of them into *enough.  Samples are spread over the ids by a
-// Weyl sequence and counted in an LDS table (two slots per sample, linear probing).
-__global__ void __launch_bounds__(kWccSamples) k_wcc_big(const uint32_t* P, uint32_t nv, uint32_t* big,
+// Weyl sequence and counted in an LDS table (two slots per sample, linear probing).  Vertices without
+// arcs are in no component worth finding, and R-MAT graphs are full of them (more than half of scale
+// 20 at edge factor 4): a thread takes the first of kWccTries vertices that has an arc, or no sample.
+// (A recompute with those vertices counted / left out, us: edge factor 2, scale 16: 73 / 58, 18: 104 /
+// 71, 20: 180 / 132, 22: 311 / 291; edge factor 4, scale 20: 190 / 144, 22: 387 / 307.)
+constexpr uint32_t kWccTries = 4;
+__global__ void __launch_bounds__(kWccSamples) k_wcc_big(DView U, const uint32_t* P, uint32_t nv, uint32_t* big,
                                                          uint32_t* enough, bool again) {
   __shared__ uint32_t key[2 * kWccSamples], cnt[2 * kWccSamples];
   __shared__ unsigned long long best;
@@ -285,21 +290,32 @@ __global__ void __launch_bounds__(kWccSamples) k_wcc_big(const uint32_t* P, uint
     cnt[i] = 0;
   }
   if (threadIdx.x == 0) best = 0;
-  const uint32_t r = wcc_root(P, (uint32_t)(((uint64_t)threadIdx.x * 0x9E3779B97F4A7C15ull >> 32) % nv));
-  __syncthreads();
-  uint32_t h = uf_order(r) & (2 * kWccSamples - 1);
-  while (true) {
-    const uint32_t old = atomicCAS(&key[h], kInvalid, r);
-    if (old == kInvalid || old == r) break;
-    h = (h + 1) & (2 * kWccSamples - 1);
+  uint32_t v[kWccTries], dv[kWccTries], s = kInvalid;
+#pragma unroll
+  for (uint32_t k = 0; k < kWccTries; ++k) {
+    v[k] = (uint32_t)(((uint64_t)(threadIdx.x + k * kWccSamples) * 0x9E3779B97F4A7C15ull >> 32) % nv);
+    dv[k] = U.deg[v[k]];
   }
-  const uint32_t n = atomicAdd(&cnt[h], 1u) + 1u;  // the last adder sees the whole count
-  // larger count first, then the smaller root
-  atomicMax(&best, ((unsigned long long)n << 32) | (0xFFFFFFFFu - r));
+#pragma unroll
+  for (uint32_t k = 0; k < kWccTries; ++k)
+    if (s == kInvalid && dv[k]) s = v[k];
+  const uint32_t samples = (uint32_t)__syncthreads_count(s != kInvalid);
+  if (s != kInvalid) {
+    const uint32_t r = wcc_root(P, s);
+    uint32_t h = uf_order(r) & (2 * kWccSamples - 1);
+    while (true) {
+      const uint32_t old = atomicCAS(&key[h], kInvalid, r);
+      if (old == kInvalid || old == r) break;
+      h = (h + 1) & (2 * kWccSamples - 1);
+    }
+    const uint32_t n = atomicAdd(&cnt[h], 1u) + 1u;  // the last adder sees the whole count
+    // larger count first, then the smaller root
+    atomicMax(&best, ((unsigned long long)n << 32) | (0xFFFFFFFFu - r));
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    *big = 0xFFFFFFFFu - (uint32_t)best;
-    *enough = (uint32_t)(best >> 32) * 2 >= kWccSamples;
+    *big = samples ? 0xFFFFFFFFu - (uint32_t)best : 0u;
+    *enough = (uint32_t)(best >> 32) * 2 >= samples;
   }
 }
 
@@ -2763,7 +2779,7 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
     hipLaunchKernelGGL(k_wcc_link, all, block, 0, stream, U, P, N, false, &c->wcc_enough);
     for (int again = 0; again < 2; ++again) {
       if (again) hipLaunchKernelGGL(k_wcc_link, all, block, 0, stream, U, P, N, true, &c->wcc_enough);
-      hipLaunchKernelGGL(k_wcc_big, dim3(1), dim3(kWccSamples), 0, stream, P, N, &c->wcc_big, &c->wcc_enough,
+      hipLaunchKernelGGL(k_wcc_big, dim3(1), dim3(kWccSamples), 0, stream, U, P, N, &c->wcc_big, &c->wcc_enough,
                          again != 0);
     }
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, &c->n_listed_light, 2u);

@@ -108,3 +108,27 @@ def test_sampled_components_of_the_same_graphs(name, filled):
     p.insert(*cut, np.ones(len(cut[0]), np.int64), exact_status=False)
     p.check_wcc()
     p.check_wcc(native.RECOMPUTE)
+
+
+# graphs most of whose vertices have no arc (those are not sampled), down to no arc at all
+@pytest.mark.parametrize("n,among,arcs", [(1, 1, 0), (300, 2, 0), (5000, 2, 1), (5000, 40, 25), (40_000, 900, 1500),
+                                          (200_000, 70_000, 140_000)])
+def test_sampled_components_among_vertices_without_arcs(n, among, arcs):
+    say(f"case: components, {arcs} arcs among {among} of {n} vertices")
+    rng = np.random.default_rng(n + arcs)
+    ids = np.sort(rng.choice(n, among, replace=False))
+    s, d = rng.integers(0, among, arcs), rng.integers(0, among, arcs)
+    d = np.where(s == d, (d + 1) % among, d)
+    key = np.unique(ids[s] * n + ids[d])
+    s, d = key // n, key % n
+    p = Pair(n, s, d, np.ones(len(s), np.int64), load_factor=2.0)
+    p.check_wcc()
+    if arcs:
+        p.delete(s[::2], d[::2])
+        p.check_wcc()
+        p.delete(s[1::2], d[1::2])  # no arc left
+        p.check_wcc()
+        for half in (slice(0, None, 2), slice(1, None, 2)):  # the slab pool has room for either
+            p.insert(s[half], d[half], np.ones(len(s[half]), np.int64))
+            p.check_wcc()
+        p.check_wcc(native.RECOMPUTE)
