@@ -168,6 +168,7 @@ __global__ void __launch_bounds__(kBlock) k_wcc_all(DView F, uint32_t* P, uint32
 // 1,330, 1,310; scale 22: 1,290, 2,220 / 1,250, 2,990; a million vertices, uniform, degree 8: 1,020 /
 // 1,570).
 constexpr uint32_t kHookLeast = 1u << 15, kHookMost = 1u << 19;
+constexpr uint32_t kRootMost = 1u << 23;  // vertices from which a recompute's walk has a lane for each again
 constexpr uint32_t kWccHook = 4;
 __device__ inline void first_words(const DView& V, uint32_t u, uint32_t (&v)[kWccHook]) {
   const uint4* q = reinterpret_cast<const uint4*>(slab_ptr(V, u));
@@ -2762,9 +2763,14 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
     // that take those (R-MAT scale 10, edge factor 4: 98 us with 4 blocks, 64 with 256).  More
     // than the lanes need make a middling graph's unions meet: scale 16, edge factor 16, with 256,
     // 1,024 and 4,096 blocks: 355, 640 and 1,115 us.
+    // Where no vertex has several buckets, a recompute's unions meet as well: its best number of blocks
+    // grows with the root of the vertices.  Grids, us, with a lane per vertex / so: side 256: 86 / 77,
+    // 512: 197 / 129, after inserts 300 / 137, 724: 315 / 197, 1,024: 370 / 250, 2,048: 713 / 713.  (Side
+    // 512 with 64, 128, 256, 512 blocks: 250, 162, 129, 143; 1,024 with 256, 512, 1,024: 318, 250, 290.)
     // An incremental pass finds nearly every arc united and only reads: all the blocks the chip holds
     // (scale 18, edge factor 8: 87 us, 108 with the lanes' 1,024).
-    const uint32_t blocks = std::max(blocks_for(N, 16384), single ? 1u : full ? 256u : kWalkBlocks);
+    uint32_t blocks = std::max(blocks_for(N, 16384), single ? 1u : full ? 256u : kWalkBlocks);
+    if (single && full && N < kRootMost) blocks = std::min(blocks, std::max(1u, (uint32_t)(std::sqrt((double)N) / 2)));
     hipLaunchKernelGGL(k_wcc_all, dim3(blocks), dim3(kBlock), 0, stream, F, P, N, g->fq[2], nh, single);
     return MK_OK;
   };
@@ -2794,7 +2800,7 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
   // Where next to no vertex has many neighbours (its arcs at creation fit its primary slabs, and most
   // arcs are from creation), there is no largest component to find early, and the unions meet on few
   // words: hooks by id, jumps and the walk over the forward view do better.  Sampled / so, us: grids
-  // of side 64: 89 / 46, 256: 106 / 107, 1,024: 878 / 450, 2,048: 831 / 820.
+  // of side 64: 81 / 36, 256: 92 / 76, 512: 150 / 127, 1,024: 515 / 260, 2,048: 800 / 712, 4,096: 7,040 / 2,125.
   const bool few = g->view[VU].on && g->view[VF].n_head == N && g->view[VU].n_head - N <= N / 512 &&
                    g->cfg.load_factor > 0.f && g->cfg.load_factor <= 1.f && g->m0 >= N &&
                    g->view[VF].added <= g->m0;

@@ -132,3 +132,26 @@ def test_sampled_components_among_vertices_without_arcs(n, among, arcs):
             p.insert(s[half], d[half], np.ones(len(s[half]), np.int64))
             p.check_wcc()
         p.check_wcc(native.RECOMPUTE)
+
+
+# the walk over graphs without vertices of several buckets, whose blocks grow with the root of the
+# vertices: the smallest, and sizes whose blocks take several rounds with a ragged last one
+@pytest.mark.parametrize("views", [native.VIEW_FWD, native.VIEW_FWD | native.VIEW_REV])
+@pytest.mark.parametrize("n", [1, 2, 257, 16_385, 70_001, 1_100_003])
+def test_all_arc_walk_of_single_buckets(n, views):
+    say(f"case: components by the all-arc walk, {n} vertices of one bucket, views {views}")
+    rng = np.random.default_rng(n)
+    ring = np.arange(n)
+    s = np.concatenate([ring[: n // 2], rng.integers(0, n, n // 4)])
+    d = np.concatenate([ring[: n // 2] + 1, rng.integers(0, n, n // 4)]) % n
+    key = np.unique(s * n + d)
+    s, d = key // n, key % n
+    s, d = s[s != d], d[s != d]
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=views, load_factor=0.0)
+    p.check_wcc()
+    p.check_wcc(native.RECOMPUTE)
+    if len(s):
+        p.delete(s[::9], d[::9])
+        p.check_wcc()
+        p.insert(s[::9], d[::9], np.ones(len(s[::9]), np.int64))
+        p.check_wcc()
