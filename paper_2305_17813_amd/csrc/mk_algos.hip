@@ -168,7 +168,8 @@ __global__ void __launch_bounds__(kBlock) k_wcc_all(DView F, uint32_t* P, uint32
 // 1,330, 1,310; scale 22: 1,290, 2,220 / 1,250, 2,990; a million vertices, uniform, degree 8: 1,020 /
 // 1,570).
 constexpr uint32_t kHookLeast = 1u << 15, kHookMost = 1u << 19;
-constexpr uint32_t kRootMost = 1u << 23;  // vertices from which a recompute's walk has a lane for each again
+// vertices from which a recompute's walk has a lane for each again: no vertex of several buckets, and others
+constexpr uint32_t kRootMost = 1u << 23, kRootMostMixed = 1u << 21;
 constexpr uint32_t kWccHook = 4;
 __device__ inline void first_words(const DView& V, uint32_t u, uint32_t (&v)[kWccHook]) {
   const uint4* q = reinterpret_cast<const uint4*>(slab_ptr(V, u));
@@ -2760,17 +2761,21 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
                          g->view[VF].nbk, N, g->fq[2], nh);
     }
     // A lane per vertex; where some have several buckets, at least 256 blocks for the groups and blocks
-    // that take those (R-MAT scale 10, edge factor 4: 98 us with 4 blocks, 64 with 256).  More
-    // than the lanes need make a middling graph's unions meet: scale 16, edge factor 16, with 256,
-    // 1,024 and 4,096 blocks: 355, 640 and 1,115 us.
-    // Where no vertex has several buckets, a recompute's unions meet as well: its best number of blocks
-    // grows with the root of the vertices.  Grids, us, with a lane per vertex / so: side 256: 86 / 77,
-    // 512: 197 / 129, after inserts 300 / 137, 724: 315 / 197, 1,024: 370 / 250, 2,048: 713 / 713.  (Side
-    // 512 with 64, 128, 256, 512 blocks: 250, 162, 129, 143; 1,024 with 256, 512, 1,024: 318, 250, 290.)
+    // that take those (R-MAT scale 10, edge factor 4: 98 us with 4 blocks, 64 with 256).
+    // In a recompute the unions of more lanes meet on few words, and the best number of blocks grows with
+    // the root of the vertices, up to sizes that want all the chip holds.  A lane per vertex / so, us: grids,
+    // no vertex of several buckets: side 256: 86 / 77, 512: 197 / 129, after inserts 300 / 137, 724: 315 /
+    // 197, 1,024: 370 / 250, 2,048: 713 / 713 (side 512 with 64, 128, 256, 512 blocks: 250, 162, 129, 143;
+    // 1,024 with 256, 512, 1,024: 318, 250, 290).  Others, medians: uniform, degree 4, 300,000 vertices: 830 /
+    // 369, 2^20: 1,069 / 415; degree 10: 667 / 565, 2,289 / 951; R-MAT edge factor 4, scale 18: 608 / 397, 19:
+    // 948 / 571, 20: 656 / 647; edge factor 16, scale 18: 720 / 582, 20: 1,908 / 1,772; scale 22 with 1,024
+    // blocks takes 1,784 and 3,161, with a lane each 1,389 and 2,739.
     // An incremental pass finds nearly every arc united and only reads: all the blocks the chip holds
     // (scale 18, edge factor 8: 87 us, 108 with the lanes' 1,024).
-    uint32_t blocks = std::max(blocks_for(N, 16384), single ? 1u : full ? 256u : kWalkBlocks);
-    if (single && full && N < kRootMost) blocks = std::min(blocks, std::max(1u, (uint32_t)(std::sqrt((double)N) / 2)));
+    uint32_t blocks = blocks_for(N, 16384);
+    if (full && N < (single ? kRootMost : kRootMostMixed))
+      blocks = std::min(blocks, std::max(1u, (uint32_t)(std::sqrt((double)N) / 2)));
+    if (!single) blocks = std::max(blocks, full ? 256u : kWalkBlocks);
     hipLaunchKernelGGL(k_wcc_all, dim3(blocks), dim3(kBlock), 0, stream, F, P, N, g->fq[2], nh, single);
     return MK_OK;
   };
