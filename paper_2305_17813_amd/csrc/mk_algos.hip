@@ -2802,13 +2802,15 @@ mk_status mk_incr_wcc_scheme(mk_graph* g, uint32_t* d_label, mk_mode mode, mk_wc
     hipLaunchKernelGGL(k_wcc_label, all, block, 0, stream, P, M, N, d_label);
     labelled = true;
   };
-  // Where next to no vertex has many neighbours (its arcs at creation fit its primary slabs, and most
-  // arcs are from creation), there is no largest component to find early, and the unions meet on few
-  // words: hooks by id, jumps and the walk over the forward view do better.  Sampled / so, us: grids
-  // of side 64: 81 / 36, 256: 92 / 76, 512: 150 / 127, 1,024: 515 / 260, 2,048: 800 / 712, 4,096: 7,040 / 2,125.
-  const bool few = g->view[VU].on && g->view[VF].n_head == N && g->view[VU].n_head - N <= N / 512 &&
-                   g->cfg.load_factor > 0.f && g->cfg.load_factor <= 1.f && g->m0 >= N &&
-                   g->view[VF].added <= g->m0;
+  // Where next to no vertex has many neighbours (at creation they fitted the primary slabs, and most arcs
+  // are from creation: arcs that came and went again do not count), there is no largest component to find
+  // early, and the unions meet on few words: hooks by id, jumps and the walk over the forward view do
+  // better.  Sampled / so, us: grids of side 64: 81 / 36, 256: 92 / 76, 512: 150 / 127, 1,024: 515 / 260,
+  // 2,048: 800 / 712, 4,096: 7,040 / 2,125.  A few chained slabs are let pass, not the chain of a hub, which
+  // one lane would walk.
+  const ViewHost& und = g->view[VU];
+  const bool few = und.on && g->view[VF].n_head == N && und.n_head - N <= N / 512 && und.pool_built <= 64 &&
+                   g->m0 >= N && g->net_added <= g->m0;
   if (full) {
     if (g->view[VU].on && !few && g->iter_scheme != MK_ITER_SCHEME2) {
       sampled();
@@ -2958,21 +2960,26 @@ mk_status mk_count_triangles(mk_graph* g, uint64_t* d_count, mk_mode mode, hipSt
     const TcClasses cls = {{g->fq[1], g->fq[2], g->fq[3]}, C->tc_class};
     unsigned long long* sum = &C->u64tmp[0];
     // |A(u)| = k takes k neighbours of degree k or more, so k^2 <= 2 m, and u's own degree is at most
-    // what its buckets were sized for and the arcs inserted since: a class that cannot have a vertex
-    // is not launched, and one that can gets no more blocks than vertices.  (The host does not
-    // know what replays of a captured insert added, nor the graph that replays of this count meet.)
-    const uint64_t added = g->captured_update || stream_capturing(stream) ? UINT64_MAX / 4 : g->view[VF].added;
+    // what its buckets were sized for, or the words of its slabs, and the arcs inserted since: a class
+    // that cannot have a vertex is not launched, and one that can gets no more blocks than vertices.  (The
+    // host does not know what replays of a captured insert added, nor the graph that replays of this count
+    // meet.)
+    const ViewHost& und = g->view[VU];
+    const bool unknown = g->captured_update || stream_capturing(stream);
+    const uint64_t added = unknown ? UINT64_MAX / 4 : g->view[VF].added;
     const uint64_t m = g->m0 + added;
-    const uint64_t degree =
-        g->cfg.load_factor > 0.f
-            ? (uint64_t)((double)g->cfg.load_factor * kKeysPerSlab * g->view[VU].nb_max) + 1 + added
-            : m;
+    uint64_t built = kKeysPerSlab * (und.nb_max + und.pool_built);  // the largest degree at creation
+    if (g->cfg.load_factor > 0.f)
+      built = std::min(built, (uint64_t)((double)g->cfg.load_factor * kKeysPerSlab * und.nb_max) + 1);
+    const uint64_t degree = built + added;
     const auto blocks = [&](uint64_t keys, uint32_t most) -> uint32_t {
       return degree <= keys || 2 * m < (keys + 1) * (keys + 1) ? 0u : (uint32_t)std::min<uint64_t>(most, m / keys + 1);
     };
     const uint32_t mid = blocks(kTcWaveKeys, CountClass<true>::kBlocks);
     const uint32_t large = blocks(CountClass<true>::kKeys, CountClass<false>::kBlocks);
-    if (g->view[VU].nb_max <= 2 && degree <= kTcWaveKeys) {
+    // (a few arcs more leave the degrees as they were; should they all meet at one vertex, the count takes
+    // longer and is the same)
+    if (und.nb_max <= 2 && built <= kTcWaveKeys && !unknown && g->net_added <= 64 + N / 64) {
       hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(sum), 2u);
       hipLaunchKernelGGL(k_tc_few, dim3(blocks_for((uint64_t)N * kGroup)), dim3(kBlock), 0, stream, U, N, sum);
       hipLaunchKernelGGL(k_tc_finish, dim3(1), dim3(64), 0, stream, g->ctr, 4, out);

@@ -1471,6 +1471,7 @@ mk_status mk_graph_create(const mk_config* cfg, void* d_arena, size_t arena_byte
   }
   // the initial arcs did not fit the pool (only an explicit, too small pool_slabs can do this)
   if (g->overflowed.load()) return fail(MK_ERR_OUT_OF_SLABS);
+  for (ViewHost& vh : g->view) vh.pool_built = vh.pool_used_est;
   *out = g;
   return MK_OK;
 }
@@ -1511,6 +1512,7 @@ mk_status mk_insert_edges(mk_graph* g, const uint32_t* d_src, const uint32_t* d_
   if (!pool_fits(g, 2 * n) && !stream_capturing(stream)) enqueue_snapshot(g, stream);
   g->batches.push_back(BatchRec{kInsertBatch, off, n, g->next_seq++});
   g->log_tail = off + n;
+  g->net_added += n;
   g->batches_applied++;
   return MK_OK;
 }
@@ -1537,6 +1539,7 @@ mk_status mk_delete_edges(mk_graph* g, const uint32_t* d_src, const uint32_t* d_
   }
   g->batches.push_back(BatchRec{kDeleteBatch, off, n, g->next_seq++});
   g->log_tail = off + n;
+  g->net_added -= std::min(g->net_added, n);
   g->batches_applied++;
   return MK_OK;
 }

@@ -37,6 +37,7 @@ struct ViewHost {
   uint32_t nb_max = 1;         // largest bucket count of a vertex (fixed at creation)
   uint64_t pool_cap = 0;       // chained slabs
   uint64_t pool_used_est = 0;  // host-side upper bound of the pool slabs in use
+  uint64_t pool_built = 0;     // pool slabs in use after creation
   uint64_t pool_hw = 0;        // bump-pointer high-water mark read back last
   uint64_t added = 0;          // slabs the inserts so far may have taken (running sum of
                                // the per-call bounds; snapshots are placed against it)
@@ -120,6 +121,7 @@ struct mk_graph {
   uint64_t dropped_seq = 0;   // batches with seq <= dropped_seq are no longer in the log
   uint64_t clean_seq = 0;     // deletes with seq <= clean_seq left no tombstone (compacted)
   bool captured_update = false;  // an update was captured: its replays are not in the log
+  uint64_t net_added = 0;     // arcs passed to inserts less those passed to deletes since (not below 0)
 
   // traversal scratch
   mk::Counters* ctr = nullptr;

@@ -136,3 +136,31 @@ def test_lattice(inserted):
     p.check_tc(native.RECOMPUTE)
     p.delete(s, d)
     p.check_tc(native.RECOMPUTE)
+
+
+# a stream of batches that come and go leaves a graph of few neighbours what it was: counts and
+# components before, between and after them, by any way of laying the chains
+@pytest.mark.parametrize("load_factor", [0.7, 2.0, 0.0])
+@pytest.mark.parametrize("batch", [40, 1500])
+def test_streams_over_a_lattice(load_factor, batch):
+    say(f"case: recounts along a stream over a lattice, batches of {batch}, load factor {load_factor}")
+    side = 40
+    v = np.arange(side * side).reshape(side, side)
+    s = np.concatenate([v[:, :-1].ravel(), v[:-1].ravel(), v[:-1, :-1].ravel()])
+    d = np.concatenate([v[:, 1:].ravel(), v[1:].ravel(), v[1:, 1:].ravel()])
+    p = Pair(side * side, s, d, np.ones(len(s), np.int64), load_factor=load_factor)
+    rng = np.random.default_rng(batch)
+    for k in range(5):
+        a = rng.integers(0, side * side, batch)
+        b = np.full(batch, 7 + k) if batch < 100 else rng.integers(0, side * side, batch)  # one vertex, or all
+        key = np.unique(a * side * side + b)
+        a, b = key // (side * side), key % (side * side)
+        new = (a != b) & ~np.isin(a * side * side + b, s * side * side + d)
+        a, b = a[new], b[new]
+        p.insert(a, b, np.ones(len(a), np.int64))
+        p.check_tc(native.RECOMPUTE)
+        p.check_wcc(native.RECOMPUTE)
+        p.delete(a, b)
+        p.check_tc(native.RECOMPUTE)
+        p.check_wcc(native.RECOMPUTE)
+    assert p.g.check() == 0
