@@ -46,7 +46,14 @@ constexpr uint32_t kSyncFirst = 4, kSyncMax = 16;  // steps between size read-ba
 // claiming, 365 marking and sweeping; 20 M reads of its 16 MB of levels brought 16 M lines into the
 // L2s, the bytes mostly stay there.  A claiming step leaves the bytes alone: testing and setting them
 // as well cost the road-like grid of 16.8 M vertices a line more per vertex (36 to 42 us a level).
+//
+// A traversal that may step bottom-up launches the sweep for every level anyway.  One that may not would
+// launch it for nothing at most levels, so it marks and sweeps only on graphs of kSweepLeast vertices and 8
+// arcs a vertex (with / without, us: 2^20 vertices, uniform, degree 8: 535 / 590; R-MAT scale 20, edge factor
+// 16: 470 / 490) and claims on all others (edge factor 4: 362 / 336; scale 18: 277 / 250; grids of side
+// 64: 455 / 350, 2,048: 1,620 / 1,437; 4,096 vertices, degree 4: 325 / 283).
 constexpr uint32_t kClaim = 0, kBottomUp = 1, kMark = 2, kMarkShare = 2;
+constexpr uint32_t kSweepLeast = 1u << 20;
 
 // Device counters of one call (in the caller's workspace).  Level L uses slot L mod 4.
 struct LvCnt {
@@ -87,7 +94,7 @@ __global__ void k_lv_seed(uint32_t* level, uint8_t* seen, uint32_t* q0, LvCnt* c
 }
 
 // Direction of level L's step, and the counters it fills.
-__global__ void k_lv_decide(LvCnt* c, uint32_t L, uint32_t nv, int allow_bu) {
+__global__ void k_lv_decide(LvCnt* c, uint32_t L, uint32_t nv, bool allow_bu, bool sweeps) {
   if (threadIdx.x != 0) return;
   const uint32_t s = L & 3, nx = (L + 1) & 3;
   c->n[nx] = 0;
@@ -97,7 +104,7 @@ __global__ void k_lv_decide(LvCnt* c, uint32_t L, uint32_t nv, int allow_bu) {
   if (L > 0) c->reached += c->n[(L - 1) & 3];
   const uint64_t nu = (uint64_t)nv - c->reached - nf;
   const uint32_t mode = allow_bu && nu > 0 && 2 * nf + mf > 6 * nu + nv / 2 ? kBottomUp
-                        : mf > nv / kMarkShare                               ? kMark
+                        : sweeps && mf > nv / kMarkShare                     ? kMark
                                                                              : kClaim;
   c->last = L > 0 ? c->mode : kClaim;
   c->mode = mode;
@@ -794,20 +801,22 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
   const DView R = g->view[VR].on ? g->view[VR].d : F;
   allow_bu = allow_bu && g->view[VR].on;
   const bool single = g->view[VF].n_head == N;
+  const bool sweeps = allow_bu || (N >= kSweepLeast && g->m0 >= 8ull * N);
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, c);
   hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, level, b.seen, N);
   hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.seen, b.q, c, F.deg, source);
   MK_LAUNCH(g, "k_lv_seed");
   uint64_t every = kSyncFirst, next_sync = kSyncFirst;
   for (uint32_t L = 0;; ++L) {
-    hipLaunchKernelGGL(k_lv_decide, dim3(1), dim3(64), 0, stream, c, L, N, (int)allow_bu);
+    hipLaunchKernelGGL(k_lv_decide, dim3(1), dim3(64), 0, stream, c, L, N, allow_bu, sweeps);
     hipLaunchKernelGGL(k_lv_td, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, c, L, level, b.seen,
                        b.q, b.multi_v, b.multi_c, single);
     if (!single)
       hipLaunchKernelGGL(k_lv_td_multi, dim3(2048), dim3(kBlock), 0, stream, F, c, L, level, b.seen, b.q,
                          b.multi_v, b.multi_c);
-    hipLaunchKernelGGL(k_lv_bu, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, R, c, L, level,
-                       b.seen, b.q, N);
+    if (sweeps)
+      hipLaunchKernelGGL(k_lv_bu, dim3(blocks_for(N, 2048)), dim3(kBlock), 0, stream, F, R, c, L, level,
+                         b.seen, b.q, N);
     MK_LAUNCH(g, "k_lv step");
     if (L + 1 == next_sync || L + 1 >= N) {
       if (next_sync >= 2 * kSyncFirst) every = std::min<uint64_t>(2 * every, kSyncMax);

@@ -162,3 +162,16 @@ def test_single_bucket_graphs(name, load_factor):
     assert G.stats()["head_slabs"][0] == n
     G.close()
     compare(n, src, dst, w, [int(src[0]), int(src[-1])], load_factor=load_factor)
+
+
+# top-down alone, large and dense enough to mark and sweep, and one vertex or a few arcs short of that
+@pytest.mark.parametrize("n,m", [(1 << 20, 9 << 20), ((1 << 20) - 1, 9 << 20), (1 << 20, 7 << 20)])
+def test_top_down_alone(n, m, orc):
+    say(f"case: levels top down, {n} vertices, {m} arcs")
+    g = I.er_graph(n, m, 3)
+    want, _ = orc.OracleGraph(n, *(np.asarray(x.cpu()).view(np.uint32) for x in g.u32())).bfs(5)
+    for views in (native.VIEW_FWD, native.VIEW_FWD | native.VIEW_REV):
+        G = native.Graph(n, *g.u32(), views=views)
+        for _ in range(2):
+            assert np.array_equal(G.bfs_levels(5, top_down_only=True)[0].cpu().numpy().view(np.uint32), want)
+        G.close()
