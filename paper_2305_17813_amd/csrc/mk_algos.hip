@@ -279,9 +279,11 @@ __device__ inline uint32_t wcc_root(const uint32_t* P, uint32_t v) {
 // Weyl sequence and counted in an LDS table (two slots per sample, linear probing).  Vertices without
 // arcs are in no component worth finding, and R-MAT graphs are full of them (more than half of scale
 // 20 at edge factor 4): a thread takes the first of kWccTries vertices that has an arc, or no sample.
-// (A recompute with those vertices counted / left out, us: edge factor 2, scale 16: 73 / 58, 18: 104 /
-// 71, 20: 180 / 132, 22: 311 / 291; edge factor 4, scale 20: 190 / 144, 22: 387 / 307.)
-constexpr uint32_t kWccTries = 4;
+// One after the other, as a block has a whole CU's random reads to itself: 9.8 us without, 11.5 with two
+// tries, 13 with three, 19 with four at once.  (A recompute with those vertices counted / left out, us:
+// edge factor 2, scale 16: 71 / 55, 18: 93 / 74, 20: 177 / 130, 22: 313 / 282; edge factor 8, scale 20:
+// 170 / 133, 22: 444 / 288.)
+constexpr uint32_t kWccTries = 2;
 __global__ void __launch_bounds__(kWccSamples) k_wcc_big(DView U, const uint32_t* P, uint32_t nv, uint32_t* big,
                                                          uint32_t* enough, bool again) {
   __shared__ uint32_t key[2 * kWccSamples], cnt[2 * kWccSamples];
@@ -292,15 +294,11 @@ __global__ void __launch_bounds__(kWccSamples) k_wcc_big(DView U, const uint32_t
     cnt[i] = 0;
   }
   if (threadIdx.x == 0) best = 0;
-  uint32_t v[kWccTries], dv[kWccTries], s = kInvalid;
-#pragma unroll
-  for (uint32_t k = 0; k < kWccTries; ++k) {
-    v[k] = (uint32_t)(((uint64_t)(threadIdx.x + k * kWccSamples) * 0x9E3779B97F4A7C15ull >> 32) % nv);
-    dv[k] = U.deg[v[k]];
+  uint32_t s = kInvalid;
+  for (uint32_t k = 0; k < kWccTries && s == kInvalid; ++k) {
+    const uint32_t v = (uint32_t)((threadIdx.x + k * kWccSamples) * 0x9E3779B97F4A7C15ull >> 32) % nv;
+    if (U.deg[v]) s = v;
   }
-#pragma unroll
-  for (uint32_t k = 0; k < kWccTries; ++k)
-    if (s == kInvalid && dv[k]) s = v[k];
   const uint32_t samples = (uint32_t)__syncthreads_count(s != kInvalid);
   if (s != kInvalid) {
     const uint32_t r = wcc_root(P, s);
