@@ -48,12 +48,14 @@ constexpr uint32_t kSyncFirst = 4, kSyncMax = 16;  // steps between size read-ba
 // as well cost the road-like grid of 16.8 M vertices a line more per vertex (36 to 42 us a level).
 //
 // A traversal that may step bottom-up launches the sweep for every level anyway.  One that may not would
-// launch it for nothing at most levels, so it marks and sweeps only on graphs of kSweepLeast vertices and 8
-// arcs a vertex (with / without, us: 2^20 vertices, uniform, degree 8: 535 / 590; R-MAT scale 20, edge factor
-// 16: 470 / 490) and claims on all others (edge factor 4: 362 / 336; scale 18: 277 / 250; grids of side
-// 64: 455 / 350, 2,048: 1,620 / 1,437; 4,096 vertices, degree 4: 325 / 283).
+// launch it for nothing at most levels, so it marks and sweeps only on graphs of kSweepDense arcs a vertex,
+// or of kSweepLeast vertices and 8 arcs a vertex, and claims on all others (with sweeps / without, us:
+// 5,000 vertices, degree 150: 104 / 115, 100,000, degree 30: 180 / 199, R-MAT scale 16, edge factor 32: 201 /
+// 219; 2^20 vertices, degree 8: 535 / 590, R-MAT scale 20, edge factor 16: 470 / 490; but edge factor 4: 362 /
+// 336, scale 18, edge factors 4 and 8: 277 / 250, 250 / 238, 4,096 vertices of degree 4, 8 and 32: 325 / 283,
+// 158 / 147, 89 / 83, grids of side 64: 455 / 350, 2,048: 1,620 / 1,437).
 constexpr uint32_t kClaim = 0, kBottomUp = 1, kMark = 2, kMarkShare = 2;
-constexpr uint32_t kSweepLeast = 1u << 20;
+constexpr uint32_t kSweepLeast = 1u << 20, kSweepDense = 24;
 
 // Device counters of one call (in the caller's workspace).  Level L uses slot L mod 4.
 struct LvCnt {
@@ -801,7 +803,7 @@ mk_status levels_run(mk_graph* g, uint32_t source, bool allow_bu, const LevelBuf
   const DView R = g->view[VR].on ? g->view[VR].d : F;
   allow_bu = allow_bu && g->view[VR].on;
   const bool single = g->view[VF].n_head == N;
-  const bool sweeps = allow_bu || (N >= kSweepLeast && g->m0 >= 8ull * N);
+  const bool sweeps = allow_bu || g->m0 >= (uint64_t)(N >= kSweepLeast ? 8 : kSweepDense) * N;
   hipLaunchKernelGGL(k_lv_clear, dim3(1), dim3(64), 0, stream, c);
   hipLaunchKernelGGL(k_lv_fill, dim3(blocks_for(N, 4096)), dim3(kBlock), 0, stream, level, b.seen, N);
   hipLaunchKernelGGL(k_lv_seed, dim3(1), dim3(64), 0, stream, level, b.seen, b.q, c, F.deg, source);

@@ -165,7 +165,8 @@ def test_single_bucket_graphs(name, load_factor):
 
 
 # top-down alone, large and dense enough to mark and sweep, and one vertex or a few arcs short of that
-@pytest.mark.parametrize("n,m", [(1 << 20, 9 << 20), ((1 << 20) - 1, 9 << 20), (1 << 20, 7 << 20)])
+@pytest.mark.parametrize("n,m", [(1 << 20, 9 << 20), ((1 << 20) - 1, 9 << 20), (1 << 20, 7 << 20), (3001, 24 * 3001),
+                                 (3001, 24 * 3001 - 1)])
 def test_top_down_alone(n, m, orc):
     say(f"case: levels top down, {n} vertices, {m} arcs")
     g = I.er_graph(n, m, 3)
