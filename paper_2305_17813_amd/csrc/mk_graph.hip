@@ -1268,7 +1268,13 @@ void launch_insert(mk_graph* g, const uint32_t* s, const uint32_t* d, const uint
 // 1M 577 / 281; scale 20 (8.6M) 300K 265 / 495, 1M 715 / 630; scale 22 (35M) 100K 121 / 1167,
 // 1M 783 / 1583, 2M 1479 / 1772.  (An atomic per cut chain and words packed by scattered 8-byte
 // stores took 1179 and 2503 us by a sweep at scale 22 with 100K and 1M ops.)
-constexpr uint64_t kCompactLogRatio = 8;
+//
+// Below kCompactLarge head slabs in all, the sweep is over in a few microseconds, and where only the
+// forward view (or the reverse one with it) is on, half to three quarters of a log pass's lanes have no
+// table: it pays from a ratio of kCompactLogFew on.  Insert, delete and compact of the forward view alone,
+// logged / sweep, us: 60,000 head slabs, an eighth as many ops 62 / 47, a 64th 45 / 45; 220,000: 69 / 55,
+// 53 / 46; 603,000: 84 / 71, 65 / 55; 2.4M: 162 / 172, 70 / 119.
+constexpr uint64_t kCompactLogRatio = 8, kCompactLogFew = 64, kCompactLarge = 3u << 19;
 // Creation fills one table after the other (k_build_all) while a chain mostly fits its head slab.
 // Where chains are longer (load factors above 1, hashing off), lanes race to extend them: each that
 // loses holds the slab it took until the launch is over, and the more arcs a launch has for one
@@ -1631,7 +1637,8 @@ mk_status mk_compact(mk_graph* g, uint32_t min_tombstones, uint64_t* h_freed, hi
   for (const BatchRec& b : g->batches)
     if (b.kind == kDeleteBatch && b.seq > g->clean_seq) ops += b.n;
   for (const ViewHost& vh : g->view) heads += vh.on ? vh.n_head : 0;
-  const bool by_log = !g->captured_update && g->dropped_seq <= g->clean_seq && kCompactLogRatio * ops <= heads;
+  const uint64_t ratio = g->view[VU].on || heads >= kCompactLarge ? kCompactLogRatio : kCompactLogFew;
+  const bool by_log = !g->captured_update && g->dropped_seq <= g->clean_seq && ratio * ops <= heads;
   ChainBits cb{};
   uint64_t words = 1;
   for (int v = 0; v < 3; ++v)

@@ -135,3 +135,35 @@ def test_either_side_of_the_ratio(more):
     p.insert(s[:k], d[:k], np.ones(k, np.int64))
     p.check_structure()
     p.check_all(algos=("wcc",))
+
+
+# without the undirected view: graphs on either side of the size from which the log is taken as with it,
+# deletes on either side of its ratio there and of the one for smaller graphs
+@pytest.mark.parametrize("views", [native.VIEW_FWD, native.VIEW_FWD | native.VIEW_REV])
+@pytest.mark.parametrize("scale,share,more", [(16, 64, 0), (16, 64, 1), (20, 8, 0), (20, 8, 1)])
+def test_ratios_without_the_undirected_view(views, scale, share, more):
+    say(f"case: compaction, views {views}, scale {scale}, 1 delete in {share} head slabs, {more} more")
+    g = I.rmat_graph(scale, 16, 31, device="cuda")
+    graphs = [native.Graph(g.n, *g.u32(), views=views, log_capacity=k) for k in (0, 4096)]  # the second one sweeps
+    heads = sum(graphs[0].stats()["head_slabs"])
+    assert (heads >= 3 << 19) == (scale == 20)
+    k = heads // share + more
+    arcs = [x[:k].contiguous() for x in g.u32()]
+    for _ in range(2):
+        for G in graphs:
+            for at in range(0, k, 4096 if G is graphs[1] else k):
+                end = min(k, at + 4096) if G is graphs[1] else k
+                G.delete_edges(arcs[0][at:end].contiguous(), arcs[1][at:end].contiguous())
+        assert graphs[0].compact() == graphs[1].compact()
+        assert graphs[0].stats()["pool_used"] == graphs[1].stats()["pool_used"]
+        for G in graphs:
+            assert G.compact() == 0
+            assert G.check() == 0
+            assert not bool(G.query_edges(arcs[0], arcs[1])[0].any())
+            for at in range(0, k, 4096):
+                G.insert_edges(*(x[at:at + 4096].contiguous() for x in arcs))
+            assert G.check() == 0
+            found, weight = G.query_edges(arcs[0], arcs[1])
+            assert bool(found.all()) and torch.equal(weight, arcs[2])
+        a, b = (sorted(zip(*(u32(x).tolist() for x in G.export()))) if scale < 20 else None for G in graphs)
+        assert a == b
