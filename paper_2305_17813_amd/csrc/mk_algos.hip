@@ -224,7 +224,9 @@ __global__ void __launch_bounds__(kBlock) k_wcc_jump(uint32_t* P, uint32_t nv) {
 //   5. k_wcc_min, k_wcc_label: the smallest id of each component becomes its root and label.
 // Uniting every vertex with two neighbours under the smaller id (instead of 1 and 2) took 1.1-1.3
 // ms at R-MAT scale 22: half of those unions hook a hub's root, and their CASes meet on a few
-// words.  With the walk of step 4 over every vertex, the recompute took 1.6 ms; it takes 0.31.
+// words.  With the walk of step 4 over every vertex, the recompute of R-MAT scale 22 as built took 1.6
+// ms; it takes 0.38 (hooks 0.12, links 0.04 to 0.13, with the way the first words happen to lie, walk
+// 0.11), and 0.9 to 1.1 after millions of uniform arcs, whose vertices hook less well.
 constexpr uint32_t kWccLinks = 2;
 constexpr uint32_t kWccSamples = 1024;
 
@@ -779,13 +781,15 @@ __global__ void __launch_bounds__(kBlock) k_pr_gather(DView R, const float* __re
 // sum as the difference of two prefixes.  A segment that runs over tile borders leaves the
 // sum of its last part in heads[t] and of the earlier ones in tails[], which k_pr_fix adds.
 //
-// What bounds an iteration: the random contribution gathers, one request per in-arc to an L2
-// channel.  So each block keeps the first kPrHot contributions in LDS: half of R-MAT scale 22's
-// arcs start there, two thirds of scale 20's.  Scale 22, per iteration: 240 us and 16 us in the
-// two small kernels (a lane or a group per vertex with all gathers through L2: 411 us and 48 us
-// in four small ones).  Of the 240 us, 94 remain without the cold gathers; 324 us are taken with
-// every gather through L2, 271 with 8,000 contributions in LDS.  The packing takes 1.0 ms a
-// call, half of it the rank reads, which have no hot-first order to help them.
+// What bounds an iteration: the random contribution gathers and the lines they bring into the
+// L2s.  So each block keeps the first kPrHot contributions in LDS: half of R-MAT scale 22's arcs
+// start there, two thirds of scale 20's.  Scale 22 as built, per iteration: 240 us, 0.94 GB fetched
+// (3.9 TB/s; list and vectors are 0.33 GB), and 16 us in the two small kernels (a lane or a group per
+// vertex with all gathers through L2: 411 us and 48 us in four small ones).  Of the 240 us, 94
+// remain without the cold gathers; 324 us are taken with every gather through L2, 271 with 8,000
+// contributions in LDS.  After millions of uniform arcs, whose sources are cold, 277 to 302 us and
+// 1.25 GB, near the rate of a copy.  The packing takes 1.0 ms a call, half of it the rank reads,
+// which have no hot-first order to help them.
 constexpr uint32_t kPrTile = 512;            // list entries and segment ends per tile
 constexpr uint32_t kPrFlatThreads = 1024;    // one block per CU: 16 waves share its hot contributions
 constexpr uint32_t kPrFlatBlocks = 256;
@@ -2175,7 +2179,7 @@ __global__ void __launch_bounds__(HubClass<Small>::kThreads) k_tc_hub(DView U, c
 // What bounds it: the streamed keys, sum over directed edges of |A(v)| (660M at R-MAT scale 18),
 // which the LDS reads (16 bytes per key) and the vector compares handle at about the rate the
 // caches deliver them.  Walking slabs and probing the other end's slab table, a 128-byte read
-// per key, took 39.5 ms at scale 18 and 1.38 s at scale 22; this takes 1.7 and 59 ms.
+// per key, took 39.5 ms at scale 18 and 1.35 to 1.56 s at scale 22; this takes 1.7 and 59 ms.
 //
 // A count of a small graph is its launches (the random graph of 4,096 vertices of degree 8: 84 us with
 // ten of them, 65 with five), so the first kernel makes room for the lists and collects the large

@@ -109,19 +109,8 @@ __device__ inline uint32_t lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Wave-aggregated append (the paper's warp enqueue, Alg. 2, with ballot + mbcnt): every
-// active lane with `p` writes `v` at a slot reserved by one atomic per wave.
-__device__ inline void wave_push(uint32_t* q, uint32_t* ctr, bool p, uint32_t v) {
-  uint64_t m = __ballot(p);
-  if (m == 0) return;
-  int leader = __builtin_ctzll(m);
-  uint32_t base = 0;
-  if (lane64() == leader) base = atomicAdd(ctr, (uint32_t)__popcll(m));
-  base = __shfl(base, leader);
-  if (p) q[base + lanes_below(m)] = v;
-}
-
 // ----------------------------------------------------------------- block-staged appends
+// The paper's warp enqueue (Alg. 2, with ballot + mbcnt) a level up.
 // Appends to a queue whose counter would otherwise take one atomic per wave (sparse pushes
 // from many waves serialize on that one address) go to an LDS buffer per output, with one
 // LDS atomic per wave; when the kernel ends, the block reserves room for each buffer with a
@@ -183,8 +172,9 @@ __device__ inline void stage_push(Stage& S, bool p, uint32_t v) {
 }
 
 // The same for kernels that push as much as they read: a buffer per wave, written out by one
-// atomic when the next push would not fit (64 x 15 entries at most, which fit after that), so that a counter sees an atomic per several hundred entries however many a block pushes.
-// What is left at the end is written by the block together.
+// atomic when the next push would not fit (64 x 15 entries at most, which fit after that), so that
+// a counter sees an atomic per several hundred entries however many a block pushes.  What is left
+// at the end is written by the block together.
 constexpr uint32_t kWaveStage = 64 * 16;
 struct WaveStage {
   uint32_t n[kBlock / 64], base;

@@ -261,8 +261,6 @@ __device__ inline void for_each_item(const DView& F, uint32_t nm, const uint32_t
   }
 }
 
-
-
 // Top-down on a round of slabs, claiming: every unreached neighbour gets level cur + 1 (the CAS
 // winner pushes it and counts its out-arcs).
 template <int K>
@@ -309,8 +307,9 @@ __device__ inline void block_add(unsigned long long* acc, unsigned long long v, 
   if (threadIdx.x == 0 && *acc) atomicAdd(out, *acc);
 }
 
-// Top-down step, single-bucket frontier vertices: a lane walks its vertex's chain.  A vertex
-// with several buckets becomes ceil(nb / 16) work items for k_lv_td_multi.
+// Top-down step, single-bucket frontier vertices: a group of 16 lanes holds up to 16 vertices and
+// reads their chains slab by slab (walk_chains).  A vertex with several buckets becomes ceil(nb / 16)
+// work items for k_lv_td_multi.
 __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L, uint32_t* level,
                                                   uint8_t* seen, uint32_t* queue, uint32_t* mu_,
                                                   uint32_t* mc_, bool single) {
@@ -336,8 +335,8 @@ __global__ void __launch_bounds__(kBlock) k_lv_td(DView F, LvCnt* c, uint32_t L,
   block_add(&acc, arcs, &c->arcs[(L + 1) & 3]);
 }
 
-// Top-down step, multi-bucket frontier vertices: a 16-lane group per work item (16 buckets),
-// a lane per bucket chain.
+// Top-down step, multi-bucket frontier vertices: a 16-lane group per work item, whose 16 bucket
+// chains it reads slab by slab.
 __global__ void __launch_bounds__(kBlock) k_lv_td_multi(DView F, LvCnt* c, uint32_t L, uint32_t* level,
                                                         uint8_t* seen, uint32_t* queue, const uint32_t* mu_,
                                                         const uint32_t* mc_) {
@@ -671,7 +670,8 @@ __device__ inline void wave_min_to(uint32_t* out, uint32_t m) {
   if ((threadIdx.x & 63) == 0 && m != kLevelInf) atomicMin(out, m);
 }
 
-// Near step, single-bucket frontier vertices (a lane each); others become 16-bucket items.
+// Near step, single-bucket frontier vertices (up to 16 to a group of 16 lanes, which reads their
+// chains slab by slab); others become 16-bucket items.
 __global__ void __launch_bounds__(kBlock) k_ds_relax(DView F, DsCnt* c, uint32_t S, DsArgs a, const uint32_t* fin,
                                                      uint32_t* fout, bool single) {
   const uint32_t s = S & 3;
@@ -698,7 +698,8 @@ __global__ void __launch_bounds__(kBlock) k_ds_relax(DView F, DsCnt* c, uint32_t
   wave_out_close(far);
 }
 
-// Near step, multi-bucket frontier vertices: a 16-lane group per item, a lane per bucket.
+// Near step, multi-bucket frontier vertices: a 16-lane group per item, whose 16 bucket chains it
+// reads slab by slab.
 __global__ void __launch_bounds__(kBlock) k_ds_relax_multi(DView F, DsCnt* c, uint32_t S, DsArgs a,
                                                            uint32_t* fout) {
   const uint32_t s = S & 3;

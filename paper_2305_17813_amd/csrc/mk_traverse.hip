@@ -180,14 +180,16 @@ constexpr uint32_t kInnerSteps = 64;
 // After a step of an inner loop: the frontier staged in S[0] becomes the block's list in LDS, or
 // the loop ends (empty, too large, heavy vertices, or out of steps) and the stages hold the
 // launch's output.  Every thread of the block gets the same answer.
-__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t* more, bool single, bool many, uint32_t& n, uint32_t& step) {
+__device__ inline bool inner_next(Stage (&S)[4], uint32_t* list, uint32_t* more, bool single, bool many,
+                                  uint32_t& n, uint32_t& step) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this step's atomics have been performed
   __syncthreads();
   // and the next step reads what they left, not a cache line from before them (a stale distance
   // of a vertex improved a step ago would push it again)
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   const uint32_t k = S[0].n;
-  const bool go = k > 0 && k + *more <= (single ? kStage : many ? kInnerMany : kInnerOn) && S[1].n == 0 && S[2].n == 0 && step + 1 < kInnerSteps;
+  const bool go = k > 0 && k + *more <= (single ? kStage : many ? kInnerMany : kInnerOn) && S[1].n == 0 &&
+                  S[2].n == 0 && step + 1 < kInnerSteps;
   if (!go) return false;
   for (uint32_t i = threadIdx.x; i < k; i += kBlock) list[i] = S[0].buf[i];
   __syncthreads();

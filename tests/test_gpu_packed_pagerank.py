@@ -143,3 +143,18 @@ def test_graph_filled_by_inserts(n, m):
             best.append(time.perf_counter() - t)
         us.append(min(best))
     assert us[0] <= 3 * us[1], us
+
+
+# hashing off, graphs of more arcs than the cases above take that way: chains of a slab, of two and of
+# fourteen behind each vertex
+@pytest.mark.parametrize("name", ["ring wider than the LDS copy", "sixteen in-arcs each", "two hundred in-arcs each"])
+def test_chains_of_several_slabs(name):
+    say(f"case: packed PageRank, {name}, hashing off")
+    s, d, n = CASES[name]
+    p = Pair(n, s, d, np.ones(len(s), np.int64), views=native.VIEW_FWD | native.VIEW_REV, load_factor=0.0)
+    p.check_pr()
+    p.delete(s[::97], d[::97], exact_status=False)
+    p.check_pr()
+    p.insert(s[::97], d[::97], np.ones(len(s[::97]), np.int64), exact_status=False)
+    p.check_pr()
+    p.check_pr(native.RECOMPUTE)
