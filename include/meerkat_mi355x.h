@@ -187,7 +187,8 @@ mk_status mk_traverse_from(mk_graph* g, uint32_t source, int weighted, void* d_w
 /* Distance-only BFS levels from `source` (the "vanilla" BFS of the experimental section:
  * 32-bit levels, no parents, against the tree variant that the maintained BFS/SSSP keep).
  * Level-synchronous; each step is top-down (the frontier's out-arcs claim unreached vertices,
- * or mark them for a sweep when there are more than N/2 of these arcs) or, with MK_VIEW_REV,
+ * or, where bottom-up steps are allowed and on large or dense graphs, mark them for a sweep when
+ * there are more than N/2 of these arcs) or, with MK_VIEW_REV,
  * bottom-up (each unreached vertex scans its in-arcs and stops at the first one on the current
  * level), chosen on the device per step by direction optimization (Beamer et al.) recast for
  * slabs: bottom-up when 2 nf + mf > 6 nu + N/2, with nf and mf
